@@ -1,0 +1,246 @@
+// fp32 GEMM on the fp32 matrix cores (v_mfma_f32_16x16x4_f32: fp32 operands, fp32 accumulation), for the fp32 configuration.
+//
+// What bounds it: the fp32 products of this library are small (a microbatch of a small model), so the time is the latency of
+// one pass over K on too few workgroups, not arithmetic.  Hence no LDS staging and no barrier in the K loop: a wave loads
+// its operands from L2 straight into the registers that the matrix instruction reads, 16 bytes per lane, and small outputs
+// have their K range divided over the waves of a workgroup, whose partial tiles are added through LDS in a fixed order.
+//
+// How the operands fit without a transpose.  A 16x16x4 step takes from lane l one value of row l%16 at k = l/16.  Which
+// memory row stands behind "row l%16" and which k behind "k = l/16" of step e is free as long as both operands agree on k:
+//   k-contiguous operand (A [M,K], B [N,K]): lane l reads 4 consecutive k of its row; value e goes to step e, so step e of
+//     a 16-wide slab multiplies k = 4 (l/16) + e.
+//   row-contiguous operand (A [K,M], B [K,N]): lane l reads NV consecutive columns of row k = 4 (l/16) + e for e = 0..3;
+//     value j goes to block j, so block j holds the columns NV (l%16) + j.
+// The matrix instruction gets B as its first operand, so a lane ends up with 4 consecutive columns of one row of C.
+//
+// Measured on the GEMMs of a [256 tokens] x 256..1024 GPT stage: 47-86 us per launch with the plain LDS-tiled kernel,
+// 5-9 us here.
+#include "kernels.h"
+
+namespace zs {
+namespace {
+
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+constexpr unsigned OUT = 0x80000000u;   // pushes a lane's offset past every descriptor (extents are below 2^30 bytes): reads 0
+
+template <int N> struct FV;
+template <> struct FV<2> { typedef f32x2 type; };
+template <> struct FV<4> { typedef f32x4 type; };
+
+__device__ __forceinline__ f32x4 load4(__amdgpu_buffer_rsrc_t rs, unsigned voff, unsigned soff) {
+  union { u32x4 u; f32x4 f; } c;
+  c.u = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)voff, (int)soff, 0);
+  return c.f;
+}
+__device__ __forceinline__ f32x2 load2(__amdgpu_buffer_rsrc_t rs, unsigned voff, unsigned soff) {
+  union { u32x2 u; f32x2 f; } c;
+  c.u = __builtin_amdgcn_raw_buffer_load_b64(rs, (int)voff, (int)soff, 0);
+  return c.f;
+}
+template <int N> __device__ __forceinline__ typename FV<N>::type loadn(__amdgpu_buffer_rsrc_t rs, unsigned voff, unsigned soff) {
+  if constexpr (N == 4) return load4(rs, voff, soff); else return load2(rs, voff, soff);
+}
+
+// Fragments of one operand for one slab of 16 k: NB blocks of 16 rows.
+template <int ROWC, int NB> struct Frag;
+template <int NB> struct Frag<0, NB> {   // k-contiguous
+  f32x4 v[NB];
+  __device__ __forceinline__ float at(int b, int e) const { return v[b][e]; }
+};
+template <int NB> struct Frag<1, NB> {   // row-contiguous
+  typename FV<NB>::type v[4];
+  __device__ __forceinline__ float at(int b, int e) const { return v[e][b]; }
+};
+
+// A workgroup owns a (16 MI WM) x (16 NI WN) tile of C: WM x WN waves side by side, times KW waves that share out K.
+template <int TA, int TB, int MI, int NI, int WM, int WN, int KW, int SEG>
+__global__ __launch_bounds__(64 * WM * WN * KW) void gemm_f32_kernel(Gemm g, int tiles_m, int tiles_n) {
+  constexpr int NQ = MI * NI;   // quads of 4 consecutive columns a lane holds
+  __shared__ f32x4 red[KW > 1 ? (KW - 1) * WM * WN * NQ * 64 : 1];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lm = lane & 15, lg = lane >> 4;
+  const int kw = wave / (WM * WN), wt = wave % (WM * WN);
+  int tm, tn;
+  gemm_tile_of(blockIdx.x, tiles_m, tiles_n, tm, tn);
+  const int z = blockIdx.y;
+  const int m0 = (tm * WM + wt / WN) * 16 * MI, n0 = (tn * WN + wt % WN) * 16 * NI;
+  const float* A = (const float*)g.A + (int64_t)z * g.sA;
+  const float* B = (const float*)g.B + (int64_t)z * g.sB;
+  const unsigned lda = (unsigned)g.lda, ldb = (unsigned)g.ldb;
+  const int nseg = SEG ? g.K / g.kseg : 1, kb = SEG ? g.kseg : g.K;
+  const __amdgpu_buffer_rsrc_t ra =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(A), 0, (int)((TA ? (g.K - 1) * lda + g.M : (g.M - 1) * lda + g.K) * 4), 0x00020000);
+  const __amdgpu_buffer_rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<float*>(B), 0, (int)((TB ? (unsigned)((nseg - 1) * g.segB) + (g.N - 1) * ldb + kb : (g.K - 1) * ldb + g.N) * 4), 0x00020000);
+
+  // per-lane byte offsets of the slab at k = 0
+  unsigned ao[TA ? 4 : MI], bo[TB ? NI : 4];
+  if constexpr (TA == 0) {
+#pragma unroll
+    for (int i = 0; i < MI; ++i) ao[i] = ((m0 + 16 * i + lm) * lda + 4 * lg) * 4;
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) ao[e] = m0 + MI * lm < g.M ? ((4 * lg + e) * lda + m0 + MI * lm) * 4 : OUT;
+  }
+  if constexpr (TB == 1) {
+#pragma unroll
+    for (int j = 0; j < NI; ++j) bo[j] = ((n0 + 16 * j + lm) * ldb + (SEG ? 0 : 4 * lg)) * 4;
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) bo[e] = n0 + NI * lm < g.N ? ((4 * lg + e) * ldb + n0 + NI * lm) * 4 : OUT;
+  }
+
+  Frag<TA, MI> fa[2];
+  Frag<1 - TB, NI> fb[2];
+  auto load = [&](Frag<TA, MI>& a, Frag<1 - TB, NI>& b, int k) {
+    const unsigned past = k + 4 * lg < g.K ? 0u : OUT;   // K is a multiple of 4 where an operand is k-contiguous
+    if constexpr (TA == 0) {
+#pragma unroll
+      for (int i = 0; i < MI; ++i) a.v[i] = load4(ra, ao[i] | past, k * 4);
+    } else {   // rows past K lie behind the descriptor
+#pragma unroll
+      for (int e = 0; e < 4; ++e) a.v[e] = loadn<MI>(ra, ao[e], k * lda * 4);
+    }
+    if constexpr (TB == 1) {
+      if constexpr (SEG) {
+        const int kl = k + 4 * lg, seg = kl / g.kseg;
+        const unsigned so = (unsigned)(seg * g.segB + (kl - seg * g.kseg)) * 4;
+#pragma unroll
+        for (int j = 0; j < NI; ++j) b.v[j] = load4(rb, past ? OUT : bo[j] + so, 0);
+      } else {
+#pragma unroll
+        for (int j = 0; j < NI; ++j) b.v[j] = load4(rb, bo[j] | past, k * 4);
+      }
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) b.v[e] = loadn<NI>(rb, bo[e], k * ldb * 4);
+    }
+  };
+  f32x4 acc[MI][NI];
+#pragma unroll
+  for (int i = 0; i < MI; ++i)
+#pragma unroll
+    for (int j = 0; j < NI; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  auto multiply = [&](const Frag<TA, MI>& a, const Frag<1 - TB, NI>& b) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+      for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < NI; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(b.at(j, e), a.at(i, e), acc[i][j], 0, 0, 0);
+  };
+
+  // this wave's slabs [s0, s1): two in flight; loads behind s1 are issued and not used
+  const int slabs = (g.K + 15) / 16, per = (slabs + KW - 1) / KW;
+  const int s0 = kw * per, s1 = min(slabs, s0 + per);
+  if (s0 < s1) {
+    load(fa[0], fb[0], s0 * 16);
+    for (int s = s0; s < s1; s += 2) {
+      load(fa[1], fb[1], (s + 1) * 16);
+      multiply(fa[0], fb[0]);
+      if (s + 1 < s1) {
+        load(fa[0], fb[0], (s + 2) * 16);
+        multiply(fa[1], fb[1]);
+      }
+    }
+  }
+
+  // A lane's quads: quad (i, q) is row m(i), columns n(q) .. n(q)+3.
+  auto row_of = [&](int i) { return m0 + (TA ? MI * lm + i : 16 * i + lm); };
+  auto col_of = [&](int q) { return n0 + (TB ? 16 * q + 4 * lg : 4 * NI * lg + 4 * q); };
+  auto quad = [&](int i, int q) {
+    f32x4 v;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      if constexpr (TB) v[e] = acc[i][q][e];
+      else v[e] = acc[i][(4 * q + e) % NI][(4 * q + e) / NI];   // column NI (4 lg + r) + j  <->  block j, register r
+    }
+    return v;
+  };
+  const float* bias = g.bias ? (const float*)g.bias + (int64_t)z * g.sBias : nullptr;
+  const float* R = g.resid ? (const float*)g.resid + (int64_t)z * g.sC : nullptr;
+  const bool rot = g.rope && z < g.rope_batches;
+  float* C = (float*)g.C + (int64_t)z * g.sC;
+  auto store = [&](f32x4 v, int m, int n) {
+    if (m >= g.M || n >= g.N) return;   // N is a multiple of 4
+    f32x4* pc = reinterpret_cast<f32x4*>(C + (int64_t)m * g.ldc + n);
+    if (bias) v += *reinterpret_cast<const f32x4*>(bias + n);
+    if (R) v += *reinterpret_cast<const f32x4*>(R + (int64_t)m * g.ldr + n);
+    if (rot) {
+      const f32x4 t = *reinterpret_cast<const f32x4*>(g.rope + (int64_t)(m % g.rope_S) * (g.rope_d / 2) + (n % g.rope_d) / 2);
+      v = f32x4{v[0] * t[0] - v[1] * t[1], v[0] * t[1] + v[1] * t[0], v[2] * t[2] - v[3] * t[3], v[2] * t[3] + v[3] * t[2]};
+    }
+    *pc = g.c_f32_accum ? *pc + v : v;
+  };
+  if constexpr (KW == 1) {
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+      for (int q = 0; q < NI; ++q) store(quad(i, q), row_of(i), col_of(q));
+  } else {
+    // quad s of the tile is stored by the wave kw = s % KW; the others leave theirs in LDS, and it adds them in the order of kw
+    constexpr int NW = WM * WN;
+#pragma unroll
+    for (int s = 0; s < NQ; ++s)
+      if (s % KW != kw) red[(((kw < s % KW ? kw : kw - 1) * NW + wt) * NQ + s) * 64 + lane] = quad(s / NI, s % NI);
+    __syncthreads();
+#pragma unroll
+    for (int s = 0; s < NQ; ++s)
+      if (s % KW == kw) {
+        f32x4 v = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int o = 0; o < KW; ++o)
+          v += o == kw ? quad(s / NI, s % NI) : red[(((o < kw ? o : o - 1) * NW + wt) * NQ + s) * 64 + lane];
+        store(v, row_of(s / NI), col_of(s % NI));
+      }
+  }
+}
+
+template <int MI, int NI, int WM, int WN, int KW> hipError_t launch(hipStream_t st, const Gemm& g) {
+  const int tm = (int)cdiv(g.M, 16 * MI * WM), tn = (int)cdiv(g.N, 16 * NI * WN);
+  dim3 grid((unsigned)(tm * tn), (unsigned)g.batch), blk(64 * WM * WN * KW);
+  if (g.kseg) hipLaunchKernelGGL((gemm_f32_kernel<0, 1, MI, NI, WM, WN, KW, 1>), grid, blk, 0, st, g, tm, tn);
+  else if (!g.transA && !g.transB) hipLaunchKernelGGL((gemm_f32_kernel<0, 0, MI, NI, WM, WN, KW, 0>), grid, blk, 0, st, g, tm, tn);
+  else if (!g.transA) hipLaunchKernelGGL((gemm_f32_kernel<0, 1, MI, NI, WM, WN, KW, 0>), grid, blk, 0, st, g, tm, tn);
+  else if (!g.transB) hipLaunchKernelGGL((gemm_f32_kernel<1, 0, MI, NI, WM, WN, KW, 0>), grid, blk, 0, st, g, tm, tn);
+  else hipLaunchKernelGGL((gemm_f32_kernel<1, 1, MI, NI, WM, WN, KW, 0>), grid, blk, 0, st, g, tm, tn);
+  return hipGetLastError();
+}
+
+}  // namespace
+
+// 16-byte loads and stores: aligned bases, strides and extents that are multiples of 4 (K only where an operand is
+// k-contiguous), and 32-bit byte offsets with room for a tile's overhang and the out-of-range push.
+bool gemm_f32_supported(const Gemm& g) {
+  auto al = [](const void* p) { return ((uintptr_t)p & 15) == 0; };
+  if (g.M < 1 || g.N < 1 || g.K < 1 || g.batch < 1 || g.batch > 65535 || g.nx || g.glu) return false;
+  if (!al(g.A) || !al(g.B) || !al(g.C) || g.lda % 4 || g.ldb % 4 || g.ldc % 4 || g.sA % 4 || g.sB % 4 || g.sC % 4) return false;
+  if (g.N % 4 || (g.transA && g.M % 4) || ((!g.transA || g.transB) && g.K % 4)) return false;
+  if (g.lda < (g.transA ? g.M : g.K) || g.ldc < g.N) return false;
+  if (g.bias && (!al(g.bias) || g.sBias % 4)) return false;
+  if (g.resid && (!al(g.resid) || g.ldr % 4)) return false;
+  if (g.rope && (!al(g.rope) || g.rope_d % 4 || g.rope_S < 1 || g.c_f32_accum)) return false;
+  if (g.kseg && (g.transA || !g.transB || g.kseg < 4 || g.kseg % 4 || g.segB % 4 || g.segB < 0 || g.K % g.kseg)) return false;
+  if (g.ldb < (!g.transB ? g.N : g.kseg ? g.kseg : g.K)) return false;
+  const int64_t rowsA = (g.transA ? g.K : g.M) + 160, rowsB = (g.transB ? g.N : g.K) + 160;   // a tile and two slabs over the end
+  const int64_t segs = g.kseg ? (g.K / g.kseg - 1) * g.segB : 0;
+  return rowsA * g.lda * 4 < (1ll << 30) && (rowsB * g.ldb + segs) * 4 < (1ll << 30);
+}
+
+// Which tile: 128x128 (4 waves of 64x64), 64x64 with K over 4 waves, or 32x32 with K over 8 waves.  The smaller ones exist
+// for outputs that give the 256 CUs too few workgroups; a wave of 32x32 loads twice the bytes per flop of one of 64x64.
+// The estimate: cycles of the busiest CU, at the 256 flops per cycle of its four matrix cores times what each form was
+// measured to reach of it, plus a fixed part per workgroup.
+hipError_t gemm_f32(hipStream_t st, const Gemm& g) {
+  auto cost = [&](int tile, double share) {
+    const int64_t wgs = cdiv(g.M, tile) * cdiv(g.N, tile) * g.batch;
+    return (double)cdiv(wgs, 256) * (2.0 * tile * tile * (double)g.K / (256.0 * share) + 1500.0);
+  };
+  const double big = cost(128, 0.8), mid = cost(64, 0.7), small = cost(32, 0.45);
+  if (small < mid && small < big) return launch<2, 2, 1, 1, 8>(st, g);
+  if (mid < big) return launch<4, 4, 1, 1, 4>(st, g);
+  return launch<4, 4, 2, 2, 1>(st, g);
+}
+
+}  // namespace zs

@@ -1,6 +1,5 @@
-// Plain LDS-tiled GEMM with fp32 FMA accumulation.  It serves the fp32 configuration (which may
-// not round below fp32 anywhere) and shapes the MFMA kernel does not take (unaligned leading
-// dimensions).  64x64x16 tiles, 256 threads, 4x4 outputs per thread, every access bounds-checked.
+// Plain LDS-tiled GEMM with fp32 FMA accumulation.  It serves the shapes that the matrix-core kernels do not take
+// (unaligned bases or leading dimensions, ragged contiguous extents, operands too large for 32-bit offsets).  64x64x16 tiles, 256 threads, 4x4 outputs per thread, every access bounds-checked.
 #include "kernels.h"
 
 #include <vector>
@@ -119,8 +118,8 @@ Gemm part_of(const Gemm& g, int p) {
   return a;
 }
 
-// One launch: the MFMA kernel when it takes the arguments, else the plain kernel (with the rotation and the
-// two-part K range done in extra passes).
+// One launch: the 16-bit or the fp32 matrix-core kernel when it takes the arguments, else the plain kernel (with the
+// rotation and the multi-part K range done in extra passes).
 hipError_t gemm_one(hipStream_t st, DType dt, const Gemm& g, int force) {
   if (gemm_select(dt, g, force) == GEMM_MFMA) return gemm_mfma(st, dt, g);   // rotation fused into its epilogue
   if (g.glu) {   // gated unit: the plain product(s), then the activation kernel over the dense [gate | up] rows
@@ -133,11 +132,12 @@ hipError_t gemm_one(hipStream_t st, DType dt, const Gemm& g, int force) {
   }
   if (g.nx) {   // multi-part K range: one plain product per part
     for (int p = 0; p <= g.nx; ++p) {
-      const hipError_t e = gemm_simple(st, dt, part_of(g, p));
+      const hipError_t e = gemm_one(st, dt, part_of(g, p), force);
       if (e != hipSuccess) return e;
     }
     return hipSuccess;
   }
+  if (dt == F32 && force != GEMM_SIMPLE && gemm_f32_supported(g)) return gemm_f32(st, g);   // rotation in its store
   hipError_t e = gemm_simple(st, dt, g);
   const int elem = dt == F32 ? 4 : 2;
   for (int z = 0; e == hipSuccess && g.rope && z < g.rope_batches && z < g.batch; ++z)

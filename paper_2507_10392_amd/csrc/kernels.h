@@ -70,6 +70,9 @@ hipError_t gemm(hipStream_t st, DType dt, const Gemm& g, int force);
 // True when gemm() runs the call as several MFMA launches because an operand exceeds the kernel's 2^30-byte range.
 bool gemm_splits(DType dt, const Gemm& g);
 hipError_t gemm_simple(hipStream_t st, DType dt, const Gemm& g);
+// fp32 products on the fp32 matrix cores (gemm_f32.hip); no multi-part K range, no gated unit.
+bool gemm_f32_supported(const Gemm& g);
+hipError_t gemm_f32(hipStream_t st, const Gemm& g);
 bool gemm_mfma_supported(DType dt, const Gemm& g);
 hipError_t gemm_mfma(hipStream_t st, DType dt, const Gemm& g);
 // Scratch bytes (Gemm::ws) with which gemm_mfma would cut the K range of this product's last round of tiles; 0 when

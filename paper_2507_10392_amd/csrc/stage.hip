@@ -419,11 +419,13 @@ DType dt_of(const stage_t* s) { return s->sh.dtype == STAGE_DTYPE_F16 ? F16 : s-
 
 bool do_gemm(stage_t* s, const Gemm& g) {
   const int impl = gemm_select(dt_of(s), g, GEMM_AUTO);
-  static const char* names[2][4] = {{"gemm_simple_nn", "gemm_simple_nt", "gemm_simple_tn", "gemm_simple_tt"},
-                                    {"gemm_mfma_nn", "gemm_mfma_nt", "gemm_mfma_tn", "gemm_mfma_tt"}};
+  static const char* names[3][4] = {{"gemm_simple_nn", "gemm_simple_nt", "gemm_simple_tn", "gemm_simple_tt"},
+                                    {"gemm_mfma_nn", "gemm_mfma_nt", "gemm_mfma_tn", "gemm_mfma_tt"},
+                                    {"gemm_f32_nn", "gemm_f32_nt", "gemm_f32_tn", "gemm_f32_tt"}};
+  const bool f32 = dt_of(s) == F32;   // the fp32 matrix-core kernel, or the plain one where its alignment rules are not met
   const bool mfma = impl == GEMM_MFMA || gemm_splits(dt_of(s), g);
   // the products that apply the gated unit in their store are kernels of their own and are timed as such
-  const char* cls = mfma && g.glu == 1 ? "gemm_mfma_nn_glu" : mfma && g.glu == 2 ? "gemm_mfma_nt_glu" : names[mfma][g.transA * 2 + g.transB];
+  const char* cls = mfma && g.glu == 1 ? "gemm_mfma_nn_glu" : mfma && g.glu == 2 ? "gemm_mfma_nt_glu" : names[f32 ? 2 : mfma][g.transA * 2 + g.transB];
   const double flops = 2.0 * g.M * g.N * g.K * (g.glu == 1 ? 2 : g.batch);
   return run(s, cls, flops, 0.0, [&] { return gemm(s->st, dt_of(s), g, GEMM_AUTO); });
 }

@@ -1,0 +1,81 @@
+"""The fp32 matrix-core kernels (what impl = 0 runs in the fp32 configuration) at the edges of their tiles, against float64."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2507_10392_amd as zs
+from harness import dev, log_report, rel_err
+
+pytestmark = pytest.mark.gpu
+
+
+def st():
+    return torch.cuda.current_stream().cuda_stream
+
+
+def back(t):
+    torch.cuda.synchronize()
+    return t.cpu().numpy().astype(np.float64)
+
+
+GEMM_CASES = [
+    # (M, N, K, transA, transB, batch, kseg, bias, resid, accum)
+    (4, 4, 4, 0, 1, 1, 0, True, True, False),             # one quad of outputs
+    (1, 4, 20, 0, 0, 1, 0, False, False, False),
+    (31, 36, 132, 0, 0, 2, 0, True, True, False),         # 32x32 tiles, ragged
+    (256, 260, 688, 0, 1, 3, 0, True, False, False),
+    (260, 64, 1, 1, 0, 1, 0, False, False, True),         # one row of K
+    (36, 1376, 77, 1, 0, 3, 0, True, True, True),         # odd K, accumulating with bias and residual
+    (520, 1000, 203, 1, 0, 2, 0, False, False, True),     # 64x64 tiles
+    (68, 72, 52, 1, 1, 1, 0, False, False, False),
+    (130, 68, 5 * 12, 0, 1, 1, 12, False, False, False),  # segments shorter than a slab
+    (257, 512, 2 * 344, 0, 1, 1, 344, False, False, False),
+    (1100, 2052, 260, 0, 0, 2, 0, True, True, False),     # 128x128 tiles, ragged
+    (1028, 2052, 131, 1, 0, 2, 0, False, False, True),
+    (130, 70, 50, 0, 0, 1, 0, True, True, False),         # contiguous extents that are no multiples of 4: the plain kernel
+]
+
+
+@pytest.mark.parametrize("case", GEMM_CASES, ids=lambda c: "x".join(str(int(v)) for v in c))
+def test_gemm_f32_matches_float64(gpu_device, case):
+    M, N, K, ta, tb, batch, kseg, use_bias, use_res, accum = case
+    print(f"[case] gemm f32 {case}", flush=True)
+    rng = np.random.default_rng(31)
+    f = lambda *s: rng.standard_normal(s).astype(np.float32)
+    A = f(batch, K, M) if ta else f(batch, M, K)
+    nseg = K // kseg if kseg else 1
+    B = f(nseg, N, kseg) if kseg else f(batch, N, K) if tb else f(batch, K, N)
+    bias, R, C0 = f(batch, N), f(batch, M, N), f(batch, M, N)
+    want = np.empty((batch, M, N))
+    for z in range(batch):
+        a = A[z].astype(np.float64).T if ta else A[z].astype(np.float64)
+        b = (np.concatenate([B[s].astype(np.float64).T for s in range(nseg)], axis=0) if kseg
+             else B[z].astype(np.float64).T if tb else B[z].astype(np.float64))
+        want[z] = a @ b + use_bias * bias[z][None, :] + use_res * R[z].astype(np.float64) + accum * C0[z]
+    dC = dev(C0) if accum else torch.full((batch, M, N), float("nan"), device="cuda")
+    dA, dB, dbias, dR = dev(A), dev(B), dev(bias) if use_bias else None, dev(R) if use_res else None
+    zs.ops.gemm(st(), 0, ta, tb, M, N, K, dA, M if ta else K, dB, (kseg or K) if tb else N, dC, N, int(accum), dbias, dR, N, batch,
+                M * K, 0 if kseg else N * K, M * N, N, kseg, N * kseg if kseg else 0, 0)
+    err = rel_err(back(dC), want)
+    log_report(f"gemm f32 {case}", [("C", err)])
+    # K roundings of at most half an ulp (6e-8) of partial sums that grow like sqrt(k): 6e-8 * sqrt(K) of the largest sum
+    # is 2e-6 at K = 1376; the bar of the other fp32 kernels is ten times that
+    assert err <= 2e-5
+
+
+def test_gemm_f32_rotation_in_the_store(gpu_device):
+    """Q|K|V projection as a batch of three whose first two results are rotated: as the plain product followed by
+    stage_op_rope, to fp32 rounding."""
+    mb, S, nh, d = 2, 37, 3, 40
+    T, H = mb * S, nh * d
+    print("[case] gemm f32 + rope", flush=True)
+    rng = np.random.default_rng(32)
+    x, w = dev(rng.standard_normal((T, H)).astype(np.float32)), dev(rng.standard_normal((3, H, H)).astype(np.float32))
+    table = torch.empty(S, d // 2, 2, device="cuda")
+    zs.ops.rope_table(st(), S, d, 10000.0, table)
+    got, want = (torch.full((T, 3 * H), float("nan"), device="cuda") for _ in range(2))
+    zs.ops.gemm_rope(st(), 0, 0, 0, T, H, H, x, H, w, H, got, 3 * H, 0, None, None, 0, 3, 0, H * H, H, 0, 0, 0, 0, table, S, d, 2)
+    zs.ops.gemm(st(), 0, 0, 0, T, H, H, x, H, w, H, want, 3 * H, 0, None, None, 0, 3, 0, H * H, H, 0, 0, 0, 1)
+    scratch = torch.empty(S, d // 2, 2, device="cuda")
+    zs.ops.rope(st(), 0, T, S, 2 * H, d, want, 3 * H, 10000.0, 1.0, scratch)
+    assert rel_err(back(got), back(want)) <= 2e-6
