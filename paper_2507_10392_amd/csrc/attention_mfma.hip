@@ -1,4 +1,5 @@
-// Flash-style causal attention on the CDNA4 matrix cores, head dim 128, bf16 in, fp32 softmax.
+// Flash-style causal attention on the CDNA4 matrix cores, 16-bit in, fp32 softmax: head dim 128, and (SPLIT) head dims below
+// it, padded with zeros to D = 64, 96 or 128.
 //
 // The S x S score matrix is never stored: K/V (forward, dQ) or Q/dO (dK/dV) tiles of 64 rows are
 // staged in LDS and every wavefront keeps its own 32 rows' operands and accumulators in
@@ -13,7 +14,17 @@
 // Backward is two kernels without atomics (fixed summation order): one owns 128 queries and
 // produces dQ, one owns 128 keys and produces dK and dV; both recompute P from the saved
 // log-sum-exp.  delta_i = dO_i . O_i is formed by the dQ kernel for its own rows and stored for the other.
+//
+// SPLIT: probabilities and dS do not lose their fp32 precision on the way into the second product: each goes in as a high
+// and a low 16-bit part (two matrix instructions on the same A fragment), which together carry 16 (bf16) or 22 (half) bits.
+// In half the low part is scaled by 2^11, and where small values matter absolutely (P and dS in the backward) it has
+// accumulators of its own, so that it stays out of the subnormal range.  The results are as far from float64 as those of the
+// wave-per-row fp32 kernel that served these head dims (4 x 16 heads of 64, S = 1000: 1.7e-3 in the outputs, their rounding, and
+// 4.3e-8 in lse; 4490 -> 124 us forward + backward in bf16, 136 us in half).  The scores' factor and the row sums are kept a
+// little better than one fp32 operation would (scale_lo, four partial sums), for the sake of lse, which is returned in fp32.
 #include "kernels.h"
+
+#include <cmath>
 
 // This file is compiled twice: as it stands for bf16, and through attention_mfma_f16.hip (which defines
 // ZS_ATTN_F16 and includes it) for IEEE half.  e16 is the 16-bit element type of the build; the two builds
@@ -33,13 +44,13 @@ namespace zs {
 
 namespace {
 
-constexpr int D = 128;             // head dim
 constexpr int TR = 64;             // rows of a staged tile
-// Padded LDS row length in elements: 304 bytes = 76 banks = 12 (mod 64).  The 16 rows that one cycle of a
-// row-fragment read touches then start in 16 different 4-bank groups (no conflicts); the 4 rows x 64 bytes
-// of a transposing read overlap in 4 of their 16 banks, the least any padding allows next to that.
-constexpr int LDT = D + 24;
-constexpr int TILE = TR * LDT;     // elements of one staged tile
+// Padded LDS row length in elements for (padded) head dim D: for D = 128, 304 bytes = 76 banks = 12 (mod 64).  The 16 rows
+// that one cycle of a row-fragment read touches then start in 16 different 4-bank groups (no conflicts); the 4 rows x 64 bytes
+// of a transposing read overlap in 4 of their 16 banks, the least any padding allows next to that.  D = 64 and 96 (44 and 60
+// banks) spread the 16 rows as well.
+template <int D> constexpr int LDT = D + 24;
+template <int D> constexpr int TILE = TR * LDT<D>;     // elements of one staged tile
 constexpr float LOG2E = 1.4426950408889634f;
 constexpr float LN2 = 0.6931471805599453f;
 
@@ -54,19 +65,19 @@ __device__ __forceinline__ e16x8 zero8() {
 }
 
 // A-operand fragment of a row-major LDS tile: lane (row = lane%32, g = lane/32) gets 8 consecutive columns.
-__device__ __forceinline__ e16x8 lds_frag(const e16* tile, int row0, int col0, int lane) {
-  return *reinterpret_cast<const e16x8*>(tile + (row0 + (lane & 31)) * LDT + col0 + 8 * (lane >> 5));
+template <int D> __device__ __forceinline__ e16x8 lds_frag(const e16* tile, int row0, int col0, int lane) {
+  return *reinterpret_cast<const e16x8*>(tile + (row0 + (lane & 31)) * LDT<D> + col0 + 8 * (lane >> 5));
 }
 
 // A-operand fragment of the TRANSPOSE of a row-major LDS tile M[k][n]: lane (i = lane%32, g = lane/32)
 // gets M[k][n0+i] for the 8 contraction slots  k = k0 + 4g + {0,1,2,3, 8,9,10,11}.  This slot order is
 // the order in which a lane's accumulator registers 8s..8s+7 of a 32-row MFMA block hold rows, so the
 // matching B operand is just those registers.
-__device__ __forceinline__ e16x8 lds_frag_tr(const e16* tile, int k0, int n0, int lane) {
+template <int D> __device__ __forceinline__ e16x8 lds_frag_tr(const e16* tile, int k0, int n0, int lane) {
   const int r = lane & 15, gi = lane >> 4;
-  const e16* p = tile + (k0 + 4 * (gi >> 1) + (r >> 2)) * LDT + n0 + 16 * (gi & 1) + 4 * (r & 3);
+  const e16* p = tile + (k0 + 4 * (gi >> 1) + (r >> 2)) * LDT<D> + n0 + 16 * (gi & 1) + 4 * (r & 3);
   const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)p);
-  const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p + 8 * LDT));
+  const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p + 8 * LDT<D>));
   union { struct { s16x4 a, b; } s; e16x8 v; } u;
   u.s.a = lo;
   u.s.b = hi;
@@ -80,43 +91,74 @@ __device__ __forceinline__ e16x8 pack8(const f32x16& a, int s) {
   return o;
 }
 
-// A 64 x 128 tile moves HBM -> registers (fetch, issued before the MFMAs of the current tile so the
-// latency hides behind them) -> LDS (put, after them).  Thread t carries 4 vectors of 16 bytes:
-// vector v = t + 256 i is row v/16, columns 8*(v%16)...
-template <int NT> struct TileRegs { e16x8 v[1024 / NT]; };   // NT threads share the 1024 vectors of a tile
-// Rows of one (batch, head) are read through a raw buffer descriptor over [first row, last row's 128 columns]:
-// the per-lane offset is one register, the tile's row offset a scalar, and rows at or past nrows fall
-// beyond num_records and read as zero without a branch.  Offsets are 32-bit: nrows * ld * 2 < 2^31.
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t head_rsrc(const e16* base, int64_t ld, int nrows) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<e16*>(base), 0, (int)((((int64_t)nrows - 1) * ld + D) * 2), 0x00020000);
-}
-template <int NT>
-__device__ __forceinline__ void fetch_tile(TileRegs<NT>& x, __amdgpu_buffer_rsrc_t rs, int ld, int row0, int tid) {
-  const int voff = ((tid >> 4) * ld + (tid & 15) * 8) * 2;
+// pack8 as a high and a low part: a = hi + lo * LO_UNIT up to 2^-17 (bf16) or 2^-22 (half) of it.
+#ifdef ZS_ATTN_F16
+constexpr float LO_SCALE = 2048.0f;   // the low half part is stored times 2^11
+constexpr bool LO_ACC = true;         // and needs accumulators of its own
+#else
+constexpr float LO_SCALE = 1.0f;
+constexpr bool LO_ACC = false;
+#endif
+constexpr float LO_UNIT = 1.0f / LO_SCALE;
+// dS goes in times 2^-4 in half, which leaves 2^20 of range on top; its low part still resolves 2^-32.
+constexpr float DS_SCALE = LO_ACC ? 0.0625f : 1.0f;
+__device__ __forceinline__ e16x8 pack8_lo(const f32x16& a, int s, const e16x8& hi, float lo_scale) {
+  e16x8 o;
 #pragma unroll
-  for (int i = 0; i < 1024 / NT; ++i) {
+  for (int e = 0; e < 8; ++e) o[e] = (e16)((a[8 * s + e] - (float)hi[e]) * lo_scale);
+  return o;
+}
+
+// A 64 x D tile moves HBM -> registers (fetch, issued before the MFMAs of the current tile so the
+// latency hides behind them) -> LDS (put, after them).  For D = 128 thread t carries 4 vectors of 16 bytes:
+// vector v = t + 256 i is row v/16, columns 8*(v%16)...
+template <int NT, int D> struct TileRegs { e16x8 v[8 * D / NT]; };   // NT threads share the 64 D/8 vectors of a tile
+// Rows of one (batch, head) are read through a raw buffer descriptor over [first row, last row's dd columns]:
+// the per-lane offset is one register (D = 96: three), the tile's row offset a scalar, and rows at or past nrows fall
+// beyond num_records and read as zero without a branch, as do the columns dd..D-1 of a padded head, whose offset is pushed
+// there.  Offsets are 32-bit: nrows * ld * 2 < 2^31.
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t head_rsrc(const e16* base, int64_t ld, int nrows, int dd) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<e16*>(base), 0, (int)((((int64_t)nrows - 1) * ld + dd) * 2), 0x00020000);
+}
+template <int NT, int D>
+__device__ __forceinline__ void fetch_tile(TileRegs<NT, D>& x, __amdgpu_buffer_rsrc_t rs, int ld, int row0, unsigned tid, int dd) {
+  constexpr unsigned RV = D / 8;   // vectors per row
+#pragma unroll
+  for (int i = 0; i < (int)(TR * RV / NT); ++i) {
     union { u32x4 u; e16x8 h; } c;
-    c.u = __builtin_amdgcn_raw_buffer_load_b128(rs, voff, (row0 + (NT / 16) * i) * ld * 2, 0);
+    if constexpr (NT % RV == 0) {
+      const int col = (int)(tid % RV) * 8;
+      const int voff = col < dd ? ((int)(tid / RV) * ld + col) * 2 : (int)0x80000000;
+      c.u = __builtin_amdgcn_raw_buffer_load_b128(rs, voff, (row0 + (int)(NT / RV) * i) * ld * 2, 0);
+    } else {
+      const unsigned v = tid + NT * i;
+      const int col = (int)(v % RV) * 8;
+      const int voff = col < dd ? ((int)(v / RV) * ld + col) * 2 : (int)0x80000000;
+      c.u = __builtin_amdgcn_raw_buffer_load_b128(rs, voff, row0 * ld * 2, 0);
+    }
     x.v[i] = c.h;
   }
 }
-template <int NT> __device__ __forceinline__ void put_tile(const TileRegs<NT>& x, e16* tile, int tid) {
+template <int NT, int D> __device__ __forceinline__ void put_tile(const TileRegs<NT, D>& x, e16* tile, unsigned tid) {
 #pragma unroll
-  for (int i = 0; i < 1024 / NT; ++i) {
-    const int v = tid + NT * i;
-    *reinterpret_cast<e16x8*>(tile + (v >> 4) * LDT + (v & 15) * 8) = x.v[i];
+  for (int i = 0; i < 8 * D / NT; ++i) {
+    const unsigned v = tid + NT * i;
+    *reinterpret_cast<e16x8*>(tile + (v / (D / 8)) * LDT<D> + (v % (D / 8)) * 8) = x.v[i];
   }
 }
 
 // Row fragments kept in registers for a whole kernel: lane (row = row0 + lane%32, g) holds, for each of the
-// 8 contraction steps over d, 8 consecutive elements.  Rows >= nrows read as zero.
-__device__ __forceinline__ void load_row_frags(e16x8 (&f)[8], const e16* __restrict__ src, int64_t ld, int row0,
-                                               int nrows, int lane) {
+// D/16 contraction steps over d, 8 consecutive elements.  Rows >= nrows and columns >= dd read as zero.
+template <int D>
+__device__ __forceinline__ void load_row_frags(e16x8 (&f)[D / 16], const e16* __restrict__ src, int64_t ld, int row0,
+                                               int nrows, int lane, int dd) {
   const int row = row0 + (lane & 31);
 #pragma unroll
-  for (int s = 0; s < 8; ++s)
-    f[s] = row < nrows ? *reinterpret_cast<const e16x8*>(src + (int64_t)row * ld + 16 * s + 8 * (lane >> 5)) : zero8();
+  for (int s = 0; s < D / 16; ++s) {
+    const int c = 16 * s + 8 * (lane >> 5);
+    f[s] = row < nrows && c < dd ? *reinterpret_cast<const e16x8*>(src + (int64_t)row * ld + c) : zero8();
+  }
 }
 
 // Row index (inside a 32-row MFMA block) held by accumulator register r of this lane.
@@ -136,8 +178,8 @@ __device__ __forceinline__ BlockId block_id(int nh, int mb) {
 // Inverse rotary rotation of 4 consecutive head-dim values (two adjacent pairs) of position pos, first
 // value at head-dim index d0 (a multiple of 4): (u, w) -> (u c + w s, -u s + w c).
 typedef float f32x4v __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ void unrotate4(float (&x)[4], const float2* __restrict__ rope, int pos, int d0) {
-  const f32x4v t = *reinterpret_cast<const f32x4v*>(rope + (int64_t)pos * (D / 2) + d0 / 2);   // (cos, sin) x 2
+__device__ __forceinline__ void unrotate4(float (&x)[4], const float2* __restrict__ rope, int pos, int d0, int dd) {
+  const f32x4v t = *reinterpret_cast<const f32x4v*>(rope + (int64_t)pos * (dd / 2) + d0 / 2);   // (cos, sin) x 2
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
     const float c = t[2 * i], sn = t[2 * i + 1], u = x[2 * i], w = x[2 * i + 1];
@@ -150,47 +192,48 @@ __device__ __forceinline__ void unrotate4(float (&x)[4], const float2* __restric
 // grid ceil(S/(32 NW))*nh*mb, NW waves; wave w owns queries q0 + 32w .. +31; heavy (late) blocks are launched first.
 // NW = 4: two workgroups per CU.  NW = 8: one workgroup per CU whose staged K/V tiles serve 256 queries, so a wave
 // issues half as many tile loads and LDS stores per key tile (used when that still gives every CU a workgroup).
-template <int NW>
+template <int NW, int D, bool SPLIT>
 __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_fwd_kernel(int S, const e16* __restrict__ q, const e16* __restrict__ k,
                                                        const e16* __restrict__ v, int64_t ld, e16* __restrict__ o,
-                                                       int64_t ldo, float* __restrict__ lse, float scale_log2, int nh,
-                                                       int mb) {
+                                                       int64_t ldo, float* __restrict__ lse, float scale_log2, float scale_lo,
+                                                       int nh, int mb, int head_dim) {
+  const int dd = SPLIT ? head_dim : D;
   extern __shared__ __align__(16) char smem_raw[];
   e16* smem = reinterpret_cast<e16*>(smem_raw);            // [2][K tile | V tile]
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const BlockId bid = block_id(nh, mb);
   const int qb = (S + 32 * NW - 1) / (32 * NW) - 1 - bid.rank, h = bid.h, b = bid.b;
   const int64_t tok0 = (int64_t)b * S;
-  const e16* qh = q + tok0 * ld + h * D;
-  const e16* kh = k + tok0 * ld + h * D;
-  const e16* vh = v + tok0 * ld + h * D;
-  const __amdgpu_buffer_rsrc_t rsk = head_rsrc(kh, ld, S), rsv = head_rsrc(vh, ld, S);
+  const e16* qh = q + tok0 * ld + h * dd;
+  const e16* kh = k + tok0 * ld + h * dd;
+  const e16* vh = v + tok0 * ld + h * dd;
+  const __amdgpu_buffer_rsrc_t rsk = head_rsrc(kh, ld, S, dd), rsv = head_rsrc(vh, ld, S, dd);
   const int q0 = qb * 32 * NW, wq0 = q0 + wave * 32;
   const int my_q = wq0 + (lane & 31);
 
-  e16x8 qf[8];
-  load_row_frags(qf, qh, ld, wq0, S, lane);
-  f32x16 oacc[4];
+  e16x8 qf[D / 16];
+  load_row_frags<D>(qf, qh, ld, wq0, S, lane, dd);
+  f32x16 oacc[D / 32];
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < D / 32; ++i)
 #pragma unroll
     for (int r = 0; r < 16; ++r) oacc[i][r] = 0.f;
   float m = -INFINITY, l = 0.f;
 
   const int last_q = min(q0 + 32 * NW - 1, S - 1);
   const int ntiles = last_q / TR + 1;
-  TileRegs<64 * NW> kr, vr;
-  fetch_tile(kr, rsk, (int)ld, 0, tid);
-  fetch_tile(vr, rsv, (int)ld, 0, tid);
+  TileRegs<64 * NW, D> kr, vr;
+  fetch_tile(kr, rsk, (int)ld, 0, tid, dd);
+  fetch_tile(vr, rsv, (int)ld, 0, tid, dd);
   put_tile(kr, smem, tid);
-  put_tile(vr, smem + TILE, tid);
+  put_tile(vr, smem + TILE<D>, tid);
   __syncthreads();
   for (int t = 0; t < ntiles; ++t) {
-    const e16* Kt = smem + (t & 1) * 2 * TILE;
-    const e16* Vt = Kt + TILE;
+    const e16* Kt = smem + (t & 1) * 2 * TILE<D>;
+    const e16* Vt = Kt + TILE<D>;
     if (t + 1 < ntiles) {
-      fetch_tile(kr, rsk, (int)ld, (t + 1) * TR, tid);
-      fetch_tile(vr, rsv, (int)ld, (t + 1) * TR, tid);
+      fetch_tile(kr, rsk, (int)ld, (t + 1) * TR, tid, dd);
+      fetch_tile(vr, rsv, (int)ld, (t + 1) * TR, tid, dd);
     }
     const int key0 = t * TR;
     if (key0 <= wq0 + 31) {   // otherwise every key of the tile is in this wave's future
@@ -200,8 +243,8 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_fwd_kernel(int 
 #pragma unroll
         for (int r = 0; r < 16; ++r) sacc[jb][r] = 0.f;
 #pragma unroll
-        for (int s = 0; s < 8; ++s)
-          sacc[jb] = ZS_ATTN_MFMA(lds_frag(Kt, jb * 32, 16 * s, lane), qf[s], sacc[jb], 0, 0, 0);
+        for (int s = 0; s < D / 16; ++s)
+          sacc[jb] = ZS_ATTN_MFMA(lds_frag<D>(Kt, jb * 32, 16 * s, lane), qf[s], sacc[jb], 0, 0, 0);
       }
       if (key0 + TR - 1 > wq0) {   // tile touches the diagonal: mask keys in the future of this lane's query
 #pragma unroll
@@ -226,19 +269,23 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_fwd_kernel(int 
         l *= alpha;
         m = mn;
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < D / 32; ++i)
 #pragma unroll
           for (int r = 0; r < 16; ++r) oacc[i][r] *= alpha;
       }
-      float rs = 0.f;
+      float rs = 0.f, part[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int jb = 0; jb < 2; ++jb)
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-          const float p = __builtin_amdgcn_exp2f(fmaf(sacc[jb][r], scale_log2, -m));
+          float x = fmaf(sacc[jb][r], scale_log2, -m);
+          if constexpr (SPLIT) x = fmaf(sacc[jb][r], scale_lo, x);
+          const float p = __builtin_amdgcn_exp2f(x);
           sacc[jb][r] = p;
-          rs += p;
+          if constexpr (SPLIT) part[r & 3] += p;
+          else rs += p;
         }
+      if constexpr (SPLIT) rs = (part[0] + part[1]) + (part[2] + part[3]);
       rs += __shfl_xor(rs, 32, 64);
       l += rs;
 #pragma unroll
@@ -246,31 +293,38 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_fwd_kernel(int 
 #pragma unroll
         for (int s2 = 0; s2 < 2; ++s2) {
           const e16x8 pf = pack8(sacc[jb], s2);
+          e16x8 pl = pf;
+          if constexpr (SPLIT) pl = pack8_lo(sacc[jb], s2, pf, 1.0f);   // P <= 2^8 of a sum l >= 1: no low accumulator needed
 #pragma unroll
-          for (int db = 0; db < 4; ++db)
-            oacc[db] = ZS_ATTN_MFMA(lds_frag_tr(Vt, jb * 32 + 16 * s2, db * 32, lane), pf,
-                                                               oacc[db], 0, 0, 0);
+          for (int db = 0; db < D / 32; ++db) {
+            const e16x8 vf = lds_frag_tr<D>(Vt, jb * 32 + 16 * s2, db * 32, lane);
+            oacc[db] = ZS_ATTN_MFMA(vf, pf, oacc[db], 0, 0, 0);
+            if constexpr (SPLIT) oacc[db] = ZS_ATTN_MFMA(vf, pl, oacc[db], 0, 0, 0);
+          }
         }
     }
     if (t + 1 < ntiles) {   // the other buffer was last read before the barrier that ended the previous iteration
-      put_tile(kr, smem + ((t + 1) & 1) * 2 * TILE, tid);
-      put_tile(vr, smem + ((t + 1) & 1) * 2 * TILE + TILE, tid);
+      put_tile(kr, smem + ((t + 1) & 1) * 2 * TILE<D>, tid);
+      put_tile(vr, smem + ((t + 1) & 1) * 2 * TILE<D> + TILE<D>, tid);
     }
     __syncthreads();
   }
   if (my_q < S) {
     const float inv = 1.0f / l;
-    e16* orow = o + (tok0 + my_q) * ldo + h * D;
+    e16* orow = o + (tok0 + my_q) * ldo + h * dd;
 #pragma unroll
-    for (int db = 0; db < 4; ++db)
+    for (int db = 0; db < D / 32; ++db)
 #pragma unroll
       for (int c = 0; c < 4; ++c) {
         e16x4 w;
 #pragma unroll
         for (int e = 0; e < 4; ++e) w[e] = (e16)(oacc[db][4 * c + e] * inv);
-        *reinterpret_cast<e16x4*>(orow + db * 32 + 8 * c + 4 * (lane >> 5)) = w;
+        if (!SPLIT || db * 32 + 8 * c + 4 * (lane >> 5) < dd)
+          *reinterpret_cast<e16x4*>(orow + db * 32 + 8 * c + 4 * (lane >> 5)) = w;
       }
-    if (lane < 32) lse[((int64_t)b * nh + h) * S + my_q] = (m + log2f(l)) * LN2;
+    if (lane < 32)   // SPLIT: formed in double, once per row: m may lag the maximum by 8, so log l alone would round like lse does
+      lse[((int64_t)b * nh + h) * S + my_q] =
+          SPLIT ? (float)((double)m * 0.6931471805599453 + log((double)l)) : (m + log2f(l)) * LN2;
   }
 }
 
@@ -278,67 +332,68 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_fwd_kernel(int 
 // grid ceil(S/(32 NW))*nh*mb, NW waves (4 or 8 as in the forward kernel); wave w owns queries q0+32w..; loops over K/V
 // tiles up to the diagonal.
 // dQ^T[d][q] += K^T[d][key] dS^T[key][q],  dS^T = P^T o (dP^T - delta_q),  dP^T = V dO^T.
-template <int NW>
-__global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_bwd_dq_kernel(int S, const e16* __restrict__ q, const e16* __restrict__ k,
+template <int NW, int D, bool SPLIT>
+__global__ __launch_bounds__(64 * NW, NW == 4 && !(SPLIT && LO_ACC && D > 64) ? 2 : 1) void attn_bwd_dq_kernel(int S, const e16* __restrict__ q, const e16* __restrict__ k,
                                                           const e16* __restrict__ v, int64_t ld,
                                                           const e16* __restrict__ o, const e16* __restrict__ dout,
                                                           int64_t ldo, const float* __restrict__ lse,
                                                           float* __restrict__ delta,
                                                           e16* __restrict__ dq, int64_t ldd, float scale, int nh,
-                                                          int mb, const float2* __restrict__ rope) {
+                                                          int mb, const float2* __restrict__ rope, int head_dim) {
+  const int dd = SPLIT ? head_dim : D;
   extern __shared__ __align__(16) char smem_raw[];
   e16* smem = reinterpret_cast<e16*>(smem_raw);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const BlockId bid = block_id(nh, mb);
   const int qb = (S + 32 * NW - 1) / (32 * NW) - 1 - bid.rank, h = bid.h, b = bid.b;
   const int64_t tok0 = (int64_t)b * S;
-  const e16* qh = q + tok0 * ld + h * D;
-  const e16* kh = k + tok0 * ld + h * D;
-  const e16* vh = v + tok0 * ld + h * D;
-  const e16* doh = dout + tok0 * ldo + h * D;
-  const __amdgpu_buffer_rsrc_t rsk = head_rsrc(kh, ld, S), rsv = head_rsrc(vh, ld, S);
+  const e16* qh = q + tok0 * ld + h * dd;
+  const e16* kh = k + tok0 * ld + h * dd;
+  const e16* vh = v + tok0 * ld + h * dd;
+  const e16* doh = dout + tok0 * ldo + h * dd;
+  const __amdgpu_buffer_rsrc_t rsk = head_rsrc(kh, ld, S, dd), rsv = head_rsrc(vh, ld, S, dd);
   const int q0 = qb * 32 * NW, wq0 = q0 + wave * 32;
   const int my_q = wq0 + (lane & 31);
   const float scale_log2 = scale * LOG2E;
 
-  e16x8 qf[8], dof[8];
-  load_row_frags(qf, qh, ld, wq0, S, lane);
-  load_row_frags(dof, doh, ldo, wq0, S, lane);
+  e16x8 qf[D / 16], dof[D / 16];
+  load_row_frags<D>(qf, qh, ld, wq0, S, lane, dd);
+  load_row_frags<D>(dof, doh, ldo, wq0, S, lane, dd);
   const int64_t stat = ((int64_t)b * nh + h) * S + min(my_q, S - 1);
   const float lse2 = lse[stat] * LOG2E;
   // delta_q = dO_q . O_q: each lane sums its 64 of the row's 128 products, lane^32 holds the others.
   // The value is also stored for the dK/dV kernel, which runs after this one.
   float dlt = 0.f;
   {
-    e16x8 of[8];
-    load_row_frags(of, o + tok0 * ldo + h * D, ldo, wq0, S, lane);
+    e16x8 of[D / 16];
+    load_row_frags<D>(of, o + tok0 * ldo + h * dd, ldo, wq0, S, lane, dd);
 #pragma unroll
-    for (int s = 0; s < 8; ++s)
+    for (int s = 0; s < D / 16; ++s)
 #pragma unroll
       for (int e = 0; e < 8; ++e) dlt = fmaf((float)dof[s][e], (float)of[s][e], dlt);
     dlt += __shfl_xor(dlt, 32, 64);
     if (lane < 32 && my_q < S) delta[stat] = dlt;
   }
-  f32x16 acc[4];
+  f32x16 acc[D / 32], acclo[SPLIT && LO_ACC ? D / 32 : 1];
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < D / 32; ++i)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc[i][r] = 0.f;
+    for (int r = 0; r < 16; ++r) { acc[i][r] = 0.f; if (SPLIT && LO_ACC) acclo[SPLIT && LO_ACC ? i : 0][r] = 0.f; }
 
   const int last_q = min(q0 + 32 * NW - 1, S - 1);
   const int ntiles = last_q / TR + 1;
-  TileRegs<64 * NW> kr, vr;
-  fetch_tile(kr, rsk, (int)ld, 0, tid);
-  fetch_tile(vr, rsv, (int)ld, 0, tid);
+  TileRegs<64 * NW, D> kr, vr;
+  fetch_tile(kr, rsk, (int)ld, 0, tid, dd);
+  fetch_tile(vr, rsv, (int)ld, 0, tid, dd);
   put_tile(kr, smem, tid);
-  put_tile(vr, smem + TILE, tid);
+  put_tile(vr, smem + TILE<D>, tid);
   __syncthreads();
   for (int t = 0; t < ntiles; ++t) {
-    const e16* Kt = smem + (t & 1) * 2 * TILE;
-    const e16* Vt = Kt + TILE;
+    const e16* Kt = smem + (t & 1) * 2 * TILE<D>;
+    const e16* Vt = Kt + TILE<D>;
     if (t + 1 < ntiles) {
-      fetch_tile(kr, rsk, (int)ld, (t + 1) * TR, tid);
-      fetch_tile(vr, rsv, (int)ld, (t + 1) * TR, tid);
+      fetch_tile(kr, rsk, (int)ld, (t + 1) * TR, tid, dd);
+      fetch_tile(vr, rsv, (int)ld, (t + 1) * TR, tid, dd);
     }
     const int key0 = t * TR;
     if (key0 <= wq0 + 31) {
@@ -349,12 +404,12 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_bwd_dq_kernel(i
 #pragma unroll
         for (int r = 0; r < 16; ++r) sacc[r] = pacc[r] = 0.f;
 #pragma unroll
-        for (int s = 0; s < 8; ++s) {
-          sacc = ZS_ATTN_MFMA(lds_frag(Kt, jb * 32, 16 * s, lane), qf[s], sacc, 0, 0, 0);
-          pacc = ZS_ATTN_MFMA(lds_frag(Vt, jb * 32, 16 * s, lane), dof[s], pacc, 0, 0, 0);
+        for (int s = 0; s < D / 16; ++s) {
+          sacc = ZS_ATTN_MFMA(lds_frag<D>(Kt, jb * 32, 16 * s, lane), qf[s], sacc, 0, 0, 0);
+          pacc = ZS_ATTN_MFMA(lds_frag<D>(Vt, jb * 32, 16 * s, lane), dof[s], pacc, 0, 0, 0);
         }
 #pragma unroll
-        for (int r = 0; r < 16; ++r) sacc[r] = __builtin_amdgcn_exp2f(fmaf(sacc[r], scale_log2, -lse2)) * (pacc[r] - dlt);
+        for (int r = 0; r < 16; ++r) sacc[r] = __builtin_amdgcn_exp2f(fmaf(sacc[r], scale_log2, -lse2)) * (pacc[r] - dlt) * (SPLIT ? DS_SCALE : 1.0f);
         if (diag) {   // keys in the future of this lane's query contribute nothing
 #pragma unroll
           for (int r = 0; r < 16; ++r)
@@ -363,29 +418,39 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_bwd_dq_kernel(i
 #pragma unroll
         for (int s2 = 0; s2 < 2; ++s2) {
           const e16x8 dsf = pack8(sacc, s2);
+          e16x8 dsl = dsf;
+          if constexpr (SPLIT) dsl = pack8_lo(sacc, s2, dsf, LO_SCALE);
 #pragma unroll
-          for (int db = 0; db < 4; ++db)
-            acc[db] = ZS_ATTN_MFMA(lds_frag_tr(Kt, jb * 32 + 16 * s2, db * 32, lane), dsf,
-                                                              acc[db], 0, 0, 0);
+          for (int db = 0; db < D / 32; ++db) {
+            const e16x8 kt = lds_frag_tr<D>(Kt, jb * 32 + 16 * s2, db * 32, lane);
+            acc[db] = ZS_ATTN_MFMA(kt, dsf, acc[db], 0, 0, 0);
+            if constexpr (SPLIT) {
+              f32x16& a = LO_ACC ? acclo[LO_ACC ? db : 0] : acc[db];
+              a = ZS_ATTN_MFMA(kt, dsl, a, 0, 0, 0);
+            }
+          }
         }
       }
     }
     if (t + 1 < ntiles) {   // the other buffer was last read before the barrier that ended the previous iteration
-      put_tile(kr, smem + ((t + 1) & 1) * 2 * TILE, tid);
-      put_tile(vr, smem + ((t + 1) & 1) * 2 * TILE + TILE, tid);
+      put_tile(kr, smem + ((t + 1) & 1) * 2 * TILE<D>, tid);
+      put_tile(vr, smem + ((t + 1) & 1) * 2 * TILE<D> + TILE<D>, tid);
     }
     __syncthreads();
   }
   if (my_q < S) {
-    e16* row = dq + (tok0 + my_q) * ldd + h * D;
+    e16* row = dq + (tok0 + my_q) * ldd + h * dd;
 #pragma unroll
-    for (int db = 0; db < 4; ++db)
+    for (int db = 0; db < D / 32; ++db)
 #pragma unroll
       for (int c = 0; c < 4; ++c) {
+        if (SPLIT && db * 32 + 8 * c + 4 * (lane >> 5) >= dd) continue;
         float x[4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) x[e] = acc[db][4 * c + e] * scale;
-        if (rope) unrotate4(x, rope, my_q, db * 32 + 8 * c + 4 * (lane >> 5));
+        for (int e = 0; e < 4; ++e)
+          x[e] = SPLIT && LO_ACC ? fmaf(acclo[SPLIT && LO_ACC ? db : 0][4 * c + e], LO_UNIT, acc[db][4 * c + e]) * (scale / DS_SCALE)
+                                 : acc[db][4 * c + e] * scale;
+        if (rope) unrotate4(x, rope, my_q, db * 32 + 8 * c + 4 * (lane >> 5), dd);
         e16x4 w;
 #pragma unroll
         for (int e = 0; e < 4; ++e) w[e] = (e16)x[e];
@@ -400,25 +465,26 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_bwd_dq_kernel(i
 // softmax arithmetic overlaps the other's MFMAs.
 // S[q][key] = Q K^T (lane = key, registers = queries), P = exp2(S c - lse_q), dP = dO V^T,
 // dV^T[d][key] += dO^T[d][q] P[q][key],  dK^T[d][key] += Q^T[d][q] dS[q][key].
-template <int NW>
+template <int NW, int D, bool SPLIT>
 __global__ __launch_bounds__(64 * NW) void attn_bwd_dkv_kernel(int S, const e16* __restrict__ q, const e16* __restrict__ k,
                                                            const e16* __restrict__ v, int64_t ld,
                                                            const e16* __restrict__ dout, int64_t ldo,
                                                            const float* __restrict__ lse, const float* __restrict__ delta,
                                                            e16* __restrict__ dk, e16* __restrict__ dv, int64_t ldd,
-                                                           float scale, int nh, int mb, const float2* __restrict__ rope) {
+                                                           float scale, int nh, int mb, const float2* __restrict__ rope, int head_dim) {
+  const int dd = SPLIT ? head_dim : D;
   extern __shared__ __align__(16) char smem_raw[];
   e16* smem = reinterpret_cast<e16*>(smem_raw);                 // [2][Q tile | dO tile]
-  float* stats = reinterpret_cast<float*>(smem + 4 * TILE);       // [2][lse2[64] | delta[64]]
+  float* stats = reinterpret_cast<float*>(smem + 4 * TILE<D>);       // [2][lse2[64] | delta[64]]
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const BlockId bid = block_id(nh, mb);
   const int kb = bid.rank, h = bid.h, b = bid.b;                   // early key blocks (most work) first
   const int64_t tok0 = (int64_t)b * S;
-  const e16* qh = q + tok0 * ld + h * D;
-  const e16* kh = k + tok0 * ld + h * D;
-  const e16* vh = v + tok0 * ld + h * D;
-  const e16* doh = dout + tok0 * ldo + h * D;
-  const __amdgpu_buffer_rsrc_t rsq = head_rsrc(qh, ld, S), rsdo = head_rsrc(doh, ldo, S);
+  const e16* qh = q + tok0 * ld + h * dd;
+  const e16* kh = k + tok0 * ld + h * dd;
+  const e16* vh = v + tok0 * ld + h * dd;
+  const e16* doh = dout + tok0 * ldo + h * dd;
+  const __amdgpu_buffer_rsrc_t rsq = head_rsrc(qh, ld, S, dd), rsdo = head_rsrc(doh, ldo, S, dd);
   const float* lse_h = lse + ((int64_t)b * nh + h) * S;
   const float* dlt_h = delta + ((int64_t)b * nh + h) * S;
   const int k0 = kb * 32 * NW, wk0 = k0 + wave * 32;
@@ -428,26 +494,29 @@ __global__ __launch_bounds__(64 * NW) void attn_bwd_dkv_kernel(int S, const e16*
   // K fragments stay in registers; the wave's 32 rows of V go to a private LDS block instead and are
   // read back as B operands (same fragment pattern as the A operands), which keeps the kernel within
   // the register budget of two waves per SIMD.
-  e16x8 kf[8];
-  load_row_frags(kf, kh, ld, wk0, S, lane);
-  e16* Vw = reinterpret_cast<e16*>(stats + 256) + wave * 32 * LDT;
+  e16x8 kf[D / 16];
+  load_row_frags<D>(kf, kh, ld, wk0, S, lane, dd);
+  e16* Vw = reinterpret_cast<e16*>(stats + 256) + wave * 32 * LDT<D>;
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    const int vv = lane + 64 * i, r = vv >> 4, c = (vv & 15) * 8;
-    *reinterpret_cast<e16x8*>(Vw + r * LDT + c) =
-        wk0 + r < S ? *reinterpret_cast<const e16x8*>(vh + (int64_t)(wk0 + r) * ld + c) : zero8();
+  for (int i = 0; i < D / 16; ++i) {
+    const int vv = lane + 64 * i, r = vv / (D / 8), c = (vv % (D / 8)) * 8;
+    *reinterpret_cast<e16x8*>(Vw + r * LDT<D> + c) =
+        wk0 + r < S && c < dd ? *reinterpret_cast<const e16x8*>(vh + (int64_t)(wk0 + r) * ld + c) : zero8();
   }
-  f32x16 dkacc[4], dvacc[4];
+  f32x16 dkacc[D / 32], dvacc[D / 32], dklo[SPLIT && LO_ACC ? D / 32 : 1], dvlo[SPLIT && LO_ACC ? D / 32 : 1];
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < D / 32; ++i)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) dkacc[i][r] = dvacc[i][r] = 0.f;
+    for (int r = 0; r < 16; ++r) {
+      dkacc[i][r] = dvacc[i][r] = 0.f;
+      if (SPLIT && LO_ACC) dklo[SPLIT && LO_ACC ? i : 0][r] = dvlo[SPLIT && LO_ACC ? i : 0][r] = 0.f;
+    }
 
-  TileRegs<64 * NW> qr, dor;
+  TileRegs<64 * NW, D> qr, dor;
   float statr = 0.f;
   auto fetch = [&](int t) {
-    fetch_tile(qr, rsq, (int)ld, t * TR, tid);
-    fetch_tile(dor, rsdo, (int)ldo, t * TR, tid);
+    fetch_tile(qr, rsq, (int)ld, t * TR, tid, dd);
+    fetch_tile(dor, rsdo, (int)ldo, t * TR, tid, dd);
     if (tid < 128) {
       const int r = t * TR + (tid & 63);
       statr = 0.f;
@@ -455,8 +524,8 @@ __global__ __launch_bounds__(64 * NW) void attn_bwd_dkv_kernel(int S, const e16*
     }
   };
   auto put = [&](int buf) {
-    put_tile(qr, smem + buf * 2 * TILE, tid);
-    put_tile(dor, smem + buf * 2 * TILE + TILE, tid);
+    put_tile(qr, smem + buf * 2 * TILE<D>, tid);
+    put_tile(dor, smem + buf * 2 * TILE<D> + TILE<D>, tid);
     if (tid < 128) stats[buf * 128 + tid] = statr;
   };
   const int t_begin = k0 / TR, t_end = (S - 1) / TR + 1;
@@ -465,8 +534,8 @@ __global__ __launch_bounds__(64 * NW) void attn_bwd_dkv_kernel(int S, const e16*
   __syncthreads();
   for (int t = t_begin; t < t_end; ++t) {
     const int buf = (t - t_begin) & 1;
-    const e16* Qt = smem + buf * 2 * TILE;
-    const e16* dOt = Qt + TILE;
+    const e16* Qt = smem + buf * 2 * TILE<D>;
+    const e16* dOt = Qt + TILE<D>;
     const float* st = stats + buf * 128;
     if (t + 1 < t_end) fetch(t + 1);
     const int qrow0 = t * TR;
@@ -478,9 +547,9 @@ __global__ __launch_bounds__(64 * NW) void attn_bwd_dkv_kernel(int S, const e16*
 #pragma unroll
         for (int r = 0; r < 16; ++r) sacc[r] = pacc[r] = 0.f;
 #pragma unroll
-        for (int s = 0; s < 8; ++s) {
-          sacc = ZS_ATTN_MFMA(lds_frag(Qt, ib * 32, 16 * s, lane), kf[s], sacc, 0, 0, 0);
-          pacc = ZS_ATTN_MFMA(lds_frag(dOt, ib * 32, 16 * s, lane), lds_frag(Vw, 0, 16 * s, lane), pacc,
+        for (int s = 0; s < D / 16; ++s) {
+          sacc = ZS_ATTN_MFMA(lds_frag<D>(Qt, ib * 32, 16 * s, lane), kf[s], sacc, 0, 0, 0);
+          pacc = ZS_ATTN_MFMA(lds_frag<D>(dOt, ib * 32, 16 * s, lane), lds_frag<D>(Vw, 0, 16 * s, lane), pacc,
                                                          0, 0, 0);
         }
 #pragma unroll
@@ -488,7 +557,7 @@ __global__ __launch_bounds__(64 * NW) void attn_bwd_dkv_kernel(int S, const e16*
           const int qi = ib * 32 + acc_row(r, lane);
           const float p = __builtin_amdgcn_exp2f(fmaf(sacc[r], scale_log2, -st[qi]));
           sacc[r] = p;
-          pacc[r] = p * (pacc[r] - st[64 + qi]);
+          pacc[r] = p * (pacc[r] - st[64 + qi]) * (SPLIT ? DS_SCALE : 1.0f);
         }
         if (diag || qrow0 + TR > S) {   // queries before this lane's key, and rows past the end, contribute nothing
 #pragma unroll
@@ -500,12 +569,22 @@ __global__ __launch_bounds__(64 * NW) void attn_bwd_dkv_kernel(int S, const e16*
 #pragma unroll
         for (int s2 = 0; s2 < 2; ++s2) {
           const e16x8 pf = pack8(sacc, s2), dsf = pack8(pacc, s2);
+          e16x8 pl = pf, dsl = dsf;
+          if constexpr (SPLIT) { pl = pack8_lo(sacc, s2, pf, LO_SCALE); dsl = pack8_lo(pacc, s2, dsf, LO_SCALE); }
 #pragma unroll
-          for (int db = 0; db < 4; ++db) {
-            dvacc[db] = ZS_ATTN_MFMA(lds_frag_tr(dOt, ib * 32 + 16 * s2, db * 32, lane), pf,
-                                                                dvacc[db], 0, 0, 0);
-            dkacc[db] = ZS_ATTN_MFMA(lds_frag_tr(Qt, ib * 32 + 16 * s2, db * 32, lane), dsf,
-                                                                dkacc[db], 0, 0, 0);
+          for (int db = 0; db < D / 32; ++db) {
+            const e16x8 dot = lds_frag_tr<D>(dOt, ib * 32 + 16 * s2, db * 32, lane);
+            dvacc[db] = ZS_ATTN_MFMA(dot, pf, dvacc[db], 0, 0, 0);
+            if constexpr (SPLIT) {
+              f32x16& a = LO_ACC ? dvlo[LO_ACC ? db : 0] : dvacc[db];
+              a = ZS_ATTN_MFMA(dot, pl, a, 0, 0, 0);
+            }
+            const e16x8 qt = lds_frag_tr<D>(Qt, ib * 32 + 16 * s2, db * 32, lane);
+            dkacc[db] = ZS_ATTN_MFMA(qt, dsf, dkacc[db], 0, 0, 0);
+            if constexpr (SPLIT) {
+              f32x16& a = LO_ACC ? dklo[LO_ACC ? db : 0] : dkacc[db];
+              a = ZS_ATTN_MFMA(qt, dsl, a, 0, 0, 0);
+            }
           }
         }
       }
@@ -514,21 +593,26 @@ __global__ __launch_bounds__(64 * NW) void attn_bwd_dkv_kernel(int S, const e16*
     __syncthreads();
   }
   if (my_k < S) {
-    e16* krow = dk + (tok0 + my_k) * ldd + h * D;
-    e16* vrow = dv + (tok0 + my_k) * ldd + h * D;
+    e16* krow = dk + (tok0 + my_k) * ldd + h * dd;
+    e16* vrow = dv + (tok0 + my_k) * ldd + h * dd;
 #pragma unroll
-    for (int db = 0; db < 4; ++db)
+    for (int db = 0; db < D / 32; ++db)
 #pragma unroll
       for (int c = 0; c < 4; ++c) {
-        float x[4];
+        if (SPLIT && db * 32 + 8 * c + 4 * (lane >> 5) >= dd) continue;
+        float x[4], y[4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) x[e] = dkacc[db][4 * c + e] * scale;
-        if (rope) unrotate4(x, rope, my_k, db * 32 + 8 * c + 4 * (lane >> 5));
+        for (int e = 0; e < 4; ++e) {
+          x[e] = SPLIT && LO_ACC ? fmaf(dklo[SPLIT && LO_ACC ? db : 0][4 * c + e], LO_UNIT, dkacc[db][4 * c + e]) * (scale / DS_SCALE)
+                                 : dkacc[db][4 * c + e] * scale;
+          y[e] = SPLIT && LO_ACC ? fmaf(dvlo[SPLIT && LO_ACC ? db : 0][4 * c + e], LO_UNIT, dvacc[db][4 * c + e]) : dvacc[db][4 * c + e];
+        }
+        if (rope) unrotate4(x, rope, my_k, db * 32 + 8 * c + 4 * (lane >> 5), dd);
         e16x4 wk, wv;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           wk[e] = (e16)x[e];
-          wv[e] = (e16)dvacc[db][4 * c + e];
+          wv[e] = (e16)y[e];
         }
         *reinterpret_cast<e16x4*>(krow + db * 32 + 8 * c + 4 * (lane >> 5)) = wk;
         *reinterpret_cast<e16x4*>(vrow + db * 32 + 8 * c + 4 * (lane >> 5)) = wv;
@@ -536,8 +620,10 @@ __global__ __launch_bounds__(64 * NW) void attn_bwd_dkv_kernel(int S, const e16*
   }
 }
 
-constexpr size_t SMEM_FWD = 4 * TILE * sizeof(e16);                    // 77824
-constexpr size_t smem_dkv(int nw) { return 4 * TILE * sizeof(e16) + 256 * sizeof(float) + (size_t)nw * 32 * LDT * sizeof(e16); }
+template <int D> constexpr size_t SMEM_FWD = 4 * TILE<D> * sizeof(e16);                    // 77824 for D = 128
+template <int D> constexpr size_t smem_dkv(int nw) {
+  return 4 * TILE<D> * sizeof(e16) + 256 * sizeof(float) + (size_t)nw * 32 * LDT<D> * sizeof(e16);
+}
 
 // Blocks of 256 rows (8 waves) instead of 128 (4 waves): for the key blocks of the dK/dV kernel whenever that still
 // gives every CU a workgroup; for the query blocks of the forward and dQ kernels only from S = 4096 on (measured: 7 % and
@@ -553,58 +639,85 @@ template <typename K> hipError_t set_smem(K kern, size_t bytes, bool& done) {
   return e;
 }
 
+// One launch of each kernel with NW waves; `set` remembers that its LDS size has been allowed.
+template <int NW, int D, bool SPLIT>
+hipError_t launch_fwd(hipStream_t st, int mb, int S, int nh, int d, const void* q, const void* k, const void* v, int64_t ld, void* o,
+                      int64_t ldo, float* lse) {
+  static bool set = false;
+  const hipError_t e = set_smem(attn_fwd_kernel<NW, D, SPLIT>, SMEM_FWD<D>, set);
+  if (e != hipSuccess) return e;
+  // SPLIT adds scale_lo * score: above zero, so that a masked score stays -inf
+  float hi = LOG2E / sqrtf((float)d), lo = 0.f;
+  if (SPLIT) {
+    const double c = 1.4426950408889634 / sqrt((double)d);
+    if ((double)hi >= c) hi = nextafterf(hi, 0.f);
+    lo = (float)(c - (double)hi);
+  }
+  hipLaunchKernelGGL((attn_fwd_kernel<NW, D, SPLIT>), dim3((unsigned)(cdiv(S, 32 * NW) * nh * mb)), dim3(64 * NW), SMEM_FWD<D>, st, S,
+                     (const e16*)q, (const e16*)k, (const e16*)v, ld, (e16*)o, ldo, lse, hi, lo, nh, mb, d);
+  return hipGetLastError();
+}
+template <int NW, int D, bool SPLIT>
+hipError_t launch_dq(hipStream_t st, int mb, int S, int nh, int d, const void* q, const void* k, const void* v, int64_t ld, const void* o,
+                     const void* dout, int64_t ldo, const float* lse, float* delta, void* dq, int64_t ldd, const float2* rope) {
+  static bool set = false;
+  const hipError_t e = set_smem(attn_bwd_dq_kernel<NW, D, SPLIT>, SMEM_FWD<D>, set);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((attn_bwd_dq_kernel<NW, D, SPLIT>), dim3((unsigned)(cdiv(S, 32 * NW) * nh * mb)), dim3(64 * NW), SMEM_FWD<D>, st,
+                     S, (const e16*)q, (const e16*)k, (const e16*)v, ld, (const e16*)o, (const e16*)dout, ldo, lse, delta, (e16*)dq,
+                     ldd, 1.0f / sqrtf((float)d), nh, mb, rope, d);
+  return hipGetLastError();
+}
+template <int NW, int D, bool SPLIT>
+hipError_t launch_dkv(hipStream_t st, int mb, int S, int nh, int d, const void* q, const void* k, const void* v, int64_t ld,
+                      const void* dout, int64_t ldo, const float* lse, const float* delta, void* dk, void* dv, int64_t ldd,
+                      const float2* rope) {
+  static bool set = false;
+  const hipError_t e = set_smem(attn_bwd_dkv_kernel<NW, D, SPLIT>, smem_dkv<D>(NW), set);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((attn_bwd_dkv_kernel<NW, D, SPLIT>), dim3((unsigned)(cdiv(S, 32 * NW) * nh * mb)), dim3(64 * NW), smem_dkv<D>(NW),
+                     st, S, (const e16*)q, (const e16*)k, (const e16*)v, ld, (const e16*)dout, ldo, lse, delta, (e16*)dk, (e16*)dv,
+                     ldd, 1.0f / sqrtf((float)d), nh, mb, rope, d);
+  return hipGetLastError();
+}
+template <int D>
+hipError_t bwd_split(hipStream_t st, int mb, int S, int nh, int d, const void* q, const void* k, const void* v, int64_t ld, const void* o,
+                     const void* dout, int64_t ldo, const float* lse, float* delta, void* dq, void* dk, void* dv, int64_t ldd,
+                     const float2* rope) {
+  const hipError_t e = launch_dq<4, D, true>(st, mb, S, nh, d, q, k, v, ld, o, dout, ldo, lse, delta, dq, ldd, rope);
+  return e != hipSuccess ? e : launch_dkv<4, D, true>(st, mb, S, nh, d, q, k, v, ld, dout, ldo, lse, delta, dk, dv, ldd, rope);
+}
+
 }  // namespace
 
 #ifndef ZS_ATTN_F16
-bool attn_mfma_supported(DType dt, int S, int d) { return (dt == BF16 || dt == F16) && d == D && S >= 1; }
+bool attn_mfma_supported(DType dt, int S, int d) { return (dt == BF16 || dt == F16) && d == 128 && S >= 1; }
 #endif
 
 hipError_t ZS_ATTN_NAME(attn_fwd_mfma)(hipStream_t st, int mb, int S, int nh, int d, const void* q, const void* k, const void* v,
                          int64_t ld, void* o, int64_t ldo, float* lse) {
   if ((int64_t)S * ld * 2 >= (1ll << 31)) return hipErrorInvalidValue;      // 32-bit buffer offsets
-  static bool cfg4 = false, cfg8 = false;
-  hipError_t e = set_smem(attn_fwd_kernel<4>, SMEM_FWD, cfg4);
-  if (e == hipSuccess) e = set_smem(attn_fwd_kernel<8>, SMEM_FWD, cfg8);
-  if (e != hipSuccess) return e;
+  if (d <= 64) return launch_fwd<4, 64, true>(st, mb, S, nh, d, q, k, v, ld, o, ldo, lse);
+  if (d <= 96) return launch_fwd<4, 96, true>(st, mb, S, nh, d, q, k, v, ld, o, ldo, lse);
+  if (d < 128) return launch_fwd<4, 128, true>(st, mb, S, nh, d, q, k, v, ld, o, ldo, lse);
   // 256 queries per workgroup when that still gives every CU a workgroup, else 128
-  if (wide_query_blocks(S, nh, mb))
-    hipLaunchKernelGGL(attn_fwd_kernel<8>, dim3((unsigned)(cdiv(S, 256) * nh * mb)), dim3(512), SMEM_FWD, st, S, (const e16*)q,
-                       (const e16*)k, (const e16*)v, ld, (e16*)o, ldo, lse, LOG2E / sqrtf((float)d), nh, mb);
-  else
-    hipLaunchKernelGGL(attn_fwd_kernel<4>, dim3((unsigned)(cdiv(S, 128) * nh * mb)), dim3(256), SMEM_FWD, st, S, (const e16*)q,
-                       (const e16*)k, (const e16*)v, ld, (e16*)o, ldo, lse, LOG2E / sqrtf((float)d), nh, mb);
-  return hipGetLastError();
+  return wide_query_blocks(S, nh, mb) ? launch_fwd<8, 128, false>(st, mb, S, nh, d, q, k, v, ld, o, ldo, lse)
+                                      : launch_fwd<4, 128, false>(st, mb, S, nh, d, q, k, v, ld, o, ldo, lse);
 }
 
 hipError_t ZS_ATTN_NAME(attn_bwd_mfma)(hipStream_t st, int mb, int S, int nh, int d, const void* q, const void* k, const void* v,
                          int64_t ld, const void* o, const void* dout, int64_t ldo, const float* lse, float* delta,
                          void* dq, void* dk, void* dv, int64_t ldd, const float2* rope) {
   if ((int64_t)S * (ld > ldo ? ld : ldo) * 2 >= (1ll << 31)) return hipErrorInvalidValue;   // 32-bit buffer offsets
-  static bool cfg1 = false, cfg1b = false, cfg2 = false, cfg3 = false;
-  hipError_t e = set_smem(attn_bwd_dq_kernel<4>, SMEM_FWD, cfg1);
-  if (e == hipSuccess) e = set_smem(attn_bwd_dq_kernel<8>, SMEM_FWD, cfg1b);
-  if (e == hipSuccess) e = set_smem(attn_bwd_dkv_kernel<4>, smem_dkv(4), cfg2);
-  if (e == hipSuccess) e = set_smem(attn_bwd_dkv_kernel<8>, smem_dkv(8), cfg3);
+  if (d <= 64) return bwd_split<64>(st, mb, S, nh, d, q, k, v, ld, o, dout, ldo, lse, delta, dq, dk, dv, ldd, rope);
+  if (d <= 96) return bwd_split<96>(st, mb, S, nh, d, q, k, v, ld, o, dout, ldo, lse, delta, dq, dk, dv, ldd, rope);
+  if (d < 128) return bwd_split<128>(st, mb, S, nh, d, q, k, v, ld, o, dout, ldo, lse, delta, dq, dk, dv, ldd, rope);
+  const hipError_t e =
+      wide_query_blocks(S, nh, mb) ? launch_dq<8, 128, false>(st, mb, S, nh, d, q, k, v, ld, o, dout, ldo, lse, delta, dq, ldd, rope)
+                                   : launch_dq<4, 128, false>(st, mb, S, nh, d, q, k, v, ld, o, dout, ldo, lse, delta, dq, ldd, rope);
   if (e != hipSuccess) return e;
-  const float scale = 1.0f / sqrtf((float)d);
-  dim3 grid((unsigned)(cdiv(S, 128) * nh * mb)), blk(256);
-  const bool wide = wide_blocks(S, nh, mb);
-  if (wide_query_blocks(S, nh, mb))
-    hipLaunchKernelGGL(attn_bwd_dq_kernel<8>, dim3((unsigned)(cdiv(S, 256) * nh * mb)), dim3(512), SMEM_FWD, st, S, (const e16*)q,
-                       (const e16*)k, (const e16*)v, ld, (const e16*)o, (const e16*)dout, ldo, lse, delta, (e16*)dq, ldd, scale, nh,
-                       mb, rope);
-  else
-    hipLaunchKernelGGL(attn_bwd_dq_kernel<4>, grid, blk, SMEM_FWD, st, S, (const e16*)q, (const e16*)k, (const e16*)v, ld,
-                       (const e16*)o, (const e16*)dout, ldo, lse, delta, (e16*)dq, ldd, scale, nh, mb, rope);
-  if (wide) {
-    hipLaunchKernelGGL(attn_bwd_dkv_kernel<8>, dim3((unsigned)(cdiv(S, 256) * nh * mb)), dim3(512), smem_dkv(8), st,
-                       S, (const e16*)q, (const e16*)k, (const e16*)v, ld, (const e16*)dout, ldo, lse, delta, (e16*)dk,
-                       (e16*)dv, ldd, scale, nh, mb, rope);
-  } else {
-    hipLaunchKernelGGL(attn_bwd_dkv_kernel<4>, grid, blk, smem_dkv(4), st, S, (const e16*)q, (const e16*)k, (const e16*)v, ld,
-                       (const e16*)dout, ldo, lse, delta, (e16*)dk, (e16*)dv, ldd, scale, nh, mb, rope);
-  }
-  return hipGetLastError();
+  return wide_blocks(S, nh, mb) ? launch_dkv<8, 128, false>(st, mb, S, nh, d, q, k, v, ld, dout, ldo, lse, delta, dk, dv, ldd, rope)
+                                : launch_dkv<4, 128, false>(st, mb, S, nh, d, q, k, v, ld, dout, ldo, lse, delta, dk, dv, ldd, rope);
 }
 
 }  // namespace zs

@@ -1,6 +1,6 @@
 // Causal softmax attention, forward and backward, one wavefront per query (or key) row, fp32
-// arithmetic, no atomics.  This is the path of the fp32 configuration and of head sizes the MFMA
-// kernel does not take; it never materialises the S x S matrix (online softmax over tiles of
+// arithmetic, no atomics.  This is the path of the fp32 configuration, of head sizes above 128 and of unaligned
+// rows, which the matrix-core kernels do not take; it never materialises the S x S matrix (online softmax over tiles of
 // 64 keys) but makes no attempt to reuse K/V across rows.
 #include "kernels.h"
 
@@ -220,9 +220,16 @@ int attn_select(DType dt, int S, int d, int force) {
   return attn_mfma_supported(dt, S, d) ? ATTN_MFMA : ATTN_SIMPLE;
 }
 
+// 16-bit heads narrower than 128 also run on the matrix cores (their fp32 probabilities split in two 16-bit parts), when
+// rows can be read in aligned 16-byte pieces through 32-bit offsets; else, and for wider heads, a wavefront per row.
+static bool attn_split_ok(DType dt, int S, int d, int force, int64_t ld_max, uintptr_t pointers, int64_t strides) {
+  return dt != F32 && force != ATTN_SIMPLE && d < 128 && (pointers & 15) == 0 && strides % 8 == 0 && (int64_t)S * ld_max * 2 < (1ll << 31);
+}
+
 hipError_t attn_fwd(hipStream_t st, DType dt, int mb, int S, int nh, int d, const void* q, const void* k,
                     const void* v, int64_t ld, void* o, int64_t ldo, float* lse, int force) {
-  if (attn_select(dt, S, d, force) == ATTN_MFMA)
+  const uintptr_t at = (uintptr_t)q | (uintptr_t)k | (uintptr_t)v | (uintptr_t)o;
+  if (attn_select(dt, S, d, force) == ATTN_MFMA || attn_split_ok(dt, S, d, force, ld, at, ld | ldo))
     return dt == F16 ? attn_fwd_mfma_f16(st, mb, S, nh, d, q, k, v, ld, o, ldo, lse)
                      : attn_fwd_mfma(st, mb, S, nh, d, q, k, v, ld, o, ldo, lse);
   return dt == F32    ? fwd_simple<float>(st, mb, S, nh, d, q, k, v, ld, o, ldo, lse)
@@ -232,7 +239,10 @@ hipError_t attn_fwd(hipStream_t st, DType dt, int mb, int S, int nh, int d, cons
 hipError_t attn_bwd(hipStream_t st, DType dt, int mb, int S, int nh, int d, const void* q, const void* k,
                     const void* v, int64_t ld, const void* o, const void* dout, int64_t ldo, const float* lse,
                     float* delta, void* dq, void* dk, void* dv, int64_t ldd, const float2* rope, int force) {
-  if (attn_select(dt, S, d, force) == ATTN_MFMA)   // rotation fused into the kernels' stores
+  const uintptr_t at = (uintptr_t)q | (uintptr_t)k | (uintptr_t)v | (uintptr_t)o | (uintptr_t)dout | (uintptr_t)dq | (uintptr_t)dk |
+                       (uintptr_t)dv | (uintptr_t)rope;
+  if (attn_select(dt, S, d, force) == ATTN_MFMA ||   // rotation fused into the kernels' stores
+      attn_split_ok(dt, S, d, force, ld > ldo ? ld : ldo, at, ld | ldo | ldd))
     return dt == F16 ? attn_bwd_mfma_f16(st, mb, S, nh, d, q, k, v, ld, o, dout, ldo, lse, delta, dq, dk, dv, ldd, rope)
                      : attn_bwd_mfma(st, mb, S, nh, d, q, k, v, ld, o, dout, ldo, lse, delta, dq, dk, dv, ldd, rope);
   hipError_t e = dt == F32    ? bwd_simple<float>(st, mb, S, nh, d, q, k, v, ld, o, dout, ldo, lse, delta, dq, dk, dv, ldd)
