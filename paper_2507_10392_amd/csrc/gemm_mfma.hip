@@ -16,13 +16,16 @@ int g_force_tile = 0;   // 0 automatic; 1: 256x256, 2: 128x128 (set through gemm
 
 // The kernel needs 16-byte aligned rows for its vector loads: base pointers 16-byte aligned and
 // every leading dimension, batch stride and segment size a multiple of 8 elements; the extent
-// along each operand's contiguous axis must be a multiple of 8 as well.
-bool gemm_mfma_supported(DType dt, const Gemm& g) {
+// along each operand's contiguous axis must be a multiple of 8 as well.  K may be anything when neither operand is
+// k-contiguous (weight gradients over an odd number of tokens): k-lines past the end lie behind both descriptors.
+bool gemm_mfma_supported(DType dt, const Gemm& g) { return g.K % 8 == 0 && gemm_mfma_takes(dt, g); }
+
+bool gemm_mfma_takes(DType dt, const Gemm& g) {
   if (dt != BF16 && dt != F16) return false;
   if (g.M < 1 || g.N < 1 || g.K < 1 || g.batch < 1) return false;
   if (!aligned16(g.A) || !aligned16(g.B)) return false;
   if (g.lda % 8 || g.ldb % 8 || g.sA % 8 || g.sB % 8) return false;
-  if (g.K % 8) return false;                       // k-contiguous operands are read 8 k at a time; tails are zero-filled
+  if (g.K % 8 && !(g.transA && !g.transB)) return false;   // k-contiguous operands are read 8 k at a time; tails are zero-filled
   if (g.transA && g.M % 8) return false;           // row-contiguous operands are read 8 rows at a time
   if (!g.transB && g.N % 8) return false;
   if (g.glu) {   // gated unit fused into the store
@@ -123,7 +126,7 @@ bool split_tail(DType dt, const Gemm& g, Gemm& head, Gemm& tail) {
   const int64_t boff = (g.transB ? n1 * g.ldb : n1) * 2;
   tail.B = (const char*)g.B + boff;
   for (int p = 0; p < g.nx; ++p) tail.Bx[p] = (const char*)g.Bx[p] + boff;
-  return gemm_mfma_supported(dt, head) && gemm_mfma_supported(dt, tail);
+  return gemm_mfma_takes(dt, head) && gemm_mfma_takes(dt, tail);
 }
 
 // ---- K range of the last round's tiles cut into chunks -------------------------------------------------------------
@@ -214,7 +217,7 @@ hipError_t gemm_mfma(hipStream_t st, DType dt, const Gemm& g) {
   const bool small = gemm_mfma_pick_tile(g) == 2;
   if (g.ws && !g_force_tile) {
     KCut k;
-    if (plan_kcut(dt, g, k) && k.ws_need <= g.ws_bytes && ((uintptr_t)g.ws & 15) == 0 && gemm_mfma_supported(dt, g)) {
+    if (plan_kcut(dt, g, k) && k.ws_need <= g.ws_bytes && ((uintptr_t)g.ws & 15) == 0 && gemm_mfma_takes(dt, g)) {
       hipError_t e = run_tile(st, dt, k.head, false);
       if (e != hipSuccess) return e;
       e = run_tile(st, dt, k.tail, false);

@@ -105,7 +105,7 @@ hipError_t gemm_simple(hipStream_t st, DType dt, const Gemm& g) {
 
 int gemm_select(DType dt, const Gemm& g, int force) {
   if (force == GEMM_SIMPLE) return GEMM_SIMPLE;
-  return gemm_mfma_supported(dt, g) ? GEMM_MFMA : GEMM_SIMPLE;
+  return gemm_mfma_takes(dt, g) ? GEMM_MFMA : GEMM_SIMPLE;
 }
 
 namespace {
@@ -196,11 +196,11 @@ bool split_k(const Gemm& g, std::vector<Gemm>& parts) {
 }  // namespace
 
 bool gemm_splits(DType dt, const Gemm& g) {
-  if (dt == F32 || gemm_mfma_supported(dt, g)) return false;
+  if (dt == F32 || gemm_mfma_takes(dt, g)) return false;
   std::vector<Gemm> parts;
   if (!(split_rows(g, parts) || split_k(g, parts))) return false;
   for (const Gemm& p : parts)
-    if (!gemm_mfma_supported(dt, p)) return false;
+    if (!gemm_mfma_takes(dt, p)) return false;
   return true;
 }
 
@@ -210,7 +210,7 @@ hipError_t gemm(hipStream_t st, DType dt, const Gemm& g, int force) {
         g.c_f32_accum || g.bias || g.resid || g.rope || g.kseg || g.nx || g.ldc != g.N || g.gu_ld != 2ll * g.N || g.gu_up != g.N)
       return hipErrorInvalidValue;
   }
-  if (dt != F32 && force != GEMM_SIMPLE && !gemm_mfma_supported(dt, g)) {
+  if (dt != F32 && force != GEMM_SIMPLE && !gemm_mfma_takes(dt, g)) {
     std::vector<Gemm> parts;
     if (g.nx) {   // the parts of a multi-part weight gradient on their own, each cut further if it has to be
       for (int p = 0; p <= g.nx; ++p) {

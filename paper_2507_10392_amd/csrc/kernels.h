@@ -73,6 +73,9 @@ hipError_t gemm_simple(hipStream_t st, DType dt, const Gemm& g);
 // fp32 products on the fp32 matrix cores (gemm_f32.hip); no multi-part K range, no gated unit.
 bool gemm_f32_supported(const Gemm& g);
 hipError_t gemm_f32(hipStream_t st, const Gemm& g);
+// What the 16-bit MFMA kernel takes (the dispatcher's rule), and the narrower set (K a multiple of 8) for which a caller may
+// force it.
+bool gemm_mfma_takes(DType dt, const Gemm& g);
 bool gemm_mfma_supported(DType dt, const Gemm& g);
 hipError_t gemm_mfma(hipStream_t st, DType dt, const Gemm& g);
 // Scratch bytes (Gemm::ws) with which gemm_mfma would cut the K range of this product's last round of tiles; 0 when

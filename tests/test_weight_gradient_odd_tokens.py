@@ -1,0 +1,36 @@
+"""16-bit weight gradients over a number of tokens that is no multiple of 8, on the matrix cores (impl = 0)."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2507_10392_amd as zs
+from harness import dev, log_report, rel_err
+from workloads import round_bf16, round_f16
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dtype", [1, 2])
+@pytest.mark.parametrize("M,N,T,batch", [(8, 8, 1, 1), (136, 264, 7, 2), (264, 136, 65, 1), (520, 1376, 1021, 3), (2048, 2056, 127, 1)])
+def test_weight_gradient_over_an_odd_number_of_tokens(gpu_device, dtype, M, N, T, batch):
+    print(f"[case] wgrad M={M} N={N} T={T} batch={batch} dtype={dtype}", flush=True)
+    rng = np.random.default_rng(51)
+    rnd, td = (round_bf16, torch.bfloat16) if dtype == 1 else (round_f16, torch.float16)
+    # rows behind the last token hold inf: nothing past it may be read into the sums
+    x, dy = (rnd(rng.standard_normal((T + 9, w)).astype(np.float32)) for w in (M, batch * N))
+    x[T:], dy[T:] = np.inf, np.inf
+    C0 = rng.standard_normal((batch, M, N)).astype(np.float32)
+    C = dev(C0)
+    zs.ops.gemm(torch.cuda.current_stream().cuda_stream, dtype, 1, 0, M, N, T, dev(x, td), M, dev(dy, td), batch * N, C, N, 1, None, None, 0,
+                batch, 0, N, M * N, 0, 0, 0, 0)
+    torch.cuda.synchronize()
+    want = np.stack([C0[z] + x[:T].astype(np.float64).T @ dy[:T, z * N:(z + 1) * N].astype(np.float64) for z in range(batch)])
+    err = rel_err(C.cpu().numpy(), want)
+    log_report(f"odd wgrad {M} {N} {T} {batch} {dtype}", [("C", err)])
+    assert err <= 2e-5            # exact 16-bit products, fp32 sums: the bar of the other accumulating products
+
+
+def test_forced_matrix_core_kernel_still_wants_multiples_of_8(gpu_device):
+    x, dy, C = (torch.zeros(64, 64, device="cuda", dtype=t) for t in (torch.bfloat16, torch.bfloat16, torch.float32))
+    with pytest.raises(zs.StageError):
+        zs.ops.gemm(torch.cuda.current_stream().cuda_stream, 1, 1, 0, 64, 64, 63, x, 64, dy, 64, C, 64, 1, None, None, 0, 1, 0, 0, 0, 0, 0, 0, 2)
