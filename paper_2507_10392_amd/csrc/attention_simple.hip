@@ -1,6 +1,6 @@
 // Causal softmax attention, forward and backward, one wavefront per query (or key) row, fp32
-// arithmetic, no atomics.  This is the path of the fp32 configuration, of head sizes above 128 and of unaligned
-// rows, which the matrix-core kernels do not take; it never materialises the S x S matrix (online softmax over tiles of
+// arithmetic, no atomics.  This is the path of head sizes above 128 and of unaligned rows, which the matrix-core
+// kernels do not take; it never materialises the S x S matrix (online softmax over tiles of
 // 64 keys) but makes no attempt to reuse K/V across rows.
 #include "kernels.h"
 
@@ -214,6 +214,12 @@ hipError_t attn_bwd_mfma_f16(hipStream_t st, int mb, int S, int nh, int d, const
                              int64_t ld, const void* o, const void* dout, int64_t ldo, const float* lse, float* delta,
                              void* dq, void* dk, void* dv, int64_t ldd, const float2* rope);
 bool attn_mfma_supported(DType dt, int S, int d);
+hipError_t attn_fwd_f32(hipStream_t st, int mb, int S, int nh, int d, const void* q, const void* k, const void* v,
+                        int64_t ld, void* o, int64_t ldo, float* lse);
+hipError_t attn_bwd_f32(hipStream_t st, int mb, int S, int nh, int d, const void* q, const void* k, const void* v,
+                        int64_t ld, const void* o, const void* dout, int64_t ldo, const float* lse, float* delta,
+                        void* dq, void* dk, void* dv, int64_t ldd, const float2* rope);
+bool attn_f32_supported(int mb, int S, int nh, int d, int64_t ld_max, uintptr_t pointers, int64_t strides);
 
 int attn_select(DType dt, int S, int d, int force) {
   if (force == ATTN_SIMPLE) return ATTN_SIMPLE;
@@ -232,6 +238,8 @@ hipError_t attn_fwd(hipStream_t st, DType dt, int mb, int S, int nh, int d, cons
   if (attn_select(dt, S, d, force) == ATTN_MFMA || attn_split_ok(dt, S, d, force, ld, at, ld | ldo))
     return dt == F16 ? attn_fwd_mfma_f16(st, mb, S, nh, d, q, k, v, ld, o, ldo, lse)
                      : attn_fwd_mfma(st, mb, S, nh, d, q, k, v, ld, o, ldo, lse);
+  if (dt == F32 && force != ATTN_SIMPLE && attn_f32_supported(mb, S, nh, d, ld, at, ld | ldo))
+    return attn_fwd_f32(st, mb, S, nh, d, q, k, v, ld, o, ldo, lse);
   return dt == F32    ? fwd_simple<float>(st, mb, S, nh, d, q, k, v, ld, o, ldo, lse)
          : dt == BF16 ? fwd_simple<bf16>(st, mb, S, nh, d, q, k, v, ld, o, ldo, lse)
                       : fwd_simple<f16>(st, mb, S, nh, d, q, k, v, ld, o, ldo, lse);
@@ -245,6 +253,8 @@ hipError_t attn_bwd(hipStream_t st, DType dt, int mb, int S, int nh, int d, cons
       attn_split_ok(dt, S, d, force, ld > ldo ? ld : ldo, at, ld | ldo | ldd))
     return dt == F16 ? attn_bwd_mfma_f16(st, mb, S, nh, d, q, k, v, ld, o, dout, ldo, lse, delta, dq, dk, dv, ldd, rope)
                      : attn_bwd_mfma(st, mb, S, nh, d, q, k, v, ld, o, dout, ldo, lse, delta, dq, dk, dv, ldd, rope);
+  if (dt == F32 && force != ATTN_SIMPLE && attn_f32_supported(mb, S, nh, d, ld > ldo ? ld : ldo, at, ld | ldo | ldd))
+    return attn_bwd_f32(st, mb, S, nh, d, q, k, v, ld, o, dout, ldo, lse, delta, dq, dk, dv, ldd, rope);
   hipError_t e = dt == F32    ? bwd_simple<float>(st, mb, S, nh, d, q, k, v, ld, o, dout, ldo, lse, delta, dq, dk, dv, ldd)
                  : dt == BF16 ? bwd_simple<bf16>(st, mb, S, nh, d, q, k, v, ld, o, dout, ldo, lse, delta, dq, dk, dv, ldd)
                               : bwd_simple<f16>(st, mb, S, nh, d, q, k, v, ld, o, dout, ldo, lse, delta, dq, dk, dv, ldd);

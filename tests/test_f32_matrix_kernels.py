@@ -5,6 +5,7 @@ import torch
 
 import paper_2507_10392_amd as zs
 from harness import dev, log_report, rel_err
+from oracle import stage_oracle as so
 
 pytestmark = pytest.mark.gpu
 
@@ -79,3 +80,56 @@ def test_gemm_f32_rotation_in_the_store(gpu_device):
     scratch = torch.empty(S, d // 2, 2, device="cuda")
     zs.ops.rope(st(), 0, T, S, 2 * H, d, want, 3 * H, 10000.0, 1.0, scratch)
     assert rel_err(back(got), back(want)) <= 2e-6
+
+
+def attention(mb, S, nh, d, qkv, do, impl, table=None, shift=0):
+    """shift: elements by which the rows start off a 16-byte boundary."""
+    H = nh * d
+    ld = 3 * H + 4
+    x = torch.as_strided(torch.zeros(mb * S * ld + 8, device="cuda"), (mb * S, 3 * H), (ld, 1), shift)
+    x.copy_(dev(qkv))
+    q, k, v = (x[:, i * H:(i + 1) * H] for i in range(3))
+    o, dqkv = (torch.full((mb * S, w), float("nan"), device="cuda") for w in (H, 3 * H))
+    lse, delta = torch.full((mb, nh, S), float("nan"), device="cuda"), torch.empty(mb, nh, S, device="cuda")
+    zs.ops.attention_fwd(st(), 0, mb, S, nh, d, q, k, v, ld, o, H, lse, impl)
+    zs.ops.attention_bwd_rope(st(), 0, mb, S, nh, d, q, k, v, ld, o, dev(do), H, lse, delta, dqkv[:, :H], dqkv[:, H:2 * H],
+                              dqkv[:, 2 * H:], 3 * H, impl, table)
+    return {"o": back(o), "lse": back(lse), "dq": back(dqkv[:, :H]), "dk": back(dqkv[:, H:2 * H]), "dv": back(dqkv[:, 2 * H:])}
+
+
+# one row; ends inside a 16-row block, on it and past it; more tiles of 32 rows than waves; head dims that fill 16-, 64- and
+# 128-column pieces partly; 136 and the unaligned rows below run on the wave-per-row kernel
+@pytest.mark.parametrize("mb,S,nh,d", [(1, 1, 1, 8), (2, 15, 1, 24), (1, 16, 3, 64), (2, 33, 2, 40), (1, 161, 2, 64), (2, 130, 1, 72),
+                                       (1, 97, 2, 128), (1, 20, 1, 136)])
+def test_attention_f32_matches_the_oracle(gpu_device, mb, S, nh, d):
+    print(f"[case] attention f32 mb={mb} S={S} nh={nh} d={d}", flush=True)
+    rng = np.random.default_rng(33)
+    H = nh * d
+    qkv, do = (rng.standard_normal((mb * S, w)).astype(np.float32) for w in (3 * H, H))
+    q, k, v = (qkv[:, i * H:(i + 1) * H].astype(np.float64).reshape(mb, S, nh, d) for i in range(3))
+    g = so.attention_bwd(do.astype(np.float64).reshape(mb, S, nh, d), q, k, v)
+    want = {"o": so.attention_fwd(q, k, v).reshape(mb * S, H), **{n: a.reshape(mb * S, H) for n, a in zip(("dq", "dk", "dv"), g)}}
+    s = np.einsum("bihd,bjhd->bhij", q, k) / np.sqrt(d)
+    want["lse"] = np.log(np.exp(np.where(np.tril(np.ones((S, S), bool)), s, -np.inf)).sum(-1))
+    got = attention(mb, S, nh, d, qkv, do, 0)
+    for n in want:
+        if S == 1 and n in ("dq", "dk"):      # one key: its probability does not depend on q and k
+            assert np.abs(got[n]).max() <= 1e-5
+            continue
+        err = rel_err(got[n], want[n])
+        log_report(f"attention f32 {mb} {S} {nh} {d}", [(n, err)])
+        assert err <= (2e-5 if n in ("o", "lse") else 5e-5), n      # the bars of the other fp32 attention tests
+
+
+def test_attention_f32_rotation_and_unaligned_rows(gpu_device):
+    mb, S, nh, d = 2, 45, 2, 40
+    print("[case] attention f32, rotation, unaligned rows", flush=True)
+    rng = np.random.default_rng(34)
+    qkv, do = (rng.standard_normal((mb * S, w * nh * d)).astype(np.float32) for w in (3, 1))
+    table = torch.empty(S, d // 2, 2, device="cuda")
+    zs.ops.rope_table(st(), S, d, 10000.0, table)
+    want = attention(mb, S, nh, d, qkv, do, 1, table)
+    for shift in (0, 1):                      # 1: the wave-per-row kernel takes it
+        got = attention(mb, S, nh, d, qkv, do, 0, table, shift)
+        for n in want:
+            assert rel_err(got[n], want[n]) <= 5e-6, (n, shift)
