@@ -121,7 +121,10 @@ Gemm part_of(const Gemm& g, int p) {
 // One launch: the 16-bit or the fp32 matrix-core kernel when it takes the arguments, else the plain kernel (with the
 // rotation and the multi-part K range done in extra passes).
 hipError_t gemm_one(hipStream_t st, DType dt, const Gemm& g, int force) {
-  if (gemm_select(dt, g, force) == GEMM_MFMA) return gemm_mfma(st, dt, g);   // rotation fused into its epilogue
+  if (gemm_select(dt, g, force) == GEMM_MFMA) {   // rotation fused into the kernels' stores
+    const int tile = force == GEMM_AUTO ? gemm_small_tile(g) : 0;
+    return tile ? gemm_small(st, dt, g, tile) : gemm_mfma(st, dt, g);
+  }
   if (g.glu) {   // gated unit: the plain product(s), then the activation kernel over the dense [gate | up] rows
     Gemm p = g;
     p.glu = 0; p.gu = nullptr;

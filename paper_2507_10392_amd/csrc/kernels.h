@@ -81,6 +81,10 @@ hipError_t gemm_mfma(hipStream_t st, DType dt, const Gemm& g);
 // Scratch bytes (Gemm::ws) with which gemm_mfma would cut the K range of this product's last round of tiles; 0 when
 // it would not (the answer depends on the shape only, not on the pointers).
 int64_t gemm_mfma_ws_bytes(const Gemm& g);
+// 16-bit products on 32x32 or 64x64 tiles (tile = 32 or 64) with K shared out over the waves of a workgroup (gemm_small.hip),
+// and which of the two is the faster way for a product that gemm_mfma_takes, 0: neither.
+int gemm_small_tile(const Gemm& g);
+hipError_t gemm_small(hipStream_t st, DType dt, const Gemm& g, int tile);
 // Workgroup tile the MFMA kernel would use: 1 = 256x256 (8 waves), 2 = 128x128 (4 waves); force_tile(0) = automatic.
 int gemm_mfma_pick_tile(const Gemm& g);
 void gemm_mfma_force_tile(int id);
