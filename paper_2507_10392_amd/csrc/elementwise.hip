@@ -67,34 +67,40 @@ __global__ __launch_bounds__(256) void norm_fwd_kernel(int Trows, int H, const T
   }
 }
 
-// Same arithmetic with the row kept in registers (one global read): H = 64 lanes x V x J exactly.  The
+// Same arithmetic with the row kept in registers (one global read): H <= 64 lanes x V x J, FULL: exactly that.  The
 // element -> lane assignment and the order of every sum equal the kernel above, so the results are identical.
-template <typename T, int KIND, int J>
-__global__ __launch_bounds__(256) void norm_fwd_reg_kernel(int Trows, const T* __restrict__ x, const T* __restrict__ g,
+template <typename T, int KIND, int J, bool FULL>
+__global__ __launch_bounds__(256) void norm_fwd_reg_kernel(int Trows, int width, const T* __restrict__ x, const T* __restrict__ g,
                                                            const T* __restrict__ b, float eps, T* __restrict__ n,
                                                            float* __restrict__ rstd, float* __restrict__ mean) {
-  constexpr int V = Vec<T>::N, H = 64 * V * J;
+  constexpr int V = Vec<T>::N;
+  const int H = FULL ? 64 * V * J : width;
   const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   if (row >= Trows) return;
   const T* xr = x + (int64_t)row * H;
   float a[J][V];
 #pragma unroll
-  for (int j = 0; j < J; ++j) load_vec(xr + (j * 64 + lane) * V, a[j]);
+  for (int j = 0; j < J; ++j)
+    if (FULL || (j * 64 + lane) * V < H) load_vec(xr + (j * 64 + lane) * V, a[j]);
   float mu = 0.f;
   if (KIND == 0) {
     float s = 0.f;
 #pragma unroll
     for (int j = 0; j < J; ++j)
+      if (FULL || (j * 64 + lane) * V < H) {
 #pragma unroll
-      for (int i = 0; i < V; ++i) s += a[j][i];
+        for (int i = 0; i < V; ++i) s += a[j][i];
+      }
     mu = wave_sum(s) / (float)H;
   }
   float s2 = 0.f;
 #pragma unroll
   for (int j = 0; j < J; ++j)
+    if (FULL || (j * 64 + lane) * V < H) {
 #pragma unroll
-    for (int i = 0; i < V; ++i) s2 += (a[j][i] - mu) * (a[j][i] - mu);
+      for (int i = 0; i < V; ++i) s2 += (a[j][i] - mu) * (a[j][i] - mu);
+    }
   const float r = 1.0f / sqrtf(wave_sum(s2) / (float)H + eps);
   if (lane == 0) {
     rstd[row] = r;
@@ -104,6 +110,7 @@ __global__ __launch_bounds__(256) void norm_fwd_reg_kernel(int Trows, const T* _
 #pragma unroll
   for (int j = 0; j < J; ++j) {
     const int c = (j * 64 + lane) * V;
+    if (!FULL && c >= H) continue;
     float gg[V], bb[V], o[V];
     load_vec(g + c, gg);
     if (KIND == 0) load_vec(b + c, bb);
@@ -113,26 +120,45 @@ __global__ __launch_bounds__(256) void norm_fwd_reg_kernel(int Trows, const T* _
   }
 }
 
-// J (row = 64 x V x J elements) for which the register-resident norm kernels are instantiated, else 0.
-static int reg_chunks(DType dt, int H) {
-  const int per = 64 * (dt == F32 ? 4 : 8);   // both 16-bit types move 8 elements per access
-  if (H % per) return 0;
-  const int J = H / per;
-  return (J == 1 || J == 2 || J == 4 || J == 8 || J == 10) ? J : 0;
+// Which register-resident norm kernel takes rows of H elements: J vectors per lane, `full` when they are exactly the row, and
+// for the backward the waves that share a row.  The row lengths of the usual model widths have exact variants; any other row
+// up to 16 (backward: 32) vectors per lane of one wave runs with its last vectors masked.  J = 0: none, longer rows take the
+// kernels that re-read the row.
+struct NormPlan { int J = 0; bool full = false; int waves = 1; };
+static int per_chunk(DType dt) { return 64 * (dt == F32 ? 4 : 8); }   // elements that a wave moves per access
+static NormPlan norm_plan_fwd(DType dt, int H) {
+  const int per = per_chunk(dt), need = (int)cdiv(H, per);
+  NormPlan p;
+  p.full = H % per == 0 && (need == 1 || need == 2 || need == 4 || need == 8 || need == 10);
+  if (need <= 8 || p.full) p.J = need;
+  else if (need <= 16) p.J = (need + 1) / 2 * 2;
+  return p;
+}
+static NormPlan norm_plan_bwd(DType dt, int H) {
+  const int per = per_chunk(dt), need = (int)cdiv(H, per);
+  NormPlan p;
+  p.full = H % per == 0 && (need == 1 || need == 2 || need == 4 || need == 8 || need == 10);
+  p.waves = need <= 4 || p.full ? 1 : need <= 8 ? 2 : need <= 16 ? 4 : 8;
+  if (need <= 32) p.J = (int)cdiv(need, p.waves);
+  return p;
 }
 
 hipError_t norm_fwd(hipStream_t st, DType dt, int kind, int T, int H, const void* x, const void* g, const void* b,
                     float eps, void* n, float* rstd, float* mean) {
   dim3 grid((unsigned)cdiv(T, 4)), blk(256);
-  const int J = reg_chunks(dt, H);
-#define LR(TT, KK, JJ) \
-  hipLaunchKernelGGL((norm_fwd_reg_kernel<TT, KK, JJ>), grid, blk, 0, st, T, (const TT*)x, (const TT*)g, (const TT*)b, eps, (TT*)n, rstd, mean)
+  const NormPlan p = norm_plan_fwd(dt, H);
+#define LR(TT, KK, JJ, FF) \
+  hipLaunchKernelGGL((norm_fwd_reg_kernel<TT, KK, JJ, FF>), grid, blk, 0, st, T, H, (const TT*)x, (const TT*)g, (const TT*)b, eps, (TT*)n, rstd, mean)
 #define LJ(TT, KK) \
-  switch (J) { case 1: LR(TT, KK, 1); break; case 2: LR(TT, KK, 2); break; case 4: LR(TT, KK, 4); break; \
-               case 8: LR(TT, KK, 8); break; default: LR(TT, KK, 10); break; }
+  if (p.full) switch (p.J) { case 1: LR(TT, KK, 1, true); break; case 2: LR(TT, KK, 2, true); break; case 4: LR(TT, KK, 4, true); break; \
+                             case 8: LR(TT, KK, 8, true); break; default: LR(TT, KK, 10, true); break; } \
+  else switch (p.J) { case 1: LR(TT, KK, 1, false); break; case 2: LR(TT, KK, 2, false); break; case 3: LR(TT, KK, 3, false); break; \
+                      case 4: LR(TT, KK, 4, false); break; case 5: LR(TT, KK, 5, false); break; case 6: LR(TT, KK, 6, false); break; \
+                      case 7: LR(TT, KK, 7, false); break; case 8: LR(TT, KK, 8, false); break; case 10: LR(TT, KK, 10, false); break; \
+                      case 12: LR(TT, KK, 12, false); break; case 14: LR(TT, KK, 14, false); break; default: LR(TT, KK, 16, false); break; }
 #define L(TT, KK) \
   hipLaunchKernelGGL((norm_fwd_kernel<TT, KK>), grid, blk, 0, st, T, H, (const TT*)x, (const TT*)g, (const TT*)b, eps, (TT*)n, rstd, mean)
-  if (J) {
+  if (p.J) {
     if (dt == F32) { if (kind == 0) { LJ(float, 0) } else { LJ(float, 1) } }
     else if (dt == BF16) { if (kind == 0) { LJ(bf16, 0) } else { LJ(bf16, 1) } }
     else { if (kind == 0) { LJ(f16, 0) } else { LJ(f16, 1) } }
@@ -192,76 +218,15 @@ __global__ __launch_bounds__(256) void norm_bwd_kernel(int Trows, int H, const T
   }
 }
 
-// ------------------------------------------------------------------ norm backward, row in registers
-// dx as norm_bwd_kernel with each row read once and kept in registers as stored (H = 64 x V x J); same
-// element -> lane assignment and summation order, hence identical results.
-template <typename T, int KIND, int J>
-__global__ __launch_bounds__(256) void norm_bwd_reg_kernel(int Trows, const T* __restrict__ dn, const T* __restrict__ x,
-                                                           const T* __restrict__ g, const float* __restrict__ rstd,
-                                                           const float* __restrict__ mean, const T* dres, T* dx) {
-  constexpr int V = Vec<T>::N, H = 64 * V * J;
-  const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63;
-  if (row >= Trows) return;
-  const float r = rstd[row];
-  const float mu = (KIND == 0) ? mean[row] : 0.f;
-  const int64_t off = (int64_t)row * H;
-  typename Vec<T>::type xv[J], dv[J];
-  float su = 0.f, sux = 0.f;
-#pragma unroll
-  for (int j = 0; j < J; ++j) {
-    const int c = (j * 64 + lane) * V;
-    xv[j] = *reinterpret_cast<const typename Vec<T>::type*>(x + off + c);
-    dv[j] = *reinterpret_cast<const typename Vec<T>::type*>(dn + off + c);
-    float gg[V];
-    load_vec(g + c, gg);
-#pragma unroll
-    for (int i = 0; i < V; ++i) {
-      const float u = to_f(dv[j][i]) * gg[i];
-      su += u;
-      sux += u * (to_f(xv[j][i]) - mu) * r;
-    }
-  }
-  const float mu_u = (KIND == 0) ? wave_sum(su) / (float)H : 0.f;
-  const float mu_ux = wave_sum(sux) / (float)H;
-#pragma unroll
-  for (int j = 0; j < J; ++j) {
-    const int c = (j * 64 + lane) * V;
-    float o[V], rs[V], gg[V];
-    load_vec(g + c, gg);
-    if (dres) load_vec(dres + off + c, rs);
-#pragma unroll
-    for (int i = 0; i < V; ++i) {
-      const float u = to_f(dv[j][i]) * gg[i];
-      o[i] = r * (u - mu_u - (to_f(xv[j][i]) - mu) * r * mu_ux) + (dres ? rs[i] : 0.f);
-    }
-    store_vec(dx + off + c, o);
-  }
-}
-
-hipError_t norm_bwd(hipStream_t st, DType dt, int kind, int T, int H, const void* dn, const void* x, const void* g,
-                    const float* rstd, const float* mean, const void* dres, void* dx) {
+static hipError_t norm_bwd(hipStream_t st, DType dt, int kind, int T, int H, const void* dn, const void* x, const void* g,
+                           const float* rstd, const float* mean, const void* dres, void* dx) {
   dim3 grid((unsigned)cdiv(T, 4)), blk(256);
-  const int J = reg_chunks(dt, H);
-#define LR(TT, KK, JJ) \
-  hipLaunchKernelGGL((norm_bwd_reg_kernel<TT, KK, JJ>), grid, blk, 0, st, T, (const TT*)dn, (const TT*)x, (const TT*)g, rstd, mean, (const TT*)dres, (TT*)dx)
-#define LJ(TT, KK) \
-  switch (J) { case 1: LR(TT, KK, 1); break; case 2: LR(TT, KK, 2); break; case 4: LR(TT, KK, 4); break; \
-               case 8: LR(TT, KK, 8); break; default: LR(TT, KK, 10); break; }
 #define L(TT, KK) \
   hipLaunchKernelGGL((norm_bwd_kernel<TT, KK>), grid, blk, 0, st, T, H, (const TT*)dn, (const TT*)x, (const TT*)g, rstd, mean, (const TT*)dres, (TT*)dx)
-  if (J) {
-    if (dt == F32) { if (kind == 0) { LJ(float, 0) } else { LJ(float, 1) } }
-    else if (dt == BF16) { if (kind == 0) { LJ(bf16, 0) } else { LJ(bf16, 1) } }
-    else { if (kind == 0) { LJ(f16, 0) } else { LJ(f16, 1) } }
-  } else {
-    if (dt == F32) { if (kind == 0) L(float, 0); else L(float, 1); }
-    else if (dt == BF16) { if (kind == 0) L(bf16, 0); else L(bf16, 1); }
-    else { if (kind == 0) L(f16, 0); else L(f16, 1); }
-  }
+  if (dt == F32) { if (kind == 0) L(float, 0); else L(float, 1); }
+  else if (dt == BF16) { if (kind == 0) L(bf16, 0); else L(bf16, 1); }
+  else { if (kind == 0) L(f16, 0); else L(f16, 1); }
 #undef L
-#undef LJ
-#undef LR
   return hipGetLastError();
 }
 
@@ -339,35 +304,47 @@ hipError_t colsum_partial(hipStream_t st, DType dt, int T, int N, const void* a,
 }
 
 // ------------------------------------------------------------------ norm backward + partial sums, row in registers
-// norm_bwd_reg_kernel and the two colsum_kernel passes over the same rows in one kernel: dn and x are read once.
-// One workgroup per row block (the blocks of colsum_partial); wave q walks rows r0+q, r0+q+4, ... of the block,
-// computes dx of each row as norm_bwd_reg_kernel does and keeps the running column sums of dn*xhat (and dn) of
-// its rows in registers; the four waves' sums are then added in the order 0..3 through LDS.  That is colsum_kernel's
-// order of additions per column, so the partial sums do not depend on which of the two routes ran.
-template <typename T, int KIND, int J>
-__global__ __launch_bounds__(256) void norm_bwd_partials_reg_kernel(int Trows, const T* __restrict__ dn, const T* __restrict__ x,
+// norm_bwd_kernel and the two colsum_kernel passes over the same rows in one kernel: dn and x are read once.
+// One workgroup per row block (the blocks of colsum_partial).  WPR = 1: four waves, wave q walks rows r0+q, r0+q+4, ... of the
+// block, computes dx of each row and keeps the running column sums of dn*xhat (and dn) of its rows in registers; the waves'
+// sums are then added in the order 0..3 through LDS: colsum_kernel's order of additions per column.  WPR = 2, 4, 8: eight
+// waves, that many of them share a row (vector j of part p covers chunk j WPR + p), their sums of u and u*xhat meet in LDS
+// once per row, and 8 / WPR rows are walked side by side.  A wave thereby holds at most 4 vectors per lane and two waves fit
+// a SIMD, one's loads under the other's arithmetic (20 instructions per element).  FULL: H = 64 V J exactly (WPR = 1); else
+// the vectors past the row's end are masked.  bf16, us: LayerNorm, 4097 rows of 3080 48 as three kernels, 33 here (46 with 7
+// vectors in one of four waves); 4096 rows of 2560 34 : 23; RMSNorm, 4096 rows of 8192 97 : 65.  Exact rows of 4096 and 5120
+// elements stay with one wave per row (32 and 39 us; 34 and 45 with two).
+template <typename T, int KIND, int J, int WPR, bool FULL>
+__global__ __launch_bounds__(WPR == 1 ? 256 : 512) void norm_bwd_partials_reg_kernel(int Trows, int width, const T* __restrict__ dn, const T* __restrict__ x,
                                                                     const T* __restrict__ g, const float* __restrict__ rstd,
                                                                     const float* __restrict__ mean, const T* dres, T* dx,
                                                                     float* __restrict__ part_g, float* __restrict__ part_b,
                                                                     int rows_per_blk) {
-  constexpr int V = Vec<T>::N, H = 64 * V * J;
-  extern __shared__ __align__(16) float red[];   // [3][H]: the sums of waves 1..3, used for part_g and then for part_b
-  const int lane = threadIdx.x & 63, q = threadIdx.x >> 6;
+  constexpr int V = Vec<T>::N, NW = WPR == 1 ? 4 : 8, RG = NW / WPR;      // waves; rows walked side by side
+  const int H = FULL ? 64 * V * J : width;
+  extern __shared__ __align__(16) float red[];   // [RG - 1][WPR J][64 V]: the sums of the later rows, for part_g and then for part_b
+  __shared__ float cross[2][NW][2];              // WPR > 1: the waves' sums of a row, two buffers in turn
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, q = wave / WPR, part = wave % WPR;
   const int r0 = blockIdx.x * rows_per_blk;
   const int r1 = min(Trows, r0 + rows_per_blk);
+  auto col = [&](int j) { return ((j * WPR + part) * 64 + lane) * V; };
+  auto in = [&](int j) { return FULL || col(j) < H; };
   float pg[J][V], pb[KIND == 0 ? J : 1][V];
 #pragma unroll
   for (int j = 0; j < J; ++j)
 #pragma unroll
     for (int i = 0; i < V; ++i) { pg[j][i] = 0.f; if (KIND == 0) pb[j][i] = 0.f; }
-  for (int row = r0 + q; row < r1; row += 4) {
-    const float r = rstd[row];
-    const float mu = (KIND == 0) ? mean[row] : 0.f;
+  int turn = 0;
+  for (int row = r0 + q; (WPR == 1 ? row : row - q) < r1; row += RG) {   // WPR > 1: the same steps in every wave, for the barrier
+    const bool live = WPR == 1 || row < r1;
+    const float r = live ? rstd[row] : 0.f;
+    const float mu = (KIND == 0 && live) ? mean[row] : 0.f;
     const int64_t off = (int64_t)row * H;
     typename Vec<T>::type xv[J], dv[J], rv[J];
 #pragma unroll
     for (int j = 0; j < J; ++j) {
-      const int c = (j * 64 + lane) * V;
+      if (!live || !in(j)) continue;
+      const int c = col(j);
       xv[j] = *reinterpret_cast<const typename Vec<T>::type*>(x + off + c);
       dv[j] = *reinterpret_cast<const typename Vec<T>::type*>(dn + off + c);
       if (dres) rv[j] = *reinterpret_cast<const typename Vec<T>::type*>(dres + off + c);
@@ -375,9 +352,9 @@ __global__ __launch_bounds__(256) void norm_bwd_partials_reg_kernel(int Trows, c
     float su = 0.f, sux = 0.f;
 #pragma unroll
     for (int j = 0; j < J; ++j) {
-      const int c = (j * 64 + lane) * V;
+      if (!live || !in(j)) continue;
       float gg[V];
-      load_vec(g + c, gg);
+      load_vec(g + col(j), gg);
 #pragma unroll
       for (int i = 0; i < V; ++i) {
         const float d = to_f(dv[j][i]), xx = to_f(xv[j][i]);
@@ -388,11 +365,22 @@ __global__ __launch_bounds__(256) void norm_bwd_partials_reg_kernel(int Trows, c
         if (KIND == 0) pb[j][i] += d;
       }
     }
-    const float mu_u = (KIND == 0) ? wave_sum(su) / (float)H : 0.f;
-    const float mu_ux = wave_sum(sux) / (float)H;
+    su = (KIND == 0) ? wave_sum(su) : 0.f;
+    sux = wave_sum(sux);
+    if constexpr (WPR > 1) {
+      if (lane == 0) { cross[turn][wave][0] = su; cross[turn][wave][1] = sux; }
+      __syncthreads();   // the other buffer was read before this barrier, so it may be written after it
+      su = sux = 0.f;
+#pragma unroll
+      for (int w = 0; w < WPR; ++w) { su += cross[turn][q * WPR + w][0]; sux += cross[turn][q * WPR + w][1]; }
+      turn ^= 1;
+    }
+    const float mu_u = su / (float)H;
+    const float mu_ux = sux / (float)H;
 #pragma unroll
     for (int j = 0; j < J; ++j) {
-      const int c = (j * 64 + lane) * V;
+      if (!live || !in(j)) continue;
+      const int c = col(j);
       float o[V], gg[V];
       load_vec(g + c, gg);
 #pragma unroll
@@ -403,13 +391,14 @@ __global__ __launch_bounds__(256) void norm_bwd_partials_reg_kernel(int Trows, c
       store_vec(dx + off + c, o);
     }
   }
-  // cross-wave sums in the order 0..3, first of dn*xhat, then (LayerNorm) of dn
+  // sums over the rows walked side by side, in order, first of dn*xhat, then (LayerNorm) of dn
 #pragma unroll
   for (int pass = 0; pass < (KIND == 0 ? 2 : 1); ++pass) {
     if (pass) __syncthreads();
-    // LDS layout [wave][j][quad of 4 columns][lane]: consecutive lanes 16 bytes apart, no bank conflicts
+    // LDS layout [row][chunk][quad of 4 columns][lane]: consecutive lanes 16 bytes apart, no bank conflicts
     constexpr int Q4 = V / 4;
     f32x4* red4 = reinterpret_cast<f32x4*>(red);
+    auto at = [&](int u, int j, int h) { return (((u - 1) * (J * WPR) + j * WPR + part) * Q4 + h) * 64 + lane; };
     if (q > 0) {
 #pragma unroll
       for (int j = 0; j < J; ++j)
@@ -417,24 +406,24 @@ __global__ __launch_bounds__(256) void norm_bwd_partials_reg_kernel(int Trows, c
         for (int h = 0; h < Q4; ++h) {
           f32x4 t;
 #pragma unroll
-          for (int e = 0; e < 4; ++e) t[e] = pass ? pb[j][4 * h + e] : pg[j][4 * h + e];
-          red4[(((q - 1) * J + j) * Q4 + h) * 64 + lane] = t;
+          for (int e = 0; e < 4; ++e) t[e] = pass ? pb[KIND == 0 ? j : 0][4 * h + e] : pg[j][4 * h + e];
+          red4[at(q, j, h)] = t;
         }
     }
-    __syncthreads();
+    if (RG > 1) __syncthreads();
     if (q == 0) {
       float* p = (pass ? part_b : part_g) + (int64_t)blockIdx.x * H;
 #pragma unroll
       for (int j = 0; j < J; ++j) {
-        const int c = (j * 64 + lane) * V;
+        if (!in(j)) continue;
 #pragma unroll
         for (int h = 0; h < Q4; ++h) {
-          const f32x4 r1 = red4[((0 * J + j) * Q4 + h) * 64 + lane], r2 = red4[((1 * J + j) * Q4 + h) * 64 + lane],
-                      r3 = red4[((2 * J + j) * Q4 + h) * 64 + lane];
           f32x4 o;
 #pragma unroll
-          for (int e = 0; e < 4; ++e) o[e] = (((pass ? pb[j][4 * h + e] : pg[j][4 * h + e]) + r1[e]) + r2[e]) + r3[e];
-          *reinterpret_cast<f32x4*>(p + c + 4 * h) = o;
+          for (int e = 0; e < 4; ++e) o[e] = pass ? pb[KIND == 0 ? j : 0][4 * h + e] : pg[j][4 * h + e];
+#pragma unroll
+          for (int u = 1; u < RG; ++u) o += red4[at(u, j, h)];
+          *reinterpret_cast<f32x4*>(p + col(j) + 4 * h) = o;
         }
       }
     }
@@ -444,16 +433,22 @@ __global__ __launch_bounds__(256) void norm_bwd_partials_reg_kernel(int Trows, c
 hipError_t norm_bwd_partials(hipStream_t st, DType dt, int kind, int T, int H, const void* dn, const void* x, const void* g,
                              const float* rstd, const float* mean, const void* dres, void* dx, float* part_g,
                              float* part_b, int nblk) {
-  const int J = reg_chunks(dt, H);
-  if (J && nblk >= 1 && part_g && (kind != 0 || part_b)) {   // one pass over the rows
+  const NormPlan p = norm_plan_bwd(dt, H);
+  if (p.J && nblk >= 1 && part_g && (kind != 0 || part_b)) {   // one pass over the rows
     const int rows_per_blk = (int)cdiv(T, nblk);
-    dim3 grid((unsigned)nblk), blk(256);
-    const size_t smem = 3 * (size_t)H * sizeof(float);
-#define LR(TT, KK, JJ) \
-  hipLaunchKernelGGL((norm_bwd_partials_reg_kernel<TT, KK, JJ>), grid, blk, smem, st, T, (const TT*)dn, (const TT*)x, (const TT*)g, rstd, mean, (const TT*)dres, (TT*)dx, part_g, part_b, rows_per_blk)
+    const int nw = p.waves == 1 ? 4 : 8;
+    dim3 grid((unsigned)nblk), blk(64 * nw);
+    const size_t smem = (size_t)(nw / p.waves - 1) * p.waves * p.J * per_chunk(dt) * sizeof(float);
+#define LR(TT, KK, JJ, WW, FF) \
+  hipLaunchKernelGGL((norm_bwd_partials_reg_kernel<TT, KK, JJ, WW, FF>), grid, blk, smem, st, T, H, (const TT*)dn, (const TT*)x, (const TT*)g, rstd, mean, (const TT*)dres, (TT*)dx, part_g, part_b, rows_per_blk)
 #define LJ(TT, KK) \
-  switch (J) { case 1: LR(TT, KK, 1); break; case 2: LR(TT, KK, 2); break; case 4: LR(TT, KK, 4); break; \
-               case 8: LR(TT, KK, 8); break; default: LR(TT, KK, 10); break; }
+  if (p.full) switch (p.J) { case 1: LR(TT, KK, 1, 1, true); break; case 2: LR(TT, KK, 2, 1, true); break; case 4: LR(TT, KK, 4, 1, true); break; \
+                             case 8: LR(TT, KK, 8, 1, true); break; default: LR(TT, KK, 10, 1, true); break; } \
+  else if (p.waves == 1) switch (p.J) { case 1: LR(TT, KK, 1, 1, false); break; case 2: LR(TT, KK, 2, 1, false); break; \
+                                        case 3: LR(TT, KK, 3, 1, false); break; default: LR(TT, KK, 4, 1, false); break; } \
+  else if (p.waves == 2) { if (p.J == 3) LR(TT, KK, 3, 2, false); else LR(TT, KK, 4, 2, false); } \
+  else if (p.waves == 4) { if (p.J == 3) LR(TT, KK, 3, 4, false); else LR(TT, KK, 4, 4, false); } \
+  else { if (p.J == 3) LR(TT, KK, 3, 8, false); else LR(TT, KK, 4, 8, false); }
     if (dt == F32) { if (kind == 0) { LJ(float, 0) } else { LJ(float, 1) } }
     else if (dt == BF16) { if (kind == 0) { LJ(bf16, 0) } else { LJ(bf16, 1) } }
     else { if (kind == 0) { LJ(f16, 0) } else { LJ(f16, 1) } }
