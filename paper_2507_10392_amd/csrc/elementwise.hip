@@ -26,7 +26,7 @@ template <typename T, int KIND>
 __global__ __launch_bounds__(256) void norm_fwd_kernel(int Trows, int H, const T* __restrict__ x,
                                                        const T* __restrict__ g, const T* __restrict__ b, float eps,
                                                        T* __restrict__ n, float* __restrict__ rstd,
-                                                       float* __restrict__ mean) {
+                                                       float* __restrict__ mean, T* __restrict__ copy) {
   constexpr int V = Vec<T>::N;
   const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
@@ -61,6 +61,7 @@ __global__ __launch_bounds__(256) void norm_fwd_kernel(int Trows, int H, const T
     load_vec(xr + c, a);
     load_vec(g + c, gg);
     if (KIND == 0) load_vec(b + c, bb);
+    if (copy) store_vec(copy + (int64_t)row * H + c, a);
 #pragma unroll
     for (int i = 0; i < V; ++i) o[i] = (a[i] - mu) * r * gg[i] + (KIND == 0 ? bb[i] : 0.f);
     store_vec(nr + c, o);
@@ -72,7 +73,7 @@ __global__ __launch_bounds__(256) void norm_fwd_kernel(int Trows, int H, const T
 template <typename T, int KIND, int J, bool FULL>
 __global__ __launch_bounds__(256) void norm_fwd_reg_kernel(int Trows, int width, const T* __restrict__ x, const T* __restrict__ g,
                                                            const T* __restrict__ b, float eps, T* __restrict__ n,
-                                                           float* __restrict__ rstd, float* __restrict__ mean) {
+                                                           float* __restrict__ rstd, float* __restrict__ mean, T* __restrict__ copy) {
   constexpr int V = Vec<T>::N;
   const int H = FULL ? 64 * V * J : width;
   const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -114,6 +115,7 @@ __global__ __launch_bounds__(256) void norm_fwd_reg_kernel(int Trows, int width,
     float gg[V], bb[V], o[V];
     load_vec(g + c, gg);
     if (KIND == 0) load_vec(b + c, bb);
+    if (copy) store_vec(copy + (int64_t)row * H + c, a[j]);   // the values as loaded: bit for bit
 #pragma unroll
     for (int i = 0; i < V; ++i) o[i] = (a[j][i] - mu) * r * gg[i] + (KIND == 0 ? bb[i] : 0.f);
     store_vec(nr + c, o);
@@ -144,11 +146,11 @@ static NormPlan norm_plan_bwd(DType dt, int H) {
 }
 
 hipError_t norm_fwd(hipStream_t st, DType dt, int kind, int T, int H, const void* x, const void* g, const void* b,
-                    float eps, void* n, float* rstd, float* mean) {
+                    float eps, void* n, float* rstd, float* mean, void* copy) {
   dim3 grid((unsigned)cdiv(T, 4)), blk(256);
   const NormPlan p = norm_plan_fwd(dt, H);
 #define LR(TT, KK, JJ, FF) \
-  hipLaunchKernelGGL((norm_fwd_reg_kernel<TT, KK, JJ, FF>), grid, blk, 0, st, T, H, (const TT*)x, (const TT*)g, (const TT*)b, eps, (TT*)n, rstd, mean)
+  hipLaunchKernelGGL((norm_fwd_reg_kernel<TT, KK, JJ, FF>), grid, blk, 0, st, T, H, (const TT*)x, (const TT*)g, (const TT*)b, eps, (TT*)n, rstd, mean, (TT*)copy)
 #define LJ(TT, KK) \
   if (p.full) switch (p.J) { case 1: LR(TT, KK, 1, true); break; case 2: LR(TT, KK, 2, true); break; case 4: LR(TT, KK, 4, true); break; \
                              case 8: LR(TT, KK, 8, true); break; default: LR(TT, KK, 10, true); break; } \
@@ -157,7 +159,7 @@ hipError_t norm_fwd(hipStream_t st, DType dt, int kind, int T, int H, const void
                       case 7: LR(TT, KK, 7, false); break; case 8: LR(TT, KK, 8, false); break; case 10: LR(TT, KK, 10, false); break; \
                       case 12: LR(TT, KK, 12, false); break; case 14: LR(TT, KK, 14, false); break; default: LR(TT, KK, 16, false); break; }
 #define L(TT, KK) \
-  hipLaunchKernelGGL((norm_fwd_kernel<TT, KK>), grid, blk, 0, st, T, H, (const TT*)x, (const TT*)g, (const TT*)b, eps, (TT*)n, rstd, mean)
+  hipLaunchKernelGGL((norm_fwd_kernel<TT, KK>), grid, blk, 0, st, T, H, (const TT*)x, (const TT*)g, (const TT*)b, eps, (TT*)n, rstd, mean, (TT*)copy)
   if (p.J) {
     if (dt == F32) { if (kind == 0) { LJ(float, 0) } else { LJ(float, 1) } }
     else if (dt == BF16) { if (kind == 0) { LJ(bf16, 0) } else { LJ(bf16, 1) } }

@@ -89,9 +89,10 @@ hipError_t gemm_small(hipStream_t st, DType dt, const Gemm& g, int tile);
 int gemm_mfma_pick_tile(const Gemm& g);
 void gemm_mfma_force_tile(int id);
 
-// kind 0 LayerNorm (mean and rstd saved), 1 RMSNorm (rstd saved).  b and mean may be NULL for RMSNorm.
+// kind 0 LayerNorm (mean and rstd saved), 1 RMSNorm (rstd saved).  b and mean may be NULL for RMSNorm.  copy (or NULL) receives
+// x as it is: the pass that reads a stage's input also keeps it.
 hipError_t norm_fwd(hipStream_t st, DType dt, int kind, int T, int H, const void* x, const void* g, const void* b,
-                    float eps, void* n, float* rstd, float* mean);
+                    float eps, void* n, float* rstd, float* mean, void* copy = nullptr);
 // dx = (dres ? dres : 0) + norm'(x)^T dn (dres may alias dx), plus the partial column sums of the gain (and, for LayerNorm,
 // bias) gradient over row blocks of cdiv(T, nblk) rows: part_g[blk, c] = sum_t dn * xhat, part_b[blk, c] = sum_t dn (part_b may be NULL for
 // RMSNorm).  For the row lengths of the register-resident kernels this is ONE kernel that reads dn and x once (a

@@ -431,8 +431,9 @@ bool do_gemm(stage_t* s, const Gemm& g) {
 }
 
 // ---- forward of one layer ---------------------------------------------------------------------
-// x_in -> y (y may be NULL: recompute pass, the output is not needed).
-bool layer_forward(stage_t* s, int l, const char* x_in, LayerActs& A, char* y) {
+// x_in -> y (y may be NULL: recompute pass, the output is not needed).  x_src: the layer's input is there and the first norm
+// copies it to x_in.
+bool layer_forward(stage_t* s, int l, char* x_in, LayerActs& A, char* y, const void* x_src = nullptr) {
   const Shape& h = s->sh;
   const DType dt = dt_of(s);
   const int T = h.T, H = h.H, F = h.F;
@@ -441,9 +442,11 @@ bool layer_forward(stage_t* s, int l, const char* x_in, LayerActs& A, char* y) {
   const bool gpt = h.arch == STAGE_ARCH_GPT;
   auto W = [&](const char* n) { return s->P(s->seg_off(p + n)); };
 
-  if (!run(s, "norm_fwd", 0, 2 * thb, [&] {
-        return gpt ? norm_fwd(s->st, dt, 0, T, H, x_in, W("ln1.g"), W("ln1.b"), s->cfg.norm_eps, A.n1, A.rstd1, A.mean1)
-                   : norm_fwd(s->st, dt, 1, T, H, x_in, W("rms1.g"), nullptr, s->cfg.norm_eps, A.n1, A.rstd1, nullptr); }))
+  const void* x = x_src ? x_src : x_in;
+  void* keep = x_src ? x_in : nullptr;
+  if (!run(s, "norm_fwd", 0, (x_src ? 3 : 2) * thb, [&] {
+        return gpt ? norm_fwd(s->st, dt, 0, T, H, x, W("ln1.g"), W("ln1.b"), s->cfg.norm_eps, A.n1, A.rstd1, A.mean1, keep)
+                   : norm_fwd(s->st, dt, 1, T, H, x, W("rms1.g"), nullptr, s->cfg.norm_eps, A.n1, A.rstd1, nullptr, keep); }))
     return false;
   Gemm g;
   g.M = T; g.K = H; g.A = A.n1; g.lda = H; g.C = A.qkv; g.ldc = 3 * H;
@@ -845,15 +848,14 @@ int stage_forward(stage_t* s, int32_t mb, const void* x_or_ids, void* y_out, con
     if (!run(s, "embed", 0, 2.0 * TH, [&] {
           return embed_fwd(s->st, dt, h.T, h.H, h.V, pl.ids[mb], s->P(s->seg_off("embed.E")), x0); }))
       return STAGE_ERR_DEVICE;
-  } else if (!run(s, "copy", 0, 2.0 * TH, [&] { return copy_bytes(s->st, x0, x_or_ids, TH); })) {
-    return STAGE_ERR_DEVICE;
   }
   char* final_y = nullptr;
   if (h.head) final_y = h.recompute ? pl.hstash[k] : pl.hacts[mb].y;
   for (int l = 0; l < h.L; ++l) {
     LayerActs& A = h.recompute ? pl.acts[0] : pl.acts[(size_t)mb * h.L + l];
     char* y = l + 1 < h.L ? in_of(l + 1) : (h.head ? final_y : (char*)y_out);
-    if (!layer_forward(s, l, in_of(l), A, y)) return STAGE_ERR_DEVICE;
+    // the caller's input is kept by the first layer's first norm, which reads it anyway
+    if (!layer_forward(s, l, in_of(l), A, y, l == 0 && !h.embed ? x_or_ids : nullptr)) return STAGE_ERR_DEVICE;
   }
   if (h.head) {
     if (!run(s, "copy", 0, 8.0 * h.T, [&] { return copy_bytes(s->st, pl.targets[mb], targets, 4ll * h.T); })) return STAGE_ERR_DEVICE;
