@@ -112,7 +112,7 @@ __device__ __forceinline__ e16x8 pack8_lo(const f32x16& a, int s, const e16x8& h
 // A 64 x D tile moves HBM -> registers (fetch, issued before the MFMAs of the current tile so the
 // latency hides behind them) -> LDS (put, after them).  For D = 128 thread t carries 4 vectors of 16 bytes:
 // vector v = t + 256 i is row v/16, columns 8*(v%16)...
-template <int NT, int D> struct TileRegs { e16x8 v[8 * D / NT]; };   // NT threads share the 64 D/8 vectors of a tile
+template <int NT, int D> struct TileRegs { e16x8 v[(8 * D + NT - 1) / NT]; };   // NT threads share the 64 D/8 vectors of a tile
 // Rows of one (batch, head) are read through a raw buffer descriptor over [first row, last row's dd columns]:
 // the per-lane offset is one register (D = 96: three), the tile's row offset a scalar, and rows at or past nrows fall
 // beyond num_records and read as zero without a branch, as do the columns dd..D-1 of a padded head, whose offset is pushed
@@ -125,7 +125,7 @@ template <int NT, int D>
 __device__ __forceinline__ void fetch_tile(TileRegs<NT, D>& x, __amdgpu_buffer_rsrc_t rs, int ld, int row0, unsigned tid, int dd) {
   constexpr unsigned RV = D / 8;   // vectors per row
 #pragma unroll
-  for (int i = 0; i < (int)(TR * RV / NT); ++i) {
+  for (int i = 0; i < (8 * D + NT - 1) / NT; ++i) {
     union { u32x4 u; e16x8 h; } c;
     if constexpr (NT % RV == 0) {
       const int col = (int)(tid % RV) * 8;
@@ -142,8 +142,9 @@ __device__ __forceinline__ void fetch_tile(TileRegs<NT, D>& x, __amdgpu_buffer_r
 }
 template <int NT, int D> __device__ __forceinline__ void put_tile(const TileRegs<NT, D>& x, e16* tile, unsigned tid) {
 #pragma unroll
-  for (int i = 0; i < 8 * D / NT; ++i) {
+  for (int i = 0; i < (8 * D + NT - 1) / NT; ++i) {
     const unsigned v = tid + NT * i;
+    if (8 * D % NT != 0 && v >= 8 * D) break;   // D = 96 on 512 threads
     *reinterpret_cast<e16x8*>(tile + (v / (D / 8)) * LDT<D> + (v % (D / 8)) * 8) = x.v[i];
   }
 }
@@ -186,6 +187,38 @@ __device__ __forceinline__ void unrotate4(float (&x)[4], const float2* __restric
     x[2 * i] = u * c + w * sn;
     x[2 * i + 1] = w * c - u * sn;
   }
+}
+
+// acc (+ its low part) of the second of two waves that share rows is added to the first one's through LDS: 16 KB per pair for
+// D = 128.  LDS must be free; it is free again when the call returns.
+template <int D, int NL>
+__device__ __forceinline__ void merge_halves(f32x16 (&acc)[D / 32], f32x16 (&lo)[NL], f32x4* red, int half, int wave, int lane) {
+  if constexpr (NL > 1) {
+#pragma unroll
+    for (int i = 0; i < D / 32; ++i)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][r] = fmaf(lo[i][r], LO_UNIT, acc[i][r]);
+  }
+  red += wave * (D / 32) * 4 * 64;
+  if (half == 1) {
+#pragma unroll
+    for (int i = 0; i < D / 32; ++i)
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+        red[(i * 4 + c) * 64 + lane] = f32x4{acc[i][4 * c], acc[i][4 * c + 1], acc[i][4 * c + 2], acc[i][4 * c + 3]};
+  }
+  __syncthreads();
+  if (half == 0) {
+#pragma unroll
+    for (int i = 0; i < D / 32; ++i)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        const f32x4 o = red[(i * 4 + c) * 64 + lane];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[i][4 * c + e] += o[e];
+      }
+  }
+  __syncthreads();
 }
 
 // ------------------------------------------------------------------------------------------ forward
@@ -332,7 +365,8 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_fwd_kernel(int 
 // grid ceil(S/(32 NW))*nh*mb, NW waves (4 or 8 as in the forward kernel); wave w owns queries q0+32w..; loops over K/V
 // tiles up to the diagonal.
 // dQ^T[d][q] += K^T[d][key] dS^T[key][q],  dS^T = P^T o (dP^T - delta_q),  dP^T = V dO^T.
-template <int NW, int D, bool SPLIT>
+// QS = 2: two waves share 32 queries, each taking one half of every tile's keys; their sums meet in LDS at the end.
+template <int NW, int QS, int D, bool SPLIT>
 __global__ __launch_bounds__(64 * NW, NW == 4 && !(SPLIT && LO_ACC && D > 64) ? 2 : 1) void attn_bwd_dq_kernel(int S, const e16* __restrict__ q, const e16* __restrict__ k,
                                                           const e16* __restrict__ v, int64_t ld,
                                                           const e16* __restrict__ o, const e16* __restrict__ dout,
@@ -343,16 +377,17 @@ __global__ __launch_bounds__(64 * NW, NW == 4 && !(SPLIT && LO_ACC && D > 64) ? 
   const int dd = SPLIT ? head_dim : D;
   extern __shared__ __align__(16) char smem_raw[];
   e16* smem = reinterpret_cast<e16*>(smem_raw);
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  constexpr int QW = NW / QS;   // groups of 32 queries
+  const int tid = threadIdx.x, lane = tid & 63, wave = QS == 1 ? tid >> 6 : (tid >> 6) % QW, half = QS == 1 ? 0 : (tid >> 6) / QW;
   const BlockId bid = block_id(nh, mb);
-  const int qb = (S + 32 * NW - 1) / (32 * NW) - 1 - bid.rank, h = bid.h, b = bid.b;
+  const int qb = (S + 32 * QW - 1) / (32 * QW) - 1 - bid.rank, h = bid.h, b = bid.b;
   const int64_t tok0 = (int64_t)b * S;
   const e16* qh = q + tok0 * ld + h * dd;
   const e16* kh = k + tok0 * ld + h * dd;
   const e16* vh = v + tok0 * ld + h * dd;
   const e16* doh = dout + tok0 * ldo + h * dd;
   const __amdgpu_buffer_rsrc_t rsk = head_rsrc(kh, ld, S, dd), rsv = head_rsrc(vh, ld, S, dd);
-  const int q0 = qb * 32 * NW, wq0 = q0 + wave * 32;
+  const int q0 = qb * 32 * QW, wq0 = q0 + wave * 32;
   const int my_q = wq0 + (lane & 31);
   const float scale_log2 = scale * LOG2E;
 
@@ -372,7 +407,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 && !(SPLIT && LO_ACC && D > 64) ? 
 #pragma unroll
       for (int e = 0; e < 8; ++e) dlt = fmaf((float)dof[s][e], (float)of[s][e], dlt);
     dlt += __shfl_xor(dlt, 32, 64);
-    if (lane < 32 && my_q < S) delta[stat] = dlt;
+    if (half == 0 && lane < 32 && my_q < S) delta[stat] = dlt;
   }
   f32x16 acc[D / 32], acclo[SPLIT && LO_ACC ? D / 32 : 1];
 #pragma unroll
@@ -380,7 +415,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 && !(SPLIT && LO_ACC && D > 64) ? 
 #pragma unroll
     for (int r = 0; r < 16; ++r) { acc[i][r] = 0.f; if (SPLIT && LO_ACC) acclo[SPLIT && LO_ACC ? i : 0][r] = 0.f; }
 
-  const int last_q = min(q0 + 32 * NW - 1, S - 1);
+  const int last_q = min(q0 + 32 * QW - 1, S - 1);
   const int ntiles = last_q / TR + 1;
   TileRegs<64 * NW, D> kr, vr;
   fetch_tile(kr, rsk, (int)ld, 0, tid, dd);
@@ -399,7 +434,8 @@ __global__ __launch_bounds__(64 * NW, NW == 4 && !(SPLIT && LO_ACC && D > 64) ? 
     if (key0 <= wq0 + 31) {
       const bool diag = key0 + TR - 1 > wq0;
 #pragma unroll
-      for (int jb = 0; jb < 2; ++jb) {
+      for (int j = 0; j < 2 / QS; ++j) {
+        const int jb = QS == 2 ? half : j;
         f32x16 sacc, pacc;
 #pragma unroll
         for (int r = 0; r < 16; ++r) sacc[r] = pacc[r] = 0.f;
@@ -438,7 +474,8 @@ __global__ __launch_bounds__(64 * NW, NW == 4 && !(SPLIT && LO_ACC && D > 64) ? 
     }
     __syncthreads();
   }
-  if (my_q < S) {
+  if constexpr (QS == 2) merge_halves<D>(acc, acclo, reinterpret_cast<f32x4*>(smem_raw), half, wave, lane);
+  if (my_q < S && half == 0) {
     e16* row = dq + (tok0 + my_q) * ldd + h * dd;
 #pragma unroll
     for (int db = 0; db < D / 32; ++db)
@@ -448,8 +485,8 @@ __global__ __launch_bounds__(64 * NW, NW == 4 && !(SPLIT && LO_ACC && D > 64) ? 
         float x[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e)
-          x[e] = SPLIT && LO_ACC ? fmaf(acclo[SPLIT && LO_ACC ? db : 0][4 * c + e], LO_UNIT, acc[db][4 * c + e]) * (scale / DS_SCALE)
-                                 : acc[db][4 * c + e] * scale;
+          x[e] = SPLIT && LO_ACC && QS == 1 ? fmaf(acclo[SPLIT && LO_ACC ? db : 0][4 * c + e], LO_UNIT, acc[db][4 * c + e]) * (scale / DS_SCALE)
+                                 : acc[db][4 * c + e] * (SPLIT ? scale / DS_SCALE : scale);
         if (rope) unrotate4(x, rope, my_q, db * 32 + 8 * c + 4 * (lane >> 5), dd);
         e16x4 w;
 #pragma unroll
@@ -465,7 +502,8 @@ __global__ __launch_bounds__(64 * NW, NW == 4 && !(SPLIT && LO_ACC && D > 64) ? 
 // softmax arithmetic overlaps the other's MFMAs.
 // S[q][key] = Q K^T (lane = key, registers = queries), P = exp2(S c - lse_q), dP = dO V^T,
 // dV^T[d][key] += dO^T[d][q] P[q][key],  dK^T[d][key] += Q^T[d][q] dS[q][key].
-template <int NW, int D, bool SPLIT>
+// QS = 2: two waves share 32 keys, each taking one half of every tile's queries; their sums meet in LDS at the end.
+template <int NW, int QS, int D, bool SPLIT>
 __global__ __launch_bounds__(64 * NW) void attn_bwd_dkv_kernel(int S, const e16* __restrict__ q, const e16* __restrict__ k,
                                                            const e16* __restrict__ v, int64_t ld,
                                                            const e16* __restrict__ dout, int64_t ldo,
@@ -476,7 +514,8 @@ __global__ __launch_bounds__(64 * NW) void attn_bwd_dkv_kernel(int S, const e16*
   extern __shared__ __align__(16) char smem_raw[];
   e16* smem = reinterpret_cast<e16*>(smem_raw);                 // [2][Q tile | dO tile]
   float* stats = reinterpret_cast<float*>(smem + 4 * TILE<D>);       // [2][lse2[64] | delta[64]]
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  constexpr int KWV = NW / QS;   // groups of 32 keys
+  const int tid = threadIdx.x, lane = tid & 63, wave = QS == 1 ? tid >> 6 : (tid >> 6) % KWV, half = QS == 1 ? 0 : (tid >> 6) / KWV;
   const BlockId bid = block_id(nh, mb);
   const int kb = bid.rank, h = bid.h, b = bid.b;                   // early key blocks (most work) first
   const int64_t tok0 = (int64_t)b * S;
@@ -487,7 +526,7 @@ __global__ __launch_bounds__(64 * NW) void attn_bwd_dkv_kernel(int S, const e16*
   const __amdgpu_buffer_rsrc_t rsq = head_rsrc(qh, ld, S, dd), rsdo = head_rsrc(doh, ldo, S, dd);
   const float* lse_h = lse + ((int64_t)b * nh + h) * S;
   const float* dlt_h = delta + ((int64_t)b * nh + h) * S;
-  const int k0 = kb * 32 * NW, wk0 = k0 + wave * 32;
+  const int k0 = kb * 32 * KWV, wk0 = k0 + wave * 32;
   const int my_k = wk0 + (lane & 31);
   const float scale_log2 = scale * LOG2E;
 
@@ -499,6 +538,7 @@ __global__ __launch_bounds__(64 * NW) void attn_bwd_dkv_kernel(int S, const e16*
   e16* Vw = reinterpret_cast<e16*>(stats + 256) + wave * 32 * LDT<D>;
 #pragma unroll
   for (int i = 0; i < D / 16; ++i) {
+    if (QS == 2 && half) break;   // the first of the two waves brings the rows, the barrier before the loop publishes them
     const int vv = lane + 64 * i, r = vv / (D / 8), c = (vv % (D / 8)) * 8;
     *reinterpret_cast<e16x8*>(Vw + r * LDT<D> + c) =
         wk0 + r < S && c < dd ? *reinterpret_cast<const e16x8*>(vh + (int64_t)(wk0 + r) * ld + c) : zero8();
@@ -539,10 +579,11 @@ __global__ __launch_bounds__(64 * NW) void attn_bwd_dkv_kernel(int S, const e16*
     const float* st = stats + buf * 128;
     if (t + 1 < t_end) fetch(t + 1);
     const int qrow0 = t * TR;
-    if (qrow0 + TR - 1 >= wk0) {   // otherwise every query of the tile precedes this wave's keys
+    if (qrow0 + (QS == 2 ? 32 * half + 31 : TR - 1) >= wk0) {   // otherwise every query of the tile precedes this wave's keys
       const bool diag = qrow0 < wk0 + 31;
 #pragma unroll
-      for (int ib = 0; ib < 2; ++ib) {
+      for (int i = 0; i < 2 / QS; ++i) {
+        const int ib = QS == 2 ? half : i;
         f32x16 sacc, pacc;
 #pragma unroll
         for (int r = 0; r < 16; ++r) sacc[r] = pacc[r] = 0.f;
@@ -592,7 +633,11 @@ __global__ __launch_bounds__(64 * NW) void attn_bwd_dkv_kernel(int S, const e16*
     if (t + 1 < t_end) put(buf ^ 1);
     __syncthreads();
   }
-  if (my_k < S) {
+  if constexpr (QS == 2) {
+    merge_halves<D>(dvacc, dvlo, reinterpret_cast<f32x4*>(smem_raw), half, wave, lane);
+    merge_halves<D>(dkacc, dklo, reinterpret_cast<f32x4*>(smem_raw), half, wave, lane);
+  }
+  if (my_k < S && half == 0) {
     e16* krow = dk + (tok0 + my_k) * ldd + h * dd;
     e16* vrow = dv + (tok0 + my_k) * ldd + h * dd;
 #pragma unroll
@@ -603,9 +648,9 @@ __global__ __launch_bounds__(64 * NW) void attn_bwd_dkv_kernel(int S, const e16*
         float x[4], y[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          x[e] = SPLIT && LO_ACC ? fmaf(dklo[SPLIT && LO_ACC ? db : 0][4 * c + e], LO_UNIT, dkacc[db][4 * c + e]) * (scale / DS_SCALE)
-                                 : dkacc[db][4 * c + e] * scale;
-          y[e] = SPLIT && LO_ACC ? fmaf(dvlo[SPLIT && LO_ACC ? db : 0][4 * c + e], LO_UNIT, dvacc[db][4 * c + e]) : dvacc[db][4 * c + e];
+          x[e] = SPLIT && LO_ACC && QS == 1 ? fmaf(dklo[SPLIT && LO_ACC ? db : 0][4 * c + e], LO_UNIT, dkacc[db][4 * c + e]) * (scale / DS_SCALE)
+                                 : dkacc[db][4 * c + e] * (SPLIT ? scale / DS_SCALE : scale);
+          y[e] = SPLIT && LO_ACC && QS == 1 ? fmaf(dvlo[SPLIT && LO_ACC ? db : 0][4 * c + e], LO_UNIT, dvacc[db][4 * c + e]) : dvacc[db][4 * c + e];
         }
         if (rope) unrotate4(x, rope, my_k, db * 32 + 8 * c + 4 * (lane >> 5), dd);
         e16x4 wk, wv;
@@ -657,35 +702,48 @@ hipError_t launch_fwd(hipStream_t st, int mb, int S, int nh, int d, const void* 
                      (const e16*)q, (const e16*)k, (const e16*)v, ld, (e16*)o, ldo, lse, hi, lo, nh, mb, d);
   return hipGetLastError();
 }
-template <int NW, int D, bool SPLIT>
+template <int NW, int QS, int D, bool SPLIT>
 hipError_t launch_dq(hipStream_t st, int mb, int S, int nh, int d, const void* q, const void* k, const void* v, int64_t ld, const void* o,
                      const void* dout, int64_t ldo, const float* lse, float* delta, void* dq, int64_t ldd, const float2* rope) {
   static bool set = false;
-  const hipError_t e = set_smem(attn_bwd_dq_kernel<NW, D, SPLIT>, SMEM_FWD<D>, set);
+  const hipError_t e = set_smem(attn_bwd_dq_kernel<NW, QS, D, SPLIT>, SMEM_FWD<D>, set);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((attn_bwd_dq_kernel<NW, D, SPLIT>), dim3((unsigned)(cdiv(S, 32 * NW) * nh * mb)), dim3(64 * NW), SMEM_FWD<D>, st,
+  hipLaunchKernelGGL((attn_bwd_dq_kernel<NW, QS, D, SPLIT>), dim3((unsigned)(cdiv(S, 32 * (NW / QS)) * nh * mb)), dim3(64 * NW), SMEM_FWD<D>, st,
                      S, (const e16*)q, (const e16*)k, (const e16*)v, ld, (const e16*)o, (const e16*)dout, ldo, lse, delta, (e16*)dq,
                      ldd, 1.0f / sqrtf((float)d), nh, mb, rope, d);
   return hipGetLastError();
 }
-template <int NW, int D, bool SPLIT>
+template <int NW, int QS, int D, bool SPLIT>
 hipError_t launch_dkv(hipStream_t st, int mb, int S, int nh, int d, const void* q, const void* k, const void* v, int64_t ld,
                       const void* dout, int64_t ldo, const float* lse, const float* delta, void* dk, void* dv, int64_t ldd,
                       const float2* rope) {
   static bool set = false;
-  const hipError_t e = set_smem(attn_bwd_dkv_kernel<NW, D, SPLIT>, smem_dkv<D>(NW), set);
+  const hipError_t e = set_smem(attn_bwd_dkv_kernel<NW, QS, D, SPLIT>, smem_dkv<D>(NW / QS), set);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((attn_bwd_dkv_kernel<NW, D, SPLIT>), dim3((unsigned)(cdiv(S, 32 * NW) * nh * mb)), dim3(64 * NW), smem_dkv<D>(NW),
+  hipLaunchKernelGGL((attn_bwd_dkv_kernel<NW, QS, D, SPLIT>), dim3((unsigned)(cdiv(S, 32 * (NW / QS)) * nh * mb)), dim3(64 * NW), smem_dkv<D>(NW / QS),
                      st, S, (const e16*)q, (const e16*)k, (const e16*)v, ld, (const e16*)dout, ldo, lse, delta, (e16*)dk, (e16*)dv,
                      ldd, 1.0f / sqrtf((float)d), nh, mb, rope, d);
   return hipGetLastError();
 }
-template <int D>
-hipError_t bwd_split(hipStream_t st, int mb, int S, int nh, int d, const void* q, const void* k, const void* v, int64_t ld, const void* o,
-                     const void* dout, int64_t ldo, const float* lse, float* delta, void* dq, void* dk, void* dv, int64_t ldd,
-                     const float2* rope) {
-  const hipError_t e = launch_dq<4, D, true>(st, mb, S, nh, d, q, k, v, ld, o, dout, ldo, lse, delta, dq, ldd, rope);
-  return e != hipSuccess ? e : launch_dkv<4, D, true>(st, mb, S, nh, d, q, k, v, ld, dout, ldo, lse, delta, dk, dv, ldd, rope);
+// Blocks of 128 rows: with 8 waves, two of them per 32 rows, or with 4.  The kernels' LDS leaves a CU one workgroup (dK/dV) or
+// two (dQ), so the 4-wave forms keep 4 waves of a CU at work, or 8 where dQ has two workgroups for it.  Sharing rows costs a
+// merge at the end (16 KB per pair and accumulator through LDS), which a row block with four tiles does not win back in dQ.
+// 16 heads of 128, S = 2048: dK/dV 112 : 77 us, dQ 72 : 57 us (4 : 8 waves); 8 heads, S = 1000: both 92 : 67 us; 4 heads,
+// S = 256: dK/dV 24 : 20 us, dQ 17.9 : 18.8 us.
+template <int D, bool SPLIT>
+hipError_t bwd_128(hipStream_t st, int mb, int S, int nh, int d, const void* q, const void* k, const void* v, int64_t ld, const void* o,
+                   const void* dout, int64_t ldo, const float* lse, float* delta, void* dq, void* dk, void* dv, int64_t ldd,
+                   const float2* rope, bool wide_dkv) {
+  if constexpr (SPLIT && LO_ACC && D > 64) {   // the low accumulators of wide half heads leave no registers for 8 waves
+    const hipError_t e = launch_dq<4, 1, D, SPLIT>(st, mb, S, nh, d, q, k, v, ld, o, dout, ldo, lse, delta, dq, ldd, rope);
+    return e != hipSuccess ? e : launch_dkv<4, 1, D, SPLIT>(st, mb, S, nh, d, q, k, v, ld, dout, ldo, lse, delta, dk, dv, ldd, rope);
+  } else {
+    const hipError_t e = cdiv(S, 128) * nh * mb < 512 && S > 256
+                             ? launch_dq<8, 2, D, SPLIT>(st, mb, S, nh, d, q, k, v, ld, o, dout, ldo, lse, delta, dq, ldd, rope)
+                             : launch_dq<4, 1, D, SPLIT>(st, mb, S, nh, d, q, k, v, ld, o, dout, ldo, lse, delta, dq, ldd, rope);
+    if (e != hipSuccess || wide_dkv) return e;
+    return launch_dkv<8, 2, D, SPLIT>(st, mb, S, nh, d, q, k, v, ld, dout, ldo, lse, delta, dk, dv, ldd, rope);
+  }
 }
 
 }  // namespace
@@ -709,15 +767,15 @@ hipError_t ZS_ATTN_NAME(attn_bwd_mfma)(hipStream_t st, int mb, int S, int nh, in
                          int64_t ld, const void* o, const void* dout, int64_t ldo, const float* lse, float* delta,
                          void* dq, void* dk, void* dv, int64_t ldd, const float2* rope) {
   if ((int64_t)S * (ld > ldo ? ld : ldo) * 2 >= (1ll << 31)) return hipErrorInvalidValue;   // 32-bit buffer offsets
-  if (d <= 64) return bwd_split<64>(st, mb, S, nh, d, q, k, v, ld, o, dout, ldo, lse, delta, dq, dk, dv, ldd, rope);
-  if (d <= 96) return bwd_split<96>(st, mb, S, nh, d, q, k, v, ld, o, dout, ldo, lse, delta, dq, dk, dv, ldd, rope);
-  if (d < 128) return bwd_split<128>(st, mb, S, nh, d, q, k, v, ld, o, dout, ldo, lse, delta, dq, dk, dv, ldd, rope);
+  if (d <= 64) return bwd_128<64, true>(st, mb, S, nh, d, q, k, v, ld, o, dout, ldo, lse, delta, dq, dk, dv, ldd, rope, false);
+  if (d <= 96) return bwd_128<96, true>(st, mb, S, nh, d, q, k, v, ld, o, dout, ldo, lse, delta, dq, dk, dv, ldd, rope, false);
+  if (d < 128) return bwd_128<128, true>(st, mb, S, nh, d, q, k, v, ld, o, dout, ldo, lse, delta, dq, dk, dv, ldd, rope, false);
+  const bool wide = wide_blocks(S, nh, mb);
   const hipError_t e =
-      wide_query_blocks(S, nh, mb) ? launch_dq<8, 128, false>(st, mb, S, nh, d, q, k, v, ld, o, dout, ldo, lse, delta, dq, ldd, rope)
-                                   : launch_dq<4, 128, false>(st, mb, S, nh, d, q, k, v, ld, o, dout, ldo, lse, delta, dq, ldd, rope);
-  if (e != hipSuccess) return e;
-  return wide_blocks(S, nh, mb) ? launch_dkv<8, 128, false>(st, mb, S, nh, d, q, k, v, ld, dout, ldo, lse, delta, dk, dv, ldd, rope)
-                                : launch_dkv<4, 128, false>(st, mb, S, nh, d, q, k, v, ld, dout, ldo, lse, delta, dk, dv, ldd, rope);
+      wide_query_blocks(S, nh, mb) ? launch_dq<8, 1, 128, false>(st, mb, S, nh, d, q, k, v, ld, o, dout, ldo, lse, delta, dq, ldd, rope)
+                                   : bwd_128<128, false>(st, mb, S, nh, d, q, k, v, ld, o, dout, ldo, lse, delta, dq, dk, dv, ldd, rope, wide);
+  if (e != hipSuccess || !wide) return e;
+  return launch_dkv<8, 1, 128, false>(st, mb, S, nh, d, q, k, v, ld, dout, ldo, lse, delta, dk, dv, ldd, rope);
 }
 
 }  // namespace zs

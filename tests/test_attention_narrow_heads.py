@@ -105,3 +105,22 @@ def test_narrow_heads_with_inverse_rotation_and_unaligned_rows(gpu_device, dtype
         got = run(dtype, mb, S, nh, d, qkv, do, 0, table, shift)
         for n in plain:               # impl 1 rounds dq and dk once more, before it rotates them: two roundings apart at most
             assert rel_err(got[n], plain[n]) <= 2 * unit, (n, shift)
+
+
+@pytest.mark.parametrize("dtype", [1, 2])
+@pytest.mark.parametrize("mb,S,nh", [(1, 31, 1), (2, 257, 1), (1, 321, 2), (1, 385, 3)])
+def test_heads_of_128_whose_rows_two_waves_share(gpu_device, mb, S, nh, dtype):
+    """Backward of few head-sequences (8 waves per block of 128 rows, two on the same 32) against the oracle; the last block
+    holds 1, 31, 65 or 128 rows."""
+    d = 128
+    print(f"[case] attention bwd mb={mb} S={S} nh={nh} dtype={dtype}", flush=True)
+    rng = np.random.default_rng(44)
+    rnd = round_bf16 if dtype == 1 else round_f16
+    H = nh * d
+    qkv, do = (rnd(rng.standard_normal((mb * S, w)).astype(np.float32)) for w in (3 * H, H))
+    q, k, v = (qkv[:, i * H:(i + 1) * H].astype(np.float64).reshape(mb, S, nh, d) for i in range(3))
+    g = so.attention_bwd(do.astype(np.float64).reshape(mb, S, nh, d), q, k, v)
+    got = run(dtype, mb, S, nh, d, qkv, do, 0)
+    for n, a in zip(("dq", "dk", "dv"), g):
+        # probabilities and dS are rounded to 16 bits, as before, then the sums: the bar of the other 16-bit attention tests
+        assert rel_err(got[n], a.reshape(mb * S, H)) <= 2e-2, n
