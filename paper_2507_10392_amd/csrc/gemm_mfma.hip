@@ -210,6 +210,49 @@ __global__ __launch_bounds__(256) void add_partials_kernel(float* C, int64_t ldc
 
 }  // namespace
 
+// ---- two halves of K side by side ----------------------------------------------------------------------------------
+// An input gradient over few tokens has few tiles and a long K (512 x 4096 with K = 22016: 128 tiles of 128x128, half the
+// CUs idle).  With scratch for two fp32 results its halves run as a batch of two, and a second kernel adds and rounds them.
+// Taken when the tiles do not fill 128 CUs' worth twice over and a half is still long against the added pass (1.2 us per
+// MB of result at 4 TB/s and its launch, against 7.8 ns per k).
+namespace {
+bool plan_halves(const Gemm& g, Gemm& h) {
+  if (!g.ws || g.transA || !g.transB || g.c_f32_accum || g.batch != 1 || g.bias || g.resid || g.rope || g.glu || g.nx) return false;
+  const int64_t tiles = cdiv(g.M, 128) * cdiv(g.N, 128);
+  if (tiles > 128 || g.N % 8 || ((uintptr_t)g.ws & 15) || g.ws_bytes < 8ll * g.M * g.N) return false;
+  h = g;
+  h.ws = nullptr; h.ws_bytes = 0;
+  if (g.kseg) {
+    if (g.K != 2 * g.kseg) return false;
+    h.kseg = 0; h.segB = 0; h.sB = g.segB;
+  } else {
+    if (g.K % 16) return false;
+    h.sB = g.K / 2;
+  }
+  h.K = g.K / 2; h.sA = h.K;
+  h.C = g.ws; h.ldc = g.N; h.sC = (int64_t)g.M * g.N;
+  h.batch = 2; h.c_f32_accum = 1; h.c_overwrite = 1;
+  const double gain = 7.8e-3 * h.K, cost = 6.0 + (double)g.M * g.N * 10.0 / 4.0e6;   // us
+  return gain > 1.5 * cost;
+}
+
+// C = p[0] + p[1], rounded: 8 columns per thread.
+template <typename E>
+__global__ __launch_bounds__(256) void add_halves_kernel(int64_t nvec, int vec_per_row, const float* __restrict__ p, int64_t half, E* __restrict__ C,
+                                                         int64_t ldc) {
+  typedef typename Vec<E>::type E8;
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= nvec) return;
+  const f32x4* a = reinterpret_cast<const f32x4*>(p + i * 8);
+  const f32x4* b = reinterpret_cast<const f32x4*>(p + half + i * 8);
+  const f32x4 lo = a[0] + b[0], hi = a[1] + b[1];
+  E8 o;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) o[e] = (E)(e < 4 ? lo[e & 3] : hi[e & 3]);
+  *reinterpret_cast<E8*>(C + i / vec_per_row * ldc + (i % vec_per_row) * 8) = o;
+}
+}  // namespace
+
 int64_t gemm_mfma_ws_bytes(const Gemm& g) {
   KCut k;
   return (!g_force_tile && plan_kcut(BF16, g, k)) ? k.ws_need : 0;
@@ -229,6 +272,16 @@ hipError_t gemm_mfma(hipStream_t st, DType dt, const Gemm& g) {
                          k.tail.nchunks - 1);
       return hipGetLastError();
     }
+  }
+  Gemm halves;
+  if (!g_force_tile && plan_halves(g, halves) && gemm_mfma_takes(dt, halves)) {
+    const hipError_t e = run_tile(st, dt, halves, gemm_mfma_pick_tile(halves) == 2);
+    if (e != hipSuccess) return e;
+    const int64_t nvec = (int64_t)g.M * g.N / 8;
+    const dim3 grid((unsigned)cdiv(nvec, 256));
+    if (dt == F16) hipLaunchKernelGGL(add_halves_kernel<f16>, grid, dim3(256), 0, st, nvec, g.N / 8, (const float*)g.ws, halves.sC, (f16*)g.C, g.ldc);
+    else hipLaunchKernelGGL(add_halves_kernel<bf16>, grid, dim3(256), 0, st, nvec, g.N / 8, (const float*)g.ws, halves.sC, (bf16*)g.C, g.ldc);
+    return hipGetLastError();
   }
   Gemm head, tail;
   if (!g_force_tile && split_tail(dt, g, head, tail)) {

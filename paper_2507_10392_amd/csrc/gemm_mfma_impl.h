@@ -570,7 +570,7 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BM * BN <= 128 * 128) ? 2 : 1)
   if (ACC) {
     if (chunk == 0) {
       float* Ct = (float*)g.C + (int64_t)z * g.sC + (int64_t)m0 * g.ldc + n0;
-      epilogue_accum<BM, BN, NT, MI, NJ>(Ct, (int)g.ldc, min(BM, g.M - m0), min(BN, g.N - n0), false, acc, wave / WN, wn, tid,
+      epilogue_accum<BM, BN, NT, MI, NJ>(Ct, (int)g.ldc, min(BM, g.M - m0), min(BN, g.N - n0), !PAIR && g.c_overwrite, acc, wave / WN, wn, tid,
                                          reinterpret_cast<float*>(smem_raw));
     } else {   // partial tile number (chunk-1) * tile_count + position inside the launch's range
       const int64_t slot = (int64_t)(chunk - 1) * g.tile_count + sub;

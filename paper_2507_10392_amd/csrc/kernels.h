@@ -17,7 +17,9 @@ namespace zs {
 //             their own, part 0 from A, B and part p from Ax[p-1], Bx[p-1] (same leading dimensions and batch
 //             strides); parts 0..nx-1 have kseg rows each, the last one the remaining K - nx*kseg > 0 rows:
 //             C += sum_p A_p^T B_p in one K loop (weight gradients of several microbatches).
-//   ws != NULL (nx > 0 only): ws_bytes of scratch that the MFMA path may use when the 256x256 tiles of the product do
+//   ws != NULL (nx = 0, an input gradient): ws_bytes of scratch with which a product of few tiles and long K may run its two
+//             halves of K side by side, as fp32 results in ws that a second kernel adds and rounds.
+//   ws != NULL (nx > 0): ws_bytes of scratch that the MFMA path may use when the 256x256 tiles of the product do
 //             not fill whole rounds of 256 workgroups: the tiles beyond the whole rounds (the last ones of the kernel's
 //             tile order, over all batches) then have their K
 //             range cut into chunks of whole parts that run side by side, chunk 0 adding to C and the others writing
@@ -49,6 +51,7 @@ struct Gemm {
   int kseg = 0; int64_t segB = 0;
   int nx = 0; const void* Ax[GEMM_MAX_PARTS - 1] = {}; const void* Bx[GEMM_MAX_PARTS - 1] = {};
   void* ws = nullptr; int64_t ws_bytes = 0;
+  int c_overwrite = 0;   // with c_f32_accum, set by gemm_mfma for partial results: the product is stored, not added
   // set by gemm_mfma for the launches of a product that is cut, not by callers: the launch covers tiles
   // tile_base .. tile_base + tile_count - 1 of the order gemm_tile_of (over all batches), each in nchunks chunks of chunk_parts parts
   int chunk_parts = 0, nchunks = 1, tile_base = 0, tile_count = 0;

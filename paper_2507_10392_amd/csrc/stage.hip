@@ -557,6 +557,8 @@ bool layer_backward(stage_t* s, int l, const char* x_in, LayerActs& A, const cha
   g.M = T; g.N = H; g.A = dff; g.transB = 1; g.C = pl.gN; g.ldc = H; g.ldb = F;
   if (gpt) { g.K = F; g.lda = F; g.B = W("W1"); }
   else { g.K = 2 * F; g.lda = 2 * F; g.B = W("Wg"); g.kseg = F; g.segB = (int64_t)H * F; }
+  // free at this point, and one after the other in the scratch: gO and gQKV (written later), gF1 (da has been used)
+  g.ws = pl.gO; g.ws_bytes = pl.gF1 + (int64_t)T * F * h.E - pl.gO;
   if (!do_gemm(s, g)) return false;
   g = Gemm();
   g.M = H; g.N = F; g.K = T; g.A = A.n2; g.lda = H; g.transA = 1; g.B = dff; g.c_f32_accum = 1; g.ldc = F;
@@ -596,6 +598,7 @@ bool layer_backward(stage_t* s, int l, const char* x_in, LayerActs& A, const cha
   g.M = T; g.N = H; g.K = 3 * H; g.A = gqkv; g.lda = 3 * H; g.transB = 1; g.C = pl.gN; g.ldc = H;
   if (gpt) { g.B = W("Wqkv"); g.ldb = 3 * H; }
   else { g.B = W("Wq"); g.ldb = H; g.kseg = H; g.segB = (int64_t)H * H; }
+  g.ws = pl.gF1; g.ws_bytes = (int64_t)T * F * h.E;
   if (!do_gemm(s, g)) return false;
   g = Gemm();
   g.M = H; g.K = T; g.A = A.n1; g.lda = H; g.transA = 1; g.B = gqkv; g.ldb = 3 * H; g.c_f32_accum = 1;
