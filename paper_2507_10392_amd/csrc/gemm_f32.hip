@@ -14,7 +14,7 @@
 // The matrix instruction gets B as its first operand, so a lane ends up with 4 consecutive columns of one row of C.
 //
 // Measured on the GEMMs of a [256 tokens] x 256..1024 GPT stage: 47-86 us per launch with the plain LDS-tiled kernel,
-// 5-9 us here.
+// 3.4-6.5 us here.
 #include "kernels.h"
 
 namespace zs {
@@ -25,6 +25,7 @@ typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 constexpr unsigned OUT = 0x80000000u;   // pushes a lane's offset past every descriptor (extents are below 2^30 bytes): reads 0
 
 template <int N> struct FV;
+template <> struct FV<1> { typedef float type; };
 template <> struct FV<2> { typedef f32x2 type; };
 template <> struct FV<4> { typedef f32x4 type; };
 
@@ -39,7 +40,9 @@ __device__ __forceinline__ f32x2 load2(__amdgpu_buffer_rsrc_t rs, unsigned voff,
   return c.f;
 }
 template <int N> __device__ __forceinline__ typename FV<N>::type loadn(__amdgpu_buffer_rsrc_t rs, unsigned voff, unsigned soff) {
-  if constexpr (N == 4) return load4(rs, voff, soff); else return load2(rs, voff, soff);
+  if constexpr (N == 4) return load4(rs, voff, soff);
+  else if constexpr (N == 2) return load2(rs, voff, soff);
+  else return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, (int)voff, (int)soff, 0));
 }
 
 // Fragments of one operand for one slab of 16 k: NB blocks of 16 rows.
@@ -50,10 +53,13 @@ template <int NB> struct Frag<0, NB> {   // k-contiguous
 };
 template <int NB> struct Frag<1, NB> {   // row-contiguous
   typename FV<NB>::type v[4];
-  __device__ __forceinline__ float at(int b, int e) const { return v[e][b]; }
+  __device__ __forceinline__ float at(int b, int e) const {
+    if constexpr (NB == 1) return v[e]; else return v[e][b];
+  }
 };
 
-// A workgroup owns a (16 MI WM) x (16 NI WN) tile of C: WM x WN waves side by side, times KW waves that share out K.
+// A workgroup owns a (16 MI WM) x (16 NI WN) tile of C (MI, NI = 1, 2 or 4): WM x WN waves side by side, times KW waves
+// that share out K.
 template <int TA, int TB, int MI, int NI, int WM, int WN, int KW, int SEG>
 __global__ __launch_bounds__(64 * WM * WN * KW) void gemm_f32_kernel(Gemm g, int tiles_m, int tiles_n) {
   constexpr int NQ = MI * NI;   // quads of 4 consecutive columns a lane holds
@@ -228,19 +234,27 @@ bool gemm_f32_supported(const Gemm& g) {
   return rowsA * g.lda * 4 < (1ll << 30) && (rowsB * g.ldb + segs) * 4 < (1ll << 30);
 }
 
-// Which tile: 128x128 (4 waves of 64x64), 64x64 with K over 4 waves, or 32x32 with K over 8 waves.  The smaller ones exist
-// for outputs that give the 256 CUs too few workgroups; a wave of 32x32 loads twice the bytes per flop of one of 64x64.
-// The estimate: cycles of the busiest CU, at the 256 flops per cycle of its four matrix cores times what each form was
-// measured to reach of it, plus a fixed part per workgroup.
+// Which tile: 128x128 (4 waves of 64x64), 64x64 with K over 4 waves, or 32x32, 16x32 or 16x16 with K over 8 waves.  The smaller
+// ones exist for outputs that give the 256 CUs too few workgroups; the fewer outputs a wave has the more bytes it loads per
+// flop.  The estimate: cycles of the busiest CU, at the 256 flops per cycle of its four matrix cores times what each form was
+// measured to reach of it, plus a fixed part per workgroup.  256 x 256, K = 1024: 9.6 us on 32x32, 7.0 on 16x32, 5.9 on
+// 16x16; 256 x 512, K = 2752 in two segments 25.1, 19.3 and 24.2; 256 x 1024, K = 256 4.9, 5.5 and 6.1; 64x64 9.4.
 hipError_t gemm_f32(hipStream_t st, const Gemm& g) {
-  auto cost = [&](int tile, double share) {
-    const int64_t wgs = cdiv(g.M, tile) * cdiv(g.N, tile) * g.batch;
-    return (double)cdiv(wgs, 256) * (2.0 * tile * tile * (double)g.K / (256.0 * share) + 1500.0);
-  };
-  const double big = cost(128, 0.8), mid = cost(64, 0.7), small = cost(32, 0.45);
-  if (small < mid && small < big) return launch<2, 2, 1, 1, 8>(st, g);
-  if (mid < big) return launch<4, 4, 1, 1, 4>(st, g);
-  return launch<4, 4, 2, 2, 1>(st, g);
+  const struct { int m, n; double share; } forms[5] = {{128, 128, 0.8}, {64, 64, 0.7}, {32, 32, 0.45}, {16, 32, 0.4}, {16, 16, 0.3}};
+  int best = 0;
+  double least = 0.0;
+  for (int i = 0; i < 5; ++i) {
+    const int64_t wgs = cdiv(g.M, forms[i].m) * cdiv(g.N, forms[i].n) * g.batch;
+    const double t = (double)cdiv(wgs, 256) * (2.0 * forms[i].m * forms[i].n * (double)g.K / (256.0 * forms[i].share) + 1500.0);
+    if (i == 0 || t < least) { best = i; least = t; }
+  }
+  switch (best) {
+    case 0: return launch<4, 4, 2, 2, 1>(st, g);
+    case 1: return launch<4, 4, 1, 1, 4>(st, g);
+    case 2: return launch<2, 2, 1, 1, 8>(st, g);
+    case 3: return launch<1, 2, 1, 1, 8>(st, g);
+    default: return launch<1, 1, 1, 1, 8>(st, g);
+  }
 }
 
 }  // namespace zs

@@ -23,8 +23,10 @@ GEMM_CASES = [
     # (M, N, K, transA, transB, batch, kseg, bias, resid, accum)
     (4, 4, 4, 0, 1, 1, 0, True, True, False),             # one quad of outputs
     (1, 4, 20, 0, 0, 1, 0, False, False, False),
-    (31, 36, 132, 0, 0, 2, 0, True, True, False),         # 32x32 tiles, ragged
-    (256, 260, 688, 0, 1, 3, 0, True, False, False),
+    (31, 36, 132, 0, 0, 2, 0, True, True, False),         # 16x16 tiles, ragged
+    (252, 260, 100, 1, 0, 1, 0, False, False, True),      # 16x32, both operands row-contiguous
+    (100, 132, 52, 1, 0, 1, 0, True, False, False),       # 16x16, both operands row-contiguous
+    (256, 260, 688, 0, 1, 3, 0, True, False, False),      # 32x32
     (260, 64, 1, 1, 0, 1, 0, False, False, True),         # one row of K
     (36, 1376, 77, 1, 0, 3, 0, True, True, True),         # odd K, accumulating with bias and residual
     (520, 1000, 203, 1, 0, 2, 0, False, False, True),     # 64x64 tiles
