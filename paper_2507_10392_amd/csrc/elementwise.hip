@@ -645,11 +645,12 @@ hipError_t swiglu_bwd(hipStream_t st, DType dt, int T, int F, const void* gu, co
 // ------------------------------------------------------------------ embedding
 template <typename T>
 __global__ __launch_bounds__(256) void embed_fwd_kernel(int H, int V, const int32_t* __restrict__ ids,
-                                                        const T* __restrict__ E, T* __restrict__ x) {
+                                                        const T* __restrict__ E, T* __restrict__ x, int32_t* __restrict__ keep) {
   constexpr int VN = Vec<T>::N;
   typedef typename Vec<T>::type vec_t;
   const int t = blockIdx.x;
   const int id = ids[t];
+  if (keep && threadIdx.x == 0) keep[t] = id;
   const bool ok = id >= 0 && id < V;
   for (int c = threadIdx.x * VN; c < H; c += 256 * VN) {
     vec_t v;
@@ -661,10 +662,10 @@ __global__ __launch_bounds__(256) void embed_fwd_kernel(int H, int V, const int3
     *reinterpret_cast<vec_t*>(x + (int64_t)t * H + c) = v;
   }
 }
-hipError_t embed_fwd(hipStream_t st, DType dt, int T, int H, int V, const int32_t* ids, const void* E, void* x) {
-  if (dt == F32) hipLaunchKernelGGL(embed_fwd_kernel<float>, dim3(T), dim3(256), 0, st, H, V, ids, (const float*)E, (float*)x);
-  else if (dt == BF16) hipLaunchKernelGGL(embed_fwd_kernel<bf16>, dim3(T), dim3(256), 0, st, H, V, ids, (const bf16*)E, (bf16*)x);
-  else hipLaunchKernelGGL(embed_fwd_kernel<f16>, dim3(T), dim3(256), 0, st, H, V, ids, (const f16*)E, (f16*)x);
+hipError_t embed_fwd(hipStream_t st, DType dt, int T, int H, int V, const int32_t* ids, const void* E, void* x, int32_t* keep) {
+  if (dt == F32) hipLaunchKernelGGL(embed_fwd_kernel<float>, dim3(T), dim3(256), 0, st, H, V, ids, (const float*)E, (float*)x, keep);
+  else if (dt == BF16) hipLaunchKernelGGL(embed_fwd_kernel<bf16>, dim3(T), dim3(256), 0, st, H, V, ids, (const bf16*)E, (bf16*)x, keep);
+  else hipLaunchKernelGGL(embed_fwd_kernel<f16>, dim3(T), dim3(256), 0, st, H, V, ids, (const f16*)E, (f16*)x, keep);
   return hipGetLastError();
 }
 
@@ -723,7 +724,7 @@ hipError_t embed_bwd(hipStream_t st, DType dt, int T, int H, int V, const int32_
 template <typename T, bool VEC>
 __global__ __launch_bounds__(256) void ce_fwd_kernel(int V, const T* __restrict__ z, int64_t ldz,
                                                      const int32_t* __restrict__ targets, float* __restrict__ lse,
-                                                     float* __restrict__ rowloss) {
+                                                     float* __restrict__ rowloss, int32_t* __restrict__ keep) {
   constexpr int VN = Vec<T>::N;
   __shared__ float red[4];
   const int t = blockIdx.x;
@@ -758,6 +759,7 @@ __global__ __launch_bounds__(256) void ce_fwd_kernel(int V, const T* __restrict_
   if (threadIdx.x == 0) {
     const float l = mx + logf(s);
     const int tg = targets[t];
+    if (keep) keep[t] = tg;
     lse[t] = l;
     rowloss[t] = (tg >= 0 && tg < V) ? l - to_f(zr[tg]) : 0.f;
   }
@@ -770,12 +772,12 @@ __global__ __launch_bounds__(256) void mean_kernel(int n, const float* __restric
   if (threadIdx.x == 0) *out = s / (float)n;
 }
 hipError_t ce_fwd(hipStream_t st, DType dt, int T, int V, const void* z, int64_t ldz, const int32_t* targets,
-                  float* lse, float* rowloss, float* loss) {
+                  float* lse, float* rowloss, float* loss, int32_t* keep) {
   const int VN = dt == F32 ? 4 : 8;
   const bool vec = V % VN == 0 && ldz % VN == 0 && ((uintptr_t)z & 15) == 0;
 #define CE_FWD(TT) \
-  if (vec) hipLaunchKernelGGL((ce_fwd_kernel<TT, true>), dim3(T), dim3(256), 0, st, V, (const TT*)z, ldz, targets, lse, rowloss); \
-  else hipLaunchKernelGGL((ce_fwd_kernel<TT, false>), dim3(T), dim3(256), 0, st, V, (const TT*)z, ldz, targets, lse, rowloss)
+  if (vec) hipLaunchKernelGGL((ce_fwd_kernel<TT, true>), dim3(T), dim3(256), 0, st, V, (const TT*)z, ldz, targets, lse, rowloss, keep); \
+  else hipLaunchKernelGGL((ce_fwd_kernel<TT, false>), dim3(T), dim3(256), 0, st, V, (const TT*)z, ldz, targets, lse, rowloss, keep)
   if (dt == F32) { CE_FWD(float); } else if (dt == BF16) { CE_FWD(bf16); } else { CE_FWD(f16); }
 #undef CE_FWD
   hipLaunchKernelGGL(mean_kernel, dim3(1), dim3(256), 0, st, T, rowloss, loss);

@@ -137,13 +137,14 @@ hipError_t attn_bwd(hipStream_t st, DType dt, int mb, int S, int nh, int d, cons
                     const void* v, int64_t ld, const void* o, const void* dout, int64_t ldo, const float* lse,
                     float* delta, void* dq, void* dk, void* dv, int64_t ldd, const float2* rope, int force);
 
-// x[t,:] = E[ids[t],:] (rows of ids outside [0,V) give zeros).
-hipError_t embed_fwd(hipStream_t st, DType dt, int T, int H, int V, const int32_t* ids, const void* E, void* x);
+// x[t,:] = E[ids[t],:] (rows of ids outside [0,V) give zeros).  keep (or NULL) receives the ids.
+hipError_t embed_fwd(hipStream_t st, DType dt, int T, int H, int V, const int32_t* ids, const void* E, void* x, int32_t* keep = nullptr);
 // dE[id,:] += sum over the tokens with that id, added in increasing token order.
 hipError_t embed_bwd(hipStream_t st, DType dt, int T, int H, int V, const int32_t* ids, const void* dx, float* dE);
-// lse[t] = logsumexp(z[t,:]); rowloss[t] = lse[t] - z[t,target[t]]; then *loss = mean_t rowloss[t].
+// lse[t] = logsumexp(z[t,:]); rowloss[t] = lse[t] - z[t,target[t]]; then *loss = mean_t rowloss[t].  keep (or NULL) receives
+// the targets.
 hipError_t ce_fwd(hipStream_t st, DType dt, int T, int V, const void* z, int64_t ldz, const int32_t* targets,
-                  float* lse, float* rowloss, float* loss);
+                  float* lse, float* rowloss, float* loss, int32_t* keep = nullptr);
 // z[t,j] <- scale * (exp(z[t,j]-lse[t]) - [j == target[t]])   (scale = loss_scale / T)
 hipError_t ce_bwd(hipStream_t st, DType dt, int T, int V, void* z, int64_t ldz, const int32_t* targets,
                   const float* lse, float scale);

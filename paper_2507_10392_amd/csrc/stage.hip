@@ -614,18 +614,20 @@ bool layer_backward(stage_t* s, int l, const char* x_in, LayerActs& A, const cha
                              gpt ? partial_of(s, p + "ln1.b") : nullptr, s->plan.nblk); });
 }
 
-bool head_forward(stage_t* s, const char* y, HeadActs& A, const int32_t* targets, float* loss_out) {
+// y_out and keep_targets (or NULL) receive y and the targets.
+bool head_forward(stage_t* s, const char* y, HeadActs& A, const int32_t* targets, float* loss_out, void* y_out = nullptr,
+                  int32_t* keep_targets = nullptr) {
   const Shape& h = s->sh;
   const DType dt = dt_of(s);
-  if (!run(s, "norm_fwd", 0, 2.0 * h.T * h.H * h.E, [&] {
-        return norm_fwd(s->st, dt, 1, h.T, h.H, y, s->P(s->seg_off("final_norm.g")), nullptr, s->cfg.norm_eps, A.nf, A.rstd, nullptr); }))
+  if (!run(s, "norm_fwd", 0, (y_out ? 3.0 : 2.0) * h.T * h.H * h.E, [&] {
+        return norm_fwd(s->st, dt, 1, h.T, h.H, y, s->P(s->seg_off("final_norm.g")), nullptr, s->cfg.norm_eps, A.nf, A.rstd, nullptr, y_out); }))
     return false;
   Gemm g;
   g.M = h.T; g.N = h.V; g.K = h.H; g.A = A.nf; g.lda = h.H; g.B = s->P(s->seg_off("head.Wh")); g.ldb = h.V;
   g.C = A.logits; g.ldc = h.V;
   if (!do_gemm(s, g)) return false;
   return run(s, "cross_entropy", 0, (double)h.T * h.V * h.E, [&] {
-    return ce_fwd(s->st, dt, h.T, h.V, A.logits, h.V, targets, A.lse, A.rowloss, loss_out); });
+    return ce_fwd(s->st, dt, h.T, h.V, A.logits, h.V, targets, A.lse, A.rowloss, loss_out, keep_targets); });
 }
 
 bool head_backward(stage_t* s, const char* y, HeadActs& A, const int32_t* targets, float loss_scale, char* dcur) {
@@ -847,9 +849,10 @@ int stage_forward(stage_t* s, int32_t mb, const void* x_or_ids, void* y_out, con
   auto in_of = [&](int l) { return h.recompute ? pl.stash[(size_t)k * h.L + l] : pl.acts[(size_t)mb * h.L + l].x_in; };
   char* x0 = in_of(0);
   if (h.embed) {
-    if (!run(s, "copy", 0, 8.0 * h.T, [&] { return copy_bytes(s->st, pl.ids[mb], x_or_ids, 4ll * h.T); })) return STAGE_ERR_DEVICE;
-    if (!run(s, "embed", 0, 2.0 * TH, [&] {
-          return embed_fwd(s->st, dt, h.T, h.H, h.V, pl.ids[mb], s->P(s->seg_off("embed.E")), x0); }))
+    // the kernels that read the ids, the targets and the last layer's output also write the copies that are kept of them: a copy
+    // of its own is 2-3 us of the queue each, 24 of the 430 launches of a small LLaMA step
+    if (!run(s, "embed", 0, 2.0 * TH + 8.0 * h.T, [&] {
+          return embed_fwd(s->st, dt, h.T, h.H, h.V, (const int32_t*)x_or_ids, s->P(s->seg_off("embed.E")), x0, pl.ids[mb]); }))
       return STAGE_ERR_DEVICE;
   }
   char* final_y = nullptr;
@@ -861,10 +864,8 @@ int stage_forward(stage_t* s, int32_t mb, const void* x_or_ids, void* y_out, con
     if (!layer_forward(s, l, in_of(l), A, y, l == 0 && !h.embed ? x_or_ids : nullptr)) return STAGE_ERR_DEVICE;
   }
   if (h.head) {
-    if (!run(s, "copy", 0, 8.0 * h.T, [&] { return copy_bytes(s->st, pl.targets[mb], targets, 4ll * h.T); })) return STAGE_ERR_DEVICE;
     HeadActs& HA = h.recompute ? pl.hacts[0] : pl.hacts[mb];
-    if (!head_forward(s, final_y, HA, pl.targets[mb], loss_out)) return STAGE_ERR_DEVICE;
-    if (y_out && !run(s, "copy", 0, 2.0 * TH, [&] { return copy_bytes(s->st, y_out, final_y, TH); })) return STAGE_ERR_DEVICE;
+    if (!head_forward(s, final_y, HA, targets, loss_out, y_out, pl.targets[mb])) return STAGE_ERR_DEVICE;
   }
   if (h.offload && !offload_store(s, k, mb)) return STAGE_ERR_DEVICE;
   s->slot[mb] = 1;
