@@ -20,7 +20,7 @@
 // In half the low part is scaled by 2^11, and where small values matter absolutely (P and dS in the backward) it has
 // accumulators of its own, so that it stays out of the subnormal range.  The results are as far from float64 as those of the
 // wave-per-row fp32 kernel that served these head dims (4 x 16 heads of 64, S = 1000: 1.7e-3 in the outputs, their rounding, and
-// 4.3e-8 in lse; 4490 -> 124 us forward + backward in bf16, 136 us in half).  The scores' factor and the row sums are kept a
+// 2.3e-8 in lse; 4490 -> 97 us forward + backward in bf16).  The scores' factor and the row sums are kept a
 // little better than one fp32 operation would (scale_lo, four partial sums), for the sake of lse, which is returned in fp32.
 #include "kernels.h"
 
@@ -391,6 +391,9 @@ __global__ __launch_bounds__(64 * NW, NW == 4 && !(SPLIT && LO_ACC && D > 64) ? 
   const int my_q = wq0 + (lane & 31);
   const float scale_log2 = scale * LOG2E;
 
+  TileRegs<64 * NW, D> kr, vr;   // the first tiles are in flight while delta is formed
+  fetch_tile(kr, rsk, (int)ld, 0, tid, dd);
+  fetch_tile(vr, rsv, (int)ld, 0, tid, dd);
   e16x8 qf[D / 16], dof[D / 16];
   load_row_frags<D>(qf, qh, ld, wq0, S, lane, dd);
   load_row_frags<D>(dof, doh, ldo, wq0, S, lane, dd);
@@ -417,9 +420,6 @@ __global__ __launch_bounds__(64 * NW, NW == 4 && !(SPLIT && LO_ACC && D > 64) ? 
 
   const int last_q = min(q0 + 32 * QW - 1, S - 1);
   const int ntiles = last_q / TR + 1;
-  TileRegs<64 * NW, D> kr, vr;
-  fetch_tile(kr, rsk, (int)ld, 0, tid, dd);
-  fetch_tile(vr, rsv, (int)ld, 0, tid, dd);
   put_tile(kr, smem, tid);
   put_tile(vr, smem + TILE<D>, tid);
   __syncthreads();
@@ -533,16 +533,46 @@ __global__ __launch_bounds__(64 * NW) void attn_bwd_dkv_kernel(int S, const e16*
   // K fragments stay in registers; the wave's 32 rows of V go to a private LDS block instead and are
   // read back as B operands (same fragment pattern as the A operands), which keeps the kernel within
   // the register budget of two waves per SIMD.
+  // Everything the kernel reads before its loop (the first tile, K, V) is in flight before the first wait: a small LLaMA step
+  // (S = 256, 16 launches) is 18 us shorter for it, 4 x 16 heads of 64 at S = 1000 98 -> 97 us.
+  TileRegs<64 * NW, D> qr, dor;
+  float statr = 0.f;
+  bool stat_in = false;
+  // The scaling of lse and the zeros past S wait for put(): either would make the wave wait here, for the tile's loads too.
+  auto fetch = [&](int t) {
+    fetch_tile(qr, rsq, (int)ld, t * TR, tid, dd);
+    fetch_tile(dor, rsdo, (int)ldo, t * TR, tid, dd);
+    if (tid < 128) {
+      const int r = t * TR + (tid & 63);
+      stat_in = r < S;
+      statr = (tid < 64 ? lse_h : dlt_h)[min(r, S - 1)];
+    }
+  };
+  auto put = [&](int buf) {
+    put_tile(qr, smem + buf * 2 * TILE<D>, tid);
+    put_tile(dor, smem + buf * 2 * TILE<D> + TILE<D>, tid);
+    if (tid < 128) stats[buf * 128 + tid] = stat_in ? statr * (tid < 64 ? LOG2E : 1.0f) : 0.f;
+  };
+  const int t_begin = k0 / TR, t_end = (S - 1) / TR + 1;
+  fetch(t_begin);
   e16x8 kf[D / 16];
   load_row_frags<D>(kf, kh, ld, wk0, S, lane, dd);
-  e16* Vw = reinterpret_cast<e16*>(stats + 256) + wave * 32 * LDT<D>;
+  if (QS == 1 || half == 0) {   // QS = 2: the first of the two waves brings the rows, the barrier before the loop publishes them
+    e16* Vw = reinterpret_cast<e16*>(stats + 256) + wave * 32 * LDT<D>;
+    const __amdgpu_buffer_rsrc_t rsv = head_rsrc(vh, ld, S, dd);   // rows past S read as zero
+    union { u32x4 u; e16x8 h; } w[D / 16];
 #pragma unroll
-  for (int i = 0; i < D / 16; ++i) {
-    if (QS == 2 && half) break;   // the first of the two waves brings the rows, the barrier before the loop publishes them
-    const int vv = lane + 64 * i, r = vv / (D / 8), c = (vv % (D / 8)) * 8;
-    *reinterpret_cast<e16x8*>(Vw + r * LDT<D> + c) =
-        wk0 + r < S && c < dd ? *reinterpret_cast<const e16x8*>(vh + (int64_t)(wk0 + r) * ld + c) : zero8();
+    for (int i = 0; i < D / 16; ++i) {
+      const int vv = lane + 64 * i, r = vv / (D / 8), c = (vv % (D / 8)) * 8;
+      w[i].u = __builtin_amdgcn_raw_buffer_load_b128(rsv, c < dd ? (int)(((unsigned)(wk0 + r) * (unsigned)ld + c) * 2u) : (int)0x80000000, 0, 0);
+    }
+#pragma unroll
+    for (int i = 0; i < D / 16; ++i) {
+      const int vv = lane + 64 * i, r = vv / (D / 8), c = (vv % (D / 8)) * 8;
+      *reinterpret_cast<e16x8*>(Vw + r * LDT<D> + c) = w[i].h;
+    }
   }
+  const e16* Vw = reinterpret_cast<e16*>(stats + 256) + wave * 32 * LDT<D>;
   f32x16 dkacc[D / 32], dvacc[D / 32], dklo[SPLIT && LO_ACC ? D / 32 : 1], dvlo[SPLIT && LO_ACC ? D / 32 : 1];
 #pragma unroll
   for (int i = 0; i < D / 32; ++i)
@@ -552,24 +582,6 @@ __global__ __launch_bounds__(64 * NW) void attn_bwd_dkv_kernel(int S, const e16*
       if (SPLIT && LO_ACC) dklo[SPLIT && LO_ACC ? i : 0][r] = dvlo[SPLIT && LO_ACC ? i : 0][r] = 0.f;
     }
 
-  TileRegs<64 * NW, D> qr, dor;
-  float statr = 0.f;
-  auto fetch = [&](int t) {
-    fetch_tile(qr, rsq, (int)ld, t * TR, tid, dd);
-    fetch_tile(dor, rsdo, (int)ldo, t * TR, tid, dd);
-    if (tid < 128) {
-      const int r = t * TR + (tid & 63);
-      statr = 0.f;
-      if (r < S) statr = tid < 64 ? lse_h[r] * LOG2E : dlt_h[r];
-    }
-  };
-  auto put = [&](int buf) {
-    put_tile(qr, smem + buf * 2 * TILE<D>, tid);
-    put_tile(dor, smem + buf * 2 * TILE<D> + TILE<D>, tid);
-    if (tid < 128) stats[buf * 128 + tid] = statr;
-  };
-  const int t_begin = k0 / TR, t_end = (S - 1) / TR + 1;
-  fetch(t_begin);
   put(0);
   __syncthreads();
   for (int t = t_begin; t < t_end; ++t) {
