@@ -13,6 +13,7 @@
 // Measured, forward + backward, against the wave-per-row kernel: 8 heads of 64, S = 128: 91 -> 30 us; 4 heads of 128, S = 256:
 // 273 -> 51 us; 16 heads of 64, S = 1000: 2080 -> 188 us; the errors against float64 are smaller (dk 8.1e-7 -> 4.8e-7).
 #include "kernels.h"
+#include "attention_rows.h"
 
 namespace zs {
 namespace {
@@ -95,8 +96,8 @@ __device__ __forceinline__ Block block_of(int nh, int mb) {
   return Block{(int)blockIdx.x / nhb, hb % nh, hb / nh};
 }
 
-// Sum of the waves' accumulators, quad by quad: wave w gets the sums of the quads q with q % KW == w.
-template <int DS, typename F> __device__ __forceinline__ void merge(f32x4* red, const f32x4 (&acc)[DS], int wave, int lane, F&& out) {
+// Sum of the waves' accumulators, quad by quad: wave w gets the sums of the quads q with q % KW == w, quad q as mine[q / KW].
+template <int DS> __device__ __forceinline__ void merge(f32x4 (&mine)[DS / KW], f32x4* red, const f32x4 (&acc)[DS], int wave, int lane) {
 #pragma unroll
   for (int q = 0; q < DS; ++q)
     if (q % KW != wave) red[((wave < q % KW ? wave : wave - 1) * DS + q) * 64 + lane] = quad<DS>(acc, q);
@@ -107,8 +108,25 @@ template <int DS, typename F> __device__ __forceinline__ void merge(f32x4* red, 
       f32x4 v = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int o = 0; o < KW; ++o) v += o == wave ? quad<DS>(acc, q) : red[((o < wave ? o : o - 1) * DS + q) * 64 + lane];
-      out(q, v);
+      mine[q / KW] = v;
     }
+}
+
+// Rows of the block that hold a non-finite value, as bits 0..15.  A wave looks at the quads it stores, stores the other rows'
+// and redoes these: all columns, of which it writes the ones of its own quads (column c belongs to wave (c / 4) % KW), so the
+// waves need not wait for one another.
+__device__ __forceinline__ unsigned rows_of(float mark) {
+  const unsigned long long m = __ballot(!(mark == 0.f));
+  return (unsigned)((m | m >> 16 | m >> 32 | m >> 48) & 0xffffu);
+}
+__device__ __forceinline__ bool owns(int wave, int c) { return (c >> 2) % KW == wave; }
+template <int DS> __device__ __forceinline__ float mark_of(const f32x4 (&x)[DS / KW]) {
+  float mark = 0.f;
+#pragma unroll
+  for (int i = 0; i < DS / KW; ++i)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) mark = mark_non_finite(mark, x[i][e]);
+  return mark;
 }
 
 // ------------------------------------------------------------------------------------------ forward
@@ -117,6 +135,7 @@ __global__ __launch_bounds__(64 * KW) void attn_fwd_f32_kernel(int S, int dd, co
                                                               const float* __restrict__ v, int64_t ld, float* __restrict__ o,
                                                               int64_t ldo, float* __restrict__ lse, float scale, int nh, int mb) {
   __shared__ f32x4 red[(KW - 1) * DS * 64];
+  __shared__ float rowbuf[KW][32 * DS];   // rows that are redone
   __shared__ float ms[KW][16], ls[KW][16];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const Block blk = block_of(nh, mb);
@@ -190,10 +209,20 @@ __global__ __launch_bounds__(64 * KW) void attn_fwd_f32_kernel(int S, int dd, co
   const float mine = expf(m - mt) / lt;   // a wave that saw no key: exp(-inf) = 0
 #pragma unroll
   for (int s = 0; s < DS; ++s) acc[s] *= mine;
-  merge<DS>(red, acc, wave, lane, [&](int qd, const f32x4& x) {
-    const int col = quad_col(qd, lane);
-    if (my_q < S && col < dd) *reinterpret_cast<f32x4*>(o + (tok0 + my_q) * ldo + blk.h * dd + col) = x;
-  });
+  f32x4 out[DS / KW];
+  merge<DS>(out, red, acc, wave, lane);
+  unsigned redo = rows_of(my_q < S ? mark_of<DS>(out) : 0.f);
+#pragma unroll
+  for (int i = 0; i < DS / KW; ++i) {
+    const int col = quad_col(KW * i + wave, lane);
+    if (my_q < S && col < dd && !(redo >> (lane & 15) & 1)) *reinterpret_cast<f32x4*>(o + (tok0 + my_q) * ldo + blk.h * dd + col) = out[i];
+  }
+  const int64_t at = tok0 * ld + blk.h * dd;
+  for (; redo; redo &= redo - 1) {
+    const int i = q0 + __ffs(redo) - 1;
+    float* row = o + (tok0 + i) * ldo + blk.h * dd;
+    attn_fwd_row<DS / 4>(rowbuf[wave], i, dd, q + at, k + at, v + at, ld, scale, lane, [&](int c, float x) { if (owns(wave, c)) row[c] = x; });
+  }
   if (wave == 0 && lane < 16 && my_q < S) lse[((int64_t)blk.b * nh + blk.h) * S + my_q] = mt + logf(lt);
 }
 
@@ -206,6 +235,7 @@ __global__ __launch_bounds__(64 * KW) void attn_bwd_dq_f32_kernel(int S, int dd,
                                                                  float* __restrict__ dq, int64_t ldd, float scale, int nh, int mb,
                                                                  const float2* __restrict__ rope) {
   __shared__ f32x4 red[(KW - 1) * DS * 64];
+  __shared__ float rowbuf[KW][32 * DS];   // rows that are redone
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const Block blk = block_of(nh, mb);
   const int q0 = ((S + 15) / 16 - 1 - blk.rank) * 16, my_q = q0 + (lane & 15);
@@ -256,13 +286,27 @@ __global__ __launch_bounds__(64 * KW) void attn_bwd_dq_f32_kernel(int S, int dd,
       }
     }
   }
-  merge<DS>(red, acc, wave, lane, [&](int qd, f32x4 x) {
-    const int col = quad_col(qd, lane);
-    if (my_q >= S || col >= dd) return;
-    x *= scale;
+  f32x4 out[DS / KW];
+  merge<DS>(out, red, acc, wave, lane);
+  unsigned redo = rows_of(my_q < S ? mark_of<DS>(out) : 0.f);
+#pragma unroll
+  for (int i = 0; i < DS / KW; ++i) {
+    const int col = quad_col(KW * i + wave, lane);
+    if (my_q >= S || col >= dd || (redo >> (lane & 15) & 1)) continue;
+    f32x4 x = out[i] * scale;
     if (rope) x = unrotate(x, rope, my_q, col, dd);
     *reinterpret_cast<f32x4*>(dq + (tok0 + my_q) * ldd + blk.h * dd + col) = x;
-  });
+  }
+  const int64_t at = tok0 * ld + blk.h * dd;
+  for (; redo; redo &= redo - 1) {
+    const int r = __ffs(redo) - 1, i = q0 + r;
+    float* row = dq + (tok0 + i) * ldd + blk.h * dd;
+    attn_dq_row<DS / 4>(rowbuf[wave], i, dd, q + at, k + at, v + at, ld, dout + tok0 * ldo + blk.h * dd, ldo, __shfl(li, r, 64),
+                        __shfl(dlt, r, 64), scale, lane, [&](int c, float x) {
+                          if (rope) x = unrotate_column(x, rope, i, c, dd);
+                          if (owns(wave, c)) row[c] = x;
+                        });
+  }
 }
 
 // ------------------------------------------------------------------------------------------ dK, dV
@@ -274,6 +318,7 @@ __global__ __launch_bounds__(64 * KW) void attn_bwd_dkv_f32_kernel(int S, int dd
                                                                   float* __restrict__ dk, float* __restrict__ dv, int64_t ldd, float scale,
                                                                   int nh, int mb, const float2* __restrict__ rope) {
   __shared__ f32x4 red[(KW - 1) * DS * 64];
+  __shared__ float rowbuf[KW][32 * DS];   // rows that are redone
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const Block blk = block_of(nh, mb);
   const int k0 = blk.rank * 16, my_k = k0 + (lane & 15);
@@ -329,18 +374,31 @@ __global__ __launch_bounds__(64 * KW) void attn_bwd_dkv_f32_kernel(int S, int dd
       }
     }
   }
-  merge<DS>(red, dva, wave, lane, [&](int qd, const f32x4& x) {
-    const int col = quad_col(qd, lane);
-    if (my_k < S && col < dd) *reinterpret_cast<f32x4*>(dv + (tok0 + my_k) * ldd + blk.h * dd + col) = x;
-  });
+  f32x4 outv[DS / KW], outk[DS / KW];
+  merge<DS>(outv, red, dva, wave, lane);
   __syncthreads();   // the second merge reuses the buffer
-  merge<DS>(red, dka, wave, lane, [&](int qd, f32x4 x) {
-    const int col = quad_col(qd, lane);
-    if (my_k >= S || col >= dd) return;
-    x *= scale;
+  merge<DS>(outk, red, dka, wave, lane);
+  unsigned redo = rows_of(my_k < S ? mark_of<DS>(outv) + mark_of<DS>(outk) : 0.f);
+#pragma unroll
+  for (int i = 0; i < DS / KW; ++i) {
+    const int col = quad_col(KW * i + wave, lane);
+    if (my_k >= S || col >= dd || (redo >> (lane & 15) & 1)) continue;
+    const int64_t to = (tok0 + my_k) * ldd + blk.h * dd + col;
+    f32x4 x = outk[i] * scale;
     if (rope) x = unrotate(x, rope, my_k, col, dd);
-    *reinterpret_cast<f32x4*>(dk + (tok0 + my_k) * ldd + blk.h * dd + col) = x;
-  });
+    *reinterpret_cast<f32x4*>(dv + to) = outv[i];
+    *reinterpret_cast<f32x4*>(dk + to) = x;
+  }
+  const int64_t at = tok0 * ld + blk.h * dd;
+  for (; redo; redo &= redo - 1) {
+    const int j = k0 + __ffs(redo) - 1;
+    const int64_t to = (tok0 + j) * ldd + blk.h * dd;
+    attn_dkv_row<DS / 4>(rowbuf[wave], j, S, dd, q + at, k + at, v + at, ld, dout + tok0 * ldo + blk.h * dd, ldo, lse_h, dlt_h, scale, lane,
+                         [&](int c, float xk, float xv) {
+                           if (rope) xk = unrotate_column(xk, rope, j, c, dd);
+                           if (owns(wave, c)) { dk[to + c] = xk; dv[to + c] = xv; }
+                         });
+  }
 }
 
 }  // namespace
