@@ -105,7 +105,9 @@ int stage_op_swiglu(void* stream, int32_t dtype, int32_t T, int32_t F, const voi
 
 /* Causal softmax attention per (sequence, head): o_i = sum_{j<=i} softmax_j(q_i.k_j/sqrt(d)) v_j.
  * q, k, v: first elements of [mb*S, nh*d] blocks with row stride ld; o row stride ldo;
- * lse: float[mb,nh,S] = log sum_j exp(s_ij).  impl: 0 auto, 1 wave-per-row kernel, 2 MFMA kernel. */
+ * lse: float[mb,nh,S] = log sum_j exp(s_ij).  impl: 0 auto, 1 wave-per-row kernel, 2 MFMA kernel.
+ * inf or NaN in a token's q, k, v or dout reaches only the rows that see the token, here and in the gradients below; the one
+ * exception are 16-bit heads of 128 (impl 0 and 2), where it also reaches rows of the same tile that do not see the token. */
 int stage_op_attention_fwd(void* stream, int32_t dtype, int32_t mb, int32_t S, int32_t nh, int32_t d, const void* q,
                            const void* k, const void* v, int64_t ld, void* o, int64_t ldo, float* lse, int32_t impl);
 /* Gradients dq, dk, dv (row stride ldd) from dout; delta: float[mb,nh,S] scratch. */

@@ -15,14 +15,18 @@
 // produces dQ, one owns 128 keys and produces dK and dV; both recompute P from the saved
 // log-sum-exp.  delta_i = dO_i . O_i is formed by the dQ kernel for its own rows and stored for the other.
 //
-// SPLIT: probabilities and dS do not lose their fp32 precision on the way into the second product: each goes in as a high
-// and a low 16-bit part (two matrix instructions on the same A fragment), which together carry 16 (bf16) or 22 (half) bits.
-// In half the low part is scaled by 2^11, and where small values matter absolutely (P and dS in the backward) it has
-// accumulators of its own, so that it stays out of the subnormal range.  The results are as far from float64 as those of the
-// wave-per-row fp32 kernel that served these head dims (4 x 16 heads of 64, S = 1000: 1.7e-3 in the outputs, their rounding, and
-// 2.3e-8 in lse; 4490 -> 97 us forward + backward in bf16).  The scores' factor and the row sums are kept a
+// SPLIT: probabilities and dS, fp32 in the wave-per-row kernel that served these head dims, go into the second product as a
+// high and a low 16-bit part (two matrix instructions on the same A fragment), which together keep 16 (bf16) or 22 (half) of
+// their 24 bits.  In half the low part is scaled by 2^11, and where small values matter absolutely (P and dS in the backward) it
+// has accumulators of its own, so that it stays out of the subnormal range.  The errors against float64 are those of the
+// wave-per-row kernel (S = 64 .. 4096, d = 64, 80, 96: 1.6e-3 to 1.9e-3 in bf16 and 2.0e-4 to 2.5e-4 in half, both the outputs'
+// rounding, equal within 0.2 %; lse 2.3e-8 against 4.3e-8; 4 x 16 heads of 64, S = 1000: 4490 -> 97 us forward + backward in
+// bf16).  The scores' factor and the row sums are kept a
 // little better than one fp32 operation would (scale_lo, four partial sums), for the sake of lse, which is returned in fp32.
+// A row whose sums are not finite is computed again in fp32, one wave per row: masked rows enter a product with weight zero,
+// which does not hold off inf and NaN (attention_rows.h).
 #include "kernels.h"
+#include "attention_rows.h"
 
 #include <cmath>
 
@@ -240,6 +244,21 @@ __device__ __forceinline__ void merge_halves(f32x16 (&acc)[D / 32], f32x16 (&lo)
   __syncthreads();
 }
 
+// SPLIT: rows of the wave whose sums are not finite, as bits 0..31 (lane and lane ^ 32 hold a row's columns).  They are redone
+// row by row: see attention_rows.h.
+template <int N> __device__ __forceinline__ float mark_of(const f32x16 (&x)[N]) {
+  float mark = 0.f;
+#pragma unroll
+  for (int i = 0; i < N; ++i)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) mark = mark_non_finite(mark, x[i][r]);
+  return mark;
+}
+__device__ __forceinline__ unsigned rows_of(bool live, float mark) {
+  const unsigned long long m = __ballot(live && !(mark == 0.f));
+  return (unsigned)m | (unsigned)(m >> 32);
+}
+
 // ------------------------------------------------------------------------------------------ forward
 // grid ceil(S/(32 NW))*nh*mb, NW waves; wave w owns queries q0 + 32w .. +31; heavy (late) blocks are launched first.
 // NW = 4: two workgroups per CU.  NW = 8: one workgroup per CU whose staged K/V tiles serve 256 queries, so a wave
@@ -361,6 +380,8 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_fwd_kernel(int 
     }
     __syncthreads();
   }
+  unsigned redo = 0;
+  if constexpr (SPLIT) redo = rows_of(my_q < S, mark_of(oacc));
   if (my_q < S) {
     const float inv = 1.0f / l;
     e16* orow = o + (tok0 + my_q) * ldo + h * dd;
@@ -371,12 +392,20 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_fwd_kernel(int 
         e16x4 w;
 #pragma unroll
         for (int e = 0; e < 4; ++e) w[e] = (e16)(oacc[db][4 * c + e] * inv);
-        if (!SPLIT || db * 32 + 8 * c + 4 * (lane >> 5) < dd)
+        if (!SPLIT || (db * 32 + 8 * c + 4 * (lane >> 5) < dd && !(redo >> (lane & 31) & 1)))
           *reinterpret_cast<e16x4*>(orow + db * 32 + 8 * c + 4 * (lane >> 5)) = w;
       }
     if (lane < 32)   // SPLIT: formed in double, once per row: m may lag the maximum by 8, so log l alone would round like lse does
       lse[((int64_t)b * nh + h) * S + my_q] =
           SPLIT ? (float)((double)m * 0.6931471805599453 + log((double)l)) : (m + log2f(l)) * LN2;
+  }
+  if constexpr (SPLIT) {
+    for (; redo; redo &= redo - 1) {
+      const int i = wq0 + __ffs(redo) - 1;
+      e16* row = o + (tok0 + i) * ldo + h * dd;
+      attn_fwd_row<2>(reinterpret_cast<float*>(smem_raw) + wave * 256, i, dd, qh, kh, vh, ld, 1.0f / sqrtf((float)dd), lane,
+                      [&](int c, float x) { row[c] = (e16)x; });
+    }
   }
 }
 
@@ -494,25 +523,42 @@ __global__ __launch_bounds__(64 * NW, NW == 4 && !(SPLIT && LO_ACC && D > 64) ? 
     __syncthreads();
   }
   if constexpr (QS == 2) merge_halves<D>(acc, acclo, reinterpret_cast<f32x4*>(smem_raw), half, wave, lane);
+  if constexpr (SPLIT && LO_ACC && QS == 1) {
+#pragma unroll
+    for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[db][r] = fmaf(acclo[db][r], LO_UNIT, acc[db][r]);
+  }
+  unsigned redo = 0;
+  if constexpr (SPLIT) redo = rows_of(my_q < S && half == 0, mark_of(acc));
   if (my_q < S && half == 0) {
     e16* row = dq + (tok0 + my_q) * ldd + h * dd;
 #pragma unroll
     for (int db = 0; db < D / 32; ++db)
 #pragma unroll
-      for (int r = 0; r < 16; ++r)
-        acc[db][r] = SPLIT && LO_ACC && QS == 1 ? fmaf(acclo[SPLIT && LO_ACC ? db : 0][r], LO_UNIT, acc[db][r]) * (scale / DS_SCALE)
-                               : acc[db][r] * (SPLIT ? scale / DS_SCALE : scale);
+      for (int r = 0; r < 16; ++r) acc[db][r] *= SPLIT ? scale / DS_SCALE : scale;
     if (rope) unrotate_row<D, D / 32>(acc, rope, my_q, lane, dd);
 #pragma unroll
     for (int db = 0; db < D / 32; ++db)
 #pragma unroll
       for (int c = 0; c < 4; ++c) {
-        if (SPLIT && db * 32 + 8 * c + 4 * (lane >> 5) >= dd) continue;
+        if (SPLIT && (db * 32 + 8 * c + 4 * (lane >> 5) >= dd || (redo >> (lane & 31) & 1))) continue;
         e16x4 w;
 #pragma unroll
         for (int e = 0; e < 4; ++e) w[e] = (e16)acc[db][4 * c + e];
         *reinterpret_cast<e16x4*>(row + db * 32 + 8 * c + 4 * (lane >> 5)) = w;
       }
+  }
+  if constexpr (SPLIT) {
+    for (; redo; redo &= redo - 1) {
+      const int r = __ffs(redo) - 1, i = wq0 + r;
+      e16* row = dq + (tok0 + i) * ldd + h * dd;
+      attn_dq_row<2>(reinterpret_cast<float*>(smem_raw) + wave * 256, i, dd, qh, kh, vh, ld, doh, ldo,
+                     lse[((int64_t)b * nh + h) * S + i], __shfl(dlt, r, 64), scale, lane, [&](int c, float x) {
+                       if (rope) x = unrotate_column(x, rope, i, c, dd);
+                       row[c] = (e16)x;
+                     });
+    }
   }
 }
 
@@ -669,30 +715,51 @@ __global__ __launch_bounds__(64 * NW) void attn_bwd_dkv_kernel(int S, const e16*
     merge_halves<D>(dvacc, dvlo, reinterpret_cast<f32x4*>(smem_raw), half, wave, lane);
     merge_halves<D>(dkacc, dklo, reinterpret_cast<f32x4*>(smem_raw), half, wave, lane);
   }
+  if constexpr (SPLIT && LO_ACC && QS == 1) {
+#pragma unroll
+    for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        dkacc[db][r] = fmaf(dklo[db][r], LO_UNIT, dkacc[db][r]);
+        dvacc[db][r] = fmaf(dvlo[db][r], LO_UNIT, dvacc[db][r]);
+      }
+  }
+  unsigned redo = 0;
+  if constexpr (SPLIT) redo = rows_of(my_k < S && half == 0, mark_of(dkacc) + mark_of(dvacc));
   if (my_k < S && half == 0) {
     e16* krow = dk + (tok0 + my_k) * ldd + h * dd;
     e16* vrow = dv + (tok0 + my_k) * ldd + h * dd;
 #pragma unroll
     for (int db = 0; db < D / 32; ++db)
 #pragma unroll
-      for (int r = 0; r < 16; ++r)
-        dkacc[db][r] = SPLIT && LO_ACC && QS == 1 ? fmaf(dklo[SPLIT && LO_ACC ? db : 0][r], LO_UNIT, dkacc[db][r]) * (scale / DS_SCALE)
-                                 : dkacc[db][r] * (SPLIT ? scale / DS_SCALE : scale);
+      for (int r = 0; r < 16; ++r) dkacc[db][r] *= SPLIT ? scale / DS_SCALE : scale;
     if (rope) unrotate_row<D, SPLIT ? 1 : 2>(dkacc, rope, my_k, lane, dd);   // the registers that dV leaves: no spills
 #pragma unroll
     for (int db = 0; db < D / 32; ++db)
 #pragma unroll
       for (int c = 0; c < 4; ++c) {
-        if (SPLIT && db * 32 + 8 * c + 4 * (lane >> 5) >= dd) continue;
+        if (SPLIT && (db * 32 + 8 * c + 4 * (lane >> 5) >= dd || (redo >> (lane & 31) & 1))) continue;
         e16x4 wk, wv;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           wk[e] = (e16)dkacc[db][4 * c + e];
-          wv[e] = (e16)(SPLIT && LO_ACC && QS == 1 ? fmaf(dvlo[SPLIT && LO_ACC ? db : 0][4 * c + e], LO_UNIT, dvacc[db][4 * c + e]) : dvacc[db][4 * c + e]);
+          wv[e] = (e16)dvacc[db][4 * c + e];
         }
         *reinterpret_cast<e16x4*>(krow + db * 32 + 8 * c + 4 * (lane >> 5)) = wk;
         *reinterpret_cast<e16x4*>(vrow + db * 32 + 8 * c + 4 * (lane >> 5)) = wv;
       }
+  }
+  if constexpr (SPLIT) {
+    for (; redo; redo &= redo - 1) {
+      const int j = wk0 + __ffs(redo) - 1;
+      const int64_t to = (tok0 + j) * ldd + h * dd;
+      attn_dkv_row<2>(reinterpret_cast<float*>(smem_raw) + wave * 256, j, S, dd, qh, kh, vh, ld, doh, ldo, lse_h, dlt_h, scale, lane,
+                      [&](int c, float xk, float xv) {
+                        if (rope) xk = unrotate_column(xk, rope, j, c, dd);
+                        dk[to + c] = (e16)xk;
+                        dv[to + c] = (e16)xv;
+                      });
+    }
   }
 }
 

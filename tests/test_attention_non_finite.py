@@ -46,7 +46,8 @@ def same(name, got, want, bar):
 
 
 # one block; a last block of one row; several tiles and, in 16 bits above S = 256, rows that two waves share; padded head dims
-CASES = [(0, 1, 45, 2, 64), (0, 2, 97, 1, 40), (0, 1, 161, 1, 128)]
+CASES = [(0, 1, 45, 2, 64), (0, 2, 97, 1, 40), (0, 1, 161, 1, 128),
+         *((t, *c) for t in (1, 2) for c in ((1, 45, 2, 64), (2, 97, 1, 40), (1, 300, 2, 64), (1, 161, 1, 96), (1, 321, 1, 104)))]
 
 
 @pytest.mark.parametrize("dtype,mb,S,nh,d", CASES)
