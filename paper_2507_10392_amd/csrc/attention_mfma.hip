@@ -104,7 +104,8 @@ constexpr float LO_SCALE = 1.0f;
 constexpr bool LO_ACC = false;
 #endif
 constexpr float LO_UNIT = 1.0f / LO_SCALE;
-// dS goes in times 2^-4 in half, which leaves 2^20 of range on top; its low part still resolves 2^-32.
+// dS goes in times 2^-4 in half, which leaves 2^20 of range on top; its low part still resolves 2^-32.  Above that the high part
+// is inf and the sums of the row are not finite, so the row is redone in fp32 and keeps the fp32 kernel's range.
 constexpr float DS_SCALE = LO_ACC ? 0.0625f : 1.0f;
 __device__ __forceinline__ e16x8 pack8_lo(const f32x16& a, int s, const e16x8& hi, float lo_scale) {
   e16x8 o;

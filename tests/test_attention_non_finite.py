@@ -88,3 +88,24 @@ def test_gradients_of_the_rows_that_do_not_see_it_stay_finite(gpu_device, dtype,
         same(n, got[:, at * H:(at + 1) * H], want[:, at * H:(at + 1) * H], 2 * BAR[dtype])
     clean = got[:row, :H] if which == "k" else got[row + 1:S, H:]
     assert torch.isfinite(clean).all()
+
+
+@pytest.mark.parametrize("mb,S,nh,d", [(1, 45, 2, 64), (1, 300, 2, 64), (1, 161, 1, 96), (1, 70, 1, 104)])
+def test_half_gradients_beyond_the_range_of_the_split(gpu_device, mb, S, nh, d):
+    """dS above 2^20, where its high half part overflows, with Q and K so small that dq and dk are ordinary half values."""
+    print(f"[case] large dS mb={mb} S={S} nh={nh} d={d}", flush=True)
+    rng = np.random.default_rng(63)
+    H = nh * d
+    x = rng.standard_normal((mb * S, 3 * H)).astype(np.float32)
+    x[:, :2 * H] *= 1e-3
+    x[:, 2 * H:] *= 300.0
+    do = dev((1e4 * np.clip(rng.standard_normal((mb * S, H)), -2, 2)).astype(np.float32), TD[2])
+    qkv = dev(x, TD[2])
+    o, lse = forward(2, mb, S, nh, d, qkv, 0)
+    v, g = qkv[:, 2 * H:].double(), do.double()
+    ds = (v * g).view(mb * S, nh, d)[1].sum(-1) / 2     # two keys, probabilities of about a half: dS of the second query's own
+    assert ds.abs().max() > 2.0 ** 20 and torch.isfinite(o).all()
+    got, want = (backward(2, mb, S, nh, d, qkv, o, do, lse, i) for i in (0, 1))
+    assert torch.isfinite(want).all()
+    for n, at in (("dq", 0), ("dk", 1), ("dv", 2)):
+        same(n, got[:, at * H:(at + 1) * H], want[:, at * H:(at + 1) * H], BAR[2])
