@@ -24,6 +24,7 @@ import time
 ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
+PEAK_F32_TFLOPS = 157.3        # MI355X dense fp32 MFMA peak (256 CUs x 4 SIMDs x 64 flop/clk x 2.4 GHz)
 PEAK_BF16_TFLOPS = 2500.0      # MI355X dense bf16 MFMA peak (256 CUs x 4 SIMDs x 1024 flop/clk x 2.4 GHz)
 PEAK_HBM_GBS = 8000.0
 
@@ -529,8 +530,9 @@ def run_workload(torch, zs, cfg, steps, warmup, *, kernel_events=True, graph_mod
         dom = max(kernels, key=lambda n: kernels[n]["ms_per_step"])
         k = kernels[dom]
         if "tflops" in k:
-            roofline = {"kernel": dom, "bound": "mfma", "achieved": k["tflops"], "peak": PEAK_BF16_TFLOPS,
-                        "unit": "TFLOP/s", "frac": k["tflops"] / PEAK_BF16_TFLOPS}
+            peak = PEAK_F32_TFLOPS if cfg.dtype == 0 else PEAK_BF16_TFLOPS
+            roofline = {"kernel": dom, "bound": "mfma", "achieved": k["tflops"], "peak": peak,
+                        "unit": "TFLOP/s", "frac": k["tflops"] / peak}
         else:
             roofline = {"kernel": dom, "bound": "hbm", "achieved": k.get("gbs", 0.0), "peak": PEAK_HBM_GBS,
                         "unit": "GB/s", "frac": k.get("gbs", 0.0) / PEAK_HBM_GBS}

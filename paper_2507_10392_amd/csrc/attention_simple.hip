@@ -118,20 +118,23 @@ int attn_select(DType dt, int S, int d, int force) {
   return attn_mfma_supported(dt, S, d) ? ATTN_MFMA : ATTN_SIMPLE;
 }
 
-// 16-bit heads narrower than 128 also run on the matrix cores (their fp32 probabilities split in two 16-bit parts), when
-// rows can be read in aligned 16-byte pieces through 32-bit offsets; else, and for wider heads, a wavefront per row.
-static bool attn_split_ok(DType dt, int S, int d, int force, int64_t ld_max, uintptr_t pointers, int64_t strides) {
-  return dt != F32 && force != ATTN_SIMPLE && d < 128 && (pointers & 15) == 0 && strides % 8 == 0 && (int64_t)S * ld_max * 2 < (1ll << 31);
+// Heads of 128 in 16 bits always run on the matrix cores.  Narrower 16-bit heads (their fp32 probabilities split in two 16-bit
+// parts) and fp32 heads do when rows can be read in aligned 16-byte pieces through 32-bit offsets; else, and for wider heads, a
+// wavefront per row.
+AttnRoute attn_route(DType dt, int mb, int S, int nh, int d, int64_t ld_max, uintptr_t pointers, int64_t strides, int force) {
+  if (attn_select(dt, S, d, force) == ATTN_MFMA) return ATTN_ROUTE_MFMA;
+  if (force == ATTN_SIMPLE) return ATTN_ROUTE_SIMPLE;
+  if (dt == F32) return attn_f32_supported(mb, S, nh, d, ld_max, pointers, strides) ? ATTN_ROUTE_F32 : ATTN_ROUTE_SIMPLE;
+  return d < 128 && (pointers & 15) == 0 && strides % 8 == 0 && (int64_t)S * ld_max * 2 < (1ll << 31) ? ATTN_ROUTE_SPLIT : ATTN_ROUTE_SIMPLE;
 }
 
 hipError_t attn_fwd(hipStream_t st, DType dt, int mb, int S, int nh, int d, const void* q, const void* k,
                     const void* v, int64_t ld, void* o, int64_t ldo, float* lse, int force) {
-  const uintptr_t at = (uintptr_t)q | (uintptr_t)k | (uintptr_t)v | (uintptr_t)o;
-  if (attn_select(dt, S, d, force) == ATTN_MFMA || attn_split_ok(dt, S, d, force, ld, at, ld | ldo))
+  const AttnRoute route = attn_route(dt, mb, S, nh, d, ld, (uintptr_t)q | (uintptr_t)k | (uintptr_t)v | (uintptr_t)o, ld | ldo, force);
+  if (route == ATTN_ROUTE_MFMA || route == ATTN_ROUTE_SPLIT)
     return dt == F16 ? attn_fwd_mfma_f16(st, mb, S, nh, d, q, k, v, ld, o, ldo, lse)
                      : attn_fwd_mfma(st, mb, S, nh, d, q, k, v, ld, o, ldo, lse);
-  if (dt == F32 && force != ATTN_SIMPLE && attn_f32_supported(mb, S, nh, d, ld, at, ld | ldo))
-    return attn_fwd_f32(st, mb, S, nh, d, q, k, v, ld, o, ldo, lse);
+  if (route == ATTN_ROUTE_F32) return attn_fwd_f32(st, mb, S, nh, d, q, k, v, ld, o, ldo, lse);
   return dt == F32    ? fwd_simple<float>(st, mb, S, nh, d, q, k, v, ld, o, ldo, lse)
          : dt == BF16 ? fwd_simple<bf16>(st, mb, S, nh, d, q, k, v, ld, o, ldo, lse)
                       : fwd_simple<f16>(st, mb, S, nh, d, q, k, v, ld, o, ldo, lse);
@@ -141,12 +144,11 @@ hipError_t attn_bwd(hipStream_t st, DType dt, int mb, int S, int nh, int d, cons
                     float* delta, void* dq, void* dk, void* dv, int64_t ldd, const float2* rope, int force) {
   const uintptr_t at = (uintptr_t)q | (uintptr_t)k | (uintptr_t)v | (uintptr_t)o | (uintptr_t)dout | (uintptr_t)dq | (uintptr_t)dk |
                        (uintptr_t)dv | (uintptr_t)rope;
-  if (attn_select(dt, S, d, force) == ATTN_MFMA ||   // rotation fused into the kernels' stores
-      attn_split_ok(dt, S, d, force, ld > ldo ? ld : ldo, at, ld | ldo | ldd))
+  const AttnRoute route = attn_route(dt, mb, S, nh, d, ld > ldo ? ld : ldo, at, ld | ldo | ldd, force);
+  if (route == ATTN_ROUTE_MFMA || route == ATTN_ROUTE_SPLIT)   // rotation fused into the kernels' stores
     return dt == F16 ? attn_bwd_mfma_f16(st, mb, S, nh, d, q, k, v, ld, o, dout, ldo, lse, delta, dq, dk, dv, ldd, rope)
                      : attn_bwd_mfma(st, mb, S, nh, d, q, k, v, ld, o, dout, ldo, lse, delta, dq, dk, dv, ldd, rope);
-  if (dt == F32 && force != ATTN_SIMPLE && attn_f32_supported(mb, S, nh, d, ld > ldo ? ld : ldo, at, ld | ldo | ldd))
-    return attn_bwd_f32(st, mb, S, nh, d, q, k, v, ld, o, dout, ldo, lse, delta, dq, dk, dv, ldd, rope);
+  if (route == ATTN_ROUTE_F32) return attn_bwd_f32(st, mb, S, nh, d, q, k, v, ld, o, dout, ldo, lse, delta, dq, dk, dv, ldd, rope);
   hipError_t e = dt == F32    ? bwd_simple<float>(st, mb, S, nh, d, q, k, v, ld, o, dout, ldo, lse, delta, dq, dk, dv, ldd)
                  : dt == BF16 ? bwd_simple<bf16>(st, mb, S, nh, d, q, k, v, ld, o, dout, ldo, lse, delta, dq, dk, dv, ldd)
                               : bwd_simple<f16>(st, mb, S, nh, d, q, k, v, ld, o, dout, ldo, lse, delta, dq, dk, dv, ldd);

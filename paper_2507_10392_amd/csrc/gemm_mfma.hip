@@ -216,8 +216,8 @@ __global__ __launch_bounds__(256) void add_partials_kernel(float* C, int64_t ldc
 // Taken when the tiles do not fill 128 CUs' worth twice over and a half is still long against the added pass (1.2 us per
 // MB of result at 4 TB/s and its launch, against 7.8 ns per k).
 namespace {
-bool plan_halves(const Gemm& g, Gemm& h) {
-  if (!g.ws || g.transA || !g.transB || g.c_f32_accum || g.batch != 1 || g.bias || g.resid || g.rope || g.glu || g.nx) return false;
+bool plan_halves(DType dt, const Gemm& g, Gemm& h) {
+  if (g_force_tile || !g.ws || g.transA || !g.transB || g.c_f32_accum || g.batch != 1 || g.bias || g.resid || g.rope || g.glu || g.nx) return false;
   const int64_t tiles = cdiv(g.M, 128) * cdiv(g.N, 128);
   if (tiles > 128 || g.N % 8 || ((uintptr_t)g.ws & 15) || g.ws_bytes < 8ll * g.M * g.N) return false;
   h = g;
@@ -233,7 +233,7 @@ bool plan_halves(const Gemm& g, Gemm& h) {
   h.C = g.ws; h.ldc = g.N; h.sC = (int64_t)g.M * g.N;
   h.batch = 2; h.c_f32_accum = 1; h.c_overwrite = 1;
   const double gain = 7.8e-3 * h.K, cost = 6.0 + (double)g.M * g.N * 10.0 / 4.0e6;   // us
-  return gain > 1.5 * cost;
+  return gain > 1.5 * cost && gemm_mfma_takes(dt, h);
 }
 
 // C = p[0] + p[1], rounded: 8 columns per thread.
@@ -252,6 +252,11 @@ __global__ __launch_bounds__(256) void add_halves_kernel(int64_t nvec, int vec_p
   *reinterpret_cast<E8*>(C + i / vec_per_row * ldc + (i % vec_per_row) * 8) = o;
 }
 }  // namespace
+
+bool gemm_mfma_halves(DType dt, const Gemm& g) {
+  Gemm h;
+  return plan_halves(dt, g, h);
+}
 
 int64_t gemm_mfma_ws_bytes(const Gemm& g) {
   KCut k;
@@ -274,7 +279,7 @@ hipError_t gemm_mfma(hipStream_t st, DType dt, const Gemm& g) {
     }
   }
   Gemm halves;
-  if (!g_force_tile && plan_halves(g, halves) && gemm_mfma_takes(dt, halves)) {
+  if (plan_halves(dt, g, halves)) {
     const hipError_t e = run_tile(st, dt, halves, gemm_mfma_pick_tile(halves) == 2);
     if (e != hipSuccess) return e;
     const int64_t nvec = (int64_t)g.M * g.N / 8;

@@ -118,13 +118,19 @@ Gemm part_of(const Gemm& g, int p) {
   return a;
 }
 
+GemmRoute route_one(DType dt, const Gemm& g, int force) {
+  if (gemm_select(dt, g, force) == GEMM_MFMA)
+    return force == GEMM_AUTO && gemm_small_tile(g) ? ROUTE_SMALL : gemm_mfma_halves(dt, g) ? ROUTE_HALVES : ROUTE_STAGED;
+  return dt == F32 && force != GEMM_SIMPLE && gemm_f32_supported(g) ? ROUTE_F32 : ROUTE_SIMPLE;
+}
+
 // One launch: the 16-bit or the fp32 matrix-core kernel when it takes the arguments, else the plain kernel (with the
 // rotation and the multi-part K range done in extra passes).
 hipError_t gemm_one(hipStream_t st, DType dt, const Gemm& g, int force) {
-  if (gemm_select(dt, g, force) == GEMM_MFMA) {   // rotation fused into the kernels' stores
-    const int tile = force == GEMM_AUTO ? gemm_small_tile(g) : 0;
-    return tile ? gemm_small(st, dt, g, tile) : gemm_mfma(st, dt, g);
-  }
+  const GemmRoute route = route_one(dt, g, force);   // the matrix-core kernels have the rotation in their stores
+  if (route == ROUTE_SMALL) return gemm_small(st, dt, g, gemm_small_tile(g));
+  if (route == ROUTE_STAGED || route == ROUTE_HALVES) return gemm_mfma(st, dt, g);
+  if (route == ROUTE_F32) return gemm_f32(st, g);
   if (g.glu) {   // gated unit: the plain product(s), then the activation kernel over the dense [gate | up] rows
     Gemm p = g;
     p.glu = 0; p.gu = nullptr;
@@ -140,7 +146,6 @@ hipError_t gemm_one(hipStream_t st, DType dt, const Gemm& g, int force) {
     }
     return hipSuccess;
   }
-  if (dt == F32 && force != GEMM_SIMPLE && gemm_f32_supported(g)) return gemm_f32(st, g);   // rotation in its store
   hipError_t e = gemm_simple(st, dt, g);
   const int elem = dt == F32 ? 4 : 2;
   for (int z = 0; e == hipSuccess && g.rope && z < g.rope_batches && z < g.batch; ++z)
@@ -198,13 +203,17 @@ bool split_k(const Gemm& g, std::vector<Gemm>& parts) {
 
 }  // namespace
 
-bool gemm_splits(DType dt, const Gemm& g) {
-  if (dt == F32 || gemm_mfma_takes(dt, g)) return false;
-  std::vector<Gemm> parts;
-  if (!(split_rows(g, parts) || split_k(g, parts))) return false;
-  for (const Gemm& p : parts)
-    if (!gemm_mfma_takes(dt, p)) return false;
-  return true;
+GemmRoute gemm_route(DType dt, const Gemm& g) {
+  if (dt != F32 && !gemm_mfma_takes(dt, g)) {   // several launches: as gemm() cuts it
+    if (g.nx) return gemm_route(dt, part_of(g, 0));
+    std::vector<Gemm> parts;
+    if (split_rows(g, parts) || split_k(g, parts)) return gemm_route(dt, parts[0]);
+  }
+  const GemmRoute route = route_one(dt, g, GEMM_AUTO);
+  if (route != ROUTE_SIMPLE || !(g.glu || g.nx)) return route;
+  Gemm p = g.nx ? part_of(g, 0) : g;            // taken apart by gemm_one: the plain product
+  p.glu = 0; p.gu = nullptr;
+  return route_one(dt, p, GEMM_AUTO);
 }
 
 hipError_t gemm(hipStream_t st, DType dt, const Gemm& g, int force) {

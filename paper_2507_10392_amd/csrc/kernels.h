@@ -70,8 +70,11 @@ enum GemmImpl { GEMM_AUTO = 0, GEMM_SIMPLE = 1, GEMM_MFMA = 2 };
 // Returns which implementation a call with these arguments runs (GEMM_SIMPLE or GEMM_MFMA).
 int gemm_select(DType dt, const Gemm& g, int force);
 hipError_t gemm(hipStream_t st, DType dt, const Gemm& g, int force);
-// True when gemm() runs the call as several MFMA launches because an operand exceeds the kernel's 2^30-byte range.
-bool gemm_splits(DType dt, const Gemm& g);
+// The kernels behind gemm(): plain, fp32 matrix cores, 16-bit matrix cores on small tiles, on staged tiles as two halves of K
+// that a second kernel adds (see ws), and on staged tiles.  gemm_route is the
+// choice that gemm(GEMM_AUTO) makes for a call (of its first launch, where it takes several), for the names of timing classes.
+enum GemmRoute { ROUTE_SIMPLE, ROUTE_F32, ROUTE_SMALL, ROUTE_HALVES, ROUTE_STAGED };
+GemmRoute gemm_route(DType dt, const Gemm& g);
 hipError_t gemm_simple(hipStream_t st, DType dt, const Gemm& g);
 // fp32 products on the fp32 matrix cores (gemm_f32.hip); no multi-part K range, no gated unit.
 bool gemm_f32_supported(const Gemm& g);
@@ -81,6 +84,8 @@ hipError_t gemm_f32(hipStream_t st, const Gemm& g);
 bool gemm_mfma_takes(DType dt, const Gemm& g);
 bool gemm_mfma_supported(DType dt, const Gemm& g);
 hipError_t gemm_mfma(hipStream_t st, DType dt, const Gemm& g);
+// True when gemm_mfma runs this product as two halves of K.
+bool gemm_mfma_halves(DType dt, const Gemm& g);
 // Scratch bytes (Gemm::ws) with which gemm_mfma would cut the K range of this product's last round of tiles; 0 when
 // it would not (the answer depends on the shape only, not on the pointers).
 int64_t gemm_mfma_ws_bytes(const Gemm& g);
@@ -128,6 +133,10 @@ hipError_t swiglu_bwd(hipStream_t st, DType dt, int T, int F, const void* gu, co
 // buffer with row stride ld (elements); token t = b*S + s.  lse is float[mb, nh, S].
 enum AttnImpl { ATTN_AUTO = 0, ATTN_SIMPLE = 1, ATTN_MFMA = 2 };
 int attn_select(DType dt, int S, int d, int force);
+// The kernels behind attn_fwd and attn_bwd: a wave per row, fp32 matrix cores, 16-bit matrix cores (head dim 128, and narrower
+// heads with split probabilities).  pointers: all arguments or-ed together; strides: all row strides or-ed together.
+enum AttnRoute { ATTN_ROUTE_SIMPLE, ATTN_ROUTE_F32, ATTN_ROUTE_MFMA, ATTN_ROUTE_SPLIT };
+AttnRoute attn_route(DType dt, int mb, int S, int nh, int d, int64_t ld_max, uintptr_t pointers, int64_t strides, int force);
 hipError_t attn_fwd(hipStream_t st, DType dt, int mb, int S, int nh, int d, const void* q, const void* k,
                     const void* v, int64_t ld, void* o, int64_t ldo, float* lse, int force);
 // delta is float[mb, nh, S] scratch.  dq, dk, dv are laid out like q, k, v with row stride ldd.

@@ -418,16 +418,27 @@ bool offload_load(stage_t* s, int k, int mb) {
 DType dt_of(const stage_t* s) { return s->sh.dtype == STAGE_DTYPE_F16 ? F16 : s->sh.bf ? BF16 : F32; }
 
 bool do_gemm(stage_t* s, const Gemm& g) {
-  const int impl = gemm_select(dt_of(s), g, GEMM_AUTO);
-  static const char* names[3][4] = {{"gemm_simple_nn", "gemm_simple_nt", "gemm_simple_tn", "gemm_simple_tt"},
-                                    {"gemm_mfma_nn", "gemm_mfma_nt", "gemm_mfma_tn", "gemm_mfma_tt"},
-                                    {"gemm_f32_nn", "gemm_f32_nt", "gemm_f32_tn", "gemm_f32_tt"}};
-  const bool f32 = dt_of(s) == F32;   // the fp32 matrix-core kernel, or the plain one where its alignment rules are not met
-  const bool mfma = impl == GEMM_MFMA || gemm_splits(dt_of(s), g);
+  static const char* names[5][4] = {{"gemm_simple_nn", "gemm_simple_nt", "gemm_simple_tn", "gemm_simple_tt"},
+                                    {"gemm_f32_nn", "gemm_f32_nt", "gemm_f32_tn", "gemm_f32_tt"},
+                                    {"gemm_small_nn", "gemm_small_nt", "gemm_small_tn", "gemm_small_tt"},
+                                    {"gemm_halves_nn", "gemm_halves_nt", "gemm_halves_tn", "gemm_halves_tt"},
+                                    {"gemm_mfma_nn", "gemm_mfma_nt", "gemm_mfma_tn", "gemm_mfma_tt"}};
   // the products that apply the gated unit in their store are kernels of their own and are timed as such
-  const char* cls = mfma && g.glu == 1 ? "gemm_mfma_nn_glu" : mfma && g.glu == 2 ? "gemm_mfma_nt_glu" : names[f32 ? 2 : mfma][g.transA * 2 + g.transB];
+  static const char* glu_names[2][2] = {{"gemm_small_nn_glu", "gemm_small_nt_glu"}, {"gemm_mfma_nn_glu", "gemm_mfma_nt_glu"}};
+  const GemmRoute route = gemm_route(dt_of(s), g);
+  const char* cls = g.glu && route >= ROUTE_SMALL ? glu_names[route == ROUTE_STAGED][g.glu == 2]
+                                                   : names[route][g.transA * 2 + g.transB];
   const double flops = 2.0 * g.M * g.N * g.K * (g.glu == 1 ? 2 : g.batch);
   return run(s, cls, flops, 0.0, [&] { return gemm(s->st, dt_of(s), g, GEMM_AUTO); });
+}
+
+// Timing class of the attention of this stage: fwd and bwd run the same route, since every row stride and base is a multiple
+// of 16 bytes (workspace buffers of 256-byte alignment, hidden a multiple of 8).
+const char* attn_class(const stage_t* s, const LayerActs& A, bool bwd) {
+  static const char* names[4][2] = {{"attn_fwd_simple", "attn_bwd_simple"}, {"attn_fwd_f32", "attn_bwd_f32"},
+                                    {"attn_fwd_mfma", "attn_bwd_mfma"}, {"attn_fwd_mfma_split", "attn_bwd_mfma_split"}};
+  const Shape& h = s->sh;
+  return names[attn_route(dt_of(s), h.mb, h.S, h.nh, h.d, 3ll * h.H, (uintptr_t)A.qkv | (uintptr_t)A.o, 3ll * h.H | h.H, ATTN_AUTO)][bwd];
 }
 
 // ---- forward of one layer ---------------------------------------------------------------------
@@ -457,7 +468,7 @@ bool layer_forward(stage_t* s, int l, char* x_in, LayerActs& A, char* y, const v
   }
   if (!do_gemm(s, g)) return false;
   const double attn_flops = 4.0 * h.mb * h.nh * (double)h.S * (h.S + 1) / 2 * h.d;
-  if (!run(s, attn_select(dt, h.S, h.d, 0) == ATTN_MFMA ? "attn_fwd_mfma" : "attn_fwd_simple", attn_flops, 0, [&] {
+  if (!run(s, attn_class(s, A, false), attn_flops, 0, [&] {
         return attn_fwd(s->st, dt, h.mb, h.S, h.nh, h.d, A.qkv, A.qkv + (int64_t)H * h.E, A.qkv + 2ll * H * h.E, 3 * H,
                         A.o, H, A.lse, ATTN_AUTO); }))
     return false;
@@ -588,7 +599,7 @@ bool layer_backward(stage_t* s, int l, const char* x_in, LayerActs& A, const cha
   // algorithmic work: dV, dP, dQ, dK over the causal half (recomputing the scores is not counted)
   const double attn_flops = 8.0 * h.mb * h.nh * (double)h.S * (h.S + 1) / 2 * h.d;
   const int64_t HE = (int64_t)H * h.E;
-  if (!run(s, attn_select(dt, h.S, h.d, 0) == ATTN_MFMA ? "attn_bwd_mfma" : "attn_bwd_simple", attn_flops, 0, [&] {
+  if (!run(s, attn_class(s, A, true), attn_flops, 0, [&] {
         return attn_bwd(s->st, dt, h.mb, h.S, h.nh, h.d, A.qkv, A.qkv + HE, A.qkv + 2 * HE, 3 * H, A.o, pl.gO, H, A.lse,
                         pl.delta, gqkv, gqkv + HE, gqkv + 2 * HE, 3 * H, gpt ? nullptr : pl.rope, ATTN_AUTO); }))
     return false;
