@@ -1,4 +1,4 @@
-"""One layer wide enough, on few enough tokens, that the input gradients' products run as two halves of K side by side."""
+"""Layers on few tokens, whose input gradients have few tiles and a long K, against the oracle."""
 import pytest
 
 from harness import TOL, GpuStage, compare_step, oracle_step
@@ -7,16 +7,33 @@ from workloads import get_config, make_inputs
 pytestmark = pytest.mark.gpu
 
 
-# Llama: gate|up gradients (two segments of the FFN width); GPT: the FFN's and, with K = 3 * hidden, the QKV projection's;
-# 136 tokens leave the last tile row ragged
-@pytest.mark.parametrize("name,hidden,heads,ffn,seq", [("C3t", 1024, 8, 4096, 256), ("C3h", 1024, 8, 4096, 136), ("C2t", 1024, 8, 8192, 256),
-                                                       ("C2t", 2048, 16, 8192, 136)])
-def test_layer_on_few_tokens_against_the_oracle(gpu_device, name, hidden, heads, ffn, seq):
+def run(name, hidden, heads, ffn, seq):
     cfg = get_config(name).with_(layers=1, hidden=hidden, heads=heads, ffn=ffn, seq=seq, num_microbatches=1)
     print(f"[case] few tokens {name} hidden={hidden} ffn={ffn} seq={seq}", flush=True)
     scale = 256.0 if cfg.dtype == 2 else 1.0
     inp = make_inputs(cfg, perturbed=True, num_microbatches=1, dy_scale=scale)
     g = GpuStage(cfg, inp, max_microbatches=1)
+    g.stage.profile(True)
     gpu = g.run_microbatches(inp, M=1)
+    classes = g.stage.profile_read()
     compare_step(cfg, gpu, oracle_step(cfg, inp, M=1), TOL[cfg.dtype])
     g.stage.close()
+    return classes
+
+
+# small enough for the 32x32 tiles of gemm_small.hip, K in two segments (Llama) and in one (GPT); 136 tokens leave the last tile
+# row ragged
+@pytest.mark.parametrize("name,hidden,heads,ffn,seq", [("C3t", 1024, 8, 4096, 256), ("C3h", 1024, 8, 4096, 136), ("C2t", 1024, 8, 8192, 256),
+                                                       ("C2t", 2048, 16, 8192, 136)])
+def test_layer_on_few_tokens_against_the_oracle(gpu_device, name, hidden, heads, ffn, seq):
+    assert "gemm_small_nt" in run(name, hidden, heads, ffn, seq)
+
+
+# 80 tiles of 128x128: too many for the small tiles, and so few that the two halves of K run side by side as fp32 results in
+# scratch.  Llama: the gate|up gradient (its two segments become the batch); GPT: the FFN's and, where the scratch that is free at
+# its time holds two results (ffn >= 4 hidden), the QKV projection's.  600 tokens leave the last tile row ragged.
+@pytest.mark.parametrize("name,ffn,seq,products", [("C3t", 2048, 640, 1), ("C3t", 2056, 600, 1), ("C3h", 2048, 600, 1), ("C2t", 8192, 600, 2),
+                                                   ("C2h", 8192, 640, 2), ("C2h", 4096, 600, 1)])
+def test_input_gradients_as_two_halves_of_k(gpu_device, name, ffn, seq, products):
+    classes = run(name, 2048, 16, ffn, seq)
+    assert classes.get("gemm_halves_nt", {"launches": 0})["launches"] == products, sorted(classes)
