@@ -108,7 +108,7 @@ def test_narrow_heads_with_inverse_rotation_and_unaligned_rows(gpu_device, dtype
 
 
 @pytest.mark.parametrize("dtype", [1, 2])
-@pytest.mark.parametrize("mb,S,nh", [(1, 31, 1), (2, 257, 1), (1, 321, 2), (1, 385, 3)])
+@pytest.mark.parametrize("mb,S,nh", [(1, 31, 1), (2, 257, 1), (1, 321, 2), (1, 384, 3), (1, 385, 3)])
 def test_heads_of_128_whose_rows_two_waves_share(gpu_device, mb, S, nh, dtype):
     """Backward of few head-sequences (8 waves per block of 128 rows, two on the same 32) against the oracle; the last block
     holds 1, 31, 65 or 128 rows."""

@@ -33,8 +33,15 @@ GEMM_CASES = [
     (68, 72, 52, 1, 1, 1, 0, False, False, False),
     (130, 68, 5 * 12, 0, 1, 1, 12, False, False, False),  # segments shorter than a slab
     (257, 512, 2 * 344, 0, 1, 1, 344, False, False, False),
-    (1100, 2052, 260, 0, 0, 2, 0, True, True, False),     # 128x128 tiles, ragged
+    (1100, 2052, 260, 0, 0, 2, 0, True, True, False),     # 64x64, several rounds of workgroups
     (1028, 2052, 131, 1, 0, 2, 0, False, False, True),
+    # 128x128 tiles, ragged, in every form: 765 workgroups are three rounds of the 256 CUs and 2970 of 64x64 twelve, by the rule's
+    # estimate half as long again
+    (1100, 2052, 68, 0, 0, 5, 0, True, True, False),
+    (1100, 2052, 68, 0, 1, 5, 0, False, False, False),
+    (1100, 2052, 72, 0, 1, 5, 36, True, False, False),
+    (1028, 2052, 67, 1, 0, 5, 0, False, False, True),
+    (1028, 2052, 68, 1, 1, 5, 0, False, True, False),
     (130, 70, 50, 0, 0, 1, 0, True, True, False),         # contiguous extents that are no multiples of 4: the plain kernel
 ]
 

@@ -1,4 +1,4 @@
-"""Norms over rows of any width: masked last vectors, rows shared by two and four waves, rows too long for registers."""
+"""Norms over rows of any width: masked last vectors, rows shared by two, four and eight waves, rows too long for registers."""
 import numpy as np
 import pytest
 import torch
@@ -15,10 +15,11 @@ EPS = 1e-5
 
 @pytest.mark.parametrize("dtype", [0, 1, 2])
 @pytest.mark.parametrize("kind", [0, 1])
-# widths in chunks of 64 lanes x 16 bytes (256 fp32 or 512 16-bit elements): within the first; 2 and a bit; 7 and a bit; just
-# over 8 (two waves); just under 16; just over 16 (four waves); 32; just over 32 (re-reading kernels)
-@pytest.mark.parametrize("chunks,T,nblk", [(0.125, 5, 5), (2.0625, 37, 7), (7.5, 33, 4), (8.0625, 19, 6), (15.9375, 9, 2), (16.0625, 11, 3),
-                                           (32, 6, 6), (32.0625, 3, 2)])
+# widths in chunks of 64 lanes x 16 bytes (256 fp32 or 512 16-bit elements).  Backward: within the first and 2 and a bit, one wave
+# per row; 5 and a bit (three chunks per wave) and 7 and a bit (four), two waves; just over 8 (three per wave) and just under 16,
+# four waves; just over 16 and 32, eight waves; just over 32, re-reading kernels.  Forward: one wave up to 16, then re-reading.
+@pytest.mark.parametrize("chunks,T,nblk", [(0.125, 5, 5), (2.0625, 37, 7), (5.0625, 21, 5), (5.5, 10, 3), (7.5, 33, 4), (8.0625, 19, 6),
+                                           (15.9375, 9, 2), (16.0625, 11, 3), (32, 6, 6), (32.0625, 3, 2)])
 def test_norm_any_width(gpu_device, kind, dtype, chunks, T, nblk):
     H = int(chunks * (256 if dtype == 0 else 512))
     print(f"[case] norm kind={kind} dtype={dtype} T={T} H={H} nblk={nblk}", flush=True)

@@ -30,6 +30,28 @@ def test_weight_gradient_over_an_odd_number_of_tokens(gpu_device, dtype, M, N, T
     assert err <= 2e-5            # exact 16-bit products, fp32 sums: the bar of the other accumulating products
 
 
+@pytest.mark.parametrize("dtype", [1, 2])
+# 32x32 and 64x64 tiles, then staged tiles
+@pytest.mark.parametrize("M,N,parts,last", [(40, 72, 3, 1), (520, 1376, 2, 77), (1000, 1016, 5, 127), (2048, 2056, 3, 77), (2048, 4104, 4, 201)])
+def test_last_of_several_parts_with_an_odd_number_of_tokens(gpu_device, M, N, parts, last, dtype):
+    print(f"[case] wgrad parts M={M} N={N} parts={parts} last={last} dtype={dtype}", flush=True)
+    rng = np.random.default_rng(52)
+    rnd, td = (round_bf16, torch.bfloat16) if dtype == 1 else (round_f16, torch.float16)
+    rows = [128] * (parts - 1) + [last]
+    x, dy = ([rnd(rng.standard_normal((r + 9, w)).astype(np.float32)) for r in rows] for w in (M, N))
+    for a, b, r in zip(x, dy, rows):     # rows behind a part's last token hold inf
+        a[r:], b[r:] = np.inf, np.inf
+    C0 = rng.standard_normal((M, N)).astype(np.float32)
+    C = dev(C0)
+    zs.wgrad_parts(torch.cuda.current_stream().cuda_stream, dtype, M, N, 128, last, [dev(a, td) for a in x], M, [dev(a, td) for a in dy], N, C, N,
+                   1, 0, 0, 0, 0)
+    torch.cuda.synchronize()
+    want = C0 + sum(a[:r].astype(np.float64).T @ b[:r].astype(np.float64) for a, b, r in zip(x, dy, rows))
+    err = rel_err(C.cpu().numpy(), want)
+    log_report(f"odd wgrad parts {M} {N} {parts} {last} {dtype}", [("C", err)])
+    assert err <= 2e-5            # exact 16-bit products, fp32 sums: the bar of the other accumulating products
+
+
 def test_forced_matrix_core_kernel_still_wants_multiples_of_8(gpu_device):
     x, dy, C = (torch.zeros(64, 64, device="cuda", dtype=t) for t in (torch.bfloat16, torch.bfloat16, torch.float32))
     with pytest.raises(zs.StageError):
