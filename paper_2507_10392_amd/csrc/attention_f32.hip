@@ -112,14 +112,16 @@ template <int DS> __device__ __forceinline__ void merge(f32x4 (&mine)[DS / KW], 
     }
 }
 
-// Rows of the block that hold a non-finite value, as bits 0..15.  A wave looks at the quads it stores, stores the other rows'
-// and redoes these: all columns, of which it writes the ones of its own quads (column c belongs to wave (c / 4) % KW), so the
-// waves need not wait for one another.
-__device__ __forceinline__ unsigned rows_of(float mark) {
+// Rows of the block that hold a non-finite value in any wave's quads, as bits 0..15.
+__device__ __forceinline__ unsigned rows_of(unsigned* masks, float mark, int wave) {
   const unsigned long long m = __ballot(!(mark == 0.f));
-  return (unsigned)((m | m >> 16 | m >> 32 | m >> 48) & 0xffffu);
+  masks[wave] = (unsigned)((m | m >> 16 | m >> 32 | m >> 48) & 0xffffu);
+  __syncthreads();
+  unsigned rows = 0;
+#pragma unroll
+  for (int w = 0; w < KW; ++w) rows |= masks[w];
+  return rows;
 }
-__device__ __forceinline__ bool owns(int wave, int c) { return (c >> 2) % KW == wave; }
 template <int DS> __device__ __forceinline__ float mark_of(const f32x4 (&x)[DS / KW]) {
   float mark = 0.f;
 #pragma unroll
@@ -136,6 +138,7 @@ __global__ __launch_bounds__(64 * KW) void attn_fwd_f32_kernel(int S, int dd, co
                                                               int64_t ldo, float* __restrict__ lse, float scale, int nh, int mb) {
   __shared__ f32x4 red[(KW - 1) * DS * 64];
   __shared__ float rowbuf[KW][32 * DS];   // rows that are redone
+  __shared__ unsigned masks[KW];
   __shared__ float ms[KW][16], ls[KW][16];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const Block blk = block_of(nh, mb);
@@ -211,18 +214,17 @@ __global__ __launch_bounds__(64 * KW) void attn_fwd_f32_kernel(int S, int dd, co
   for (int s = 0; s < DS; ++s) acc[s] *= mine;
   f32x4 out[DS / KW];
   merge<DS>(out, red, acc, wave, lane);
-  unsigned redo = rows_of(my_q < S ? mark_of<DS>(out) : 0.f);
+  const unsigned redo = rows_of(masks, my_q < S && lt == lt ? mark_of<DS>(out) : 0.f, wave);
 #pragma unroll
   for (int i = 0; i < DS / KW; ++i) {
     const int col = quad_col(KW * i + wave, lane);
     if (my_q < S && col < dd && !(redo >> (lane & 15) & 1)) *reinterpret_cast<f32x4*>(o + (tok0 + my_q) * ldo + blk.h * dd + col) = out[i];
   }
   const int64_t at = tok0 * ld + blk.h * dd;
-  for (; redo; redo &= redo - 1) {
-    const int i = q0 + __ffs(redo) - 1;
-    float* row = o + (tok0 + i) * ldo + blk.h * dd;
-    attn_fwd_row<DS / 4>(rowbuf[wave], i, dd, q + at, k + at, v + at, ld, scale, lane, [&](int c, float x) { if (owns(wave, c)) row[c] = x; });
-  }
+  for_dealt_rows(&redo, 1, KW, wave, [&](int, int r) {
+    float* row = o + (tok0 + q0 + r) * ldo + blk.h * dd;
+    attn_fwd_row<DS / 4>(rowbuf[wave], q0 + r, dd, q + at, k + at, v + at, ld, scale, lane, [&](int c, float x) { row[c] = x; });
+  });
   if (wave == 0 && lane < 16 && my_q < S) lse[((int64_t)blk.b * nh + blk.h) * S + my_q] = mt + logf(lt);
 }
 
@@ -236,6 +238,7 @@ __global__ __launch_bounds__(64 * KW) void attn_bwd_dq_f32_kernel(int S, int dd,
                                                                  const float2* __restrict__ rope) {
   __shared__ f32x4 red[(KW - 1) * DS * 64];
   __shared__ float rowbuf[KW][32 * DS];   // rows that are redone
+  __shared__ unsigned masks[KW];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const Block blk = block_of(nh, mb);
   const int q0 = ((S + 15) / 16 - 1 - blk.rank) * 16, my_q = q0 + (lane & 15);
@@ -288,7 +291,7 @@ __global__ __launch_bounds__(64 * KW) void attn_bwd_dq_f32_kernel(int S, int dd,
   }
   f32x4 out[DS / KW];
   merge<DS>(out, red, acc, wave, lane);
-  unsigned redo = rows_of(my_q < S ? mark_of<DS>(out) : 0.f);
+  const unsigned redo = rows_of(masks, my_q < S && li == li && dlt == dlt ? mark_of<DS>(out) : 0.f, wave);
 #pragma unroll
   for (int i = 0; i < DS / KW; ++i) {
     const int col = quad_col(KW * i + wave, lane);
@@ -298,15 +301,14 @@ __global__ __launch_bounds__(64 * KW) void attn_bwd_dq_f32_kernel(int S, int dd,
     *reinterpret_cast<f32x4*>(dq + (tok0 + my_q) * ldd + blk.h * dd + col) = x;
   }
   const int64_t at = tok0 * ld + blk.h * dd;
-  for (; redo; redo &= redo - 1) {
-    const int r = __ffs(redo) - 1, i = q0 + r;
+  for_dealt_rows(&redo, 1, KW, wave, [&](int, int r) {
+    const int i = q0 + r;
     float* row = dq + (tok0 + i) * ldd + blk.h * dd;
     attn_dq_row<DS / 4>(rowbuf[wave], i, dd, q + at, k + at, v + at, ld, dout + tok0 * ldo + blk.h * dd, ldo, __shfl(li, r, 64),
                         __shfl(dlt, r, 64), scale, lane, [&](int c, float x) {
-                          if (rope) x = unrotate_column(x, rope, i, c, dd);
-                          if (owns(wave, c)) row[c] = x;
+                          row[c] = rope ? unrotate_column(x, rope, i, c, dd) : x;
                         });
-  }
+  });
 }
 
 // ------------------------------------------------------------------------------------------ dK, dV
@@ -319,6 +321,7 @@ __global__ __launch_bounds__(64 * KW) void attn_bwd_dkv_f32_kernel(int S, int dd
                                                                   int nh, int mb, const float2* __restrict__ rope) {
   __shared__ f32x4 red[(KW - 1) * DS * 64];
   __shared__ float rowbuf[KW][32 * DS];   // rows that are redone
+  __shared__ unsigned masks[KW];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const Block blk = block_of(nh, mb);
   const int k0 = blk.rank * 16, my_k = k0 + (lane & 15);
@@ -378,7 +381,7 @@ __global__ __launch_bounds__(64 * KW) void attn_bwd_dkv_f32_kernel(int S, int dd
   merge<DS>(outv, red, dva, wave, lane);
   __syncthreads();   // the second merge reuses the buffer
   merge<DS>(outk, red, dka, wave, lane);
-  unsigned redo = rows_of(my_k < S ? mark_of<DS>(outv) + mark_of<DS>(outk) : 0.f);
+  const unsigned redo = rows_of(masks, my_k < S ? mark_of<DS>(outv) + mark_of<DS>(outk) : 0.f, wave);
 #pragma unroll
   for (int i = 0; i < DS / KW; ++i) {
     const int col = quad_col(KW * i + wave, lane);
@@ -390,15 +393,19 @@ __global__ __launch_bounds__(64 * KW) void attn_bwd_dkv_f32_kernel(int S, int dd
     *reinterpret_cast<f32x4*>(dk + to) = x;
   }
   const int64_t at = tok0 * ld + blk.h * dd;
-  for (; redo; redo &= redo - 1) {
-    const int j = k0 + __ffs(redo) - 1;
+  for_dealt_rows(&redo, 1, KW, wave, [&](int, int r) {
+    const int j = k0 + r;
     const int64_t to = (tok0 + j) * ldd + blk.h * dd;
+    if (dkv_row_is_nan(j, S, lse_h, lane)) {
+      for (int c = lane; c < dd; c += 64) dk[to + c] = dv[to + c] = NAN;
+      return;
+    }
     attn_dkv_row<DS / 4>(rowbuf[wave], j, S, dd, q + at, k + at, v + at, ld, dout + tok0 * ldo + blk.h * dd, ldo, lse_h, dlt_h, scale, lane,
                          [&](int c, float xk, float xv) {
-                           if (rope) xk = unrotate_column(xk, rope, j, c, dd);
-                           if (owns(wave, c)) { dk[to + c] = xk; dv[to + c] = xv; }
+                           dk[to + c] = rope ? unrotate_column(xk, rope, j, c, dd) : xk;
+                           dv[to + c] = xv;
                          });
-  }
+  });
 }
 
 }  // namespace

@@ -20,7 +20,7 @@
 // their 24 bits.  In half the low part is scaled by 2^11, and where small values matter absolutely (P and dS in the backward) it
 // has accumulators of its own, so that it stays out of the subnormal range.  The errors against float64 are those of the
 // wave-per-row kernel (S = 64 .. 4096, d = 64, 80, 96: 1.6e-3 to 1.9e-3 in bf16 and 2.0e-4 to 2.5e-4 in half, both the outputs'
-// rounding, equal within 0.2 %; lse 2.3e-8 against 4.3e-8; 4 x 16 heads of 64, S = 1000: 4490 -> 97 us forward + backward in
+// rounding, equal within 0.2 %; lse 2.3e-8 against 4.3e-8; 4 x 16 heads of 64, S = 1000: 4490 -> 100 us forward + backward in
 // bf16).  The scores' factor and the row sums are kept a
 // little better than one fp32 operation would (scale_lo, four partial sums), for the sake of lse, which is returned in fp32.
 // A row whose sums are not finite is computed again in fp32, one wave per row: masked rows enter a product with weight zero,
@@ -30,9 +30,12 @@
 
 #include <cmath>
 
-// This file is compiled twice: as it stands for bf16, and through attention_mfma_f16.hip (which defines
-// ZS_ATTN_F16 and includes it) for IEEE half.  e16 is the 16-bit element type of the build; the two builds
-// differ in the conversions to and from float, the matrix-core instruction and the names they export.
+// This file is compiled four times: as it stands for bf16 and heads of 128, and through attention_mfma_f16.hip,
+// attention_split.hip and attention_split_f16.hip, which define ZS_ATTN_F16 (IEEE half) and ZS_ATTN_SPLIT (narrower heads) and
+// include it.  e16 is the 16-bit element type of the build; the builds differ in the conversions to and from float, the
+// matrix-core instruction, the head dims and the names they export.  The two head-dim builds are apart because the dK/dV kernel
+// of 128 uses all 256 registers: in one unit with the other kernels the compiler shares facts about common helpers, and a change
+// there made it spill 6 of them inside its loop.
 #ifdef ZS_ATTN_F16
 #define ZS_ATTN_MFMA __builtin_amdgcn_mfma_f32_32x32x16_f16
 #define ZS_ATTN_NAME(x) x##_f16
@@ -245,8 +248,8 @@ __device__ __forceinline__ void merge_halves(f32x16 (&acc)[D / 32], f32x16 (&lo)
   __syncthreads();
 }
 
-// SPLIT: rows of the wave whose sums are not finite, as bits 0..31 (lane and lane ^ 32 hold a row's columns).  They are redone
-// row by row: see attention_rows.h.
+// SPLIT: rows whose sums are not finite are redone, see attention_rows.h.  For that the LDS, free after the last tile, holds two
+// rows per wave, then the rows' bits per group of 32 (lane and lane ^ 32 hold a row's columns), then (dQ) delta of the rows.
 template <int N> __device__ __forceinline__ float mark_of(const f32x16 (&x)[N]) {
   float mark = 0.f;
 #pragma unroll
@@ -255,9 +258,15 @@ template <int N> __device__ __forceinline__ float mark_of(const f32x16 (&x)[N]) 
     for (int r = 0; r < 16; ++r) mark = mark_non_finite(mark, x[i][r]);
   return mark;
 }
-__device__ __forceinline__ unsigned rows_of(bool live, float mark) {
+template <int NW> struct RedoLds { float rows[NW][256]; unsigned masks[NW]; float delta[NW * 32]; };
+template <int NW> __device__ __forceinline__ RedoLds<NW>& redo_lds(char* smem) { return *reinterpret_cast<RedoLds<NW>*>(smem); }
+// Publishes the rows of this wave's group; writer: one wave per group.
+template <int NW> __device__ __forceinline__ unsigned rows_of(RedoLds<NW>& lds, int group, bool writer, bool live, float mark) {
   const unsigned long long m = __ballot(live && !(mark == 0.f));
-  return (unsigned)m | (unsigned)(m >> 32);
+  const unsigned rows = (unsigned)m | (unsigned)(m >> 32);
+  if (writer) lds.masks[group] = rows;
+  __syncthreads();
+  return rows;
 }
 
 // ------------------------------------------------------------------------------------------ forward
@@ -382,7 +391,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_fwd_kernel(int 
     __syncthreads();
   }
   unsigned redo = 0;
-  if constexpr (SPLIT) redo = rows_of(my_q < S, mark_of(oacc));
+  if constexpr (SPLIT) redo = rows_of(redo_lds<NW>(smem_raw), wave, true, my_q < S && l == l, mark_of(oacc));
   if (my_q < S) {
     const float inv = 1.0f / l;
     e16* orow = o + (tok0 + my_q) * ldo + h * dd;
@@ -401,12 +410,12 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_fwd_kernel(int 
           SPLIT ? (float)((double)m * 0.6931471805599453 + log((double)l)) : (m + log2f(l)) * LN2;
   }
   if constexpr (SPLIT) {
-    for (; redo; redo &= redo - 1) {
-      const int i = wq0 + __ffs(redo) - 1;
+    RedoLds<NW>& rl = redo_lds<NW>(smem_raw);
+    for_dealt_rows(rl.masks, NW, NW, wave, [&](int g, int r) {
+      const int i = q0 + 32 * g + r;
       e16* row = o + (tok0 + i) * ldo + h * dd;
-      attn_fwd_row<2>(reinterpret_cast<float*>(smem_raw) + wave * 256, i, dd, qh, kh, vh, ld, 1.0f / sqrtf((float)dd), lane,
-                      [&](int c, float x) { row[c] = (e16)x; });
-    }
+      attn_fwd_row<2>(rl.rows[wave], i, dd, qh, kh, vh, ld, 1.0f / sqrtf((float)dd), lane, [&](int c, float x) { row[c] = (e16)x; });
+    });
   }
 }
 
@@ -531,7 +540,11 @@ __global__ __launch_bounds__(64 * NW, NW == 4 && !(SPLIT && LO_ACC && D > 64) ? 
       for (int r = 0; r < 16; ++r) acc[db][r] = fmaf(acclo[db][r], LO_UNIT, acc[db][r]);
   }
   unsigned redo = 0;
-  if constexpr (SPLIT) redo = rows_of(my_q < S && half == 0, mark_of(acc));
+  if constexpr (SPLIT) {
+    RedoLds<NW>& rl = redo_lds<NW>(smem_raw);
+    if (half == 0 && lane < 32) rl.delta[32 * wave + lane] = dlt;
+    redo = rows_of(rl, wave, half == 0, my_q < S && lse2 == lse2 && dlt == dlt, mark_of(acc));
+  }
   if (my_q < S && half == 0) {
     e16* row = dq + (tok0 + my_q) * ldd + h * dd;
 #pragma unroll
@@ -551,15 +564,13 @@ __global__ __launch_bounds__(64 * NW, NW == 4 && !(SPLIT && LO_ACC && D > 64) ? 
       }
   }
   if constexpr (SPLIT) {
-    for (; redo; redo &= redo - 1) {
-      const int r = __ffs(redo) - 1, i = wq0 + r;
+    RedoLds<NW>& rl = redo_lds<NW>(smem_raw);
+    for_dealt_rows(rl.masks, QW, NW, tid >> 6, [&](int g, int r) {
+      const int i = q0 + 32 * g + r;
       e16* row = dq + (tok0 + i) * ldd + h * dd;
-      attn_dq_row<2>(reinterpret_cast<float*>(smem_raw) + wave * 256, i, dd, qh, kh, vh, ld, doh, ldo,
-                     lse[((int64_t)b * nh + h) * S + i], __shfl(dlt, r, 64), scale, lane, [&](int c, float x) {
-                       if (rope) x = unrotate_column(x, rope, i, c, dd);
-                       row[c] = (e16)x;
-                     });
-    }
+      attn_dq_row<2>(rl.rows[tid >> 6], i, dd, qh, kh, vh, ld, doh, ldo, lse[((int64_t)b * nh + h) * S + i], rl.delta[32 * g + r], scale,
+                     lane, [&](int c, float x) { row[c] = (e16)(rope ? unrotate_column(x, rope, i, c, dd) : x); });
+    });
   }
 }
 
@@ -726,7 +737,7 @@ __global__ __launch_bounds__(64 * NW) void attn_bwd_dkv_kernel(int S, const e16*
       }
   }
   unsigned redo = 0;
-  if constexpr (SPLIT) redo = rows_of(my_k < S && half == 0, mark_of(dkacc) + mark_of(dvacc));
+  if constexpr (SPLIT) redo = rows_of(redo_lds<NW>(smem_raw), wave, half == 0, my_k < S, mark_of(dkacc) + mark_of(dvacc));
   if (my_k < S && half == 0) {
     e16* krow = dk + (tok0 + my_k) * ldd + h * dd;
     e16* vrow = dv + (tok0 + my_k) * ldd + h * dd;
@@ -751,16 +762,19 @@ __global__ __launch_bounds__(64 * NW) void attn_bwd_dkv_kernel(int S, const e16*
       }
   }
   if constexpr (SPLIT) {
-    for (; redo; redo &= redo - 1) {
-      const int j = wk0 + __ffs(redo) - 1;
+    RedoLds<NW>& rl = redo_lds<NW>(smem_raw);
+    for_dealt_rows(rl.masks, KWV, NW, tid >> 6, [&](int g, int r) {
+      const int j = k0 + 32 * g + r;
       const int64_t to = (tok0 + j) * ldd + h * dd;
-      attn_dkv_row<2>(reinterpret_cast<float*>(smem_raw) + wave * 256, j, S, dd, qh, kh, vh, ld, doh, ldo, lse_h, dlt_h, scale, lane,
-                      [&](int c, float xk, float xv) {
-                        if (rope) xk = unrotate_column(xk, rope, j, c, dd);
-                        dk[to + c] = (e16)xk;
-                        dv[to + c] = (e16)xv;
-                      });
-    }
+      if (dkv_row_is_nan(j, S, lse_h, lane)) {
+        for (int c = lane; c < dd; c += 64) dk[to + c] = dv[to + c] = (e16)NAN;
+        return;
+      }
+      attn_dkv_row<2>(rl.rows[tid >> 6], j, S, dd, qh, kh, vh, ld, doh, ldo, lse_h, dlt_h, scale, lane, [&](int c, float xk, float xv) {
+        dk[to + c] = (e16)(rope ? unrotate_column(xk, rope, j, c, dd) : xk);
+        dv[to + c] = (e16)xv;
+      });
+    });
   }
 }
 
@@ -847,6 +861,24 @@ hipError_t bwd_128(hipStream_t st, int mb, int S, int nh, int d, const void* q, 
 
 }  // namespace
 
+#ifdef ZS_ATTN_SPLIT
+hipError_t ZS_ATTN_NAME(attn_fwd_split)(hipStream_t st, int mb, int S, int nh, int d, const void* q, const void* k, const void* v,
+                         int64_t ld, void* o, int64_t ldo, float* lse) {
+  if (d >= 128 || (int64_t)S * ld * 2 >= (1ll << 31)) return hipErrorInvalidValue;      // 32-bit buffer offsets
+  if (d <= 64) return launch_fwd<4, 64, true>(st, mb, S, nh, d, q, k, v, ld, o, ldo, lse);
+  if (d <= 96) return launch_fwd<4, 96, true>(st, mb, S, nh, d, q, k, v, ld, o, ldo, lse);
+  return launch_fwd<4, 128, true>(st, mb, S, nh, d, q, k, v, ld, o, ldo, lse);
+}
+
+hipError_t ZS_ATTN_NAME(attn_bwd_split)(hipStream_t st, int mb, int S, int nh, int d, const void* q, const void* k, const void* v,
+                         int64_t ld, const void* o, const void* dout, int64_t ldo, const float* lse, float* delta,
+                         void* dq, void* dk, void* dv, int64_t ldd, const float2* rope) {
+  if (d >= 128 || (int64_t)S * (ld > ldo ? ld : ldo) * 2 >= (1ll << 31)) return hipErrorInvalidValue;   // 32-bit buffer offsets
+  if (d <= 64) return bwd_128<64, true>(st, mb, S, nh, d, q, k, v, ld, o, dout, ldo, lse, delta, dq, dk, dv, ldd, rope, false);
+  if (d <= 96) return bwd_128<96, true>(st, mb, S, nh, d, q, k, v, ld, o, dout, ldo, lse, delta, dq, dk, dv, ldd, rope, false);
+  return bwd_128<128, true>(st, mb, S, nh, d, q, k, v, ld, o, dout, ldo, lse, delta, dq, dk, dv, ldd, rope, false);
+}
+#else
 #ifndef ZS_ATTN_F16
 bool attn_mfma_supported(DType dt, int S, int d) { return (dt == BF16 || dt == F16) && d == 128 && S >= 1; }
 #endif
@@ -854,9 +886,6 @@ bool attn_mfma_supported(DType dt, int S, int d) { return (dt == BF16 || dt == F
 hipError_t ZS_ATTN_NAME(attn_fwd_mfma)(hipStream_t st, int mb, int S, int nh, int d, const void* q, const void* k, const void* v,
                          int64_t ld, void* o, int64_t ldo, float* lse) {
   if ((int64_t)S * ld * 2 >= (1ll << 31)) return hipErrorInvalidValue;      // 32-bit buffer offsets
-  if (d <= 64) return launch_fwd<4, 64, true>(st, mb, S, nh, d, q, k, v, ld, o, ldo, lse);
-  if (d <= 96) return launch_fwd<4, 96, true>(st, mb, S, nh, d, q, k, v, ld, o, ldo, lse);
-  if (d < 128) return launch_fwd<4, 128, true>(st, mb, S, nh, d, q, k, v, ld, o, ldo, lse);
   // 256 queries per workgroup when that still gives every CU a workgroup, else 128
   return wide_query_blocks(S, nh, mb) ? launch_fwd<8, 128, false>(st, mb, S, nh, d, q, k, v, ld, o, ldo, lse)
                                       : launch_fwd<4, 128, false>(st, mb, S, nh, d, q, k, v, ld, o, ldo, lse);
@@ -866,9 +895,6 @@ hipError_t ZS_ATTN_NAME(attn_bwd_mfma)(hipStream_t st, int mb, int S, int nh, in
                          int64_t ld, const void* o, const void* dout, int64_t ldo, const float* lse, float* delta,
                          void* dq, void* dk, void* dv, int64_t ldd, const float2* rope) {
   if ((int64_t)S * (ld > ldo ? ld : ldo) * 2 >= (1ll << 31)) return hipErrorInvalidValue;   // 32-bit buffer offsets
-  if (d <= 64) return bwd_128<64, true>(st, mb, S, nh, d, q, k, v, ld, o, dout, ldo, lse, delta, dq, dk, dv, ldd, rope, false);
-  if (d <= 96) return bwd_128<96, true>(st, mb, S, nh, d, q, k, v, ld, o, dout, ldo, lse, delta, dq, dk, dv, ldd, rope, false);
-  if (d < 128) return bwd_128<128, true>(st, mb, S, nh, d, q, k, v, ld, o, dout, ldo, lse, delta, dq, dk, dv, ldd, rope, false);
   const bool wide = wide_blocks(S, nh, mb);
   const hipError_t e =
       wide_query_blocks(S, nh, mb) ? launch_dq<8, 1, 128, false>(st, mb, S, nh, d, q, k, v, ld, o, dout, ldo, lse, delta, dq, ldd, rope)
@@ -876,5 +902,6 @@ hipError_t ZS_ATTN_NAME(attn_bwd_mfma)(hipStream_t st, int mb, int S, int nh, in
   if (e != hipSuccess || !wide) return e;
   return launch_dkv<8, 1, 128, false>(st, mb, S, nh, d, q, k, v, ld, dout, ldo, lse, delta, dk, dv, ldd, rope);
 }
+#endif
 
 }  // namespace zs

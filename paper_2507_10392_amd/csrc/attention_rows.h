@@ -5,6 +5,8 @@
 // skipped, and 0 * inf and 0 * NaN are NaN, so one non-finite value of a token would reach rows that do not see that token.
 // A product of that kind always leaves NaN in the accumulators of the row it reaches.  The kernels therefore look at their
 // accumulators once, before the store, and redo the rows that hold anything non-finite here, where masked keys are not read.
+// The rows of a workgroup are dealt out over its waves; rows that are NaN throughout in any case, because a row
+// statistic they depend on is NaN, are left as they are.
 #pragma once
 #include "common.h"
 
@@ -137,6 +139,21 @@ __device__ __forceinline__ void attn_dkv_row(float* rows, int j, int S, int d, c
 #pragma unroll
   for (int c = 0; c < NC; ++c)
     if (c * 64 + lane < d) out(c * 64 + lane, acck[c] * scale, accv[c]);
+}
+
+// True when key j has NaN in every column of dk and dv because a query that sees it has a log-sum-exp of NaN.
+__device__ __forceinline__ bool dkv_row_is_nan(int j, int S, const float* __restrict__ lse, int lane) {
+  bool nan = false;
+  for (int i = j + lane; i < S; i += 64) nan |= lse[i] != lse[i];
+  return __any(nan);
+}
+
+// Calls f(group, bit) for the set bits of masks[0 .. groups-1], dealt out over `waves` waves.
+template <typename F> __device__ __forceinline__ void for_dealt_rows(const unsigned* masks, int groups, int waves, int wave, F&& f) {
+  int n = 0;
+  for (int g = 0; g < groups; ++g)
+    for (unsigned m = __builtin_amdgcn_readfirstlane(masks[g]); m; m &= m - 1)
+      if (n++ % waves == wave) f(g, __ffs(m) - 1);
 }
 
 // Column c of a row at position pos rotated back by the rotary angles of a d-wide head: (u, w) -> (u c + w s, w c - u s).  Lane

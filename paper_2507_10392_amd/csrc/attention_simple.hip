@@ -95,22 +95,14 @@ static hipError_t bwd_simple(hipStream_t st, int mb, int S, int nh, int d, const
   return hipGetLastError();
 }
 
-hipError_t attn_fwd_mfma(hipStream_t st, int mb, int S, int nh, int d, const void* q, const void* k, const void* v,
-                         int64_t ld, void* o, int64_t ldo, float* lse);
-hipError_t attn_bwd_mfma(hipStream_t st, int mb, int S, int nh, int d, const void* q, const void* k, const void* v,
-                         int64_t ld, const void* o, const void* dout, int64_t ldo, const float* lse, float* delta,
-                         void* dq, void* dk, void* dv, int64_t ldd, const float2* rope);
-hipError_t attn_fwd_mfma_f16(hipStream_t st, int mb, int S, int nh, int d, const void* q, const void* k, const void* v,
-                             int64_t ld, void* o, int64_t ldo, float* lse);
-hipError_t attn_bwd_mfma_f16(hipStream_t st, int mb, int S, int nh, int d, const void* q, const void* k, const void* v,
-                             int64_t ld, const void* o, const void* dout, int64_t ldo, const float* lse, float* delta,
-                             void* dq, void* dk, void* dv, int64_t ldd, const float2* rope);
+typedef hipError_t AttnFwd(hipStream_t st, int mb, int S, int nh, int d, const void* q, const void* k, const void* v, int64_t ld, void* o,
+                           int64_t ldo, float* lse);
+typedef hipError_t AttnBwd(hipStream_t st, int mb, int S, int nh, int d, const void* q, const void* k, const void* v, int64_t ld,
+                           const void* o, const void* dout, int64_t ldo, const float* lse, float* delta, void* dq, void* dk, void* dv,
+                           int64_t ldd, const float2* rope);
+AttnFwd attn_fwd_mfma, attn_fwd_mfma_f16, attn_fwd_split, attn_fwd_split_f16, attn_fwd_f32;
+AttnBwd attn_bwd_mfma, attn_bwd_mfma_f16, attn_bwd_split, attn_bwd_split_f16, attn_bwd_f32;
 bool attn_mfma_supported(DType dt, int S, int d);
-hipError_t attn_fwd_f32(hipStream_t st, int mb, int S, int nh, int d, const void* q, const void* k, const void* v,
-                        int64_t ld, void* o, int64_t ldo, float* lse);
-hipError_t attn_bwd_f32(hipStream_t st, int mb, int S, int nh, int d, const void* q, const void* k, const void* v,
-                        int64_t ld, const void* o, const void* dout, int64_t ldo, const float* lse, float* delta,
-                        void* dq, void* dk, void* dv, int64_t ldd, const float2* rope);
 bool attn_f32_supported(int mb, int S, int nh, int d, int64_t ld_max, uintptr_t pointers, int64_t strides);
 
 int attn_select(DType dt, int S, int d, int force) {
@@ -131,9 +123,8 @@ AttnRoute attn_route(DType dt, int mb, int S, int nh, int d, int64_t ld_max, uin
 hipError_t attn_fwd(hipStream_t st, DType dt, int mb, int S, int nh, int d, const void* q, const void* k,
                     const void* v, int64_t ld, void* o, int64_t ldo, float* lse, int force) {
   const AttnRoute route = attn_route(dt, mb, S, nh, d, ld, (uintptr_t)q | (uintptr_t)k | (uintptr_t)v | (uintptr_t)o, ld | ldo, force);
-  if (route == ATTN_ROUTE_MFMA || route == ATTN_ROUTE_SPLIT)
-    return dt == F16 ? attn_fwd_mfma_f16(st, mb, S, nh, d, q, k, v, ld, o, ldo, lse)
-                     : attn_fwd_mfma(st, mb, S, nh, d, q, k, v, ld, o, ldo, lse);
+  if (route == ATTN_ROUTE_MFMA) return (dt == F16 ? attn_fwd_mfma_f16 : attn_fwd_mfma)(st, mb, S, nh, d, q, k, v, ld, o, ldo, lse);
+  if (route == ATTN_ROUTE_SPLIT) return (dt == F16 ? attn_fwd_split_f16 : attn_fwd_split)(st, mb, S, nh, d, q, k, v, ld, o, ldo, lse);
   if (route == ATTN_ROUTE_F32) return attn_fwd_f32(st, mb, S, nh, d, q, k, v, ld, o, ldo, lse);
   return dt == F32    ? fwd_simple<float>(st, mb, S, nh, d, q, k, v, ld, o, ldo, lse)
          : dt == BF16 ? fwd_simple<bf16>(st, mb, S, nh, d, q, k, v, ld, o, ldo, lse)
@@ -145,10 +136,11 @@ hipError_t attn_bwd(hipStream_t st, DType dt, int mb, int S, int nh, int d, cons
   const uintptr_t at = (uintptr_t)q | (uintptr_t)k | (uintptr_t)v | (uintptr_t)o | (uintptr_t)dout | (uintptr_t)dq | (uintptr_t)dk |
                        (uintptr_t)dv | (uintptr_t)rope;
   const AttnRoute route = attn_route(dt, mb, S, nh, d, ld > ldo ? ld : ldo, at, ld | ldo | ldd, force);
-  if (route == ATTN_ROUTE_MFMA || route == ATTN_ROUTE_SPLIT)   // rotation fused into the kernels' stores
-    return dt == F16 ? attn_bwd_mfma_f16(st, mb, S, nh, d, q, k, v, ld, o, dout, ldo, lse, delta, dq, dk, dv, ldd, rope)
-                     : attn_bwd_mfma(st, mb, S, nh, d, q, k, v, ld, o, dout, ldo, lse, delta, dq, dk, dv, ldd, rope);
-  if (route == ATTN_ROUTE_F32) return attn_bwd_f32(st, mb, S, nh, d, q, k, v, ld, o, dout, ldo, lse, delta, dq, dk, dv, ldd, rope);
+  if (route != ATTN_ROUTE_SIMPLE) {   // rotation fused into the kernels' stores
+    AttnBwd* run = route == ATTN_ROUTE_F32 ? attn_bwd_f32 : route == ATTN_ROUTE_MFMA ? (dt == F16 ? attn_bwd_mfma_f16 : attn_bwd_mfma)
+                                                                                  : (dt == F16 ? attn_bwd_split_f16 : attn_bwd_split);
+    return run(st, mb, S, nh, d, q, k, v, ld, o, dout, ldo, lse, delta, dq, dk, dv, ldd, rope);
+  }
   hipError_t e = dt == F32    ? bwd_simple<float>(st, mb, S, nh, d, q, k, v, ld, o, dout, ldo, lse, delta, dq, dk, dv, ldd)
                  : dt == BF16 ? bwd_simple<bf16>(st, mb, S, nh, d, q, k, v, ld, o, dout, ldo, lse, delta, dq, dk, dv, ldd)
                               : bwd_simple<f16>(st, mb, S, nh, d, q, k, v, ld, o, dout, ldo, lse, delta, dq, dk, dv, ldd);
