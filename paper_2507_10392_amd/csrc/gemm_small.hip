@@ -297,6 +297,10 @@ template <typename E> hipError_t launch_type(hipStream_t st, const Gemm& g, int 
 // 2048, K = 1024 it loses (16.3 : 14.1), and at 512 x 4096, K = 4096 (47 : 37).
 int gemm_small_tile(const Gemm& g) {
   if (g.N % 4 || g.batch > 65535 || g.transA != g.c_f32_accum || (g.transA && g.transB)) return 0;   // the forms of the stage's products
+  // The k-lines of a row-contiguous operand that fill up the last slab lie behind its descriptor, unless their 32-bit offsets
+  // wrap around: few rows, more than 2^32 / 64 bytes apart.
+  const int64_t lines = cdiv(g.nx ? (int64_t)g.K - (int64_t)g.nx * g.kseg : g.K, 32) * 32;
+  if ((g.transA && lines * g.lda * 2 >= (1ll << 32)) || (!g.transB && lines * g.ldb * 2 >= (1ll << 32))) return 0;
   const double per_cu = (g.glu == 1 ? 2.0 : g.batch) / 256.0, k = (double)g.K;   // gate and up count like a batch of two
   const double n32 = cdiv(g.M, 32) * cdiv(g.N, 32) * per_cu, n64 = cdiv(g.M, 64) * cdiv(g.N, 64) * per_cu,
                n128 = cdiv(g.M, 128) * cdiv(g.N, 128) * per_cu;

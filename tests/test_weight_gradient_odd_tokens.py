@@ -52,6 +52,19 @@ def test_last_of_several_parts_with_an_odd_number_of_tokens(gpu_device, M, N, pa
     assert err <= 2e-5            # exact 16-bit products, fp32 sums: the bar of the other accumulating products
 
 
+@pytest.mark.parametrize("M,N,T,ld", [(64, 64, 3, 72 * 2 ** 20), (4096, 4096, 31, 33 * 2 ** 19)])
+def test_rows_so_far_apart_that_the_tile_would_wrap_around(gpu_device, M, N, T, ld):
+    """A tile's k-lines past the last token, at 32-bit byte offsets beyond 2^32, must not come back into the operand."""
+    print(f"[case] wgrad with far rows M={M} N={N} T={T} ld={ld}", flush=True)
+    torch.manual_seed(53)
+    x, dy = (torch.randn(T * ld, device="cuda", dtype=torch.bfloat16) for _ in range(2))
+    C = torch.zeros(M, N, device="cuda")
+    zs.ops.gemm(torch.cuda.current_stream().cuda_stream, 1, 1, 0, M, N, T, x, ld, dy, ld, C, N, 1, None, None, 0, 1, 0, 0, 0, 0, 0, 0, 0)
+    torch.cuda.synchronize()
+    a, b = (t.view(T, ld)[:, :w].double().cpu().numpy() for t, w in ((x, M), (dy, N)))
+    assert rel_err(C.cpu().numpy(), a.T @ b) <= 2e-5
+
+
 def test_forced_matrix_core_kernel_still_wants_multiples_of_8(gpu_device):
     x, dy, C = (torch.zeros(64, 64, device="cuda", dtype=t) for t in (torch.bfloat16, torch.bfloat16, torch.float32))
     with pytest.raises(zs.StageError):
