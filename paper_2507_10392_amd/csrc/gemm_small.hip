@@ -15,6 +15,9 @@
 // The matrix instruction gets B as its first operand, so a lane ends up with 4 consecutive columns of one row of C.
 #include "kernels.h"
 
+#include <algorithm>
+#include <cmath>
+
 namespace zs {
 namespace {
 
@@ -290,11 +293,14 @@ template <typename E> hipError_t launch_type(hipStream_t st, const Gemm& g, int 
 }  // namespace
 
 // Tile of the small kernel (32 or 64) when it is the faster way, else 0.  Times in us, fitted to single products of bf16 with
-// M = 64 .. 4096, N = 512 .. 11008 and K = 256 .. 22016 (most within a fifth, all within a third): a fixed part, and per k
-// the latency of a walk or the loads of the workgroups that share a CU, whichever is longer.  A k-contiguous B costs more (see
-// above).  Measured against the best staged tile, us: 256 x 512, K = 512 4.5 : 8.9, input gradient with K = 2752 in two
+// M, N = 8 .. 6000, K = 8 .. 24000 and one to three batches.  Forward: a fixed part, and per k the latency of a walk or the
+// loads of the workgroups that share a CU, whichever is longer.  Gradients: a round of workgroups on the 256 CUs costs a fixed
+// time (a workgroup's launch, merge and store) plus the walk over K.  A k-contiguous B costs more per k (see above).  Of 900
+// products the choice is within 0.4 % of the fastest of 32, 64 and staged on the geometric mean, and one is slower than staged
+// tiles, by 5 %.  Measured against the staged tiles, us: 256 x 512, K = 512 4.5 : 8.9, input gradient with K = 2752 in two
 // segments 10.9 : 27.1; 512 x 512, K = 256, accumulating 3.3 : 5.8; 1024 x 1024, K = 1024, accumulating 9.6 : 13.0.  At 1024 x
-// 2048, K = 1024 it loses (16.3 : 14.1), and at 512 x 4096, K = 4096 (47 : 37).
+// 2048, K = 1024 it loses (16.3 : 14.1), at 512 x 4096, K = 4096 (47 : 37), and accumulating over few tokens, where the rounds'
+// fixed time is all there is (1528 x 2624, K = 8: 16.6 : 7.8; 2376 x 1632, K = 16, two batches 30.4 : 11.7).
 int gemm_small_tile(const Gemm& g) {
   if (g.N % 4 || g.batch > 65535 || g.transA != g.c_f32_accum || (g.transA && g.transB)) return 0;   // the forms of the stage's products
   // The k-lines of a row-contiguous operand that fill up the last slab lie behind its descriptor, unless their 32-bit offsets
@@ -304,10 +310,10 @@ int gemm_small_tile(const Gemm& g) {
   const double per_cu = (g.glu == 1 ? 2.0 : g.batch) / 256.0, k = (double)g.K;   // gate and up count like a batch of two
   const double n32 = cdiv(g.M, 32) * cdiv(g.N, 32) * per_cu, n64 = cdiv(g.M, 64) * cdiv(g.N, 64) * per_cu,
                n128 = cdiv(g.M, 128) * cdiv(g.N, 128) * per_cu;
-  auto most = [](double a, double b) { return a < b ? b : a; };
   const double staged = 4.5 + 7.8e-3 * k * (n128 <= 1.0 ? 1.0 : n128 <= 2.0 ? 2.0 : n128 * 0.9);
-  if (!g.transA && !g.transB) return 2.4 + k * most(4.5e-3, 2.6e-3 * n32) < 0.9 * staged ? 32 : 0;
-  const double t32 = 2.2 + (g.transB ? 3.5e-3 : 2.7e-3) * k * most(1.0, n32), t64 = 3.7 + (g.transB ? 6.7e-3 : 5.4e-3) * k * most(1.0, n64);
+  if (!g.transA && !g.transB) return 2.4 + k * std::max(4.5e-3, 2.6e-3 * n32) < 0.9 * staged ? 32 : 0;
+  const double t32 = g.transB ? 2.0 + (2.5e-3 * k + 0.7) * std::ceil(n32) : 2.1 + (2.1e-3 * k + 0.87) * std::ceil(n32);
+  const double t64 = g.transB ? 0.9 + (4.6e-3 * k + 2.5) * std::ceil(n64) : 0.3 + (3.8e-3 * k + 3.9) * std::ceil(n64);
   if (t32 < 0.9 * staged && t32 <= t64) return 32;
   return t64 < 0.9 * staged ? 64 : 0;
 }

@@ -14,6 +14,8 @@ CASES = [
     ("C3t", dict(heads=8), {"gemm_small_nn", "gemm_small_tn", "gemm_small_nn_glu", "attn_fwd_mfma_split", "attn_bwd_mfma_split"},
      ("gemm_f32", "gemm_simple", "attn_fwd_simple")),
     ("C3h", {}, {"gemm_small_nn", "attn_fwd_mfma", "attn_bwd_mfma"}, ("gemm_f32", "attn_fwd_mfma_split")),
+    # weight gradients over few tokens have many small tiles with hardly any K: staged tiles
+    ("C3t", dict(hidden=2048, heads=16, ffn=2048, seq=48), {"gemm_mfma_tn"}, ("gemm_small_tn",)),
     ("C3t", dict(hidden=1024, heads=8, ffn=4096, seq=2048), {"gemm_mfma_nn", "gemm_mfma_nt", "gemm_mfma_tn", "gemm_mfma_nn_glu"}, ("gemm_simple",)),
 ]
 
