@@ -131,6 +131,49 @@ template <int DS> __device__ __forceinline__ float mark_of(const f32x4 (&x)[DS /
   return mark;
 }
 
+// The rows `redo` of the block are dealt out over the waves.  Calls of their own, not inlined, so that the kernels' code stays
+// what it is without them.
+template <int DS>
+__device__ __attribute__((noinline)) void redo_fwd_rows(float* rowbuf, unsigned redo, int q0, int dd, const float* q,
+                                                        const float* k, const float* v, int64_t ld, float* o, int64_t ldo, float scale) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  for_dealt_rows(&redo, 1, KW, wave, [&](int, int r) {
+    float* row = o + (int64_t)(q0 + r) * ldo;
+    attn_fwd_row<DS / 4>(rowbuf, q0 + r, dd, q, k, v, ld, scale, lane, [&](int c, float x) { row[c] = x; });
+  });
+}
+template <int DS>
+__device__ __attribute__((noinline)) void redo_dq_rows(float* rowbuf, unsigned redo, int q0, int dd, const float* q,
+                                                       const float* k, const float* v, int64_t ld, const float* dout, int64_t ldo,
+                                                       float li, float dlt, float scale, const float2* rope, float* dq, int64_t ldd) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  for_dealt_rows(&redo, 1, KW, wave, [&](int, int r) {
+    const int i = q0 + r;
+    float* row = dq + (int64_t)i * ldd;
+    attn_dq_row<DS / 4>(rowbuf, i, dd, q, k, v, ld, dout, ldo, __shfl(li, r, 64), __shfl(dlt, r, 64), scale, lane,
+                        [&](int c, float x) { row[c] = rope ? unrotate_column(x, rope, i, c, dd) : x; });
+  });
+}
+template <int DS>
+__device__ __attribute__((noinline)) void redo_dkv_rows(float* rowbuf, unsigned redo, int k0, int S, int dd, const float* q,
+                                                        const float* k, const float* v, int64_t ld, const float* dout, int64_t ldo,
+                                                        const float* lse_h, const float* dlt_h, float scale, const float2* rope,
+                                                        float* dk, float* dv, int64_t ldd) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  for_dealt_rows(&redo, 1, KW, wave, [&](int, int r) {
+    const int j = k0 + r;
+    const int64_t to = (int64_t)j * ldd;
+    if (dkv_row_is_nan(j, S, lse_h, lane)) {
+      for (int c = lane; c < dd; c += 64) dk[to + c] = dv[to + c] = NAN;
+      return;
+    }
+    attn_dkv_row<DS / 4>(rowbuf, j, S, dd, q, k, v, ld, dout, ldo, lse_h, dlt_h, scale, lane, [&](int c, float xk, float xv) {
+      dk[to + c] = rope ? unrotate_column(xk, rope, j, c, dd) : xk;
+      dv[to + c] = xv;
+    });
+  });
+}
+
 // ------------------------------------------------------------------------------------------ forward
 template <int DS, int NBUF>
 __global__ __launch_bounds__(64 * KW) void attn_fwd_f32_kernel(int S, int dd, const float* __restrict__ q, const float* __restrict__ k,
@@ -220,11 +263,10 @@ __global__ __launch_bounds__(64 * KW) void attn_fwd_f32_kernel(int S, int dd, co
     const int col = quad_col(KW * i + wave, lane);
     if (my_q < S && col < dd && !(redo >> (lane & 15) & 1)) *reinterpret_cast<f32x4*>(o + (tok0 + my_q) * ldo + blk.h * dd + col) = out[i];
   }
-  const int64_t at = tok0 * ld + blk.h * dd;
-  for_dealt_rows(&redo, 1, KW, wave, [&](int, int r) {
-    float* row = o + (tok0 + q0 + r) * ldo + blk.h * dd;
-    attn_fwd_row<DS / 4>(rowbuf[wave], q0 + r, dd, q + at, k + at, v + at, ld, scale, lane, [&](int c, float x) { row[c] = x; });
-  });
+  if (__builtin_expect(redo != 0, 0)) {
+    const int64_t at = tok0 * ld + blk.h * dd;
+    redo_fwd_rows<DS>(rowbuf[wave], redo, q0, dd, q + at, k + at, v + at, ld, o + tok0 * ldo + blk.h * dd, ldo, scale);
+  }
   if (wave == 0 && lane < 16 && my_q < S) lse[((int64_t)blk.b * nh + blk.h) * S + my_q] = mt + logf(lt);
 }
 
@@ -300,15 +342,11 @@ __global__ __launch_bounds__(64 * KW) void attn_bwd_dq_f32_kernel(int S, int dd,
     if (rope) x = unrotate(x, rope, my_q, col, dd);
     *reinterpret_cast<f32x4*>(dq + (tok0 + my_q) * ldd + blk.h * dd + col) = x;
   }
-  const int64_t at = tok0 * ld + blk.h * dd;
-  for_dealt_rows(&redo, 1, KW, wave, [&](int, int r) {
-    const int i = q0 + r;
-    float* row = dq + (tok0 + i) * ldd + blk.h * dd;
-    attn_dq_row<DS / 4>(rowbuf[wave], i, dd, q + at, k + at, v + at, ld, dout + tok0 * ldo + blk.h * dd, ldo, __shfl(li, r, 64),
-                        __shfl(dlt, r, 64), scale, lane, [&](int c, float x) {
-                          row[c] = rope ? unrotate_column(x, rope, i, c, dd) : x;
-                        });
-  });
+  if (__builtin_expect(redo != 0, 0)) {
+    const int64_t at = tok0 * ld + blk.h * dd;
+    redo_dq_rows<DS>(rowbuf[wave], redo, q0, dd, q + at, k + at, v + at, ld, dout + tok0 * ldo + blk.h * dd, ldo, li, dlt, scale,
+                     rope, dq + tok0 * ldd + blk.h * dd, ldd);
+  }
 }
 
 // ------------------------------------------------------------------------------------------ dK, dV
@@ -392,20 +430,11 @@ __global__ __launch_bounds__(64 * KW) void attn_bwd_dkv_f32_kernel(int S, int dd
     *reinterpret_cast<f32x4*>(dv + to) = outv[i];
     *reinterpret_cast<f32x4*>(dk + to) = x;
   }
-  const int64_t at = tok0 * ld + blk.h * dd;
-  for_dealt_rows(&redo, 1, KW, wave, [&](int, int r) {
-    const int j = k0 + r;
-    const int64_t to = (tok0 + j) * ldd + blk.h * dd;
-    if (dkv_row_is_nan(j, S, lse_h, lane)) {
-      for (int c = lane; c < dd; c += 64) dk[to + c] = dv[to + c] = NAN;
-      return;
-    }
-    attn_dkv_row<DS / 4>(rowbuf[wave], j, S, dd, q + at, k + at, v + at, ld, dout + tok0 * ldo + blk.h * dd, ldo, lse_h, dlt_h, scale, lane,
-                         [&](int c, float xk, float xv) {
-                           dk[to + c] = rope ? unrotate_column(xk, rope, j, c, dd) : xk;
-                           dv[to + c] = xv;
-                         });
-  });
+  if (__builtin_expect(redo != 0, 0)) {
+    const int64_t at = tok0 * ld + blk.h * dd;
+    redo_dkv_rows<DS>(rowbuf[wave], redo, k0, S, dd, q + at, k + at, v + at, ld, dout + tok0 * ldo + blk.h * dd, ldo, lse_h, dlt_h,
+                      scale, rope, dk + tok0 * ldd + blk.h * dd, dv + tok0 * ldd + blk.h * dd, ldd);
+  }
 }
 
 }  // namespace

@@ -148,6 +148,8 @@ __device__ __forceinline__ bool dkv_row_is_nan(int j, int S, const float* __rest
   return __any(nan);
 }
 
+// Whether any of masks[0 .. groups-1] in LDS has a bit: one read, where the words one after the other are as many LDS latencies.
+__device__ __forceinline__ bool any_row(const unsigned* masks, int groups, int lane) { return __any(masks[min(lane, groups - 1)] != 0); }
 // Calls f(group, bit) for the set bits of masks[0 .. groups-1], dealt out over `waves` waves.
 template <typename F> __device__ __forceinline__ void for_dealt_rows(const unsigned* masks, int groups, int waves, int wave, F&& f) {
   int n = 0;
