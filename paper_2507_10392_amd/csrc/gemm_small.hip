@@ -295,9 +295,9 @@ template <typename E> hipError_t launch_type(hipStream_t st, const Gemm& g, int 
 // Tile of the small kernel (32 or 64) when it is the faster way, else 0.  Times in us, fitted to single products of bf16 with
 // M, N = 8 .. 6000, K = 8 .. 24000 and one to three batches.  Forward: a fixed part, and per k the latency of a walk or the
 // loads of the workgroups that share a CU, whichever is longer.  Gradients: a round of workgroups on the 256 CUs costs a fixed
-// time (a workgroup's launch, merge and store) plus the walk over K.  A k-contiguous B costs more per k (see above).  Of 900
-// products the choice is within 0.4 % of the fastest of 32, 64 and staged on the geometric mean, and one is slower than staged
-// tiles, by 5 %.  Measured against the staged tiles, us: 256 x 512, K = 512 4.5 : 8.9, input gradient with K = 2752 in two
+// time (a workgroup's launch, merge and store) plus the walk over K.  A k-contiguous B costs more per k (see above).  On the
+// geometric mean of 1400 products the choice is within 0.4 % of the fastest of 32, 64 and staged, and one product is slower than
+// staged tiles, by 5 %.  Measured against the staged tiles, us: 256 x 512, K = 512 4.5 : 8.9, input gradient with K = 2752 in two
 // segments 10.9 : 27.1; 512 x 512, K = 256, accumulating 3.3 : 5.8; 1024 x 1024, K = 1024, accumulating 9.6 : 13.0.  At 1024 x
 // 2048, K = 1024 it loses (16.3 : 14.1), at 512 x 4096, K = 4096 (47 : 37), and accumulating over few tokens, where the rounds'
 // fixed time is all there is (1528 x 2624, K = 8: 16.6 : 7.8; 2376 x 1632, K = 16, two batches 30.4 : 11.7).
@@ -312,8 +312,8 @@ int gemm_small_tile(const Gemm& g) {
                n128 = cdiv(g.M, 128) * cdiv(g.N, 128) * per_cu;
   const double staged = 4.5 + 7.8e-3 * k * (n128 <= 1.0 ? 1.0 : n128 <= 2.0 ? 2.0 : n128 * 0.9);
   if (!g.transA && !g.transB) return 2.4 + k * std::max(4.5e-3, 2.6e-3 * n32) < 0.9 * staged ? 32 : 0;
-  const double t32 = g.transB ? 2.0 + (2.5e-3 * k + 0.7) * std::ceil(n32) : 2.1 + (2.1e-3 * k + 0.87) * std::ceil(n32);
-  const double t64 = g.transB ? 0.9 + (4.6e-3 * k + 2.5) * std::ceil(n64) : 0.3 + (3.8e-3 * k + 3.9) * std::ceil(n64);
+  const double t32 = g.transB ? 2.0 + (2.6e-3 * k + 0.55) * std::ceil(n32) : 2.1 + (2.3e-3 * k + 0.83) * std::ceil(n32);
+  const double t64 = g.transB ? 0.9 + (5.3e-3 * k + 2.4) * std::ceil(n64) : 0.4 + (4.0e-3 * k + 3.8) * std::ceil(n64);
   if (t32 < 0.9 * staged && t32 <= t64) return 32;
   return t64 < 0.9 * staged ? 64 : 0;
 }
