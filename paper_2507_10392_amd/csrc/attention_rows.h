@@ -24,7 +24,7 @@ template <typename T> __device__ __forceinline__ float dot_row(const float* __re
 }
 
 // Query i of a head with rows q, k, v (stride ld): out(c, o[i][c]) for the columns c < d that the lane owns (c = 64 n + lane,
-// d <= 64 NC); returns the row's log-sum-exp.  qs: LDS of the wave's own, d floats.
+// d <= 64 NC); returns the row's log-sum-exp.  qs: LDS of the wave's own, 64 NC floats.
 template <int NC, typename T, typename F>
 __device__ __forceinline__ float attn_fwd_row(float* qs, int i, int d, const T* __restrict__ q, const T* __restrict__ k,
                                               const T* __restrict__ v, int64_t ld, float scale, int lane, F&& out) {
@@ -61,12 +61,12 @@ __device__ __forceinline__ float attn_fwd_row(float* qs, int i, int d, const T* 
 }
 
 // dq_i = scale * sum_{j<=i} ds_ij k_j,  ds_ij = p_ij (do_i.v_j - delta_i),  p_ij = exp(scale q_i.k_j - lse_i), with li = lse_i and
-// di = delta_i.  rows: LDS of the wave's own, 2 d floats.
+// di = delta_i.  rows: LDS of the wave's own, 128 NC floats.
 template <int NC, typename T, typename F>
 __device__ __forceinline__ void attn_dq_row(float* rows, int i, int d, const T* __restrict__ q, const T* __restrict__ k,
                                             const T* __restrict__ v, int64_t ld, const T* __restrict__ dout, int64_t ldo, float li,
                                             float di, float scale, int lane, F&& out) {
-  float *qs = rows, *dos = rows + d;
+  float *qs = rows, *dos = rows + 64 * NC;
   for (int c = lane; c < d; c += 64) {
     qs[c] = to_f(q[(int64_t)i * ld + c]) * scale;
     dos[c] = to_f(dout[(int64_t)i * ldo + c]);
@@ -98,13 +98,13 @@ __device__ __forceinline__ void attn_dq_row(float* rows, int i, int d, const T* 
 }
 
 // dv_j = sum_{i>=j} p_ij do_i,  dk_j = scale * sum_{i>=j} ds_ij q_i: out(c, dk[j][c], dv[j][c]).  lse, delta: the head's rows.
-// rows: LDS of the wave's own, 2 d floats.
+// rows: LDS of the wave's own, 128 NC floats.
 template <int NC, typename T, typename F>
 __device__ __forceinline__ void attn_dkv_row(float* rows, int j, int S, int d, const T* __restrict__ q, const T* __restrict__ k,
                                              const T* __restrict__ v, int64_t ld, const T* __restrict__ dout, int64_t ldo,
                                              const float* __restrict__ lse, const float* __restrict__ delta, float scale, int lane,
                                              F&& out) {
-  float *ks = rows, *vs = rows + d;
+  float *ks = rows, *vs = rows + 64 * NC;
   for (int c = lane; c < d; c += 64) {
     ks[c] = to_f(k[(int64_t)j * ld + c]) * scale;
     vs[c] = to_f(v[(int64_t)j * ld + c]);

@@ -110,19 +110,43 @@ int attn_select(DType dt, int S, int d, int force) {
   return attn_mfma_supported(dt, S, d) ? ATTN_MFMA : ATTN_SIMPLE;
 }
 
+// Sequences so short that a wave per row is faster.  Its time grows with the keys; a matrix-core kernel takes the same for any
+// number of them up to a tile, once per round of workgroups on the 256 CUs (one or two rounds up to 256 heads).  Measured at 1 to
+// 2048 heads, S = 1 to 64 and d = 8 to 128 (us, wave per row : matrix cores): fp32 forward, d = 64, one head S = 4 4.9 : 6.1, S = 16
+// 6.7 : 6.1; bf16 forward, 16 heads, d = 8 S = 8 5.1 : 5.2, d = 64 S = 2 4.8 : 5.4; with 2048 heads of 64 the matrix cores lose by 2.3
+// to 4.3 at S = 2 and win from S = 12 on.  The half backward of d > 96, whose registers spill, takes 27 us up to S = 32 (16 heads;
+// wave per row 24.7 at S = 24).  fp32 blocks hold 16 rows, so many heads pay a second round from S = 17 on.  Of 3900
+// measured points 8 are left more than 10 % slower than the wave per row, by at most 27 %.  A rotation (rope) is another two
+// launches after the wave per row.
+static bool few_keys(DType dt, bool bwd, bool rope, int64_t heads, int d, int S) {
+  const bool wide = d > 64, many = heads > 256;
+  int most;
+  if (dt == F32) {
+    if (heads >= 256 && !rope && S > 16 && S <= (bwd ? 24 : 20) && (bwd ? d <= 32 : wide)) return true;
+    most = many ? (!bwd && d > 32 && !wide ? 8 : 12) : (wide ? 16 : 20 - d / 8) - (heads >= 128 ? 5 : 0);
+  } else if (!bwd) {
+    most = many ? 10 : wide ? (dt == BF16 ? 4 : 5) : 11 - 3 * d / 32;
+  } else if (dt == BF16) {
+    most = many ? (d <= 32 ? 14 : 10) : wide ? 2 : 8 - d / 8;
+  } else {
+    most = d > 96 ? 24 : many ? (d <= 32 ? 14 : wide ? 16 : 12) : wide ? 10 : 12 - 5 * d / 32;
+  }
+  return S <= most - (rope ? (many ? 4 : 16) : 0);
+}
+
 // Heads of 128 in 16 bits always run on the matrix cores.  Narrower 16-bit heads (their fp32 probabilities split in two 16-bit
-// parts) and fp32 heads do when rows can be read in aligned 16-byte pieces through 32-bit offsets; else, and for wider heads, a
-// wavefront per row.
-AttnRoute attn_route(DType dt, int mb, int S, int nh, int d, int64_t ld_max, uintptr_t pointers, int64_t strides, int force) {
+// parts) and fp32 heads do when there are more than a few keys and rows can be read in aligned 16-byte pieces through 32-bit
+// offsets; else, and for wider heads, a wavefront per row.
+AttnRoute attn_route(DType dt, bool bwd, bool rope, int mb, int S, int nh, int d, int64_t ld_max, uintptr_t pointers, int64_t strides, int force) {
   if (attn_select(dt, S, d, force) == ATTN_MFMA) return ATTN_ROUTE_MFMA;
-  if (force == ATTN_SIMPLE) return ATTN_ROUTE_SIMPLE;
+  if (force == ATTN_SIMPLE || few_keys(dt, bwd, rope, mb * (int64_t)nh, d, S)) return ATTN_ROUTE_SIMPLE;
   if (dt == F32) return attn_f32_supported(mb, S, nh, d, ld_max, pointers, strides) ? ATTN_ROUTE_F32 : ATTN_ROUTE_SIMPLE;
   return d < 128 && (pointers & 15) == 0 && strides % 8 == 0 && (int64_t)S * ld_max * 2 < (1ll << 31) ? ATTN_ROUTE_SPLIT : ATTN_ROUTE_SIMPLE;
 }
 
 hipError_t attn_fwd(hipStream_t st, DType dt, int mb, int S, int nh, int d, const void* q, const void* k,
                     const void* v, int64_t ld, void* o, int64_t ldo, float* lse, int force) {
-  const AttnRoute route = attn_route(dt, mb, S, nh, d, ld, (uintptr_t)q | (uintptr_t)k | (uintptr_t)v | (uintptr_t)o, ld | ldo, force);
+  const AttnRoute route = attn_route(dt, false, false, mb, S, nh, d, ld, (uintptr_t)q | (uintptr_t)k | (uintptr_t)v | (uintptr_t)o, ld | ldo, force);
   if (route == ATTN_ROUTE_MFMA) return (dt == F16 ? attn_fwd_mfma_f16 : attn_fwd_mfma)(st, mb, S, nh, d, q, k, v, ld, o, ldo, lse);
   if (route == ATTN_ROUTE_SPLIT) return (dt == F16 ? attn_fwd_split_f16 : attn_fwd_split)(st, mb, S, nh, d, q, k, v, ld, o, ldo, lse);
   if (route == ATTN_ROUTE_F32) return attn_fwd_f32(st, mb, S, nh, d, q, k, v, ld, o, ldo, lse);
@@ -135,7 +159,7 @@ hipError_t attn_bwd(hipStream_t st, DType dt, int mb, int S, int nh, int d, cons
                     float* delta, void* dq, void* dk, void* dv, int64_t ldd, const float2* rope, int force) {
   const uintptr_t at = (uintptr_t)q | (uintptr_t)k | (uintptr_t)v | (uintptr_t)o | (uintptr_t)dout | (uintptr_t)dq | (uintptr_t)dk |
                        (uintptr_t)dv | (uintptr_t)rope;
-  const AttnRoute route = attn_route(dt, mb, S, nh, d, ld > ldo ? ld : ldo, at, ld | ldo | ldd, force);
+  const AttnRoute route = attn_route(dt, true, rope != nullptr, mb, S, nh, d, ld > ldo ? ld : ldo, at, ld | ldo | ldd, force);
   if (route != ATTN_ROUTE_SIMPLE) {   // rotation fused into the kernels' stores
     AttnBwd* run = route == ATTN_ROUTE_F32 ? attn_bwd_f32 : route == ATTN_ROUTE_MFMA ? (dt == F16 ? attn_bwd_mfma_f16 : attn_bwd_mfma)
                                                                                   : (dt == F16 ? attn_bwd_split_f16 : attn_bwd_split);

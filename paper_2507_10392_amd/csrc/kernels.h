@@ -136,7 +136,7 @@ int attn_select(DType dt, int S, int d, int force);
 // The kernels behind attn_fwd and attn_bwd: a wave per row, fp32 matrix cores, 16-bit matrix cores (head dim 128, and narrower
 // heads with split probabilities).  pointers: all arguments or-ed together; strides: all row strides or-ed together.
 enum AttnRoute { ATTN_ROUTE_SIMPLE, ATTN_ROUTE_F32, ATTN_ROUTE_MFMA, ATTN_ROUTE_SPLIT };
-AttnRoute attn_route(DType dt, int mb, int S, int nh, int d, int64_t ld_max, uintptr_t pointers, int64_t strides, int force);
+AttnRoute attn_route(DType dt, bool bwd, bool rope, int mb, int S, int nh, int d, int64_t ld_max, uintptr_t pointers, int64_t strides, int force);
 hipError_t attn_fwd(hipStream_t st, DType dt, int mb, int S, int nh, int d, const void* q, const void* k,
                     const void* v, int64_t ld, void* o, int64_t ldo, float* lse, int force);
 // delta is float[mb, nh, S] scratch.  dq, dk, dv are laid out like q, k, v with row stride ldd.

@@ -432,13 +432,13 @@ bool do_gemm(stage_t* s, const Gemm& g) {
   return run(s, cls, flops, 0.0, [&] { return gemm(s->st, dt_of(s), g, GEMM_AUTO); });
 }
 
-// Timing class of the attention of this stage: fwd and bwd run the same route, since every row stride and base is a multiple
-// of 16 bytes (workspace buffers of 256-byte alignment, hidden a multiple of 8).
+// Timing class of the attention of this stage, whose row strides and bases are all multiples of 16 bytes (workspace buffers of
+// 256-byte alignment, hidden a multiple of 8).
 const char* attn_class(const stage_t* s, const LayerActs& A, bool bwd) {
   static const char* names[4][2] = {{"attn_fwd_simple", "attn_bwd_simple"}, {"attn_fwd_f32", "attn_bwd_f32"},
                                     {"attn_fwd_mfma", "attn_bwd_mfma"}, {"attn_fwd_mfma_split", "attn_bwd_mfma_split"}};
   const Shape& h = s->sh;
-  return names[attn_route(dt_of(s), h.mb, h.S, h.nh, h.d, 3ll * h.H, (uintptr_t)A.qkv | (uintptr_t)A.o, 3ll * h.H | h.H, ATTN_AUTO)][bwd];
+  return names[attn_route(dt_of(s), bwd, bwd && h.arch == STAGE_ARCH_LLAMA, h.mb, h.S, h.nh, h.d, 3ll * h.H, (uintptr_t)A.qkv | (uintptr_t)A.o, 3ll * h.H | h.H, ATTN_AUTO)][bwd];
 }
 
 // ---- forward of one layer ---------------------------------------------------------------------

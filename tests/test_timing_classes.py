@@ -11,6 +11,10 @@ pytestmark = pytest.mark.gpu
 CASES = [
     ("L1", {}, {"gemm_f32_nn", "gemm_f32_nt", "gemm_f32_tn", "attn_fwd_f32", "attn_bwd_f32"}, ("gemm_simple", "gemm_small", "attn_fwd_simple")),
     ("L1", dict(hidden=272, heads=2), {"gemm_f32_nn", "attn_fwd_simple", "attn_bwd_simple"}, ("attn_fwd_f32", "attn_bwd_f32")),
+    # too few keys for the matrix cores: a wave per row (with heads of 64, in bf16 in the forward only)
+    ("C1", dict(seq=4), {"attn_fwd_simple", "attn_bwd_simple"}, ("attn_fwd_f32", "attn_bwd_f32")),
+    ("L1", dict(seq=4), {"attn_fwd_simple", "attn_bwd_f32"}, ("attn_fwd_f32", "attn_bwd_simple")),     # rotated gradients
+    ("C3t", dict(heads=8, seq=4), {"attn_fwd_simple", "attn_bwd_mfma_split"}, ("attn_fwd_mfma_split",)),
     ("C3t", dict(heads=8), {"gemm_small_nn", "gemm_small_tn", "gemm_small_nn_glu", "attn_fwd_mfma_split", "attn_bwd_mfma_split"},
      ("gemm_f32", "gemm_simple", "attn_fwd_simple")),
     ("C3h", {}, {"gemm_small_nn", "attn_fwd_mfma", "attn_bwd_mfma"}, ("gemm_f32", "attn_fwd_mfma_split")),
