@@ -872,7 +872,10 @@ hipError_t launch_dkv(hipStream_t st, int mb, int S, int nh, int d, const void* 
 // two (dQ), so the 4-wave forms keep 4 waves of a CU at work, or 8 where dQ has two workgroups for it.  Sharing rows costs a
 // merge at the end (16 KB per pair and accumulator through LDS), which a row block with four tiles does not win back in dQ.
 // 16 heads of 128, S = 2048: dK/dV 112 : 77 us, dQ 72 : 57 us (4 : 8 waves); 8 heads, S = 1000: both 92 : 67 us; 4 heads,
-// S = 256: dK/dV 24 : 20 us, dQ 17.9 : 18.8 us.
+// S = 256: dK/dV 24 : 20 us, dQ 17.9 : 18.8 us.  dQ shares rows while every CU has one block; a second round of 8-wave
+// workgroups costs more than the two 4-wave ones that a CU holds side by side, unless the sequences are so long that the blocks
+// differ a lot in their work.  Both directions, S = 513, 98 heads (490 blocks) 83 us shared, 75 not; S = 1700, 24 heads (336 blocks)
+// 104 and 117.  Of 116 shapes with 216 to 550 blocks the rule takes the faster form but for 1.6 %.
 template <int D, bool SPLIT>
 hipError_t bwd_128(hipStream_t st, int mb, int S, int nh, int d, const void* q, const void* k, const void* v, int64_t ld, const void* o,
                    const void* dout, int64_t ldo, const float* lse, float* delta, void* dq, void* dk, void* dv, int64_t ldd,
@@ -881,7 +884,8 @@ hipError_t bwd_128(hipStream_t st, int mb, int S, int nh, int d, const void* q, 
     const hipError_t e = launch_dq<4, 1, D, SPLIT>(st, mb, S, nh, d, q, k, v, ld, o, dout, ldo, lse, delta, dq, ldd, rope);
     return e != hipSuccess ? e : launch_dkv<4, 1, D, SPLIT>(st, mb, S, nh, d, q, k, v, ld, dout, ldo, lse, delta, dk, dv, ldd, rope);
   } else {
-    const hipError_t e = cdiv(S, 128) * nh * mb < 512 && S > 256
+    const int64_t per_head = cdiv(S, 128), blocks = per_head * nh * mb;
+    const hipError_t e = S > 256 && blocks < 512 && blocks <= 256 + 28 * (per_head > 6 ? per_head - 6 : 0)
                              ? launch_dq<8, 2, D, SPLIT>(st, mb, S, nh, d, q, k, v, ld, o, dout, ldo, lse, delta, dq, ldd, rope)
                              : launch_dq<4, 1, D, SPLIT>(st, mb, S, nh, d, q, k, v, ld, o, dout, ldo, lse, delta, dq, ldd, rope);
     if (e != hipSuccess || wide_dkv) return e;
