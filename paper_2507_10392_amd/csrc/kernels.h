@@ -104,7 +104,8 @@ hipError_t norm_fwd(hipStream_t st, DType dt, int kind, int T, int H, const void
 // dx = (dres ? dres : 0) + norm'(x)^T dn (dres may alias dx), plus the partial column sums of the gain (and, for LayerNorm,
 // bias) gradient over row blocks of cdiv(T, nblk) rows: part_g[blk, c] = sum_t dn * xhat, part_b[blk, c] = sum_t dn (part_b may be NULL for
 // RMSNorm).  For the row lengths of the register-resident kernels this is ONE kernel that reads dn and x once (a
-// workgroup per row block); otherwise colsum_partial and norm_bwd one after the other.  Same sums either way.
+// workgroup per row block); otherwise colsum_partial and norm_bwd one after the other.  The row sums are added in a fixed order
+// that depends on how many rows a workgroup walks side by side (4, 2 or 1), colsum_partial's being that of 4.
 hipError_t norm_bwd_partials(hipStream_t st, DType dt, int kind, int T, int H, const void* dn, const void* x,
                              const void* g, const float* rstd, const float* mean, const void* dres, void* dx,
                              float* part_g, float* part_b, int nblk);
