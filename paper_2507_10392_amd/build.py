@@ -10,7 +10,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libstage.so")
 SOURCES = ["stage.hip", "ministages.hip", "ops_api.hip", "elementwise.hip", "gemm_simple.hip", "gemm_f32.hip", "gemm_small.hip", "gemm_mfma.hip", "gemm_mfma_256x256.hip",
-           "gemm_mfma_128x128.hip", "gemm_mfma_256x256_f16.hip", "gemm_mfma_128x128_f16.hip",
+           "gemm_mfma_256x192.hip", "gemm_mfma_256x128.hip", "gemm_mfma_128x128.hip", "gemm_mfma_256x256_f16.hip", "gemm_mfma_256x192_f16.hip", "gemm_mfma_256x128_f16.hip", "gemm_mfma_128x128_f16.hip",
            "attention_simple.hip", "attention_f32.hip", "attention_mfma.hip", "attention_mfma_f16.hip", "attention_split.hip", "attention_split_f16.hip", "mfma_rate.hip", "lds_probe.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wno-unused-command-line-argument"]

@@ -2,16 +2,22 @@
 // gemm_mfma_impl.h, one translation unit per tile shape.
 #include "kernels.h"
 
+#include <algorithm>
+
 namespace zs {
 
 hipError_t gemm_mfma_256x256(hipStream_t st, const Gemm& g);   // 8 wavefronts
+hipError_t gemm_mfma_256x192(hipStream_t st, const Gemm& g);
+hipError_t gemm_mfma_256x128(hipStream_t st, const Gemm& g);   // 8 wavefronts
 hipError_t gemm_mfma_128x128(hipStream_t st, const Gemm& g);   // 4 wavefronts, two workgroups per CU
 hipError_t gemm_mfma_256x256_f16(hipStream_t st, const Gemm& g);
+hipError_t gemm_mfma_256x192_f16(hipStream_t st, const Gemm& g);
+hipError_t gemm_mfma_256x128_f16(hipStream_t st, const Gemm& g);
 hipError_t gemm_mfma_128x128_f16(hipStream_t st, const Gemm& g);
 
 namespace {
 bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }
-int g_force_tile = 0;   // 0 automatic; 1: 256x256, 2: 128x128 (set through gemm_mfma_force_tile)
+int g_force_tile = 0;   // 0 automatic; 1: 256x256, 2: 128x128 (set through gemm_mfma_force_tile); unforced also 3: 256x192, 4: 256x128
 }  // namespace
 
 // The kernel needs 16-byte aligned rows for its vector loads: base pointers 16-byte aligned and
@@ -69,11 +75,21 @@ bool gemm_mfma_takes(DType dt, const Gemm& g) {
   return true;
 }
 
-// Which tile: the MI355X has 256 CUs.  256x256 tiles (8 waves, one workgroup per CU) move the fewest LDS and
-// L2 bytes per flop; 128x128 tiles (two workgroups per CU) run at about 0.8 of their rate (measured at
-// K = 4096) but waste less of the last round of workgroups and give small problems enough workgroups to
-// fill the chip.  The shape with the smaller estimated time wins.
+// Which tile: the MI355X has 256 CUs.  256x256 tiles (8 waves, one workgroup per CU) move the fewest LDS and L2 bytes per flop
+// and run at the highest rate; 256x192 and 256x128 (8 waves, one per CU) and 128x128 (4 waves, two per CU) waste less of
+// the last round of workgroups and give small products enough workgroups to fill the chip.  The tile with the smallest estimated
+// time is taken.  The estimate: per round of workgroups a fixed time (first loads, store) and a time per 64-wide slab, which
+// grows by 0.3 with the share of the chip at work (the clock drops); and the traffic of the result.  Constants fitted to 520
+// times of 130 products (M 256 .. 6000, N 768 .. 16000, K 256 .. 14000, the three layouts): of these the pick is on the geometric mean
+// within 0.3 % of the fastest tile, 8 % at worst.  us, bf16, 256x256 : 128x128 : 256x192 : 256x128: 2048 x 4096, K = 12288
+// 244 : 207 : 221 : 185; 2048 x 5120, K = 12288 (dx) 248 : 310 : 219 : 349; 2048 x 6144, K = 2048 50 : 54 : 48 : 61;
+// 2048 x 2048, K = 12288 225 : 119 : 201 : 155; 4096 x 11008, K = 4096 (dx) 297 : 357 : 318 : 348.
 namespace {
+struct TileTimes { int width, cus; double slab, round, store; };   // us; cus: workgroups that run side by side
+constexpr TileTimes TILE_TIMES[4] = {{256, 256, 1.10, 5.9, 1.0}, {128, 512, 0.774, 4.0, 0.55}, {192, 256, 0.895, 5.9, 0.75}, {128, 256, 0.68, 4.0, 1.0}};
+constexpr double HALF_SLAB = 0.492, HALF_ROUND = 2.4;              // 128x128, a round of at most 256 tiles: one per CU
+constexpr double LAUNCH = 2.7, CROWDED = 0.294, STORE_RATE = 9.3e6; // us, -, bytes per us
+
 // Estimated time of a grid of `small` 128x128 tiles in units of one round of 256x256 tiles: full rounds hold
 // 512 small tiles (two per CU, each at 0.8 of the big tile's rate); a remainder of at most 256 tiles runs
 // one per CU.
@@ -83,40 +99,47 @@ double small_rounds(int64_t small) {
 }
 // Tile columns of a grid of tiles `width` wide: a gate|up tile (glu = 1) covers width/2 columns of each matrix.
 int64_t tile_cols(const Gemm& g, int width) { return cdiv(g.N, g.glu == 1 ? width / 2 : width); }
+
+double tile_us(const Gemm& g, int tile) {
+  const TileTimes& t = TILE_TIMES[tile - 1];
+  const double slabs = (double)cdiv(g.K, 64);
+  const int64_t n = cdiv(g.M, tile == 2 ? 128 : 256) * tile_cols(g, t.width) * g.batch;
+  const double bytes = (double)g.M * g.N * g.batch * (g.c_f32_accum ? (g.c_overwrite ? 4.0 : 8.0) : g.glu == 1 ? 6.0 : g.glu == 2 ? 8.0 : g.resid ? 4.0 : 2.0);
+  const bool half = tile == 2 && n % 512 > 0 && n % 512 <= 256;
+  const int64_t full = n / t.cus + (n % t.cus > 0 && !half);
+  const double used = tile == 2 ? std::min(1.0, n / ((full + 0.5 * half) * 512.0)) : (double)n / (double)(full * t.cus);
+  const double grow = 1.0 + CROWDED * used, grow_half = 1.0 + CROWDED * std::min(1.0, n / 512.0);
+  return LAUNCH + full * (slabs * t.slab * grow + t.round) + (half ? slabs * HALF_SLAB * grow_half + HALF_ROUND : 0.0) + t.store * bytes / STORE_RATE;
+}
 }  // namespace
 
 int gemm_mfma_pick_tile(const Gemm& g) {
   if (g_force_tile) return g_force_tile;
-  const int64_t big = cdiv(g.M, 256) * tile_cols(g, 256) * g.batch;
-  const int64_t small = cdiv(g.M, 128) * tile_cols(g, 128) * g.batch;
-  // The gate|up tile stores three arrays, which weighs more on the small tile: 512 x 11008, K = 4096 (172 big tiles, 688 small
-  // ones) takes 107 us on big tiles and 131 us on small ones, where the plain product of the same tiles would be even.
-  return small_rounds(small) * (g.glu == 1 ? 1.25 : 1.0) < (double)cdiv(big, 256) ? 2 : 1;
+  int best = 1;
+  double us = tile_us(g, 1);
+  for (int tile = 2; tile <= (gemm_mfma_oblong(g) ? 4 : 2); ++tile) {
+    const double t = tile_us(g, tile);
+    if (t < us) { us = t; best = tile; }
+  }
+  return best;
 }
+
+double gemm_mfma_us(const Gemm& g) { return tile_us(g, gemm_mfma_pick_tile(g)); }
 
 void gemm_mfma_force_tile(int id) { g_force_tile = id; }
 
 namespace {
 
-hipError_t run_tile(hipStream_t st, DType dt, const Gemm& g, bool small) {
-  if (dt == F16) return small ? gemm_mfma_128x128_f16(st, g) : gemm_mfma_256x256_f16(st, g);
-  return small ? gemm_mfma_128x128(st, g) : gemm_mfma_256x256(st, g);
+hipError_t run_tile(hipStream_t st, DType dt, const Gemm& g, int tile) {
+  typedef hipError_t (*Run)(hipStream_t, const Gemm&);
+  static const Run run[2][4] = {{gemm_mfma_256x256, gemm_mfma_128x128, gemm_mfma_256x192, gemm_mfma_256x128},
+                                {gemm_mfma_256x256_f16, gemm_mfma_128x128_f16, gemm_mfma_256x192_f16, gemm_mfma_256x128_f16}};
+  return run[dt == F16][tile - 1](st, g);
 }
 
-// A grid of 256x256 tiles that ends in a round with few tiles (1376 tiles = 5 rounds + 96 tiles on 256 CUs) pays a
-// whole round for them.  When the leading tile columns make up whole rounds exactly, the product is cut along N:
-// those columns run on big tiles, the remaining ones on 128x128 tiles, which fill the chip (two workgroups per CU)
-// and take about 0.625 of a big round.  Returns false when the shape does not ask for it.
-bool split_tail(DType dt, const Gemm& g, Gemm& head, Gemm& tail) {
-  const int64_t tm = cdiv(g.M, 256), tn = tile_cols(g, 256);
-  const int64_t tiles = tm * tn * g.batch, rem = tiles % 256;
-  if (tiles < 256 || rem == 0 || rem > 128) return false;   // up to 128 big tiles make one round of small ones
-  const int64_t col = tm * g.batch;                       // tiles per tile column
-  if (rem % col) return false;
-  const int64_t c1 = tn - rem / col;                      // leading columns: (tiles - rem) tiles, whole rounds
-  if (c1 < 1) return false;
-  const int64_t n1 = c1 * (g.glu == 1 ? 128 : 256);
-  if (g.rope && n1 % g.rope_d) return false;
+// Columns [0, n1) and [n1, N) of a product as products of their own.
+bool cut_columns(DType dt, const Gemm& g, int64_t n1, Gemm& head, Gemm& tail) {
+  if (n1 < 1 || n1 >= g.N || (g.rope && n1 % g.rope_d)) return false;
   head = g; tail = g;
   head.N = (int)n1;
   tail.N = g.N - (int)n1;
@@ -129,6 +152,16 @@ bool split_tail(DType dt, const Gemm& g, Gemm& head, Gemm& tail) {
   tail.B = (const char*)g.B + boff;
   for (int p = 0; p < g.nx; ++p) tail.Bx[p] = (const char*)g.Bx[p] + boff;
   return gemm_mfma_takes(dt, head) && gemm_mfma_takes(dt, tail);
+}
+
+// A grid of 256x256 tiles that ends in a round with few tiles (1376 tiles = 5 rounds + 96 tiles on 256 CUs) pays a whole round
+// for them.  So the product may be cut along N: as many leading tile columns as fit the whole rounds run on 256-row tiles
+// `wide`, the remaining ones on whatever tile suits them.
+bool split_tail(DType dt, const Gemm& g, int wide, Gemm& head, Gemm& tail) {
+  const int width = TILE_TIMES[wide - 1].width;
+  const int64_t col = cdiv(g.M, 256) * g.batch, tiles = col * tile_cols(g, width);   // col: tiles per tile column
+  if (tiles < 256 || tiles % 256 == 0) return false;
+  return cut_columns(dt, g, tiles / 256 * 256 / col * (g.glu == 1 ? width / 2 : width), head, tail);
 }
 
 // ---- K range of the last round's tiles cut into chunks -------------------------------------------------------------
@@ -163,7 +196,7 @@ bool plan_kcut(DType dt, const Gemm& g, KCut& k) {
   const double fx = kcut_round_fixed_parts(g.kseg);
   double t_now = (double)parts + fx;                                  // a whole round
   Gemm h2, t2;
-  if (split_tail(dt, g, h2, t2))                                      // today's other way: the rest on 128x128 tiles
+  if (rem <= 128 && rem % (tm * g.batch) == 0 && split_tail(dt, g, 1, h2, t2))   // the other way: the rest on 128x128 tiles
     t_now = std::min(t_now, small_rounds(cdiv(t2.M, 128) * tile_cols(t2, 128) * t2.batch) * (parts + fx));
   double best = t_now * 0.97;                                         // a cut has to win at least 3 %
   int best_cp = 0;
@@ -264,13 +297,13 @@ int64_t gemm_mfma_ws_bytes(const Gemm& g) {
 }
 
 hipError_t gemm_mfma(hipStream_t st, DType dt, const Gemm& g) {
-  const bool small = gemm_mfma_pick_tile(g) == 2;
+  const int tile = gemm_mfma_pick_tile(g);
   if (g.ws && !g_force_tile) {
     KCut k;
     if (plan_kcut(dt, g, k) && k.ws_need <= g.ws_bytes && ((uintptr_t)g.ws & 15) == 0 && gemm_mfma_takes(dt, g)) {
-      hipError_t e = run_tile(st, dt, k.head, false);
+      hipError_t e = run_tile(st, dt, k.head, 1);
       if (e != hipSuccess) return e;
-      e = run_tile(st, dt, k.tail, false);
+      e = run_tile(st, dt, k.tail, 1);
       if (e != hipSuccess) return e;
       hipLaunchKernelGGL(add_partials_kernel, dim3((unsigned)(k.rem * 4)), dim3(256), 0, st, (float*)g.C, g.ldc, g.sC, g.M, g.N,
                          (int)cdiv(g.M, 256), (int)cdiv(g.N, 256), k.tail.tile_base, k.tail.tile_count, (const float*)g.ws,
@@ -280,7 +313,7 @@ hipError_t gemm_mfma(hipStream_t st, DType dt, const Gemm& g) {
   }
   Gemm halves;
   if (plan_halves(dt, g, halves)) {
-    const hipError_t e = run_tile(st, dt, halves, gemm_mfma_pick_tile(halves) == 2);
+    const hipError_t e = run_tile(st, dt, halves, gemm_mfma_pick_tile(halves));
     if (e != hipSuccess) return e;
     const int64_t nvec = (int64_t)g.M * g.N / 8;
     const dim3 grid((unsigned)cdiv(nvec, 256));
@@ -288,18 +321,22 @@ hipError_t gemm_mfma(hipStream_t st, DType dt, const Gemm& g) {
     else hipLaunchKernelGGL(add_halves_kernel<bf16>, grid, dim3(256), 0, st, nvec, g.N / 8, (const float*)g.ws, halves.sC, (bf16*)g.C, g.ldc);
     return hipGetLastError();
   }
-  Gemm head, tail;
-  if (!g_force_tile && split_tail(dt, g, head, tail)) {
-    // whole rounds of big tiles + the rest on small ones, against the better of the two uniform grids
-    const int64_t big = cdiv(g.M, 256) * tile_cols(g, 256) * g.batch;
-    const double t_split = (double)(big / 256) + small_rounds(cdiv(tail.M, 128) * tile_cols(tail, 128) * tail.batch);
-    const double t_uniform = small ? small_rounds(cdiv(g.M, 128) * tile_cols(g, 128) * g.batch) : (double)cdiv(big, 256);
-    if (t_split < t_uniform) {
-      const hipError_t e = run_tile(st, dt, head, false);
-      return e != hipSuccess ? e : run_tile(st, dt, tail, true);
+  if (!g_force_tile) {
+    Gemm head, tail, h, t;
+    double us = tile_us(g, tile);
+    int wide = 0;
+    for (int w : {1, 3}) {
+      if (w == 3 && !gemm_mfma_oblong(g)) continue;
+      if (!split_tail(dt, g, w, h, t)) continue;
+      const double cut = tile_us(h, w) + gemm_mfma_us(t);
+      if (cut < us) { us = cut; wide = w; head = h; tail = t; }
+    }
+    if (wide) {
+      const hipError_t e = run_tile(st, dt, head, wide);
+      return e != hipSuccess ? e : run_tile(st, dt, tail, gemm_mfma_pick_tile(tail));
     }
   }
-  return run_tile(st, dt, g, small);
+  return run_tile(st, dt, g, tile);
 }
 
 }  // namespace zs

@@ -1,10 +1,10 @@
 // 16-bit (bf16 or IEEE half) GEMM on the CDNA4 matrix cores (v_mfma_f32_16x16x32_bf16 / _f16), fp32 accumulation: the tile kernel,
 // templated on the workgroup tile BM x BN and the number of wavefronts.
 //
-// One workgroup of 4 (2 x 2) or 8 (2 x 4) wavefronts computes a BM x BN tile of C; each wavefront owns
+// One workgroup of 4 (2 x 2) or 8 (2 x 4 or 4 x 2) wavefronts computes a BM x BN tile of C; each wavefront owns
 // its part as MFMA blocks of 16x16 (4 accumulator registers per block and lane).
 // The K loop walks 64-wide slabs.  A slab of each operand is fetched from HBM with 16-byte buffer
-// loads into registers one iteration ahead and stored into one of two LDS buffers:
+// loads into registers one or two iterations ahead and stored into one of two LDS buffers:
 //   * contraction index contiguous in memory  -> LDS [row][k], 128-byte rows whose 16-byte pieces are
 //     permuted by the row index (piece p of row r at position p ^ r%8); an MFMA operand fragment
 //     (8 consecutive k of one row) is one ds_read_b128;
@@ -18,7 +18,14 @@
 // on a compact patch of C and re-use their own L2's A rows and B columns.
 // The 256x256 tile runs 8 wavefronts (128 accumulator registers each, two waves per SIMD); the 128x128 tile
 // runs 4 and needs 64 accumulator registers and 74 KB of LDS, so two workgroups share a CU.  Either way a
-// SIMD always has a second wave to issue MFMAs while the first waits for memory, LDS or a barrier.
+// SIMD has a second wave to issue MFMAs while the first waits for memory, LDS or a barrier.  The 256x192 and 256x128
+// tiles (8 waves of 64 x 96 and 64 x 64) are for grids that fill the chip better with them.
+//
+// What bounds the smaller tiles is the rate at which a CU gets lines that its L1 does not hold: with the MFMAs taken out of the
+// 256x128 kernel, 2048 x 4096, K = 8192, takes 104 of 122 us, with the loads taken out instead 86, and loading three
+// slabs ahead instead of two changes nothing.  Lines that are not cold come faster (512 x 4096, K = 12288 on 128x128 tiles 85 us
+// with operands in the memory-side cache, 129 us without).  So a bigger tile, which needs fewer lines per flop, beats a smaller
+// one wherever the grid still fills the CUs, and rows that are no multiple of 128 bytes apart cost up to half as much again.
 #pragma once
 #include "kernels.h"
 
@@ -74,35 +81,47 @@ __device__ __forceinline__ void store_kmajor(const Frag<R, NT>& f, bf16* lds, in
 }
 
 // Operand stored [K, rows] (row index contiguous).  A k-line of the slab is R/8 vectors; thread t carries
-// vectors v = t + NT*i: k = v/(R/8), row-vector = v%(R/8) (= t%(R/8) for every i).
+// vectors v = t + NT*i: k = v/(R/8), row-vector = v%(R/8).  Where R/8 divides NT that row-vector is the same for every i and one
+// offset serves all; else (R = 192) each pass has its own.
 // Row-vectors at or past the operand's last row (ragged edge tile) would read the next k-line: out of range.
-template <int R> __device__ __forceinline__ int voff_rmajor(int ld, int tid, int row0, int nrows) {
-  return row0 + (tid % (R / 8)) * 8 >= nrows ? DEAD : ((tid / (R / 8)) * ld + (tid % (R / 8)) * 8) * 2;
-}
-// The same for a tile whose first R/2 rows come from one matrix (rows row0 .. of `nrows`) and whose last R/2 rows
-// are the same rows of a second matrix lying `second` elements behind the first: gate and up projections side by side.
-template <int R> __device__ __forceinline__ int voff_rmajor_two(int ld, int tid, int row0, int nrows, int second) {
-  constexpr int PER = R / 8, HALF = PER / 2;
-  const int j = tid % PER, jj = j % HALF;
-  return row0 + jj * 8 >= nrows ? DEAD : ((tid / PER) * ld + jj * 8 + (j >= HALF ? second : 0)) * 2;
+template <int R, int NT> struct Lines {
+  static constexpr int PER = R / 8, N = NT % PER == 0 ? 1 : R * 8 / NT, KSTEP = NT / PER;   // KSTEP: k-lines of a pass (N = 1)
+  static_assert(N > 1 || KSTEP % 16 == 0, "bit 3 of a thread's k-line must not depend on the pass");
+};
+template <int R, int NT> struct LineOffsets { int v[Lines<R, NT>::N]; };
+// two: the tile's first R/2 rows come from one matrix (rows row0 .. of `nrows`) and its last R/2 rows are the same rows of a second
+// matrix lying `second` elements behind the first: gate and up projections side by side.
+template <int R, int NT, bool two>
+__device__ __forceinline__ LineOffsets<R, NT> voff_rmajor(int ld, int tid, int row0, int nrows, int second) {
+  constexpr int PER = R / 8, HALF = two ? PER / 2 : PER;
+  LineOffsets<R, NT> o;
+#pragma unroll
+  for (int i = 0; i < Lines<R, NT>::N; ++i) {
+    const int v = tid + NT * i, j = v % PER, jj = j % HALF;
+    o.v[i] = row0 + jj * 8 >= nrows ? DEAD : ((v / PER) * ld + jj * 8 + (j >= HALF ? second : 0)) * 2;
+  }
+  return o;
 }
 template <int R, int NT>
-__device__ __forceinline__ void load_rmajor(Frag<R, NT>& f, __amdgpu_buffer_rsrc_t rs, int voff, int ld, int row0, int k0,
+__device__ __forceinline__ void load_rmajor(Frag<R, NT>& f, __amdgpu_buffer_rsrc_t rs, const LineOffsets<R, NT>& voff, int ld, int row0, int k0,
                                             int i0 = 0, int i1 = R * 8 / NT) {
-  constexpr int KSTEP = NT / (R / 8);             // k-lines covered by one pass of the NT threads
+  typedef Lines<R, NT> L;
 #pragma unroll
   for (int i = 0; i < R * 8 / NT; ++i)
-    if (i >= i0 && i < i1) f.v[i] = __builtin_amdgcn_raw_buffer_load_b128(rs, voff, ((k0 + KSTEP * i) * ld + row0) * 2, 0);
+    if (i >= i0 && i < i1)
+      f.v[i] = __builtin_amdgcn_raw_buffer_load_b128(rs, voff.v[L::N == 1 ? 0 : i], ((k0 + (L::N == 1 ? L::KSTEP * i : 0)) * ld + row0) * 2, 0);
 }
 template <int R, int NT>
 __device__ __forceinline__ void store_rmajor(const Frag<R, NT>& f, bf16* lds, int tid, int i0 = 0, int i1 = R * 8 / NT) {
-  constexpr int KSTEP = NT / (R / 8), LDR = R + RPAD;
-  static_assert(KSTEP % 16 == 0, "bit 3 of a thread's k-line must not depend on the pass");
-  const int kl = tid / (R / 8);                   // k-line of pass 0; passes add multiples of 16
-  bf16* p = lds + kl * LDR + (((tid % (R / 8)) ^ (((kl >> 3) & 1) << 1)) * 8);   // 16-row chunks swap in pairs on odd eights of k
+  typedef Lines<R, NT> L;
+  constexpr int LDR = R + RPAD;
 #pragma unroll
   for (int i = 0; i < R * 8 / NT; ++i)
-    if (i >= i0 && i < i1) *reinterpret_cast<u32x4*>(p + KSTEP * i * LDR) = f.v[i];
+    if (i >= i0 && i < i1) {
+      const int v = L::N == 1 ? tid : tid + NT * i, kl = v / L::PER;   // N = 1: k-line of pass 0; passes add multiples of 16
+      // 16-row chunks swap in pairs on odd eights of k
+      *reinterpret_cast<u32x4*>(lds + (kl + (L::N == 1 ? L::KSTEP * i : 0)) * LDR + (((v % L::PER) ^ (((kl >> 3) & 1) << 1)) * 8)) = f.v[i];
+    }
 }
 
 // MFMA operand fragment for lane (row = lane%16, g = lane/16): the 8 values k = k32 + 8g .. +7 of that row
@@ -144,14 +163,16 @@ __device__ __forceinline__ void tile_origin(int pid, int tiles_m, int tiles_n, i
 // so a lane owns 4 consecutive columns per block and writes them as one float4.
 template <int BN> struct Staging { static constexpr int LDW = BN + 4; };   // padded row (floats)
 
-template <int BN, int MI, int NJ>
-__device__ __forceinline__ void stage_quads(float* stage, f32x4 (&acc)[MI][NJ], int wn, int lane) {
+// A wave's rows of the tile (16 MI of them, from wm on) lie in one half and are written when that half is staged.
+template <int BM, int BN, int MI, int NJ>
+__device__ __forceinline__ void stage_quads(float* stage, f32x4 (&acc)[MI][NJ], int half, int wm, int wn, int lane) {
   constexpr int LDW = Staging<BN>::LDW;
+  if (wm / (BM / 2) != half) return;
 #pragma unroll
   for (int i = 0; i < MI; ++i)
 #pragma unroll
     for (int j = 0; j < NJ; ++j)
-      *reinterpret_cast<f32x4*>(stage + (i * 16 + (lane & 15)) * LDW + wn + j * 16 + 4 * (lane >> 4)) = acc[i][j];
+      *reinterpret_cast<f32x4*>(stage + (wm % (BM / 2) + i * 16 + (lane & 15)) * LDW + wn + j * 16 + 4 * (lane >> 4)) = acc[i][j];
 }
 
 // Epilogue for C (fp32) += product (no bias, no residual).  Ct points at the tile's first element, of which rows x cols
@@ -163,30 +184,32 @@ __device__ __forceinline__ void stage_quads(float* stage, f32x4 (&acc)[MI][NJ], 
 // stored as it is (a partial sum that another kernel adds to C).
 template <int BM, int BN, int NT, int MI, int NJ>
 __device__ __forceinline__ void epilogue_accum(float* Ct, int ldc, int rows, int cols, bool overwrite, f32x4 (&acc)[MI][NJ],
-                                               int wave_m, int wn, int tid, float* stage) {
+                                               int wm, int wn, int tid, float* stage) {
   constexpr int LDW = Staging<BN>::LDW;
   static_assert((BM / 2) * LDW * 4 <= 2 * (slab_elems(BM) + slab_elems(BN)) * 2, "staging tile must fit the K-loop buffers");
   constexpr int VPR = BN / 4;                              // float4 per row
-  constexpr int NV = (BM / 2) * VPR / NT;                  // float4 per thread and half
+  constexpr int NS = NT % VPR == 0 ? NT : 8 * VPR;         // threads that store: whole rows at a time (BN = 192: 384 of 512)
+  constexpr int NV = (BM / 2) * VPR / NS;                  // float4 per thread and half
+  static_assert(NS <= NT && (BM / 2) * VPR % NS == 0, "a half is whole passes");
   const __amdgpu_buffer_rsrc_t rsC = make_rsrc(Ct, (uint32_t)((int64_t)(rows - 1) * ldc + cols) * 4u);
   const int lr0 = tid / VPR, cv = tid % VPR;               // vector v = tid + NT*it: row lr0 + (NT/VPR)*it, same columns
-  const bool col_ok = cv * 4 < cols;                       // cols is a multiple of 4
+  const bool col_ok = cv * 4 < cols && tid < NS;           // cols is a multiple of 4
 #pragma unroll
   for (int half = 0; half < 2; ++half) {
     __syncthreads();
-    if (wave_m == half) stage_quads<BN, MI, NJ>(stage, acc, wn, tid & 63);
+    stage_quads<BM, BN, MI, NJ>(stage, acc, half, wm, wn, tid & 63);
     u32x4 old[NV];
     uint32_t off[NV];
 #pragma unroll
     for (int it = 0; it < NV; ++it) {
-      const int row = half * (BM / 2) + lr0 + (NT / VPR) * it;
+      const int row = half * (BM / 2) + lr0 + (NS / VPR) * it;
       off[it] = col_ok ? (uint32_t)(row * ldc + cv * 4) * 4u : 0x80000000u;
       old[it] = overwrite ? u32x4{0u, 0u, 0u, 0u} : __builtin_amdgcn_raw_buffer_load_b128(rsC, (int)off[it], 0, 0);
     }
     __syncthreads();
 #pragma unroll
     for (int it = 0; it < NV; ++it) {
-      const f32x4 x = *reinterpret_cast<const f32x4*>(stage + (lr0 + (NT / VPR) * it) * LDW + cv * 4);
+      const f32x4 x = *reinterpret_cast<const f32x4*>(stage + (lr0 + (NS / VPR) * it) * LDW + cv * 4);
       union { u32x4 u; f32x4 f; } o;
       o.u = old[it];
       o.f += x;
@@ -213,21 +236,22 @@ template <> __device__ __forceinline__ f32x4 mfma_16x16x32<f16>(bf16x8 a, bf16x8
 // loaded once, and what depends on the row (residual, rotary angles, or the gate and up values of GLU = 2) is loaded
 // for a whole half before the staging barrier: the loads' latency runs under the staging instead of once per row.
 template <typename E, int BM, int BN, int NT, int MI, int NJ, int GLU>
-__device__ __forceinline__ void epilogue_store(const Gemm& g, int z, f32x4 (&acc)[MI][NJ], int m0, int n0, int wave_m,
+__device__ __forceinline__ void epilogue_store(const Gemm& g, int z, f32x4 (&acc)[MI][NJ], int m0, int n0, int wm,
                                                int wn, int tid, float* stage) {
   constexpr int LDW = Staging<BN>::LDW;
   static_assert((BM / 2) * LDW * 4 <= 2 * (slab_elems(BM) + slab_elems(BN)) * 2, "staging tile must fit the K-loop buffers");
   constexpr int VPR = BN / 8;                              // 16-byte output vectors per row
-  constexpr int NV = (BM / 2) * VPR / NT;                  // vectors per thread and half
-  constexpr int RSTEP = NT / VPR;                          // rows between a thread's consecutive vectors
-  static_assert(NT % VPR == 0 && ((BM / 2) * VPR) % NT == 0, "a thread keeps its columns");
+  constexpr int NS = NT % VPR == 0 ? NT : 16 * VPR;        // threads that store: whole rows at a time (BN = 192: 384 of 512)
+  constexpr int NV = (BM / 2) * VPR / NS;                  // vectors per thread and half
+  constexpr int RSTEP = NS / VPR;                          // rows between a thread's consecutive vectors
+  static_assert(NS <= NT && ((BM / 2) * VPR) % NS == 0, "a thread keeps its columns");
   typedef typename Vec<E>::type E8;
   const int lane = tid & 63;
   const E* bias = g.bias ? (const E*)g.bias + (int64_t)z * g.sBias : nullptr;
   const E* R = g.resid ? (const E*)g.resid + (int64_t)z * g.sC : nullptr;
   E* Cz = (E*)g.C + (int64_t)z * g.sC;
   const bool rope = g.rope && z < g.rope_batches;
-  const int lr0 = tid / VPR, cv = (tid % VPR) * 8, col = n0 + cv;
+  const int lr0 = tid / VPR, cv = (tid % VPR) * 8, col = tid < NS ? n0 + cv : g.N;
   const bool full = col + 8 <= g.N;                        // all 8 columns exist: the vector path
   const bool pre_resid = GLU == 0 && R, pre_rope = GLU == 0 && rope && !R;
   E8 bb = {};
@@ -257,7 +281,7 @@ __device__ __forceinline__ void epilogue_store(const Gemm& g, int z, f32x4 (&acc
       if (want0 && row < g.M) pre0[it] = *reinterpret_cast<const u32x4*>(src0);
       if (want1 && row < g.M) pre1[it] = *reinterpret_cast<const u32x4*>(src1);
     }
-    if (wave_m == half) stage_quads<BN, MI, NJ>(stage, acc, wn, lane);
+    stage_quads<BM, BN, MI, NJ>(stage, acc, half, wm, wn, lane);
     __syncthreads();
 #pragma unroll
     for (int it = 0; it < NV; ++it) {
@@ -329,7 +353,7 @@ __device__ __forceinline__ void epilogue_store(const Gemm& g, int z, f32x4 (&acc
 // BN/2 the up columns of the same index.  Both are rounded and stored into gu, and silu(gate) * up of the rounded
 // values goes to C: the three arrays the batched product followed by the activation kernel would leave.
 template <typename E, int BM, int BN, int NT, int MI, int NJ>
-__device__ __forceinline__ void epilogue_glu(const Gemm& g, f32x4 (&acc)[MI][NJ], int m0, int c0, int wave_m, int wn, int tid,
+__device__ __forceinline__ void epilogue_glu(const Gemm& g, f32x4 (&acc)[MI][NJ], int m0, int c0, int wm, int wn, int tid,
                                              float* stage) {
   constexpr int LDW = Staging<BN>::LDW;
   typedef typename Vec<E>::type E8;
@@ -337,7 +361,7 @@ __device__ __forceinline__ void epilogue_glu(const Gemm& g, f32x4 (&acc)[MI][NJ]
 #pragma unroll
   for (int half = 0; half < 2; ++half) {
     __syncthreads();
-    if (wave_m == half) stage_quads<BN, MI, NJ>(stage, acc, wn, lane);
+    stage_quads<BM, BN, MI, NJ>(stage, acc, half, wm, wn, lane);
     __syncthreads();
     constexpr int VPR = BN / 16;                           // 8-column pieces of each matrix per row
 #pragma unroll
@@ -369,8 +393,8 @@ __device__ __forceinline__ void epilogue_glu(const Gemm& g, f32x4 (&acc)[MI][NJ]
 template <typename E, int BM, int BN, int NW, int TA, int TB, int SEG, int ACC, int GLU>
 __global__ __launch_bounds__(64 * NW, (NW == 4 && BM * BN <= 128 * 128) ? 2 : 1) void gemm_mfma_kernel(Gemm g, int tiles_m,
                                                                                                         int tiles_n) {
-  constexpr int NT = 64 * NW, WN = NW / 2;               // threads; waves along n (2 along m)
-  constexpr int MI = BM / 32, NJ = BN / (16 * WN);       // 16x16 blocks per wave along m and n
+  constexpr int NT = 64 * NW, WM = BM > BN ? 4 : 2, WN = NW / WM;   // threads; waves along m and n
+  constexpr int MI = BM / (16 * WM), NJ = BN / (16 * WN);           // 16x16 blocks per wave along m and n
   constexpr int SLAB_A = slab_elems(BM), SLAB_B = slab_elems(BN);   // LDS elements per operand slab, either layout
   extern __shared__ __align__(16) char smem_raw[];
   bf16* smem = reinterpret_cast<bf16*>(smem_raw);        // [2 buffers][A slab | B slab]
@@ -395,7 +419,7 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BM * BN <= 128 * 128) ? 2 : 1)
   const bf16* B = (const bf16*)g.B + (int64_t)z * g.sB;
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = (wave / WN) * (BM / 2), wn = (wave % WN) * (BN / WN);
+  const int wm = (wave / WN) * (BM / WM), wn = (wave % WN) * (BN / WN);
   static_assert(GLU == 0 || (GLU == 1 && !TA && !TB && !SEG && !ACC) || (GLU == 2 && !TA && TB && !SEG && !ACC), "fused gated unit");
   const int nb0 = GLU == 1 ? n0 / 2 : n0;                // first column of the tile inside B (GLU = 1: inside each of the two)
 
@@ -407,13 +431,16 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BM * BN <= 128 * 128) ? 2 : 1)
 #pragma unroll
       for (int r = 0; r < 4; ++r) acc[i][j][r] = 0.f;
 
-  const int nk = (g.K + BK - 1) / BK;
-  // Two register stages.  While slab kt is multiplied out of one LDS buffer, slab kt+1 (loaded during the
-  // previous iteration) is written into the other buffer BETWEEN the MFMA steps, and the loads of slab
-  // kt+2 are in flight.  The LDS writes thereby overlap MFMAs instead of forming a phase of their own in
-  // which every wave of the workgroup writes and the matrix cores idle.
-  Frag<BM, NT> fa0, fa1;
-  Frag<BN, NT> fb0, fb1;
+  // While slab kt is multiplied out of one LDS buffer, slab kt+1 (loaded during the previous iteration) is written into the
+  // other buffer BETWEEN the MFMA steps, and each register that has been written is loaded again at once, with its part of slab
+  // kt+1+STAGES.  The LDS writes thereby overlap MFMAs instead of forming a phase of their own in which every wave of
+  // the workgroup writes and the matrix cores idle.  A's vectors go before B's: written and loaded in turn, operands
+  // whose rows straddle cache lines took up to 20 % longer (648 x 3040, K = 13824, rows 16 bytes off: 147 : 177 us).  With two
+  // stages the 128x128 tile's loads have two slabs' time: 2048 x 2048, K = 8192 91 -> 76 us (80 with one); the
+  // other tiles have no registers for them or gain nothing.
+  constexpr int STAGES = BM == 128 ? 2 : 1;
+  Frag<BM, NT> fa[STAGES];
+  Frag<BN, NT> fb[STAGES];
   const int lda = (int)g.lda, ldb = (int)g.ldb;
   // PAIR: the K range is made of g.nx+1 parts of kseg rows, each with operands of its own (both row-contiguous)
   constexpr bool PAIR = SEG && TA == 1 && TB == 0;
@@ -441,29 +468,36 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BM * BN <= 128 * 128) ? 2 : 1)
     return (p >= 1 && p <= p1) ? make_rsrc((const bf16*)g.Bx[p - 1] + (int64_t)z * g.sB, (uint32_t)((int64_t)(rows - 1) * ldb + g.N) * 2u)
                                : make_rsrc(B, 0u);
   };
-  // PAIR: descriptors of the part whose slabs are being loaded
-  __amdgpu_buffer_rsrc_t curA = p0 == 0 ? rsA : part_a(p0), curB = p0 == 0 ? rsB : part_b(p0);
-  const int voffA = TA == 0 ? ((tid >> 3) * lda + (tid & 7) * 8) * 2 : voff_rmajor<BM>(lda, tid, m0, g.M);
-  const int voffB = TB == 1     ? ((tid >> 3) * ldb + (tid & 7) * 8) * 2
-                    : GLU == 1 ? voff_rmajor_two<BN>(ldb, tid, nb0, g.N, (int)g.sB)
-                               : voff_rmajor<BN>(ldb, tid, n0, g.N);
+  // The load cursor: descriptors and first row (PAIR: inside the part) of the next slab to be fetched.
+  __amdgpu_buffer_rsrc_t curA = PAIR && p0 > 0 ? part_a(p0) : rsA, curB = PAIR && p0 > 0 ? part_b(p0) : rsB;
+  int curk = 0, curp = p0;
+  auto advance = [&](bool odd) {                           // odd: past a slab of odd number; parts are pairs of slabs, but for the last
+    curk += BK;
+    if (PAIR && odd && curk >= (curp < g.nx ? K1 : g.K - g.nx * K1)) {
+      ++curp;
+      curk = 0;
+      curA = part_a(curp);
+      curB = part_b(curp);
+    }
+  };
+  const int voffA = ((tid >> 3) * lda + (tid & 7) * 8) * 2, voffB = ((tid >> 3) * ldb + (tid & 7) * 8) * 2;   // k contiguous
+  const LineOffsets<BM, NT> lineA = voff_rmajor<BM, NT, false>(lda, tid, m0, g.M, 0);                           // row contiguous
+  const LineOffsets<BN, NT> lineB = voff_rmajor<BN, NT, GLU == 1>(ldb, tid, nb0, g.N, (int)g.sB);
 
   constexpr int VA = BM * 8 / NT, VB = BN * 8 / NT;        // 16-byte vectors per thread and slab
-  static_assert(VA % 4 == 0 && VB % 4 == 0, "a quarter of the slab is stored per MFMA step");
-  // Loads vectors [i0, i1) of the thread's share of slab kt, counted over the A vectors followed by the B vectors.
-  auto fetch = [&](int kt, Frag<BM, NT>& fa0, Frag<BN, NT>& fb0, int i0 = 0, int i1 = 1 << 20) {
-    const int k0 = kt * BK;
-    if (TA == 0) load_kmajor<BM, NT>(fa0, rsA, voffA, lda, m0, k0, g.K, tid, i0, i1);
-    else load_rmajor<BM, NT>(fa0, rsA, voffA, lda, m0, k0, i0, i1);
+  // Loads the thread's vectors [a0, a1) of A and [b0, b1) of B of the slab under the cursor.
+  auto fetch = [&](Frag<BM, NT>& fa, Frag<BN, NT>& fb, int a0, int a1, int b0, int b1) {
+    if (TA == 0) load_kmajor<BM, NT>(fa, curA, voffA, lda, m0, curk, g.K, tid, a0, a1);
+    else load_rmajor<BM, NT>(fa, curA, lineA, lda, m0, curk, a0, a1);
     if (TB == 1) {
       int vo = voffB;
       if (SEG && !PAIR) {  // the thread's k offset inside the slab is fixed, so one segment lookup per slab
-        const int seg = (k0 + (tid & 7) * 8) / g.kseg;
+        const int seg = (curk + (tid & 7) * 8) / g.kseg;
         vo += seg * ((int)g.segB - g.kseg) * 2;          // element (n, k) of segment seg lies at seg*segB + n*ldb + k - seg*kseg
       }
-      load_kmajor<BN, NT>(fb0, rsB, vo, ldb, n0, k0, g.K, tid, i0 - VA, i1 - VA);
+      load_kmajor<BN, NT>(fb, curB, vo, ldb, n0, curk, g.K, tid, b0, b1);
     } else {
-      load_rmajor<BN, NT>(fb0, rsB, voffB, ldb, nb0, k0, i0 - VA, i1 - VA);
+      load_rmajor<BN, NT>(fb, curB, lineB, ldb, nb0, curk, b0, b1);
     }
   };
   auto stash_a = [&](int buf, const Frag<BM, NT>& fa, int i0 = 0, int i1 = 64) {
@@ -474,19 +508,17 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BM * BN <= 128 * 128) ? 2 : 1)
     bf16* Bs = smem + buf * (SLAB_A + SLAB_B) + SLAB_A;
     if (TB == 1) store_kmajor<BN, NT>(fb, Bs, tid, i0, i1); else store_rmajor<BN, NT>(fb, Bs, tid, i0, i1);
   };
-  // multiplies the slab in LDS buffer `buf`; after each of the four MFMA steps it writes a quarter of the
-  // next slab (held in fa, fb) into the other buffer, which nobody reads now.  The loads of the slab after that
-  // are issued an eighth at a time, after every half MFMA step (`load(i0, i1)` loads vectors [i0, i1) of the thread's
-  // share): the CU's load unit takes 16 cycles per 1 KB wave load, and a wave that issues its whole share at once
-  // (64 loads per workgroup and slab, all waves at the same point of the loop) waits in that unit's queue for
+  // multiplies the slab in LDS buffer `buf`; after each of the eight regions of MFMAs it writes a quarter of one operand's part of
+  // the next slab (held in fa, fb) into the other buffer, which nobody reads now, and loads the same registers again.
+  // The loads are spread out because the CU's load unit takes 16 cycles per 1 KB wave load, and a wave that issues its whole
+  // share at once (64 loads per workgroup and slab, all waves at the same point of the loop) waits in that unit's queue for
   // hundreds of cycles in which it issues no MFMA.  The scheduling fences keep the compiler from gathering the loads
   // at the end of the loop body again.
-  constexpr int VL = (VA + VB) / 8;                        // vectors per load group
-  static_assert(MI == 8 || MI == 4, "a load group and a stash quarter go out after every MI/4 rows of MFMA blocks");
+  static_assert(MI == 8 || MI == 4, "a share of the loads and stores goes out after every MI/4 rows of MFMA blocks");
   // A slab is multiplied in 8 regions of MI/4 rows of blocks each.  The schedule is laid down by hand, with scheduling
   // fences between its parts: a region first issues the LDS reads of the NEXT region's fragments, then its own MFMAs,
-  // then a quarter of one operand's share of the next slab's stores (A and B in turn), then its share of the global loads.
-  auto multiply = [&](int buf, const Frag<BM, NT>& fa, const Frag<BN, NT>& fb, auto&& load) {
+  // then a quarter of one operand's share of the next slab's stores, then its share of the global loads.
+  auto multiply = [&](int buf, Frag<BM, NT>& fa, Frag<BN, NT>& fb) {
     const bf16* As = smem + buf * (SLAB_A + SLAB_B);
     const bf16* Bs = As + SLAB_A;
     constexpr int RI = MI / 4;                             // rows of blocks per region
@@ -516,53 +548,94 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BM * BN <= 128 * 128) ? 2 : 1)
 #pragma unroll
         for (int j = 0; j < NJ; ++j)
           acc[(e & 3) * RI + ii][j] = mfma_16x16x32<E>(b[e >> 2][j], a[e & 1][ii], acc[(e & 3) * RI + ii][j]);
-      if (e & 1) stash_b(buf ^ 1, fb, (e >> 1) * VB / 4, ((e >> 1) + 1) * VB / 4);
-      else stash_a(buf ^ 1, fa, (e >> 1) * VA / 4, ((e >> 1) + 1) * VA / 4);
+      const int i0 = e & 3, i1 = i0 + 1;
+      if (e < 4) stash_a(buf ^ 1, fa, i0 * VA / 4, i1 * VA / 4);
+      else stash_b(buf ^ 1, fb, i0 * VB / 4, i1 * VB / 4);
       __builtin_amdgcn_sched_barrier(0);
-      load(e * VL, (e + 1) * VL);
+      if (e < 4) fetch(fa, fb, i0 * VA / 4, i1 * VA / 4, 0, 0);
+      else fetch(fa, fb, 0, 0, i0 * VB / 4, i1 * VB / 4);
       __builtin_amdgcn_sched_barrier(0);
     }
   };
 
   // Slabs past K read zeros (their loads are out of range), so the loop needs no conditions: it walks K in
   // pairs of slabs and a surplus slab contributes nothing.
-  if (PAIR) {
-    // The same pipeline over a K range made of parts: the loads run one pair of slabs ahead of the products, a
-    // pair lies inside one part (kseg is a multiple of two slabs), and the descriptors change between the inner
-    // loops, so the inner loop is that of the single-range kernel.  After the last part comes an empty one whose
-    // single pair of loads returns zeros while the last real pair is multiplied.
-    auto fetch_part = [&](int kin, Frag<BM, NT>& fa, Frag<BN, NT>& fb, int i0 = 0, int i1 = 1 << 20) {
-      load_rmajor<BM, NT>(fa, curA, voffA, lda, m0, kin, i0, i1);
-      load_rmajor<BN, NT>(fb, curB, voffB, ldb, n0, kin, i0 - VA, i1 - VA);
-    };
-    const int full = K1 / (2 * BK);                                    // slab pairs of a part of kseg rows
-    const int tail = (g.K - g.nx * K1 + 2 * BK - 1) / (2 * BK);        // of the last part (rows past its end read as zero)
-    fetch_part(0, fa0, fb0);
-    stash_a(0, fa0);
-    stash_b(0, fb0);
-    fetch_part(BK, fa1, fb1);
-    __syncthreads();
-    for (int p = p0; p <= p1 + 1; ++p) {
-      const int pairs = p > p1 ? 1 : p < g.nx ? full : tail;
-      for (int j = p == p0 ? 1 : 0; j < pairs; ++j) {
-        multiply(0, fa1, fb1, [&](int i0, int i1) { fetch_part(j * 2 * BK, fa0, fb0, i0, i1); });
-        __syncthreads();
-        multiply(1, fa0, fb0, [&](int i0, int i1) { fetch_part(j * 2 * BK + BK, fa1, fb1, i0, i1); });
-        __syncthreads();
+  int nk = (g.K + BK - 1) / BK;
+  if (PAIR && ACC && gridDim.z > 1) {                      // this chunk's parts only
+    const int last = p1 < g.nx ? K1 : g.K - g.nx * K1;
+    nk = ((p1 - p0) * K1 + last + BK - 1) / BK;
+  }
+  if constexpr (MI == 4) {
+    bf16x8 a[2][MI], b[2][NJ];                             // fragments of the half slab being multiplied and of the next one
+    // Waves with 4 rows of blocks have registers for the fragments of a whole half slab (32 k) ahead, so the barrier stands
+    // between a slab's halves: behind it the next slab is complete in LDS and this slab's fragments are all in registers.
+    // This multiplies the half whose fragments are in a[ks], b[ks].  Meanwhile the fragments of the next half are read from
+    // LDS (`buf`, its half ks ^ 1), and the vectors of fa (part 0) or fb (part 1) go to LDS buffer `to` and are loaded again.
+    auto half_slab = [&](int ks, int buf, int to, Frag<BM, NT>& fa, Frag<BN, NT>& fb, int part) {
+      const bf16* As = smem + buf * (SLAB_A + SLAB_B);
+      const bf16* Bs = As + SLAB_A;
+      const int nx = ks ^ 1, k32 = nx * 32;
+#pragma unroll
+      for (int e = 0; e < MI; ++e) {
+        if (e == 0) {
+#pragma unroll
+          for (int j = 0; j < NJ; ++j) b[nx][j] = TB == 1 ? frag_kmajor(Bs, wn + j * 16, k32, lane) : frag_rmajor<BN>(Bs, wn + j * 16, k32, lane);
+        } else if (e == 1) {
+#pragma unroll
+          for (int i = 0; i < MI; ++i) a[nx][i] = TA == 0 ? frag_kmajor(As, wm + i * 16, k32, lane) : frag_rmajor<BM>(As, wm + i * 16, k32, lane);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) acc[e][j] = mfma_16x16x32<E>(b[ks][j], a[ks][e], acc[e][j]);
+        const int i0 = e * (part ? VB : VA) / 4, i1 = (e + 1) * (part ? VB : VA) / 4;
+        const int a0 = part ? 0 : i0, a1 = part ? 0 : i1, b0 = part ? i0 : 0, b1 = part ? i1 : 0;
+        stash_a(to, fa, a0, a1);
+        stash_b(to, fb, b0, b1);
+        __builtin_amdgcn_sched_barrier(0);
+        fetch(fa, fb, a0, a1, b0, b1);
+        __builtin_amdgcn_sched_barrier(0);
       }
-      curA = part_a(p + 1);
-      curB = part_b(p + 1);
+    };
+#pragma unroll
+    for (int i = 0; i < STAGES; ++i) {
+      fetch(fa[i], fb[i], 0, VA, 0, VB);
+      advance(i & 1);
+    }
+    stash_a(0, fa[0]);
+    stash_b(0, fb[0]);
+    fetch(fa[0], fb[0], 0, VA, 0, VB);
+    advance(STAGES == 1);
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) b[0][j] = TB == 1 ? frag_kmajor(smem + SLAB_A, wn + j * 16, 0, lane) : frag_rmajor<BN>(smem + SLAB_A, wn + j * 16, 0, lane);
+#pragma unroll
+    for (int i = 0; i < MI; ++i) a[0][i] = TA == 0 ? frag_kmajor(smem, wm + i * 16, 0, lane) : frag_rmajor<BM>(smem, wm + i * 16, 0, lane);
+    stash_a(1, fa[1 % STAGES]);
+    fetch(fa[1 % STAGES], fb[1 % STAGES], 0, VA, 0, 0);
+    for (int kt = 0; kt < nk; kt += 2) {
+      half_slab(0, 0, 1, fa[1 % STAGES], fb[1 % STAGES], 1);
+      advance(STAGES == 2);
+      __syncthreads();
+      half_slab(1, 1, 0, fa[0], fb[0], 0);
+      half_slab(0, 1, 0, fa[0], fb[0], 1);
+      advance(STAGES == 1);
+      __syncthreads();
+      half_slab(1, 0, 1, fa[1 % STAGES], fb[1 % STAGES], 0);
     }
   } else {
-    fetch(0, fa0, fb0);
-    stash_a(0, fa0);
-    stash_b(0, fb0);
-    fetch(1, fa1, fb1);
+    fetch(fa[0], fb[0], 0, VA, 0, VB);
+    advance(false);
+    stash_a(0, fa[0]);
+    stash_b(0, fb[0]);
+    fetch(fa[0], fb[0], 0, VA, 0, VB);
+    advance(true);
     __syncthreads();
     for (int kt = 0; kt < nk; kt += 2) {
-      multiply(0, fa1, fb1, [&](int i0, int i1) { fetch(kt + 2, fa0, fb0, i0, i1); });
+      multiply(0, fa[0], fb[0]);
+      advance(false);
       __syncthreads();
-      multiply(1, fa0, fb0, [&](int i0, int i1) { fetch(kt + 3, fa1, fb1, i0, i1); });
+      multiply(1, fa[0], fb[0]);
+      advance(true);
       __syncthreads();
     }
   }
@@ -570,16 +643,16 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BM * BN <= 128 * 128) ? 2 : 1)
   if (ACC) {
     if (chunk == 0) {
       float* Ct = (float*)g.C + (int64_t)z * g.sC + (int64_t)m0 * g.ldc + n0;
-      epilogue_accum<BM, BN, NT, MI, NJ>(Ct, (int)g.ldc, min(BM, g.M - m0), min(BN, g.N - n0), !PAIR && g.c_overwrite, acc, wave / WN, wn, tid,
+      epilogue_accum<BM, BN, NT, MI, NJ>(Ct, (int)g.ldc, min(BM, g.M - m0), min(BN, g.N - n0), !PAIR && g.c_overwrite, acc, wm, wn, tid,
                                          reinterpret_cast<float*>(smem_raw));
     } else {   // partial tile number (chunk-1) * tile_count + position inside the launch's range
       const int64_t slot = (int64_t)(chunk - 1) * g.tile_count + sub;
-      epilogue_accum<BM, BN, NT, MI, NJ>((float*)g.ws + slot * (BM * BN), BN, BM, BN, true, acc, wave / WN, wn, tid,
+      epilogue_accum<BM, BN, NT, MI, NJ>((float*)g.ws + slot * (BM * BN), BN, BM, BN, true, acc, wm, wn, tid,
                                          reinterpret_cast<float*>(smem_raw));
     }
   }
-  else if (GLU == 1) epilogue_glu<E, BM, BN, NT, MI, NJ>(g, acc, m0, nb0, wave / WN, wn, tid, reinterpret_cast<float*>(smem_raw));
-  else epilogue_store<E, BM, BN, NT, MI, NJ, GLU>(g, z, acc, m0, n0, wave / WN, wn, tid, reinterpret_cast<float*>(smem_raw));
+  else if (GLU == 1) epilogue_glu<E, BM, BN, NT, MI, NJ>(g, acc, m0, nb0, wm, wn, tid, reinterpret_cast<float*>(smem_raw));
+  else epilogue_store<E, BM, BN, NT, MI, NJ, GLU>(g, z, acc, m0, n0, wm, wn, tid, reinterpret_cast<float*>(smem_raw));
 }
 
 template <typename E, int BM, int BN, int NW, int TA, int TB, int SEG, int ACC, int GLU = 0>
@@ -605,15 +678,24 @@ template <typename E, int BM, int BN, int NW, int TA, int TB, int SEG> hipError_
   return g.c_f32_accum ? launch2<E, BM, BN, NW, TA, TB, SEG, 1>(st, g) : launch2<E, BM, BN, NW, TA, TB, SEG, 0>(st, g);
 }
 
+// The square tiles take every form, the oblong ones those of gemm_mfma_oblong.
 template <typename E, int BM, int BN, int NW> hipError_t gemm_mfma_tile(hipStream_t st, const Gemm& g) {
   if (g.glu == 1) return launch2<E, BM, BN, NW, 0, 0, 0, 0, 1>(st, g);
   if (g.glu == 2) return launch2<E, BM, BN, NW, 0, 1, 0, 0, 2>(st, g);
-  if (g.nx) return launch<E, BM, BN, NW, 1, 0, 1>(st, g);
-  if (g.kseg) return g.transA ? launch<E, BM, BN, NW, 1, 1, 1>(st, g) : launch<E, BM, BN, NW, 0, 1, 1>(st, g);
-  if (!g.transA && !g.transB) return launch<E, BM, BN, NW, 0, 0, 0>(st, g);
-  if (!g.transA && g.transB) return launch<E, BM, BN, NW, 0, 1, 0>(st, g);
-  if (g.transA && !g.transB) return launch<E, BM, BN, NW, 1, 0, 0>(st, g);
-  return launch<E, BM, BN, NW, 1, 1, 0>(st, g);
+  if constexpr (BM == BN) {
+    if (g.nx) return launch<E, BM, BN, NW, 1, 0, 1>(st, g);
+    if (g.kseg) return g.transA ? launch<E, BM, BN, NW, 1, 1, 1>(st, g) : launch<E, BM, BN, NW, 0, 1, 1>(st, g);
+    if (!g.transA && !g.transB) return launch<E, BM, BN, NW, 0, 0, 0>(st, g);
+    if (!g.transA && g.transB) return launch<E, BM, BN, NW, 0, 1, 0>(st, g);
+    if (g.transA && !g.transB) return launch<E, BM, BN, NW, 1, 0, 0>(st, g);
+    return launch<E, BM, BN, NW, 1, 1, 0>(st, g);
+  } else {
+    if (!gemm_mfma_oblong(g)) return hipErrorInvalidValue;
+    if (g.transA) return launch2<E, BM, BN, NW, 1, 0, 0, 1>(st, g);
+    if (!g.transB) return launch2<E, BM, BN, NW, 0, 0, 0, 0>(st, g);
+    if (g.kseg) return launch2<E, BM, BN, NW, 0, 1, 1, 0>(st, g);
+    return launch<E, BM, BN, NW, 0, 1, 0>(st, g);
+  }
 }
 
 }  // namespace gemm_impl

@@ -84,6 +84,10 @@ hipError_t gemm_f32(hipStream_t st, const Gemm& g);
 bool gemm_mfma_takes(DType dt, const Gemm& g);
 bool gemm_mfma_supported(DType dt, const Gemm& g);
 hipError_t gemm_mfma(hipStream_t st, DType dt, const Gemm& g);
+// Forms that the oblong tiles (256x192, 256x128) take: y = x W, dx = dy W^T, dW += x^T dy (of one part) and the gated unit's two.
+inline bool gemm_mfma_oblong(const Gemm& g) {
+  return !g.nx && (g.transA ? !g.transB && g.c_f32_accum && !g.kseg : g.transB ? !(g.kseg && g.c_f32_accum) : !g.c_f32_accum);
+}
 // True when gemm_mfma runs this product as two halves of K.
 bool gemm_mfma_halves(DType dt, const Gemm& g);
 // Scratch bytes (Gemm::ws) with which gemm_mfma would cut the K range of this product's last round of tiles; 0 when
@@ -93,8 +97,10 @@ int64_t gemm_mfma_ws_bytes(const Gemm& g);
 // and which of the two is the faster way for a product that gemm_mfma_takes, 0: neither.
 int gemm_small_tile(const Gemm& g);
 hipError_t gemm_small(hipStream_t st, DType dt, const Gemm& g, int tile);
-// Workgroup tile the MFMA kernel would use: 1 = 256x256 (8 waves), 2 = 128x128 (4 waves); force_tile(0) = automatic.
+// Workgroup tile the MFMA kernel would use: 1 = 256x256, 3 = 256x192, 4 = 256x128 (8 waves), 2 = 128x128 (4 waves), and the estimated
+// time in us; force_tile(0) = automatic.
 int gemm_mfma_pick_tile(const Gemm& g);
+double gemm_mfma_us(const Gemm& g);
 void gemm_mfma_force_tile(int id);
 
 // kind 0 LayerNorm (mean and rstd saved), 1 RMSNorm (rstd saved).  b and mean may be NULL for RMSNorm.  copy (or NULL) receives
