@@ -79,16 +79,16 @@ bool gemm_mfma_takes(DType dt, const Gemm& g) {
 // and run at the highest rate; 256x192 and 256x128 (8 waves, one per CU) and 128x128 (4 waves, two per CU) waste less of
 // the last round of workgroups and give small products enough workgroups to fill the chip.  The tile with the smallest estimated
 // time is taken.  The estimate: per round of workgroups a fixed time (first loads, store) and a time per 64-wide slab, which
-// grows by 0.3 with the share of the chip at work (the clock drops); and the traffic of the result.  Constants fitted to 520
-// times of 130 products (M 256 .. 6000, N 768 .. 16000, K 256 .. 14000, the three layouts): of these the pick is on the geometric mean
-// within 0.3 % of the fastest tile, 8 % at worst.  us, bf16, 256x256 : 128x128 : 256x192 : 256x128: 2048 x 4096, K = 12288
+// grows by 0.3 with the share of the chip at work (the clock drops); and the traffic of the result.  Constants fitted to 830
+// times of 207 products (M 256 .. 8000, N 768 .. 16000, K 64 .. 14000, the three layouts): of these the pick is on the geometric mean
+// within 0.3 % of the fastest tile, 12 % at worst.  us, bf16, 256x256 : 128x128 : 256x192 : 256x128: 2048 x 4096, K = 12288
 // 244 : 207 : 221 : 185; 2048 x 5120, K = 12288 (dx) 248 : 310 : 219 : 349; 2048 x 6144, K = 2048 50 : 54 : 48 : 61;
 // 2048 x 2048, K = 12288 225 : 119 : 201 : 155; 4096 x 11008, K = 4096 (dx) 297 : 357 : 318 : 348.
 namespace {
 struct TileTimes { int width, cus; double slab, round, store; };   // us; cus: workgroups that run side by side
-constexpr TileTimes TILE_TIMES[4] = {{256, 256, 1.10, 5.9, 1.0}, {128, 512, 0.774, 4.0, 0.55}, {192, 256, 0.895, 5.9, 0.75}, {128, 256, 0.68, 4.0, 1.0}};
+constexpr TileTimes TILE_TIMES[4] = {{256, 256, 1.10, 5.9, 1.0}, {128, 512, 0.774, 4.0, 0.52}, {192, 256, 0.895, 5.9, 0.8}, {128, 256, 0.68, 4.0, 1.0}};
 constexpr double HALF_SLAB = 0.492, HALF_ROUND = 2.4;              // 128x128, a round of at most 256 tiles: one per CU
-constexpr double LAUNCH = 2.7, CROWDED = 0.294, STORE_RATE = 9.3e6; // us, -, bytes per us
+constexpr double LAUNCH = 2.7, CROWDED = 0.294, STORE_RATE = 8.0e6; // us, -, bytes per us
 
 // Estimated time of a grid of `small` 128x128 tiles in units of one round of 256x256 tiles: full rounds hold
 // 512 small tiles (two per CU, each at 0.8 of the big tile's rate); a remainder of at most 256 tiles runs
@@ -243,52 +243,65 @@ __global__ __launch_bounds__(256) void add_partials_kernel(float* C, int64_t ldc
 
 }  // namespace
 
-// ---- two halves of K side by side ----------------------------------------------------------------------------------
-// An input gradient over few tokens has few tiles and a long K (512 x 4096 with K = 22016: 128 tiles of 128x128, half the
-// CUs idle).  With scratch for two fp32 results its halves run as a batch of two, and a second kernel adds and rounds them.
-// Taken when the tiles do not fill 128 CUs' worth twice over and a half is still long against the added pass (1.2 us per
-// MB of result at 4 TB/s and its launch, against 7.8 ns per k).
+// ---- parts of K side by side ---------------------------------------------------------------------------------------
+// An input gradient over few tokens has few tiles and a long K (512 x 4096 with K = 22016: 128 tiles of 128x128, half the CUs idle,
+// and each of the others waits for cold lines of the weights).  With scratch for as many fp32 results two or four equal parts of
+// its K, or its segments (gate and up; Q, K and V), run as a batch, and a second kernel adds and rounds them: taken when the
+// estimate of both kernels (the second one at 4.5 TB/s) is the shorter time.  us: 512 x 4096, K = 22016 in 2 parts 176 -> 130 (128x128
+// tiles); K = 12288 in 3 segments 129 -> 82.
 namespace {
-bool plan_halves(DType dt, const Gemm& g, Gemm& h) {
+bool plan_parts(DType dt, const Gemm& g, Gemm& best) {
   if (g_force_tile || !g.ws || g.transA || !g.transB || g.c_f32_accum || g.batch != 1 || g.bias || g.resid || g.rope || g.glu || g.nx) return false;
   const int64_t tiles = cdiv(g.M, 128) * cdiv(g.N, 128);
-  if (tiles > 128 || g.N % 8 || ((uintptr_t)g.ws & 15) || g.ws_bytes < 8ll * g.M * g.N) return false;
-  h = g;
-  h.ws = nullptr; h.ws_bytes = 0;
-  if (g.kseg) {
-    if (g.K != 2 * g.kseg) return false;
-    h.kseg = 0; h.segB = 0; h.sB = g.segB;
-  } else {
-    if (g.K % 16) return false;
-    h.sB = g.K / 2;
+  if (tiles > 128 || g.N % 8 || ((uintptr_t)g.ws & 15)) return false;
+  double us = 0.95 * gemm_mfma_us(g);
+  best.batch = 1;
+  for (int n = 2; n <= 4; ++n) {
+    if (g.kseg ? (int64_t)n * g.kseg != g.K : (n == 3 || g.K % (8 * n) || n * tiles > 256)) continue;
+    if (g.ws_bytes < 4ll * n * g.M * g.N) continue;
+    Gemm h = g;
+    h.ws = nullptr; h.ws_bytes = 0; h.kseg = 0; h.segB = 0;
+    h.K = g.K / n; h.sA = h.K; h.sB = g.kseg ? g.segB : h.K;
+    h.C = g.ws; h.ldc = g.N; h.sC = (int64_t)g.M * g.N;
+    h.batch = n; h.c_f32_accum = 1; h.c_overwrite = 1;
+    const double t = gemm_mfma_us(h) + LAUNCH + (double)g.M * g.N * (4 * n + 2) / 4.5e6;
+    if (t < us && gemm_mfma_takes(dt, h)) { us = t; best = h; }
   }
-  h.K = g.K / 2; h.sA = h.K;
-  h.C = g.ws; h.ldc = g.N; h.sC = (int64_t)g.M * g.N;
-  h.batch = 2; h.c_f32_accum = 1; h.c_overwrite = 1;
-  const double gain = 7.8e-3 * h.K, cost = 6.0 + (double)g.M * g.N * 10.0 / 4.0e6;   // us
-  return gain > 1.5 * cost && gemm_mfma_takes(dt, h);
+  return best.batch > 1;
 }
 
-// C = p[0] + p[1], rounded: 8 columns per thread.
-template <typename E>
-__global__ __launch_bounds__(256) void add_halves_kernel(int64_t nvec, int vec_per_row, const float* __restrict__ p, int64_t half, E* __restrict__ C,
-                                                         int64_t ldc) {
+// C = p[0] + p[1] + .. in this order, rounded: 8 columns per thread.
+template <typename E, int n>
+__global__ __launch_bounds__(256) void add_parts_kernel(int64_t nvec, int vec_per_row, const float* __restrict__ p, int64_t part, E* __restrict__ C,
+                                                        int64_t ldc) {
   typedef typename Vec<E>::type E8;
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (i >= nvec) return;
-  const f32x4* a = reinterpret_cast<const f32x4*>(p + i * 8);
-  const f32x4* b = reinterpret_cast<const f32x4*>(p + half + i * 8);
-  const f32x4 lo = a[0] + b[0], hi = a[1] + b[1];
+  f32x4 v[n][2];
+#pragma unroll
+  for (int z = 0; z < n; ++z) {
+    const f32x4* a = reinterpret_cast<const f32x4*>(p + z * part + i * 8);
+    v[z][0] = a[0];
+    v[z][1] = a[1];
+  }
+#pragma unroll
+  for (int z = 1; z < n; ++z) { v[0][0] += v[z][0]; v[0][1] += v[z][1]; }
   E8 o;
 #pragma unroll
-  for (int e = 0; e < 8; ++e) o[e] = (E)(e < 4 ? lo[e & 3] : hi[e & 3]);
+  for (int e = 0; e < 8; ++e) o[e] = (E)v[0][e / 4][e & 3];
   *reinterpret_cast<E8*>(C + i / vec_per_row * ldc + (i % vec_per_row) * 8) = o;
+}
+template <typename E> hipError_t add_parts(hipStream_t st, const Gemm& g, int n) {
+  const int64_t nvec = (int64_t)g.M * g.N / 8;
+  auto kern = n == 2 ? add_parts_kernel<E, 2> : n == 3 ? add_parts_kernel<E, 3> : add_parts_kernel<E, 4>;
+  hipLaunchKernelGGL(kern, dim3((unsigned)cdiv(nvec, 256)), dim3(256), 0, st, nvec, g.N / 8, (const float*)g.ws, (int64_t)g.M * g.N, (E*)g.C, g.ldc);
+  return hipGetLastError();
 }
 }  // namespace
 
-bool gemm_mfma_halves(DType dt, const Gemm& g) {
+int gemm_mfma_parts(DType dt, const Gemm& g) {
   Gemm h;
-  return plan_halves(dt, g, h);
+  return plan_parts(dt, g, h) ? h.batch : 1;
 }
 
 int64_t gemm_mfma_ws_bytes(const Gemm& g) {
@@ -311,15 +324,10 @@ hipError_t gemm_mfma(hipStream_t st, DType dt, const Gemm& g) {
       return hipGetLastError();
     }
   }
-  Gemm halves;
-  if (plan_halves(dt, g, halves)) {
-    const hipError_t e = run_tile(st, dt, halves, gemm_mfma_pick_tile(halves));
-    if (e != hipSuccess) return e;
-    const int64_t nvec = (int64_t)g.M * g.N / 8;
-    const dim3 grid((unsigned)cdiv(nvec, 256));
-    if (dt == F16) hipLaunchKernelGGL(add_halves_kernel<f16>, grid, dim3(256), 0, st, nvec, g.N / 8, (const float*)g.ws, halves.sC, (f16*)g.C, g.ldc);
-    else hipLaunchKernelGGL(add_halves_kernel<bf16>, grid, dim3(256), 0, st, nvec, g.N / 8, (const float*)g.ws, halves.sC, (bf16*)g.C, g.ldc);
-    return hipGetLastError();
+  Gemm parts;
+  if (plan_parts(dt, g, parts)) {
+    const hipError_t e = run_tile(st, dt, parts, gemm_mfma_pick_tile(parts));
+    return e != hipSuccess ? e : dt == F16 ? add_parts<f16>(st, g, parts.batch) : add_parts<bf16>(st, g, parts.batch);
   }
   if (!g_force_tile) {
     Gemm head, tail, h, t;
@@ -328,7 +336,7 @@ hipError_t gemm_mfma(hipStream_t st, DType dt, const Gemm& g) {
     for (int w : {1, 3}) {
       if (w == 3 && !gemm_mfma_oblong(g)) continue;
       if (!split_tail(dt, g, w, h, t)) continue;
-      const double cut = tile_us(h, w) + gemm_mfma_us(t);
+      const double cut = (tile_us(h, w) + gemm_mfma_us(t) + 1.0) * 1.03;   // cuts come out 3 % above their estimate
       if (cut < us) { us = cut; wide = w; head = h; tail = t; }
     }
     if (wide) {

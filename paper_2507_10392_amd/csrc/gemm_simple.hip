@@ -119,8 +119,11 @@ Gemm part_of(const Gemm& g, int p) {
 }
 
 GemmRoute route_one(DType dt, const Gemm& g, int force) {
-  if (gemm_select(dt, g, force) == GEMM_MFMA)
-    return force == GEMM_AUTO && gemm_small_tile(g) ? ROUTE_SMALL : gemm_mfma_halves(dt, g) ? ROUTE_HALVES : ROUTE_STAGED;
+  if (gemm_select(dt, g, force) == GEMM_MFMA) {
+    if (force == GEMM_AUTO && gemm_small_tile(g)) return ROUTE_SMALL;
+    const int parts = gemm_mfma_parts(dt, g);
+    return parts == 1 ? ROUTE_STAGED : parts == 2 ? ROUTE_HALVES : ROUTE_PARTS;
+  }
   return dt == F32 && force != GEMM_SIMPLE && gemm_f32_supported(g) ? ROUTE_F32 : ROUTE_SIMPLE;
 }
 
@@ -129,7 +132,7 @@ GemmRoute route_one(DType dt, const Gemm& g, int force) {
 hipError_t gemm_one(hipStream_t st, DType dt, const Gemm& g, int force) {
   const GemmRoute route = route_one(dt, g, force);   // the matrix-core kernels have the rotation in their stores
   if (route == ROUTE_SMALL) return gemm_small(st, dt, g, gemm_small_tile(g));
-  if (route == ROUTE_STAGED || route == ROUTE_HALVES) return gemm_mfma(st, dt, g);
+  if (route >= ROUTE_HALVES) return gemm_mfma(st, dt, g);
   if (route == ROUTE_F32) return gemm_f32(st, g);
   if (g.glu) {   // gated unit: the plain product(s), then the activation kernel over the dense [gate | up] rows
     Gemm p = g;

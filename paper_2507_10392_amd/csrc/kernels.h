@@ -17,8 +17,8 @@ namespace zs {
 //             their own, part 0 from A, B and part p from Ax[p-1], Bx[p-1] (same leading dimensions and batch
 //             strides); parts 0..nx-1 have kseg rows each, the last one the remaining K - nx*kseg > 0 rows:
 //             C += sum_p A_p^T B_p in one K loop (weight gradients of several microbatches).
-//   ws != NULL (nx = 0, an input gradient): ws_bytes of scratch with which a product of few tiles and long K may run its two
-//             halves of K side by side, as fp32 results in ws that a second kernel adds and rounds.
+//   ws != NULL (nx = 0, an input gradient): ws_bytes of scratch with which a product of few tiles and long K may run two to four
+//             parts of K side by side, as fp32 results in ws that a second kernel adds and rounds.
 //   ws != NULL (nx > 0): ws_bytes of scratch that the MFMA path may use when the 256x256 tiles of the product do
 //             not fill whole rounds of 256 workgroups: the tiles beyond the whole rounds (the last ones of the kernel's
 //             tile order, over all batches) then have their K
@@ -70,10 +70,10 @@ enum GemmImpl { GEMM_AUTO = 0, GEMM_SIMPLE = 1, GEMM_MFMA = 2 };
 // Returns which implementation a call with these arguments runs (GEMM_SIMPLE or GEMM_MFMA).
 int gemm_select(DType dt, const Gemm& g, int force);
 hipError_t gemm(hipStream_t st, DType dt, const Gemm& g, int force);
-// The kernels behind gemm(): plain, fp32 matrix cores, 16-bit matrix cores on small tiles, on staged tiles as two halves of K
-// that a second kernel adds (see ws), and on staged tiles.  gemm_route is the
+// The kernels behind gemm(): plain, fp32 matrix cores, 16-bit matrix cores on small tiles, on staged tiles as two halves or as more
+// parts of K that a second kernel adds (see ws), and on staged tiles.  gemm_route is the
 // choice that gemm(GEMM_AUTO) makes for a call (of its first launch, where it takes several), for the names of timing classes.
-enum GemmRoute { ROUTE_SIMPLE, ROUTE_F32, ROUTE_SMALL, ROUTE_HALVES, ROUTE_STAGED };
+enum GemmRoute { ROUTE_SIMPLE, ROUTE_F32, ROUTE_SMALL, ROUTE_HALVES, ROUTE_PARTS, ROUTE_STAGED };
 GemmRoute gemm_route(DType dt, const Gemm& g);
 hipError_t gemm_simple(hipStream_t st, DType dt, const Gemm& g);
 // fp32 products on the fp32 matrix cores (gemm_f32.hip); no multi-part K range, no gated unit.
@@ -88,8 +88,8 @@ hipError_t gemm_mfma(hipStream_t st, DType dt, const Gemm& g);
 inline bool gemm_mfma_oblong(const Gemm& g) {
   return !g.nx && (g.transA ? !g.transB && g.c_f32_accum && !g.kseg : g.transB ? !(g.kseg && g.c_f32_accum) : !g.c_f32_accum);
 }
-// True when gemm_mfma runs this product as two halves of K.
-bool gemm_mfma_halves(DType dt, const Gemm& g);
+// Number of parts of K that gemm_mfma runs this product in, 1: in one.
+int gemm_mfma_parts(DType dt, const Gemm& g);
 // Scratch bytes (Gemm::ws) with which gemm_mfma would cut the K range of this product's last round of tiles; 0 when
 // it would not (the answer depends on the shape only, not on the pointers).
 int64_t gemm_mfma_ws_bytes(const Gemm& g);

@@ -418,10 +418,11 @@ bool offload_load(stage_t* s, int k, int mb) {
 DType dt_of(const stage_t* s) { return s->sh.dtype == STAGE_DTYPE_F16 ? F16 : s->sh.bf ? BF16 : F32; }
 
 bool do_gemm(stage_t* s, const Gemm& g) {
-  static const char* names[5][4] = {{"gemm_simple_nn", "gemm_simple_nt", "gemm_simple_tn", "gemm_simple_tt"},
+  static const char* names[6][4] = {{"gemm_simple_nn", "gemm_simple_nt", "gemm_simple_tn", "gemm_simple_tt"},
                                     {"gemm_f32_nn", "gemm_f32_nt", "gemm_f32_tn", "gemm_f32_tt"},
                                     {"gemm_small_nn", "gemm_small_nt", "gemm_small_tn", "gemm_small_tt"},
                                     {"gemm_halves_nn", "gemm_halves_nt", "gemm_halves_tn", "gemm_halves_tt"},
+                                    {"gemm_parts_nn", "gemm_parts_nt", "gemm_parts_tn", "gemm_parts_tt"},
                                     {"gemm_mfma_nn", "gemm_mfma_nt", "gemm_mfma_tn", "gemm_mfma_tt"}};
   // the products that apply the gated unit in their store are kernels of their own and are timed as such
   static const char* glu_names[2][2] = {{"gemm_small_nn_glu", "gemm_small_nt_glu"}, {"gemm_mfma_nn_glu", "gemm_mfma_nt_glu"}};
@@ -610,6 +611,8 @@ bool layer_backward(stage_t* s, int l, const char* x_in, LayerActs& A, const cha
   if (gpt) { g.B = W("Wqkv"); g.ldb = 3 * H; }
   else { g.B = W("Wq"); g.ldb = H; g.kseg = H; g.segB = (int64_t)H * H; }
   g.ws = pl.gF1; g.ws_bytes = (int64_t)T * F * h.E;
+  // three results, for Q, K and V, need more: dff and a, next to each other, which this microbatch's products have used unless they wait
+  if (!gpt && wg.mode != 1) { g.ws = A.ff; g.ws_bytes = A.a + (int64_t)T * F * h.E - A.ff; }
   if (!do_gemm(s, g)) return false;
   g = Gemm();
   g.M = H; g.K = T; g.A = A.n1; g.lda = H; g.transA = 1; g.B = gqkv; g.ldb = 3 * H; g.c_f32_accum = 1;
@@ -655,6 +658,7 @@ bool head_backward(stage_t* s, const char* y, HeadActs& A, const int32_t* target
   g = Gemm();
   g.M = h.T; g.N = h.H; g.K = h.V; g.A = A.logits; g.lda = h.V; g.B = s->P(s->seg_off("head.Wh")); g.ldb = h.V;
   g.transB = 1; g.C = pl.gN; g.ldc = h.H;
+  g.ws = pl.gO; g.ws_bytes = pl.gF1 + (int64_t)h.T * h.F * h.E - pl.gO;   // the layers' backward writes these later
   if (!do_gemm(s, g)) return false;
   return run(s, "norm_bwd", 0, 3.0 * h.T * h.H * h.E, [&] {
     return norm_bwd_partials(s->st, dt, 1, h.T, h.H, pl.gN, y, s->P(s->seg_off("final_norm.g")), A.rstd, nullptr, nullptr,
