@@ -157,28 +157,34 @@ __device__ __forceinline__ void tile_origin(int pid, int tiles_m, int tiles_n, i
   n0 = tn * BN;
 }
 
-// Both epilogues pass the tile through LDS (free after the K loop) as fp32, in two halves of BM/2 rows.
+// All epilogues pass the tile through LDS (free after the K loop) as fp32, in two halves of BM/2 rows: every wave's first MI/2 rows
+// of blocks, then its last.  So after the first half every wave has half of its accumulator registers free, for the
+// residual, angles, gate and up values of the second: those loads go out before the first half's stores, and the wait for them
+// stands behind no store.
 // The MFMAs were issued with the operands swapped, mfma(B fragment, A fragment), which yields the
 // transposed block: acc[i][j][r] is C[row, col] of 16x16 block (i, j) with row = lane%16 and col = 4*(lane/16) + r,
 // so a lane owns 4 consecutive columns per block and writes them as one float4.
 template <int BN> struct Staging { static constexpr int LDW = BN + 4; };   // padded row (floats)
 
-// A wave's rows of the tile (16 MI of them, from wm on) lie in one half and are written when that half is staged.
-template <int BM, int BN, int MI, int NJ>
+// RW: rows of a wave.  Row of the tile that staged row r of a half holds.
+template <int RW> __device__ __forceinline__ int staged_row(int r, int half) { return r / (RW / 2) * RW + half * (RW / 2) + r % (RW / 2); }
+
+template <int BN, int MI, int NJ>
 __device__ __forceinline__ void stage_quads(float* stage, f32x4 (&acc)[MI][NJ], int half, int wm, int wn, int lane) {
   constexpr int LDW = Staging<BN>::LDW;
-  if (wm / (BM / 2) != half) return;
 #pragma unroll
-  for (int i = 0; i < MI; ++i)
+  for (int i = 0; i < MI / 2; ++i)
 #pragma unroll
     for (int j = 0; j < NJ; ++j)
-      *reinterpret_cast<f32x4*>(stage + (wm % (BM / 2) + i * 16 + (lane & 15)) * LDW + wn + j * 16 + 4 * (lane >> 4)) = acc[i][j];
+      *reinterpret_cast<f32x4*>(stage + (wm / 2 + i * 16 + (lane & 15)) * LDW + wn + j * 16 + 4 * (lane >> 4)) = acc[half * (MI / 2) + i][j];
 }
 
 // Epilogue for C (fp32) += product (no bias, no residual).  Ct points at the tile's first element, of which rows x cols
 // exist.  After staging, ALL threads walk the half tile 4 columns at a time: the old values of C are loaded 16 bytes per
-// lane (consecutive lanes, consecutive pieces of a row), all loads of a half in flight across the barrier, then sum and
-// store.  Loads and stores go through a buffer descriptor over the tile: rows past the last one fall beyond num_records
+// lane (consecutive lanes, consecutive pieces of a row), all loads of a half in flight across the barriers, then sum and
+// store.  The first half's loads go out before the barrier that ends the K loop (4096 x 4096, K = 512 on 128x128 tiles 38 -> 34 us);
+// the second half's wait until the first half's stores are out: with many rounds of workgroups at HBM rate reads, then
+// writes, then reads again are faster than all reads first (4096 x 32000, K = 2048 552 : 572 us).  Loads and stores go through a buffer descriptor over the tile: rows past the last one fall beyond num_records
 // and columns past the last one are sent there, so the ragged edge needs no branches.  A tile belongs to one workgroup and
 // launches are ordered by the stream, so the sum over microbatches is formed in a fixed order.  overwrite: the tile is
 // stored as it is (a partial sum that another kernel adds to C).
@@ -192,28 +198,31 @@ __device__ __forceinline__ void epilogue_accum(float* Ct, int ldc, int rows, int
   constexpr int NV = (BM / 2) * VPR / NS;                  // float4 per thread and half
   static_assert(NS <= NT && (BM / 2) * VPR % NS == 0, "a half is whole passes");
   const __amdgpu_buffer_rsrc_t rsC = make_rsrc(Ct, (uint32_t)((int64_t)(rows - 1) * ldc + cols) * 4u);
-  const int lr0 = tid / VPR, cv = tid % VPR;               // vector v = tid + NT*it: row lr0 + (NT/VPR)*it, same columns
+  const int lr0 = tid / VPR, cv = tid % VPR;               // vector v = tid + NS*it: staged row lr0 + (NS/VPR)*it, same columns
   const bool col_ok = cv * 4 < cols && tid < NS;           // cols is a multiple of 4
+  u32x4 old[2][NV];
+  auto offset = [&](int half, int it) {
+    return col_ok ? (int)((uint32_t)(staged_row<16 * MI>(lr0 + (NS / VPR) * it, half) * ldc + cv * 4) * 4u) : (int)0x80000000u;
+  };
+  auto load = [&](int half) {
+#pragma unroll
+    for (int it = 0; it < NV; ++it)
+      old[half][it] = overwrite ? u32x4{0u, 0u, 0u, 0u} : __builtin_amdgcn_raw_buffer_load_b128(rsC, offset(half, it), 0, 0);
+  };
+  load(0);
 #pragma unroll
   for (int half = 0; half < 2; ++half) {
     __syncthreads();
-    stage_quads<BM, BN, MI, NJ>(stage, acc, half, wm, wn, tid & 63);
-    u32x4 old[NV];
-    uint32_t off[NV];
-#pragma unroll
-    for (int it = 0; it < NV; ++it) {
-      const int row = half * (BM / 2) + lr0 + (NS / VPR) * it;
-      off[it] = col_ok ? (uint32_t)(row * ldc + cv * 4) * 4u : 0x80000000u;
-      old[it] = overwrite ? u32x4{0u, 0u, 0u, 0u} : __builtin_amdgcn_raw_buffer_load_b128(rsC, (int)off[it], 0, 0);
-    }
+    stage_quads<BN, MI, NJ>(stage, acc, half, wm, wn, tid & 63);
+    if (half == 1) load(1);
     __syncthreads();
 #pragma unroll
     for (int it = 0; it < NV; ++it) {
       const f32x4 x = *reinterpret_cast<const f32x4*>(stage + (lr0 + (NS / VPR) * it) * LDW + cv * 4);
       union { u32x4 u; f32x4 f; } o;
-      o.u = old[it];
+      o.u = old[half][it];
       o.f += x;
-      __builtin_amdgcn_raw_buffer_store_b128(o.u, rsC, (int)off[it], 0, 0);
+      __builtin_amdgcn_raw_buffer_store_b128(o.u, rsC, offset(half, it), 0, 0);
     }
   }
 }
@@ -256,15 +265,12 @@ __device__ __forceinline__ void epilogue_store(const Gemm& g, int z, f32x4 (&acc
   const bool pre_resid = GLU == 0 && R, pre_rope = GLU == 0 && rope && !R;
   E8 bb = {};
   if (GLU == 0 && bias && full) bb = *reinterpret_cast<const E8*>(bias + col);
-#pragma unroll
-  for (int half = 0; half < 2; ++half) {
-    __syncthreads();                                       // K-loop reads / previous half's reads are done
-    const int row0 = m0 + half * (BM / 2) + lr0;
-    u32x4 pre0[NV], pre1[NV];                              // one source address per slot, so each slot has one load
-    const bool want0 = full && (GLU == 2 || pre_resid || pre_rope), want1 = full && (GLU == 2 || pre_rope);
+  u32x4 pre0[2][NV], pre1[2][NV];                          // one source address per slot, so each slot has one load
+  const bool want0 = full && (GLU == 2 || pre_resid || pre_rope), want1 = full && (GLU == 2 || pre_rope);
+  auto load = [&](int half) {
 #pragma unroll
     for (int it = 0; it < NV; ++it) {
-      const int row = row0 + RSTEP * it;
+      const int row = m0 + staged_row<16 * MI>(lr0 + RSTEP * it, half);
       const E* src0 = nullptr;
       const E* src1 = nullptr;
       if (GLU == 2) {
@@ -277,22 +283,28 @@ __device__ __forceinline__ void epilogue_store(const Gemm& g, int z, f32x4 (&acc
         src0 = reinterpret_cast<const E*>(cs);
         src1 = reinterpret_cast<const E*>(cs + 2);
       }
-      pre0[it] = pre1[it] = u32x4{0, 0, 0, 0};
-      if (want0 && row < g.M) pre0[it] = *reinterpret_cast<const u32x4*>(src0);
-      if (want1 && row < g.M) pre1[it] = *reinterpret_cast<const u32x4*>(src1);
+      pre0[half][it] = pre1[half][it] = u32x4{0, 0, 0, 0};
+      if (want0 && row < g.M) pre0[half][it] = *reinterpret_cast<const u32x4*>(src0);
+      if (want1 && row < g.M) pre1[half][it] = *reinterpret_cast<const u32x4*>(src1);
     }
-    stage_quads<BM, BN, MI, NJ>(stage, acc, half, wm, wn, lane);
+  };
+  load(0);
+#pragma unroll
+  for (int half = 0; half < 2; ++half) {
+    __syncthreads();                                       // K-loop reads / previous half's reads are done
+    stage_quads<BN, MI, NJ>(stage, acc, half, wm, wn, lane);
+    if (half == 0) load(1);
     __syncthreads();
 #pragma unroll
     for (int it = 0; it < NV; ++it) {
-      const int lr = lr0 + RSTEP * it, row = row0 + RSTEP * it;
+      const int lr = lr0 + RSTEP * it, row = m0 + staged_row<16 * MI>(lr, half);
       if (row >= g.M || col >= g.N) continue;
       const f32x4 x0 = *reinterpret_cast<const f32x4*>(stage + lr * LDW + cv);
       const f32x4 x1 = *reinterpret_cast<const f32x4*>(stage + lr * LDW + cv + 4);
       float x[8] = {x0[0], x0[1], x0[2], x0[3], x1[0], x1[1], x1[2], x1[3]};
       if (GLU == 2) {   // x is da: (gate, up) of these 8 columns become (dgate, dup) in place (N is a multiple of 8)
         E* pg = (E*)g.gu + (int64_t)row * g.gu_ld + col;
-        const E8 gg = __builtin_bit_cast(E8, pre0[it]), uu = __builtin_bit_cast(E8, pre1[it]);
+        const E8 gg = __builtin_bit_cast(E8, pre0[half][it]), uu = __builtin_bit_cast(E8, pre1[half][it]);
         E8 og, ou;
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
@@ -311,15 +323,15 @@ __device__ __forceinline__ void epilogue_store(const Gemm& g, int z, f32x4 (&acc
           for (int e = 0; e < 8; ++e) x[e] += (float)bb[e];
         }
         if (R) {
-          const E8 rr = __builtin_bit_cast(E8, pre0[it]);
+          const E8 rr = __builtin_bit_cast(E8, pre0[half][it]);
 #pragma unroll
           for (int e = 0; e < 8; ++e) x[e] += (float)rr[e];
         }
         if (rope) {   // rotate the 4 adjacent pairs by the angles of this row's position
           f32x4 t0, t1;
           if (pre_rope) {
-            t0 = __builtin_bit_cast(f32x4, pre0[it]);
-            t1 = __builtin_bit_cast(f32x4, pre1[it]);
+            t0 = __builtin_bit_cast(f32x4, pre0[half][it]);
+            t1 = __builtin_bit_cast(f32x4, pre1[half][it]);
           } else {
             const f32x4* cs = reinterpret_cast<const f32x4*>(g.rope + (int64_t)(row % g.rope_S) * (g.rope_d / 2) + (col % g.rope_d) / 2);
             t0 = cs[0];
@@ -361,14 +373,14 @@ __device__ __forceinline__ void epilogue_glu(const Gemm& g, f32x4 (&acc)[MI][NJ]
 #pragma unroll
   for (int half = 0; half < 2; ++half) {
     __syncthreads();
-    stage_quads<BM, BN, MI, NJ>(stage, acc, half, wm, wn, lane);
+    stage_quads<BN, MI, NJ>(stage, acc, half, wm, wn, lane);
     __syncthreads();
     constexpr int VPR = BN / 16;                           // 8-column pieces of each matrix per row
 #pragma unroll
     for (int it = 0; it < (BM / 2) * VPR / NT; ++it) {
       const int v = tid + NT * it;
       const int lr = v / VPR, cv = (v % VPR) * 8, col = c0 + cv;
-      const int row = m0 + half * (BM / 2) + lr;
+      const int row = m0 + staged_row<16 * MI>(lr, half);
       if (row >= g.M || col >= g.N) continue;              // N is a multiple of 8
       const float* sp = stage + lr * LDW + cv;
       const f32x4 g0 = *reinterpret_cast<const f32x4*>(sp), g1 = *reinterpret_cast<const f32x4*>(sp + 4);
