@@ -237,14 +237,13 @@ static hipError_t norm_bwd(hipStream_t st, DType dt, int kind, int T, int H, con
 // row group q walks rows r0+q, r0+q+4, ... of the block, four rows in flight per thread, and the four
 // groups' sums are added in the order 0..3 through LDS, so the result does not depend on timing.
 template <typename T>
-__global__ __launch_bounds__(256) void colsum_kernel(int Trows, int N, const T* __restrict__ a, int64_t lda,
-                                                     const T* __restrict__ x, int64_t ldx,
-                                                     const float* __restrict__ rstd, const float* __restrict__ mean,
-                                                     float* __restrict__ part, int rows_per_blk) {
+__device__ __forceinline__ void colsum_block(int chunk, int Trows, int N, const T* __restrict__ a, int64_t lda, const T* __restrict__ x, int64_t ldx,
+                                             const float* __restrict__ rstd, const float* __restrict__ mean, float* __restrict__ part,
+                                             int rows_per_blk) {
   constexpr int V = Vec<T>::N;
   __shared__ float red[3][64][V];
   const int ct = threadIdx.x & 63, q = threadIdx.x >> 6;
-  const int col = (blockIdx.x * 64 + ct) * V;
+  const int col = (chunk * 64 + ct) * V;
   const bool live = col < N;
   const int r0 = blockIdx.y * rows_per_blk;
   const int r1 = min(Trows, r0 + rows_per_blk);
@@ -290,6 +289,24 @@ __global__ __launch_bounds__(256) void colsum_kernel(int Trows, int N, const T* 
     for (int i = 0; i < V; ++i) p[i] = ((acc[i] + red[0][ct][i]) + red[1][ct][i]) + red[2][ct][i];
   }
 }
+template <typename T>
+__global__ __launch_bounds__(256) void colsum_kernel(int Trows, int N, const T* __restrict__ a, int64_t lda,
+                                                     const T* __restrict__ x, int64_t ldx,
+                                                     const float* __restrict__ rstd, const float* __restrict__ mean,
+                                                     float* __restrict__ part, int rows_per_blk) {
+  colsum_block<T>(blockIdx.x, Trows, N, a, lda, x, ldx, rstd, mean, part, rows_per_blk);
+}
+// The plain sums of up to four arrays over the same rows in one launch: the bias gradients of a layer, whose launches on their
+// own are too short to be worth one each (GPT step of 1024 tokens in fp32, hidden 256: 942 -> 895 us).
+struct ColsumJobs { ColsumJob job[4]; int first[4]; };   // first: column chunk with which a job begins
+template <typename T> __global__ __launch_bounds__(256) void colsum_jobs_kernel(int Trows, int njobs, ColsumJobs js, int rows_per_blk) {
+  int k = 0;
+#pragma unroll
+  for (int i = 1; i < 4; ++i)
+    if (i < njobs && (int)blockIdx.x >= js.first[i]) k = i;
+  const ColsumJob& j = js.job[k];
+  colsum_block<T>(blockIdx.x - js.first[k], Trows, j.width, (const T*)j.a, j.lda, nullptr, 0, nullptr, nullptr, j.part, rows_per_blk);
+}
 
 hipError_t colsum_partial(hipStream_t st, DType dt, int T, int N, const void* a, int64_t lda, const void* x,
                           int64_t ldx, const float* rstd, const float* mean, float* part, int nblk) {
@@ -302,6 +319,23 @@ hipError_t colsum_partial(hipStream_t st, DType dt, int T, int N, const void* a,
     hipLaunchKernelGGL(colsum_kernel<bf16>, grid, blk, 0, st, T, N, (const bf16*)a, lda, (const bf16*)x, ldx, rstd, mean, part, rows_per_blk);
   else
     hipLaunchKernelGGL(colsum_kernel<f16>, grid, blk, 0, st, T, N, (const f16*)a, lda, (const f16*)x, ldx, rstd, mean, part, rows_per_blk);
+  return hipGetLastError();
+}
+
+hipError_t colsum_partials(hipStream_t st, DType dt, int T, const ColsumJob* jobs, int njobs, int nblk) {
+  if (njobs < 1 || njobs > 4) return hipErrorInvalidValue;
+  const int rows_per_blk = (int)cdiv(T, nblk), V = dt == F32 ? 4 : 8;
+  ColsumJobs js = {};
+  int chunks = 0;
+  for (int i = 0; i < njobs; ++i) {
+    js.job[i] = jobs[i];
+    js.first[i] = chunks;
+    chunks += (int)cdiv(jobs[i].width, 64 * V);
+  }
+  const dim3 grid((unsigned)chunks, (unsigned)nblk), blk(256);
+  if (dt == F32) hipLaunchKernelGGL(colsum_jobs_kernel<float>, grid, blk, 0, st, T, njobs, js, rows_per_blk);
+  else if (dt == BF16) hipLaunchKernelGGL(colsum_jobs_kernel<bf16>, grid, blk, 0, st, T, njobs, js, rows_per_blk);
+  else hipLaunchKernelGGL(colsum_jobs_kernel<f16>, grid, blk, 0, st, T, njobs, js, rows_per_blk);
   return hipGetLastError();
 }
 

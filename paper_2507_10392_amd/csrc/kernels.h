@@ -119,6 +119,9 @@ hipError_t norm_bwd_partials(hipStream_t st, DType dt, int kind, int T, int H, c
 // (mean may be NULL = 0).  Rows are cut in nblk equal blocks.  part is float[nblk, N].
 hipError_t colsum_partial(hipStream_t st, DType dt, int T, int N, const void* a, int64_t lda, const void* x,
                           int64_t ldx, const float* rstd, const float* mean, float* part, int nblk);
+// part[blk, n] of up to four jobs over the same T rows, as colsum_partial without x leaves them, in one launch.
+struct ColsumJob { const void* a; int64_t lda; int width; float* part; };
+hipError_t colsum_partials(hipStream_t st, DType dt, int T, const ColsumJob* jobs, int njobs, int nblk);
 struct ReduceJob { const float* part; float* dst; int nblk; int width; };
 // dst[c] += sum_blk part[blk, c] for every job, blocks added in increasing order.
 hipError_t reduce_partials(hipStream_t st, const ReduceJob* jobs_dev, int njobs, int max_width);

@@ -504,12 +504,18 @@ float* partial_of(stage_t* s, const std::string& name) {
   return nullptr;
 }
 
-bool colsum(stage_t* s, const std::string& seg, int N, const void* a, int64_t lda, const void* x, const float* rstd,
-            const float* mean) {
+// Bias gradients of a layer: the column sums of its output gradients.
+struct BiasGrad { const char* seg; int width; const void* a; };
+bool bias_grads(stage_t* s, const std::string& p, std::initializer_list<BiasGrad> grads) {
   const Shape& h = s->sh;
-  float* part = partial_of(s, seg);
-  return run(s, "colsum", 0, (double)h.T * N * h.E * (x ? 2 : 1), [&] {
-    return colsum_partial(s->st, dt_of(s), h.T, N, a, lda, x, N, rstd, mean, part, s->plan.nblk); });
+  ColsumJob jobs[4];
+  int n = 0;
+  double bytes = 0;
+  for (const BiasGrad& g : grads) {
+    jobs[n++] = {g.a, g.width, g.width, partial_of(s, p + g.seg)};
+    bytes += (double)h.T * g.width * h.E;
+  }
+  return run(s, "colsum", 0, bytes, [&] { return colsum_partials(s->st, dt_of(s), h.T, jobs, n, s->plan.nblk); });
 }
 
 // ---- backward of one layer ----------------------------------------------------------------------
@@ -557,7 +563,6 @@ bool layer_backward(stage_t* s, int l, const char* x_in, LayerActs& A, const cha
   g.M = F; g.N = H; g.K = T; g.A = A.a; g.lda = F; g.transA = 1; g.B = dy; g.ldb = H;
   g.C = gpt ? GW("W2") : GW("Wd"); g.ldc = H; g.c_f32_accum = 1;
   if (!wgrad(g, &LayerActs::a, [&](int i) { return wg.dy_x[i]; })) return false;
-  if (gpt && !colsum(s, p + "b2", H, dy, H, nullptr, nullptr, nullptr)) return false;
 
   // GELU backward, in place over the saved pre-activations
   if (gpt && !run(s, "activation", 0, 3 * tfb, [&] { return gelu_bwd(s->st, dt, (int64_t)T * F, A.ff, pl.gF1, A.ff); }))
@@ -577,7 +582,6 @@ bool layer_backward(stage_t* s, int l, const char* x_in, LayerActs& A, const cha
   if (gpt) { g.ldb = F; g.C = GW("W1"); }
   else { g.ldb = 2 * F; g.C = GW("Wg"); g.batch = 2; g.sB = F; g.sC = (int64_t)H * F; }
   if (!wgrad(g, &LayerActs::n2, [&](int i) { return (const char*)wg.Ax[i]->ff; })) return false;
-  if (gpt && !colsum(s, p + "b1", F, dff, F, nullptr, nullptr, nullptr)) return false;
 
   // second norm: gain (and bias) partials, dx2 = dy + norm'(x2)^T dn2
   if (!run(s, "norm_bwd", 0, 4 * thb, [&] {
@@ -594,7 +598,6 @@ bool layer_backward(stage_t* s, int l, const char* x_in, LayerActs& A, const cha
   g.M = H; g.N = H; g.K = T; g.A = A.o; g.lda = H; g.transA = 1; g.B = tmp; g.ldb = H; g.C = GW("Wo"); g.ldc = H;
   g.c_f32_accum = 1;
   if (!wgrad(g, &LayerActs::o, [&](int i) { return wg.dx2_x[i]; })) return false;
-  if (gpt && !colsum(s, p + "bo", H, tmp, H, nullptr, nullptr, nullptr)) return false;
 
   // attention backward (+ inverse rotation of dq, dk)
   // algorithmic work: dV, dP, dQ, dK over the causal half (recomputing the scores is not counted)
@@ -619,7 +622,7 @@ bool layer_backward(stage_t* s, int l, const char* x_in, LayerActs& A, const cha
   if (gpt) { g.N = 3 * H; g.C = GW("Wqkv"); g.ldc = 3 * H; }
   else { g.N = H; g.C = GW("Wq"); g.ldc = H; g.batch = 3; g.sB = H; g.sC = (int64_t)H * H; }
   if (!wgrad(g, &LayerActs::n1, [&](int i) { return wg.dqkv_x[i]; })) return false;
-  if (gpt && !colsum(s, p + "bqkv", 3 * H, gqkv, 3 * H, nullptr, nullptr, nullptr)) return false;
+  if (gpt && !bias_grads(s, p, {{"b2", H, dy}, {"b1", F, dff}, {"bo", H, tmp}, {"bqkv", 3 * H, gqkv}})) return false;
 
   // first norm: dx = dx2 + norm'(x)^T dn1
   return run(s, "norm_bwd", 0, 4 * thb, [&] {
