@@ -219,6 +219,34 @@ GemmRoute gemm_route(DType dt, const Gemm& g) {
   return route_one(dt, p, GEMM_AUTO);
 }
 
+// Products that leave most of the chip idle cost a launch, a walk over K and a store each; in one grid they cost the longest.  A
+// group of 16-bit products has to win 10 % by the estimates.
+GemmRoute gemm_group_route(DType dt, const Gemm* g, int n) {
+  if (n < 2 || n > GEMM_GROUP_MAX) return ROUTE_SIMPLE;
+  double us = 0.0;
+  int64_t blocks = 0;
+  for (int i = 0; i < n; ++i) {
+    if (g[i].nx || g[i].kseg || !g[i].transA || g[i].transB || !g[i].c_f32_accum || g[i].bias || g[i].resid || g[i].K != g[0].K) return ROUTE_SIMPLE;
+    blocks += cdiv(g[i].M, 32) * cdiv(g[i].N, 32) * g[i].batch;
+    if (dt == F32) {
+      if (!gemm_f32_supported(g[i])) return ROUTE_SIMPLE;
+      continue;
+    }
+    if (!gemm_mfma_takes(dt, g[i]) || !gemm_small_takes(g[i])) return ROUTE_SIMPLE;
+    double own = 0.0;
+    us += gemm_small_tile(g[i], &own) ? own : gemm_mfma_us(g[i]);
+  }
+  if (blocks >= (1ll << 31)) return ROUTE_SIMPLE;
+  return dt == F32 ? ROUTE_F32 : gemm_small_group_us(g, n) < 0.9 * us ? ROUTE_SMALL : ROUTE_SIMPLE;
+}
+
+hipError_t gemm_group(hipStream_t st, DType dt, const Gemm* g, int n) {
+  const GemmRoute route = gemm_group_route(dt, g, n);
+  if (route == ROUTE_F32) return gemm_f32_group(st, g, n);
+  if (route == ROUTE_SMALL) return gemm_small_group(st, dt, g, n);
+  return hipErrorInvalidValue;
+}
+
 hipError_t gemm(hipStream_t st, DType dt, const Gemm& g, int force) {
   if (g.glu) {   // the fall-back's activation kernel walks dense rows
     if ((g.glu != 1 && g.glu != 2) || !g.gu || !g.C || g.batch != 1 || g.transA || (g.glu == 1) == (g.transB != 0) ||

@@ -79,7 +79,7 @@ enum Form { NN, NT, NT_SEG, TN_ACC, TN_PARTS, NN_GLU, NT_GLU };
 // T: blocks of 16 rows and columns a wave's tile has each way (2: 32x32, 4: 64x64), KW: waves that share out K, NBUF: slabs
 // held (NBUF - 1 of them in flight).  NN_GLU: the tile has two blocks of 16 columns of each of the two projections.
 template <typename E, int FORM, int T, int KW, int NBUF>
-__global__ __launch_bounds__(64 * KW) void gemm_small_kernel(Gemm g, int tiles_m, int tiles_n) {
+__device__ __forceinline__ void small_tile(const Gemm& g, int tiles_m, int tiles_n, int pid, int z) {
   constexpr int TA = FORM == TN_ACC || FORM == TN_PARTS, TB = FORM == NT || FORM == NT_SEG || FORM == NT_GLU;
   constexpr bool GLU1 = FORM == NN_GLU, ACC = TA;
   constexpr int NB = GLU1 ? 2 : T;                 // blocks of columns of one matrix B
@@ -90,10 +90,10 @@ __global__ __launch_bounds__(64 * KW) void gemm_small_kernel(Gemm g, int tiles_m
   const int lm = lane & 15, lg = lane >> 4;
   // ids are dealt round-robin to the 8 XCDs; each gets a contiguous run of the tile order
   const int ntiles = tiles_m * tiles_n;
-  int pid = blockIdx.x, tm, tn;
+  int tm, tn;
   if (pid < ntiles / 8 * 8) pid = (pid % 8) * (ntiles / 8) + pid / 8;
   gemm_tile_of(pid, tiles_m, tiles_n, tm, tn);
-  const int z = blockIdx.y, m0 = tm * 16 * T, n0 = tn * 16 * NB;
+  const int m0 = tm * 16 * T, n0 = tn * 16 * NB;
   const E* A = (const E*)g.A + (int64_t)z * g.sA;
   const E* B = (const E*)g.B + (int64_t)z * g.sB;
   const unsigned lda = (unsigned)g.lda, ldb = (unsigned)g.ldb;
@@ -270,6 +270,22 @@ __global__ __launch_bounds__(64 * KW) void gemm_small_kernel(Gemm g, int tiles_m
     }
 }
 
+template <typename E, int FORM, int T, int KW, int NBUF>
+__global__ __launch_bounds__(64 * KW) void gemm_small_kernel(Gemm g, int tiles_m, int tiles_n) {
+  small_tile<E, FORM, T, KW, NBUF>(g, tiles_m, tiles_n, blockIdx.x, blockIdx.y);
+}
+// Weight gradients of a layer in one launch (see gemm_group).
+template <typename E, int T, int KW, int NBUF> __global__ __launch_bounds__(64 * KW) void gemm_small_group_kernel(GemmGroup q) {
+  int tiles_m, tiles_n, pid, z;
+  const Gemm g = q.product_of(blockIdx.x, tiles_m, tiles_n, pid, z);
+  small_tile<E, TN_ACC, T, KW, NBUF>(g, tiles_m, tiles_n, pid, z);
+}
+template <typename E, int T, int KW, int NBUF> hipError_t launch_group(hipStream_t st, const Gemm* g, int n) {
+  GemmGroup q(g, n, 16 * T, 16 * T);
+  hipLaunchKernelGGL((gemm_small_group_kernel<E, T, KW, NBUF>), dim3((unsigned)q.total), dim3(64 * KW), 0, st, q);
+  return hipGetLastError();
+}
+
 template <typename E, int FORM, int T, int KW, int NBUF> hipError_t launch(hipStream_t st, const Gemm& g) {
   const int tm = (int)cdiv(g.M, 16 * T), tn = (int)cdiv(g.N, 16 * (FORM == NN_GLU ? 2 : T));
   hipLaunchKernelGGL((gemm_small_kernel<E, FORM, T, KW, NBUF>), dim3((unsigned)(tm * tn), (unsigned)g.batch), dim3(64 * KW), 0, st, g, tm, tn);
@@ -292,6 +308,14 @@ template <typename E> hipError_t launch_type(hipStream_t st, const Gemm& g, int 
 
 }  // namespace
 
+bool gemm_small_takes(const Gemm& g) {
+  if (g.N % 4 || g.batch > 65535 || g.transA != g.c_f32_accum || (g.transA && g.transB)) return false;   // the forms of the stage's products
+  // The k-lines of a row-contiguous operand that fill up the last slab lie behind its descriptor, unless their 32-bit offsets
+  // wrap around: few rows, more than 2^32 / 64 bytes apart.
+  const int64_t lines = cdiv(g.nx ? (int64_t)g.K - (int64_t)g.nx * g.kseg : g.K, 32) * 32;
+  return !(g.transA && lines * g.lda * 2 >= (1ll << 32)) && !(!g.transB && lines * g.ldb * 2 >= (1ll << 32));
+}
+
 // Tile of the small kernel (32 or 64) when it is the faster way, else 0.  Times in us, fitted to single products of bf16 with
 // M, N = 8 .. 6000, K = 8 .. 24000 and one to three batches.  Forward: a fixed part, and per k the latency of a walk or the
 // loads of the workgroups that share a CU, whichever is longer.  Gradients: a round of workgroups on the 256 CUs costs a fixed
@@ -301,12 +325,8 @@ template <typename E> hipError_t launch_type(hipStream_t st, const Gemm& g, int 
 // segments 10.9 : 27.1; 512 x 512, K = 256, accumulating 3.3 : 5.8; 1024 x 1024, K = 1024, accumulating 9.6 : 13.0.  At 1024 x
 // 2048, K = 1024 it loses (16.3 : 14.1), at 512 x 4096, K = 4096 (47 : 37), and accumulating over few tokens, where the rounds'
 // fixed time is all there is (1528 x 2624, K = 8: 16.6 : 7.8; 2376 x 1632, K = 16, two batches 30.4 : 11.7).
-int gemm_small_tile(const Gemm& g) {
-  if (g.N % 4 || g.batch > 65535 || g.transA != g.c_f32_accum || (g.transA && g.transB)) return 0;   // the forms of the stage's products
-  // The k-lines of a row-contiguous operand that fill up the last slab lie behind its descriptor, unless their 32-bit offsets
-  // wrap around: few rows, more than 2^32 / 64 bytes apart.
-  const int64_t lines = cdiv(g.nx ? (int64_t)g.K - (int64_t)g.nx * g.kseg : g.K, 32) * 32;
-  if ((g.transA && lines * g.lda * 2 >= (1ll << 32)) || (!g.transB && lines * g.ldb * 2 >= (1ll << 32))) return 0;
+int gemm_small_tile(const Gemm& g, double* us) {
+  if (!gemm_small_takes(g)) return 0;
   const double per_cu = (g.glu == 1 ? 2.0 : g.batch) / 256.0, k = (double)g.K;   // gate and up count like a batch of two
   const double n32 = cdiv(g.M, 32) * cdiv(g.N, 32) * per_cu, n64 = cdiv(g.M, 64) * cdiv(g.N, 64) * per_cu,
                n128 = cdiv(g.M, 128) * cdiv(g.N, 128) * per_cu;
@@ -314,12 +334,27 @@ int gemm_small_tile(const Gemm& g) {
   if (!g.transA && !g.transB) return 2.4 + k * std::max(4.5e-3, 2.6e-3 * n32) < 0.9 * staged ? 32 : 0;
   const double t32 = g.transB ? 2.0 + (2.6e-3 * k + 0.55) * std::ceil(n32) : 2.1 + (2.3e-3 * k + 0.83) * std::ceil(n32);
   const double t64 = g.transB ? 0.9 + (5.3e-3 * k + 2.4) * std::ceil(n64) : 0.4 + (4.0e-3 * k + 3.8) * std::ceil(n64);
+  if (us) *us = std::min(t32, t64);
   if (t32 < 0.9 * staged && t32 <= t64) return 32;
   return t64 < 0.9 * staged ? 64 : 0;
 }
 
 hipError_t gemm_small(hipStream_t st, DType dt, const Gemm& g, int tile) {
   return dt == F16 ? launch_type<f16>(st, g, tile) : launch_type<bf16>(st, g, tile);
+}
+
+// Grouped weight gradients: 64x64 tiles whose two waves share K, so that four workgroups fit a CU and a layer of hidden 512 is one
+// round.  The time in us, fitted to 13 layers (hidden 256 .. 2048, 64 .. 2048 tokens) that ran both ways, against the sum of the
+// products' own times.  us per microbatch, forward and backward, one after the other : grouped: Llama, hidden 512, 256 tokens 143.8 :
+// 133.6; GPT, hidden 512, 1024 tokens 229 : 216; Llama, hidden 768, 512 tokens 236 : 226; it loses for Llama, hidden 1024, 1024 tokens
+// (341 : 349) and hidden 2048, 64 tokens (340 : 370).
+double gemm_small_group_us(const Gemm* g, int n) {
+  double tiles = 0.0;
+  for (int i = 0; i < n; ++i) tiles += (double)cdiv(g[i].M, 64) * cdiv(g[i].N, 64) * g[i].batch / 256.0;
+  return 4.35 + std::max(tiles, 1.0) * (1.37 + 3.98e-3 * g[0].K);
+}
+hipError_t gemm_small_group(hipStream_t st, DType dt, const Gemm* g, int n) {
+  return dt == F16 ? launch_group<f16, 4, 2, 3>(st, g, n) : launch_group<bf16, 4, 2, 3>(st, g, n);
 }
 
 }  // namespace zs

@@ -66,6 +66,35 @@ __host__ __device__ inline void gemm_tile_of(int pos, int tiles_m, int tiles_n, 
   tm = first + (pos % width) % gsz;
   tn = (pos % width) / gsz;
 }
+// Up to four weight gradients (C += A^T B, transA = 1, c_f32_accum = 1, one part) whose tiles share one grid, one product after the
+// other, each of them batch after batch.
+constexpr int GEMM_GROUP_MAX = 4;
+struct GemmGroup {
+  struct Product { const void *A, *B; void* C; int64_t lda, ldb, ldc, sA, sB, sC; int M, N, K, first, tiles_m, tiles_n; } p[GEMM_GROUP_MAX];
+  int n, total;
+  GemmGroup(const Gemm* g, int count, int tile_m, int tile_n) : p(), n(count), total(0) {
+    for (int i = 0; i < n; ++i) {
+      const int tm = (int)cdiv(g[i].M, tile_m), tn = (int)cdiv(g[i].N, tile_n);
+      p[i] = {g[i].A, g[i].B, g[i].C, g[i].lda, g[i].ldb, g[i].ldc, g[i].sA, g[i].sB, g[i].sC, g[i].M, g[i].N, g[i].K, total, tm, tn};
+      total += tm * tn * g[i].batch;
+    }
+  }
+  // Block of the grid -> its product, and its place in there.
+  __device__ __forceinline__ Gemm product_of(int block, int& tiles_m, int& tiles_n, int& pid, int& z) const {
+    int k = 0;
+#pragma unroll
+    for (int i = 1; i < GEMM_GROUP_MAX; ++i)
+      if (i < n && block >= p[i].first) k = i;
+    const Product& q = p[k];
+    Gemm g;
+    g.M = q.M; g.N = q.N; g.K = q.K; g.transA = 1; g.c_f32_accum = 1;
+    g.A = q.A; g.lda = q.lda; g.sA = q.sA; g.B = q.B; g.ldb = q.ldb; g.sB = q.sB; g.C = q.C; g.ldc = q.ldc; g.sC = q.sC;
+    tiles_m = q.tiles_m; tiles_n = q.tiles_n;
+    z = (block - q.first) / (tiles_m * tiles_n);
+    pid = (block - q.first) % (tiles_m * tiles_n);
+    return g;
+  }
+};
 enum GemmImpl { GEMM_AUTO = 0, GEMM_SIMPLE = 1, GEMM_MFMA = 2 };
 // Returns which implementation a call with these arguments runs (GEMM_SIMPLE or GEMM_MFMA).
 int gemm_select(DType dt, const Gemm& g, int force);
@@ -75,10 +104,15 @@ hipError_t gemm(hipStream_t st, DType dt, const Gemm& g, int force);
 // choice that gemm(GEMM_AUTO) makes for a call (of its first launch, where it takes several), for the names of timing classes.
 enum GemmRoute { ROUTE_SIMPLE, ROUTE_F32, ROUTE_SMALL, ROUTE_HALVES, ROUTE_PARTS, ROUTE_STAGED };
 GemmRoute gemm_route(DType dt, const Gemm& g);
+// n (at most GEMM_GROUP_MAX) weight gradients over the same rows, with outputs of their own, in one launch, and the route of that
+// launch; ROUTE_SIMPLE: one after the other is the faster way, or the only one.
+GemmRoute gemm_group_route(DType dt, const Gemm* g, int n);
+hipError_t gemm_group(hipStream_t st, DType dt, const Gemm* g, int n);
 hipError_t gemm_simple(hipStream_t st, DType dt, const Gemm& g);
 // fp32 products on the fp32 matrix cores (gemm_f32.hip); no multi-part K range, no gated unit.
 bool gemm_f32_supported(const Gemm& g);
 hipError_t gemm_f32(hipStream_t st, const Gemm& g);
+hipError_t gemm_f32_group(hipStream_t st, const Gemm* g, int n);
 // What the 16-bit MFMA kernel takes (the dispatcher's rule), and the narrower set (K a multiple of 8) for which a caller may
 // force it.
 bool gemm_mfma_takes(DType dt, const Gemm& g);
@@ -93,10 +127,14 @@ int gemm_mfma_parts(DType dt, const Gemm& g);
 // Scratch bytes (Gemm::ws) with which gemm_mfma would cut the K range of this product's last round of tiles; 0 when
 // it would not (the answer depends on the shape only, not on the pointers).
 int64_t gemm_mfma_ws_bytes(const Gemm& g);
-// 16-bit products on 32x32 or 64x64 tiles (tile = 32 or 64) with K shared out over the waves of a workgroup (gemm_small.hip),
-// and which of the two is the faster way for a product that gemm_mfma_takes, 0: neither.
-int gemm_small_tile(const Gemm& g);
+// 16-bit products on 32x32 or 64x64 tiles (tile = 32 or 64) with K shared out over the waves of a workgroup (gemm_small.hip): the
+// products they can run of those that gemm_mfma_takes, and which of the two is the faster way, 0: neither (us receives the
+// estimated time of a gradient's product); and the estimated time of a group.
+bool gemm_small_takes(const Gemm& g);
+int gemm_small_tile(const Gemm& g, double* us = nullptr);
 hipError_t gemm_small(hipStream_t st, DType dt, const Gemm& g, int tile);
+double gemm_small_group_us(const Gemm* g, int n);
+hipError_t gemm_small_group(hipStream_t st, DType dt, const Gemm* g, int n);
 // Workgroup tile the MFMA kernel would use: 1 = 256x256, 3 = 256x192, 4 = 256x128 (8 waves), 2 = 128x128 (4 waves), and the estimated
 // time in us; force_tile(0) = automatic.
 int gemm_mfma_pick_tile(const Gemm& g);

@@ -433,6 +433,13 @@ bool do_gemm(stage_t* s, const Gemm& g) {
   return run(s, cls, flops, 0.0, [&] { return gemm(s->st, dt_of(s), g, GEMM_AUTO); });
 }
 
+// The weight gradients of a layer in one launch, where gemm_group takes them so.
+bool do_gemm_group(stage_t* s, GemmRoute route, const Gemm* g, int n) {
+  double flops = 0;
+  for (int i = 0; i < n; ++i) flops += 2.0 * g[i].M * g[i].N * g[i].K * g[i].batch;
+  return run(s, route == ROUTE_F32 ? "gemm_f32_tn" : "gemm_small_tn", flops, 0.0, [&] { return gemm_group(s->st, dt_of(s), g, n); });
+}
+
 // Timing class of the attention of this stage, whose row strides and bases are all multiples of 16 bytes (workspace buffers of
 // 256-byte alignment, hidden a multiple of 8).
 const char* attn_class(const stage_t* s, const LayerActs& A, bool bwd) {
@@ -529,6 +536,29 @@ struct WgradPlan {
   const char *dy_x[GEMM_MAX_PARTS - 1] = {}, *dx2_x[GEMM_MAX_PARTS - 1] = {}, *dqkv_x[GEMM_MAX_PARTS - 1] = {};   // ... and their dy, dx2, dqkv
 };
 
+// The four products dW += X^T dY of layer l over one microbatch: FFN down, FFN up (Llama: gate and up), attention output, QKV.
+struct LayerWgrads { Gemm down, up, out, qkv; };
+LayerWgrads layer_wgrads(stage_t* s, int l, const LayerActs& A, const char* dy, const char* dx2, const char* dqkv) {
+  const Shape& h = s->sh;
+  const int T = h.T, H = h.H, F = h.F;
+  const bool gpt = h.arch == STAGE_ARCH_GPT;
+  const std::string p = "L" + std::to_string(l) + ".";
+  auto product = [&](const char* w, int M, int N, const char* x, const char* d, int64_t ldd) {
+    Gemm g;
+    g.M = M; g.N = N; g.K = T; g.transA = 1; g.A = x; g.lda = M; g.B = d; g.ldb = ldd;
+    g.C = s->G(s->seg_off(p + w)); g.ldc = N; g.c_f32_accum = 1;
+    return g;
+  };
+  LayerWgrads w;
+  w.down = product(gpt ? "W2" : "Wd", F, H, A.a, dy, H);
+  w.up = product(gpt ? "W1" : "Wg", H, F, A.n2, A.ff, gpt ? F : 2 * F);
+  if (!gpt) { w.up.batch = 2; w.up.sB = F; w.up.sC = (int64_t)H * F; }
+  w.out = product("Wo", H, H, A.o, dx2, H);
+  w.qkv = product(gpt ? "Wqkv" : "Wq", H, gpt ? 3 * H : H, A.n1, dqkv, 3 * H);
+  if (!gpt) { w.qkv.batch = 3; w.qkv.sB = H; w.qkv.sC = (int64_t)H * H; }
+  return w;
+}
+
 bool layer_backward(stage_t* s, int l, const char* x_in, LayerActs& A, const char* dy, char* tmp, char* dx, char* gqkv,
                     const WgradPlan& wg) {
   const Shape& h = s->sh;
@@ -539,12 +569,15 @@ bool layer_backward(stage_t* s, int l, const char* x_in, LayerActs& A, const cha
   const double thb = (double)T * H * h.E, tfb = (double)T * F * h.E;
   Plan& pl = s->plan;
   auto W = [&](const char* n) { return s->P(s->seg_off(p + n)); };
-  auto GW = [&](const char* n) { return s->G(s->seg_off(p + n)); };
   Gemm g;
+  const LayerWgrads dw = layer_wgrads(s, l, A, dy, tmp, gqkv);
+  // small products wait until the last of their operands is there and share a launch
+  const Gemm group[4] = {dw.up, dw.down, dw.qkv, dw.out};
+  const GemmRoute group_route = wg.mode == 0 ? gemm_group_route(dt, group, 4) : ROUTE_SIMPLE;
   // dW += X^T dY over this microbatch's tokens, and over the deferred microbatches' too when there are any:
   // xsel picks the activation of a deferred microbatch, dsel its gradient operand
   auto wgrad = [&](Gemm w, char* LayerActs::*xsel, auto dsel) {
-    if (wg.mode == 1) return true;
+    if (wg.mode == 1 || group_route != ROUTE_SIMPLE) return true;
     if (wg.mode == 2) {
       w.nx = wg.nx; w.kseg = T; w.K = (wg.nx + 1) * T;
       for (int i = 0; i < wg.nx; ++i) { w.Ax[i] = wg.Ax[i]->*xsel; w.Bx[i] = dsel(i); }
@@ -559,10 +592,7 @@ bool layer_backward(stage_t* s, int l, const char* x_in, LayerActs& A, const cha
   // Llama: the store turns (gate, up), saved in ff, into (dgate, dup) in place; da itself is not kept
   if (!gpt) { g.glu = 2; g.gu = A.ff; g.gu_ld = 2 * F; g.gu_up = F; }
   if (!do_gemm(s, g)) return false;
-  g = Gemm();
-  g.M = F; g.N = H; g.K = T; g.A = A.a; g.lda = F; g.transA = 1; g.B = dy; g.ldb = H;
-  g.C = gpt ? GW("W2") : GW("Wd"); g.ldc = H; g.c_f32_accum = 1;
-  if (!wgrad(g, &LayerActs::a, [&](int i) { return wg.dy_x[i]; })) return false;
+  if (!wgrad(dw.down, &LayerActs::a, [&](int i) { return wg.dy_x[i]; })) return false;
 
   // GELU backward, in place over the saved pre-activations
   if (gpt && !run(s, "activation", 0, 3 * tfb, [&] { return gelu_bwd(s->st, dt, (int64_t)T * F, A.ff, pl.gF1, A.ff); }))
@@ -577,11 +607,7 @@ bool layer_backward(stage_t* s, int l, const char* x_in, LayerActs& A, const cha
   // free at this point, and one after the other in the scratch: gO and gQKV (written later), gF1 (da has been used)
   g.ws = pl.gO; g.ws_bytes = pl.gF1 + (int64_t)T * F * h.E - pl.gO;
   if (!do_gemm(s, g)) return false;
-  g = Gemm();
-  g.M = H; g.N = F; g.K = T; g.A = A.n2; g.lda = H; g.transA = 1; g.B = dff; g.c_f32_accum = 1; g.ldc = F;
-  if (gpt) { g.ldb = F; g.C = GW("W1"); }
-  else { g.ldb = 2 * F; g.C = GW("Wg"); g.batch = 2; g.sB = F; g.sC = (int64_t)H * F; }
-  if (!wgrad(g, &LayerActs::n2, [&](int i) { return (const char*)wg.Ax[i]->ff; })) return false;
+  if (!wgrad(dw.up, &LayerActs::n2, [&](int i) { return (const char*)wg.Ax[i]->ff; })) return false;
 
   // second norm: gain (and bias) partials, dx2 = dy + norm'(x2)^T dn2
   if (!run(s, "norm_bwd", 0, 4 * thb, [&] {
@@ -594,10 +620,7 @@ bool layer_backward(stage_t* s, int l, const char* x_in, LayerActs& A, const cha
   g = Gemm();
   g.M = T; g.N = H; g.K = H; g.A = tmp; g.lda = H; g.B = W("Wo"); g.ldb = H; g.transB = 1; g.C = pl.gO; g.ldc = H;
   if (!do_gemm(s, g)) return false;
-  g = Gemm();
-  g.M = H; g.N = H; g.K = T; g.A = A.o; g.lda = H; g.transA = 1; g.B = tmp; g.ldb = H; g.C = GW("Wo"); g.ldc = H;
-  g.c_f32_accum = 1;
-  if (!wgrad(g, &LayerActs::o, [&](int i) { return wg.dx2_x[i]; })) return false;
+  if (!wgrad(dw.out, &LayerActs::o, [&](int i) { return wg.dx2_x[i]; })) return false;
 
   // attention backward (+ inverse rotation of dq, dk)
   // algorithmic work: dV, dP, dQ, dK over the causal half (recomputing the scores is not counted)
@@ -608,6 +631,8 @@ bool layer_backward(stage_t* s, int l, const char* x_in, LayerActs& A, const cha
                         pl.delta, gqkv, gqkv + HE, gqkv + 2 * HE, 3 * H, gpt ? nullptr : pl.rope, ATTN_AUTO); }))
     return false;
 
+  if (group_route != ROUTE_SIMPLE && !do_gemm_group(s, group_route, group, 4)) return false;
+
   // QKV projection: dn1 = dqkv [Wq|Wk|Wv]^T ; dW += n1^T dqkv
   g = Gemm();
   g.M = T; g.N = H; g.K = 3 * H; g.A = gqkv; g.lda = 3 * H; g.transB = 1; g.C = pl.gN; g.ldc = H;
@@ -617,11 +642,7 @@ bool layer_backward(stage_t* s, int l, const char* x_in, LayerActs& A, const cha
   // three results, for Q, K and V, need more: dff and a, next to each other, which this microbatch's products have used unless they wait
   if (!gpt && wg.mode != 1) { g.ws = A.ff; g.ws_bytes = A.a + (int64_t)T * F * h.E - A.ff; }
   if (!do_gemm(s, g)) return false;
-  g = Gemm();
-  g.M = H; g.K = T; g.A = A.n1; g.lda = H; g.transA = 1; g.B = gqkv; g.ldb = 3 * H; g.c_f32_accum = 1;
-  if (gpt) { g.N = 3 * H; g.C = GW("Wqkv"); g.ldc = 3 * H; }
-  else { g.N = H; g.C = GW("Wq"); g.ldc = H; g.batch = 3; g.sB = H; g.sC = (int64_t)H * H; }
-  if (!wgrad(g, &LayerActs::n1, [&](int i) { return wg.dqkv_x[i]; })) return false;
+  if (!wgrad(dw.qkv, &LayerActs::n1, [&](int i) { return wg.dqkv_x[i]; })) return false;
   if (gpt && !bias_grads(s, p, {{"b2", H, dy}, {"b1", F, dff}, {"bo", H, tmp}, {"bqkv", 3 * H, gqkv}})) return false;
 
   // first norm: dx = dx2 + norm'(x)^T dn1
@@ -677,40 +698,20 @@ bool flush_deferred(stage_t* s) {
   if (nd == 0) return true;
   const Shape& h = s->sh;
   Plan& pl = s->plan;
-  const int T = h.T, H = h.H, F = h.F;
-  const bool gpt = h.arch == STAGE_ARCH_GPT;
   for (int l = h.L - 1; l >= 0; --l) {
     auto acts = [&](int i) -> const LayerActs& { return pl.acts[(size_t)s->deferred[i] * h.L + l]; };
-    const std::string p = "L" + std::to_string(l) + ".";
-    auto GW = [&](const char* n) { return s->G(s->seg_off(p + n)); };
-    auto parts = [&](Gemm& g, char* LayerActs::*xsel, auto dsel) {   // part 0 = first deferred, the others follow
-      g.A = acts(0).*xsel; g.B = dsel(0);
-      g.K = nd * T;
-      if (nd > 1) { g.nx = nd - 1; g.kseg = T; g.ws = pl.kcut; g.ws_bytes = pl.kcut_bytes; }
+    const LayerWgrads dw = layer_wgrads(s, l, acts(0), pl.kdy[l], pl.kdx2[l], pl.kdqkv[l]);   // part 0 = first deferred, the others follow
+    auto multiply = [&](Gemm g, char* LayerActs::*xsel, auto dsel) {
+      g.K = nd * h.T;
+      if (nd > 1) { g.nx = nd - 1; g.kseg = h.T; g.ws = pl.kcut; g.ws_bytes = pl.kcut_bytes; }
       for (int i = 1; i < nd; ++i) { g.Ax[i - 1] = acts(i).*xsel; g.Bx[i - 1] = dsel(i); }
+      return do_gemm(s, g);
     };
-    Gemm g;
-    g.M = F; g.N = H; g.lda = F; g.transA = 1; g.ldb = H;
-    g.C = gpt ? GW("W2") : GW("Wd"); g.ldc = H; g.c_f32_accum = 1;
-    parts(g, &LayerActs::a, [&](int i) { return (const char*)pl.kdy[(size_t)i * h.L + l]; });
-    if (!do_gemm(s, g)) return false;
-    g = Gemm();
-    g.M = H; g.N = F; g.lda = H; g.transA = 1; g.c_f32_accum = 1; g.ldc = F;
-    if (gpt) { g.ldb = F; g.C = GW("W1"); }
-    else { g.ldb = 2 * F; g.C = GW("Wg"); g.batch = 2; g.sB = F; g.sC = (int64_t)H * F; }
-    parts(g, &LayerActs::n2, [&](int i) { return (const char*)acts(i).ff; });
-    if (!do_gemm(s, g)) return false;
-    g = Gemm();
-    g.M = H; g.N = H; g.lda = H; g.transA = 1; g.ldb = H; g.C = GW("Wo"); g.ldc = H;
-    g.c_f32_accum = 1;
-    parts(g, &LayerActs::o, [&](int i) { return (const char*)pl.kdx2[(size_t)i * h.L + l]; });
-    if (!do_gemm(s, g)) return false;
-    g = Gemm();
-    g.M = H; g.lda = H; g.transA = 1; g.ldb = 3 * H; g.c_f32_accum = 1;
-    if (gpt) { g.N = 3 * H; g.C = GW("Wqkv"); g.ldc = 3 * H; }
-    else { g.N = H; g.C = GW("Wq"); g.ldc = H; g.batch = 3; g.sB = H; g.sC = (int64_t)H * H; }
-    parts(g, &LayerActs::n1, [&](int i) { return (const char*)pl.kdqkv[(size_t)i * h.L + l]; });
-    if (!do_gemm(s, g)) return false;
+    if (!multiply(dw.down, &LayerActs::a, [&](int i) { return (const char*)pl.kdy[(size_t)i * h.L + l]; }) ||
+        !multiply(dw.up, &LayerActs::n2, [&](int i) { return (const char*)acts(i).ff; }) ||
+        !multiply(dw.out, &LayerActs::o, [&](int i) { return (const char*)pl.kdx2[(size_t)i * h.L + l]; }) ||
+        !multiply(dw.qkv, &LayerActs::n1, [&](int i) { return (const char*)pl.kdqkv[(size_t)i * h.L + l]; }))
+      return false;
   }
   s->deferred.clear();
   return true;
