@@ -13,7 +13,7 @@
 //
 // Backward is two kernels without atomics (fixed summation order): one owns 128 queries and
 // produces dQ, one owns 128 keys and produces dK and dV; both recompute P from the saved
-// log-sum-exp.  delta_i = dO_i . O_i is formed by the dQ kernel for its own rows and stored for the other.
+// log-sum-exp.  delta_i = dO_i . O_i is formed by the dQ kernel for its own rows and stored for the other, or by both where they share a launch.
 //
 // SPLIT: probabilities and dS, fp32 in the wave-per-row kernel that served these head dims, go into the second product as a
 // high and a low 16-bit part (two matrix instructions on the same A fragment), which together keep 16 (bf16) or 22 (half) of
@@ -179,8 +179,8 @@ __device__ __forceinline__ int acc_row(int r, int lane) { return 8 * (r >> 2) + 
 // ids go to different XCDs round-robin; with nh*mb a multiple of 8 a head keeps its XCD, whose L2 then
 // holds the K/V (or Q/dO) rows its blocks stream.
 struct BlockId { int rank, h, b; };
-__device__ __forceinline__ BlockId block_id(int nh, int mb) {
-  const int nhb = nh * mb, id = blockIdx.x, hb = id % nhb;
+__device__ __forceinline__ BlockId block_id(int id, int nh, int mb) {
+  const int nhb = nh * mb, hb = id % nhb;
   return BlockId{id / nhb, hb % nh, hb / nh};
 }
 
@@ -328,7 +328,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_fwd_kernel(int 
   extern __shared__ __align__(16) char smem_raw[];
   e16* smem = reinterpret_cast<e16*>(smem_raw);            // [2][K tile | V tile]
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const BlockId bid = block_id(nh, mb);
+  const BlockId bid = block_id(blockIdx.x, nh, mb);
   const int qb = (S + 32 * NW - 1) / (32 * NW) - 1 - bid.rank, h = bid.h, b = bid.b;
   const int64_t tok0 = (int64_t)b * S;
   const e16* qh = q + tok0 * ld + h * dd;
@@ -467,19 +467,16 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_fwd_kernel(int 
 // dQ^T[d][q] += K^T[d][key] dS^T[key][q],  dS^T = P^T o (dP^T - delta_q),  dP^T = V dO^T.
 // QS = 2: two waves share 32 queries, each taking one half of every tile's keys; their sums meet in LDS at the end.
 template <int NW, int QS, int D, bool SPLIT>
-__global__ __launch_bounds__(64 * NW, NW == 4 && !(SPLIT && LO_ACC && D > 64) ? 2 : 1) void attn_bwd_dq_kernel(int S, const e16* __restrict__ q, const e16* __restrict__ k,
-                                                          const e16* __restrict__ v, int64_t ld,
-                                                          const e16* __restrict__ o, const e16* __restrict__ dout,
-                                                          int64_t ldo, const float* __restrict__ lse,
-                                                          float* __restrict__ delta,
-                                                          e16* __restrict__ dq, int64_t ldd, float scale, int nh,
-                                                          int mb, const float2* __restrict__ rope, int head_dim) {
+__device__ __forceinline__ void dq_block(int block, int S, const e16* __restrict__ q, const e16* __restrict__ k, const e16* __restrict__ v, int64_t ld,
+                                         const e16* __restrict__ o, const e16* __restrict__ dout, int64_t ldo, const float* __restrict__ lse,
+                                         float* __restrict__ delta, e16* __restrict__ dq, int64_t ldd, float scale, int nh, int mb,
+                                         const float2* __restrict__ rope, int head_dim) {
   const int dd = SPLIT ? head_dim : D;
   extern __shared__ __align__(16) char smem_raw[];
   e16* smem = reinterpret_cast<e16*>(smem_raw);
   constexpr int QW = NW / QS;   // groups of 32 queries
   const int tid = threadIdx.x, lane = tid & 63, wave = QS == 1 ? tid >> 6 : (tid >> 6) % QW, half = QS == 1 ? 0 : (tid >> 6) / QW;
-  const BlockId bid = block_id(nh, mb);
+  const BlockId bid = block_id(block, nh, mb);
   const int qb = (S + 32 * QW - 1) / (32 * QW) - 1 - bid.rank, h = bid.h, b = bid.b;
   const int64_t tok0 = (int64_t)b * S;
   const e16* qh = q + tok0 * ld + h * dd;
@@ -612,6 +609,17 @@ __global__ __launch_bounds__(64 * NW, NW == 4 && !(SPLIT && LO_ACC && D > 64) ? 
   }
 }
 
+template <int NW, int QS, int D, bool SPLIT>
+__global__ __launch_bounds__(64 * NW, NW == 4 && !(SPLIT && LO_ACC && D > 64) ? 2 : 1) void attn_bwd_dq_kernel(int S, const e16* __restrict__ q, const e16* __restrict__ k,
+                                                          const e16* __restrict__ v, int64_t ld,
+                                                          const e16* __restrict__ o, const e16* __restrict__ dout,
+                                                          int64_t ldo, const float* __restrict__ lse,
+                                                          float* __restrict__ delta,
+                                                          e16* __restrict__ dq, int64_t ldd, float scale, int nh,
+                                                          int mb, const float2* __restrict__ rope, int head_dim) {
+  dq_block<NW, QS, D, SPLIT>(blockIdx.x, S, q, k, v, ld, o, dout, ldo, lse, delta, dq, ldd, scale, nh, mb, rope, head_dim);
+}
+
 // ------------------------------------------------------------------------------------------ dK, dV
 // grid ceil(S/(32 NW))*nh*mb, NW waves; wave w owns keys k0+32w..; loops over Q/dO tiles from the diagonal to the
 // end.  With 8 waves the staged Q/dO tiles serve 256 keys and two waves share each SIMD, so one wave's
@@ -621,20 +629,29 @@ __global__ __launch_bounds__(64 * NW, NW == 4 && !(SPLIT && LO_ACC && D > 64) ? 
 // QS = 2: two waves share 32 keys, each taking one half of every tile's queries; their sums meet in LDS at the end.
 // The waves per SIMD are stated because the scheduler otherwise aims for more than the registers allow and issues LDS reads later
 // (heads of 64 at S = 1000: 46 -> 48 us).
-template <int NW, int QS, int D, bool SPLIT>
+// BOTH: dQ and dK/dV in one launch, for grids that leave CUs idle when they run one after the other: the blocks from dkv_blocks on are
+// dQ's.  No block reads what another one writes: delta of a tile's rows is formed here from dO and the same rows of O, 16 lanes to a
+// row, instead of read.
+template <int NW, int QS, int D, bool SPLIT, bool BOTH>
 __global__ __attribute__((amdgpu_waves_per_eu(SPLIT && LO_ACC && D > 64 ? 1 : 2, 2))) __launch_bounds__(64 * NW) void attn_bwd_dkv_kernel(int S, const e16* __restrict__ q, const e16* __restrict__ k,
                                                            const e16* __restrict__ v, int64_t ld,
                                                            const e16* __restrict__ dout, int64_t ldo,
                                                            const float* __restrict__ lse, const float* __restrict__ delta,
                                                            e16* __restrict__ dk, e16* __restrict__ dv, int64_t ldd,
-                                                           float scale, int nh, int mb, const float2* __restrict__ rope, int head_dim) {
+                                                           float scale, int nh, int mb, const float2* __restrict__ rope, int head_dim,
+                                                           int dkv_blocks, const e16* __restrict__ o, float* __restrict__ delta_out, e16* __restrict__ dq) {
+  static_assert(!BOTH || (!SPLIT && 64 * NW % (D / 8) == 0 && D == 128), "16 lanes share a row; rows that are redone read delta");
+  if (BOTH && (int)blockIdx.x >= dkv_blocks) {
+    dq_block<NW, QS, D, SPLIT>(blockIdx.x - dkv_blocks, S, q, k, v, ld, o, dout, ldo, lse, delta_out, dq, ldd, scale, nh, mb, rope, head_dim);
+    return;
+  }
   const int dd = SPLIT ? head_dim : D;
   extern __shared__ __align__(16) char smem_raw[];
   e16* smem = reinterpret_cast<e16*>(smem_raw);                 // [2][Q tile | dO tile]
   float* stats = reinterpret_cast<float*>(smem + 4 * TILE<D>);       // [2][lse2[64] | delta[64]]
   constexpr int KWV = NW / QS;   // groups of 32 keys
   const int tid = threadIdx.x, lane = tid & 63, wave = QS == 1 ? tid >> 6 : (tid >> 6) % KWV, half = QS == 1 ? 0 : (tid >> 6) / KWV;
-  const BlockId bid = block_id(nh, mb);
+  const BlockId bid = block_id(blockIdx.x, nh, mb);
   const int kb = bid.rank, h = bid.h, b = bid.b;                   // early key blocks (most work) first
   const int64_t tok0 = (int64_t)b * S;
   const e16* qh = q + tok0 * ld + h * dd;
@@ -643,7 +660,8 @@ __global__ __attribute__((amdgpu_waves_per_eu(SPLIT && LO_ACC && D > 64 ? 1 : 2,
   const e16* doh = dout + tok0 * ldo + h * dd;
   const __amdgpu_buffer_rsrc_t rsq = head_rsrc(qh, ld, S, dd), rsdo = head_rsrc(doh, ldo, S, dd);
   const float* lse_h = lse + ((int64_t)b * nh + h) * S;
-  const float* dlt_h = delta + ((int64_t)b * nh + h) * S;
+  const float* dlt_h = BOTH ? nullptr : delta + ((int64_t)b * nh + h) * S;
+  const __amdgpu_buffer_rsrc_t rso = head_rsrc(BOTH ? o + tok0 * ldo + h * dd : doh, ldo, S, dd);
   const int k0 = kb * 32 * KWV, wk0 = k0 + wave * 32;
   const int my_k = wk0 + (lane & 31);
   const float scale_log2 = scale * LOG2E;
@@ -653,23 +671,35 @@ __global__ __attribute__((amdgpu_waves_per_eu(SPLIT && LO_ACC && D > 64 ? 1 : 2,
   // the register budget of two waves per SIMD.
   // Everything the kernel reads before its loop (the first tile, K, V) is in flight before the first wait: a small LLaMA step
   // (S = 256, 16 launches) is 18 us shorter for it, 4 x 16 heads of 64 at S = 1000 98 -> 97 us.
-  TileRegs<64 * NW, D> qr, dor;
+  TileRegs<64 * NW, D> qr, dor, orow;   // orow: of O
   float statr = 0.f;
   bool stat_in = false;
   // The scaling of lse and the zeros past S wait for put(): either would make the wave wait here, for the tile's loads too.
   auto fetch = [&](int t) {
     fetch_tile(qr, rsq, (int)ld, t * TR, tid, dd);
     fetch_tile(dor, rsdo, (int)ldo, t * TR, tid, dd);
-    if (tid < 128) {
+    if constexpr (BOTH) fetch_tile(orow, rso, (int)ldo, t * TR, tid, dd);
+    if (tid < (BOTH ? 64 : 128)) {
       const int r = t * TR + (tid & 63);
       stat_in = r < S;
-      statr = (tid < 64 ? lse_h : dlt_h)[min(r, S - 1)];
+      statr = (BOTH || tid < 64 ? lse_h : dlt_h)[min(r, S - 1)];
     }
   };
   auto put = [&](int buf) {
     put_tile(qr, smem + buf * 2 * TILE<D>, tid);
     put_tile(dor, smem + buf * 2 * TILE<D> + TILE<D>, tid);
-    if (tid < 128) stats[buf * 128 + tid] = stat_in ? statr * (tid < 64 ? LOG2E : 1.0f) : 0.f;
+    if (tid < (BOTH ? 64 : 128)) stats[buf * 128 + tid] = stat_in ? statr * (tid < 64 ? LOG2E : 1.0f) : 0.f;
+    if constexpr (BOTH) {   // rows past S are zeros
+#pragma unroll
+      for (int i = 0; i < 8 * D / (64 * NW); ++i) {
+        float x = 0.f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) x = fmaf((float)dor.v[i][e], (float)orow.v[i][e], x);
+#pragma unroll
+        for (int m = 1; m < D / 8; m *= 2) x += __shfl_xor(x, m, 64);
+        if (tid % (D / 8) == 0) stats[buf * 128 + 64 + tid / (D / 8) + 64 * NW / (D / 8) * i] = x;
+      }
+    }
   };
   const int t_begin = k0 / TR, t_end = (S - 1) / TR + 1;
   fetch(t_begin);
@@ -861,11 +891,25 @@ hipError_t launch_dkv(hipStream_t st, int mb, int S, int nh, int d, const void* 
                       const void* dout, int64_t ldo, const float* lse, const float* delta, void* dk, void* dv, int64_t ldd,
                       const float2* rope) {
   static bool set = false;
-  const hipError_t e = set_smem(attn_bwd_dkv_kernel<NW, QS, D, SPLIT>, smem_dkv<D>(NW / QS), set);
+  const hipError_t e = set_smem(attn_bwd_dkv_kernel<NW, QS, D, SPLIT, false>, smem_dkv<D>(NW / QS), set);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((attn_bwd_dkv_kernel<NW, QS, D, SPLIT>), dim3((unsigned)(cdiv(S, 32 * (NW / QS)) * nh * mb)), dim3(64 * NW), smem_dkv<D>(NW / QS),
+  hipLaunchKernelGGL((attn_bwd_dkv_kernel<NW, QS, D, SPLIT, false>), dim3((unsigned)(cdiv(S, 32 * (NW / QS)) * nh * mb)), dim3(64 * NW), smem_dkv<D>(NW / QS),
                      st, S, (const e16*)q, (const e16*)k, (const e16*)v, ld, (const e16*)dout, ldo, lse, delta, (e16*)dk, (e16*)dv,
-                     ldd, 1.0f / sqrtf((float)d), nh, mb, rope, d);
+                     ldd, 1.0f / sqrtf((float)d), nh, mb, rope, d, 0, nullptr, nullptr, nullptr);
+  return hipGetLastError();
+}
+// dQ and dK/dV together, 8 waves to a block of 128 rows, two of them per 32 rows.
+template <int D>
+hipError_t launch_bwd(hipStream_t st, int mb, int S, int nh, const void* q, const void* k, const void* v, int64_t ld, const void* o, const void* dout,
+                      int64_t ldo, const float* lse, float* delta, void* dq, void* dk, void* dv, int64_t ldd, const float2* rope) {
+  constexpr size_t SMEM = smem_dkv<D>(4) > SMEM_FWD<D> ? smem_dkv<D>(4) : SMEM_FWD<D>;
+  static bool set = false;
+  const hipError_t e = set_smem(attn_bwd_dkv_kernel<8, 2, D, false, true>, SMEM, set);
+  if (e != hipSuccess) return e;
+  const int blocks = (int)(cdiv(S, 128) * nh * mb);
+  hipLaunchKernelGGL((attn_bwd_dkv_kernel<8, 2, D, false, true>), dim3((unsigned)(2 * blocks)), dim3(512), SMEM, st, S, (const e16*)q, (const e16*)k,
+                     (const e16*)v, ld, (const e16*)dout, ldo, lse, nullptr, (e16*)dk, (e16*)dv, ldd, 1.0f / sqrtf((float)D), nh, mb, rope, D,
+                     blocks, (const e16*)o, delta, (e16*)dq);
   return hipGetLastError();
 }
 // Blocks of 128 rows: with 8 waves, two of them per 32 rows, or with 4.  The kernels' LDS leaves a CU one workgroup (dK/dV) or
@@ -876,6 +920,11 @@ hipError_t launch_dkv(hipStream_t st, int mb, int S, int nh, int d, const void* 
 // workgroups costs more than the two 4-wave ones that a CU holds side by side, unless the sequences are so long that the blocks
 // differ a lot in their work.  Both directions, S = 513, 98 heads (490 blocks) 83 us shared, 75 not; S = 1700, 24 heads (336 blocks)
 // 104 and 117.  Of 116 shapes with 216 to 550 blocks the rule takes the faster form but for 1.6 %.
+// Where 2 x blocks leave CUs idle, or nearly, dQ and dK/dV share a launch and the time is that of dK/dV, whose blocks then form delta
+// themselves.  Separate : together, us: 4 heads, S = 256 31.4 : 20.0; 32 heads, S = 512 45.5 : 32.9; 16 heads, S = 2048 (256 blocks) 115 :
+// 100.  Up to 256 blocks the long sequences' unequal blocks fill one another's gaps; 288 blocks are a tie at S = 2048, 480 lose 22 %.
+// Sequences of one or two blocks have equal ones, and a second round costs what it saves: S = 128, 160 blocks 27.7 : 28.2, 240 30.4 : 33.8;
+// S = 200, 192 blocks 32.2 : 26.5, 200 33.6 : 35.9; S = 300, 252 blocks 38.3 : 39.5.
 template <int D, bool SPLIT>
 hipError_t bwd_128(hipStream_t st, int mb, int S, int nh, int d, const void* q, const void* k, const void* v, int64_t ld, const void* o,
                    const void* dout, int64_t ldo, const float* lse, float* delta, void* dq, void* dk, void* dv, int64_t ldd,
@@ -885,6 +934,9 @@ hipError_t bwd_128(hipStream_t st, int mb, int S, int nh, int d, const void* q, 
     return e != hipSuccess ? e : launch_dkv<4, 1, D, SPLIT>(st, mb, S, nh, d, q, k, v, ld, dout, ldo, lse, delta, dk, dv, ldd, rope);
   } else {
     const int64_t per_head = cdiv(S, 128), blocks = per_head * nh * mb;
+    if constexpr (!SPLIT && D == 128)
+      if (!wide_dkv && blocks <= (per_head == 1 ? 128 : per_head < 4 ? 192 : 256))
+        return launch_bwd<D>(st, mb, S, nh, q, k, v, ld, o, dout, ldo, lse, delta, dq, dk, dv, ldd, rope);
     const hipError_t e = S > 256 && blocks < 512 && blocks <= 256 + 28 * (per_head > 6 ? per_head - 6 : 0)
                              ? launch_dq<8, 2, D, SPLIT>(st, mb, S, nh, d, q, k, v, ld, o, dout, ldo, lse, delta, dq, ldd, rope)
                              : launch_dq<4, 1, D, SPLIT>(st, mb, S, nh, d, q, k, v, ld, o, dout, ldo, lse, delta, dq, ldd, rope);
