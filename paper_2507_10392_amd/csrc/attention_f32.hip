@@ -91,9 +91,9 @@ __device__ __forceinline__ f32x4 unrotate(const f32x4& x, const float2* rope, in
 }
 // Blocks with the most work first, over all heads (a causal block's work grows with its distance from the start or the end).
 struct Block { int rank, h, b; };
-__device__ __forceinline__ Block block_of(int nh, int mb) {
-  const int nhb = nh * mb, hb = blockIdx.x % nhb;
-  return Block{(int)blockIdx.x / nhb, hb % nh, hb / nh};
+__device__ __forceinline__ Block block_of(int id, int nh, int mb) {
+  const int nhb = nh * mb, hb = id % nhb;
+  return Block{id / nhb, hb % nh, hb / nh};
 }
 
 // Sum of the waves' accumulators, quad by quad: wave w gets the sums of the quads q with q % KW == w, quad q as mine[q / KW].
@@ -157,8 +157,14 @@ __device__ __attribute__((noinline)) void redo_dq_rows(float* rowbuf, unsigned r
 template <int DS>
 __device__ __attribute__((noinline)) void redo_dkv_rows(float* rowbuf, unsigned redo, int k0, int S, int dd, const float* q,
                                                         const float* k, const float* v, int64_t ld, const float* dout, int64_t ldo,
-                                                        const float* lse_h, const float* dlt_h, float scale, const float2* rope,
-                                                        float* dk, float* dv, int64_t ldd) {
+                                                        const float* lse_h, const float* dlt_h, const float* o, float scale,
+                                                        const float2* rope, float* dk, float* dv, int64_t ldd) {
+  auto delta = [&](int i) {   // dlt_h = NULL: from the rows of O
+    if (dlt_h) return dlt_h[i];
+    float x = 0.f;
+    for (int c = 0; c < dd; ++c) x = fmaf(dout[(int64_t)i * ldo + c], o[(int64_t)i * ldo + c], x);
+    return x;
+  };
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   for_dealt_rows(&redo, 1, KW, wave, [&](int, int r) {
     const int j = k0 + r;
@@ -167,7 +173,7 @@ __device__ __attribute__((noinline)) void redo_dkv_rows(float* rowbuf, unsigned 
       for (int c = lane; c < dd; c += 64) dk[to + c] = dv[to + c] = NAN;
       return;
     }
-    attn_dkv_row<DS / 4>(rowbuf, j, S, dd, q, k, v, ld, dout, ldo, lse_h, dlt_h, scale, lane, [&](int c, float xk, float xv) {
+    attn_dkv_row<DS / 4>(rowbuf, j, S, dd, q, k, v, ld, dout, ldo, lse_h, delta, scale, lane, [&](int c, float xk, float xv) {
       dk[to + c] = rope ? unrotate_column(xk, rope, j, c, dd) : xk;
       dv[to + c] = xv;
     });
@@ -184,7 +190,7 @@ __global__ __launch_bounds__(64 * KW) void attn_fwd_f32_kernel(int S, int dd, co
   __shared__ unsigned masks[KW];
   __shared__ float ms[KW][16], ls[KW][16];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const Block blk = block_of(nh, mb);
+  const Block blk = block_of(blockIdx.x, nh, mb);
   const int q0 = ((S + 15) / 16 - 1 - blk.rank) * 16, my_q = q0 + (lane & 15);
   const int64_t tok0 = (int64_t)blk.b * S;
   const Head hq = head_of(q + tok0 * ld + blk.h * dd, ld, S, dd), hk = head_of(k + tok0 * ld + blk.h * dd, ld, S, dd),
@@ -271,18 +277,18 @@ __global__ __launch_bounds__(64 * KW) void attn_fwd_f32_kernel(int S, int dd, co
 }
 
 // ------------------------------------------------------------------------------------------ dQ (and delta = dO . O)
+template <int DS> struct BwdLds {
+  f32x4 red[(KW - 1) * DS * 64];
+  float rowbuf[KW][32 * DS];   // rows that are redone
+  unsigned masks[KW];
+};
 template <int DS, int NBUF>
-__global__ __launch_bounds__(64 * KW) void attn_bwd_dq_f32_kernel(int S, int dd, const float* __restrict__ q, const float* __restrict__ k,
-                                                                 const float* __restrict__ v, int64_t ld, const float* __restrict__ o,
-                                                                 const float* __restrict__ dout, int64_t ldo,
-                                                                 const float* __restrict__ lse, float* __restrict__ delta,
-                                                                 float* __restrict__ dq, int64_t ldd, float scale, int nh, int mb,
-                                                                 const float2* __restrict__ rope) {
-  __shared__ f32x4 red[(KW - 1) * DS * 64];
-  __shared__ float rowbuf[KW][32 * DS];   // rows that are redone
-  __shared__ unsigned masks[KW];
+__device__ __forceinline__ void dq_block(BwdLds<DS>& lds, int block, int S, int dd, const float* __restrict__ q, const float* __restrict__ k,
+                                         const float* __restrict__ v, int64_t ld, const float* __restrict__ o, const float* __restrict__ dout,
+                                         int64_t ldo, const float* __restrict__ lse, float* __restrict__ delta, float* __restrict__ dq,
+                                         int64_t ldd, float scale, int nh, int mb, const float2* __restrict__ rope) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const Block blk = block_of(nh, mb);
+  const Block blk = block_of(block, nh, mb);
   const int q0 = ((S + 15) / 16 - 1 - blk.rank) * 16, my_q = q0 + (lane & 15);
   const int64_t tok0 = (int64_t)blk.b * S;
   const Head hq = head_of(q + tok0 * ld + blk.h * dd, ld, S, dd), hk = head_of(k + tok0 * ld + blk.h * dd, ld, S, dd),
@@ -332,8 +338,8 @@ __global__ __launch_bounds__(64 * KW) void attn_bwd_dq_f32_kernel(int S, int dd,
     }
   }
   f32x4 out[DS / KW];
-  merge<DS>(out, red, acc, wave, lane);
-  const unsigned redo = rows_of(masks, my_q < S && li == li && dlt == dlt ? mark_of<DS>(out) : 0.f, wave);
+  merge<DS>(out, lds.red, acc, wave, lane);
+  const unsigned redo = rows_of(lds.masks, my_q < S && li == li && dlt == dlt ? mark_of<DS>(out) : 0.f, wave);
 #pragma unroll
   for (int i = 0; i < DS / KW; ++i) {
     const int col = quad_col(KW * i + wave, lane);
@@ -344,39 +350,61 @@ __global__ __launch_bounds__(64 * KW) void attn_bwd_dq_f32_kernel(int S, int dd,
   }
   if (__builtin_expect(redo != 0, 0)) {
     const int64_t at = tok0 * ld + blk.h * dd;
-    redo_dq_rows<DS>(rowbuf[wave], redo, q0, dd, q + at, k + at, v + at, ld, dout + tok0 * ldo + blk.h * dd, ldo, li, dlt, scale,
+    redo_dq_rows<DS>(lds.rowbuf[wave], redo, q0, dd, q + at, k + at, v + at, ld, dout + tok0 * ldo + blk.h * dd, ldo, li, dlt, scale,
                      rope, dq + tok0 * ldd + blk.h * dd, ldd);
   }
 }
 
-// ------------------------------------------------------------------------------------------ dK, dV
 template <int DS, int NBUF>
+__global__ __launch_bounds__(64 * KW) void attn_bwd_dq_f32_kernel(int S, int dd, const float* __restrict__ q, const float* __restrict__ k,
+                                                                 const float* __restrict__ v, int64_t ld, const float* __restrict__ o,
+                                                                 const float* __restrict__ dout, int64_t ldo,
+                                                                 const float* __restrict__ lse, float* __restrict__ delta,
+                                                                 float* __restrict__ dq, int64_t ldd, float scale, int nh, int mb,
+                                                                 const float2* __restrict__ rope) {
+  __shared__ BwdLds<DS> lds;
+  dq_block<DS, NBUF>(lds, blockIdx.x, S, dd, q, k, v, ld, o, dout, ldo, lse, delta, dq, ldd, scale, nh, mb, rope);
+}
+
+// ------------------------------------------------------------------------------------------ dK, dV
+// QBUF > 0: dQ (with QBUF buffers) and dK/dV in one launch, for grids that leave CUs idle when they run one after the other: the
+// blocks from dkv_blocks on are dQ's.  No block reads what another one writes: delta of a tile's rows is formed here from dO and
+// the same rows of O, in dQ's order of additions, instead of read.
+template <int DS, int NBUF, int QBUF>
 __global__ __launch_bounds__(64 * KW) void attn_bwd_dkv_f32_kernel(int S, int dd, const float* __restrict__ q, const float* __restrict__ k,
                                                                   const float* __restrict__ v, int64_t ld,
                                                                   const float* __restrict__ dout, int64_t ldo,
                                                                   const float* __restrict__ lse, const float* __restrict__ delta,
                                                                   float* __restrict__ dk, float* __restrict__ dv, int64_t ldd, float scale,
-                                                                  int nh, int mb, const float2* __restrict__ rope) {
-  __shared__ f32x4 red[(KW - 1) * DS * 64];
-  __shared__ float rowbuf[KW][32 * DS];   // rows that are redone
-  __shared__ unsigned masks[KW];
+                                                                  int nh, int mb, const float2* __restrict__ rope, int dkv_blocks,
+                                                                  const float* __restrict__ o, float* __restrict__ delta_out, float* __restrict__ dq) {
+  constexpr bool BOTH = QBUF > 0;
+  constexpr int R = BOTH ? 3 : 2, KSTEPS = 2 * R, STEPS = KSTEPS + 4;   // steps by k of 16 rows, of a tile, and all of a tile
+  static_assert(STEPS % NBUF == 0, "a tile ends with the buffer before the one it began with");
+  __shared__ BwdLds<DS> lds;
+  if constexpr (BOTH)
+    if ((int)blockIdx.x >= dkv_blocks) {
+      dq_block<DS, QBUF>(lds, blockIdx.x - dkv_blocks, S, dd, q, k, v, ld, o, dout, ldo, lse, delta_out, dq, ldd, scale, nh, mb, rope);
+      return;
+    }
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const Block blk = block_of(nh, mb);
+  const Block blk = block_of(blockIdx.x, nh, mb);
   const int k0 = blk.rank * 16, my_k = k0 + (lane & 15);
   const int64_t tok0 = (int64_t)blk.b * S;
   const Head hq = head_of(q + tok0 * ld + blk.h * dd, ld, S, dd), hk = head_of(k + tok0 * ld + blk.h * dd, ld, S, dd),
-             hv = head_of(v + tok0 * ld + blk.h * dd, ld, S, dd), hdo = head_of(dout + tok0 * ldo + blk.h * dd, ldo, S, dd);
+             hv = head_of(v + tok0 * ld + blk.h * dd, ld, S, dd), hdo = head_of(dout + tok0 * ldo + blk.h * dd, ldo, S, dd),
+             ho = BOTH ? head_of(o + tok0 * ldo + blk.h * dd, ldo, S, dd) : hdo;
   const float* lse_h = lse + ((int64_t)blk.b * nh + blk.h) * S;
-  const float* dlt_h = delta + ((int64_t)blk.b * nh + blk.h) * S;
+  const float* dlt_h = BOTH ? nullptr : delta + ((int64_t)blk.b * nh + blk.h) * S;
   f32x4 kf[DS], vf[DS], dka[DS], dva[DS], buf[NBUF][DS];
   load_k<DS>(kf, hk, k0, lane, dd);
   load_k<DS>(vf, hv, k0, lane, dd);
 #pragma unroll
   for (int s = 0; s < DS; ++s) dka[s] = dva[s] = f32x4{0.f, 0.f, 0.f, 0.f};
-  // order of use: Q, dO of rows 0-15 by k, the same of rows 16-31, then by columns dO, Q of rows 0-15 and of rows 16-31
+  // order of use: Q, dO (BOTH: and O) of rows 0-15 by k, the same of rows 16-31, then by columns dO, Q of rows 0-15 and of rows 16-31
   auto load = [&](f32x4 (&f)[DS], int step, int tile) {
-    const int row0 = tile * TK + 16 * ((step >> 1) & 1);
-    if (step < 4) load_k<DS>(f, step & 1 ? hdo : hq, row0, lane, dd); else load_r<DS>(f, step & 1 ? hq : hdo, row0, lane, dd);
+    if (step < KSTEPS) load_k<DS>(f, step % R == 0 ? hq : step % R == 1 ? hdo : ho, tile * TK + 16 * (step / R), lane, dd);
+    else load_r<DS>(f, (step - KSTEPS) & 1 ? hq : hdo, tile * TK + 16 * ((step - KSTEPS) >> 1), lane, dd);
   };
   const int first = k0 / TK + wave, tiles = (S + TK - 1) / TK;
   if (first < tiles) {
@@ -391,35 +419,47 @@ __global__ __launch_bounds__(64 * KW) void attn_bwd_dkv_f32_kernel(int S, int dd
         for (int r = 0; r < 4; ++r) {
           const int i = min(t * TK + 16 * ib + 4 * (lane >> 4) + r, S - 1);
           li[ib][r] = lse_h[i];
-          di[ib][r] = dlt_h[i];
+          if (!BOTH) di[ib][r] = dlt_h[i];
         }
+      f32x4 dp;
 #pragma unroll
-      for (int step = 0; step < 8; ++step) {
+      for (int step = 0; step < STEPS; ++step) {
+        const int ib = step / R;
+        if (BOTH && step < KSTEPS && step % R == 2) {   // before the load into the buffer of dO
+          float x = 0.f;
+#pragma unroll
+          for (int s = 0; s < DS; ++s)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) x = fmaf(buf[(step - 1) % NBUF][s][e], buf[step % NBUF][s][e], x);
+          x = over_groups_sum(x);                        // row l%16
+#pragma unroll
+          for (int r = 0; r < 4; ++r) di[ib][r] = __shfl(x, 4 * (lane >> 4) + r, 64);
+        }
         const int ahead = step + NBUF - 1;
-        load(buf[ahead % NBUF], ahead % 8, ahead < 8 ? t : t + KW);
-        if (step < 4) {
-          const int ib = step >> 1;
-          if (!(step & 1)) { p[ib] = dot<DS>(buf[step % NBUF], kf); continue; }
-          const f32x4 dp = dot<DS>(buf[step % NBUF], vf);
+        load(buf[ahead % NBUF], ahead % STEPS, ahead < STEPS ? t : t + KW);
+        if (step < KSTEPS) {
+          if (step % R == 0) { p[ib] = dot<DS>(buf[step % NBUF], kf); continue; }
+          if (step % R == 1) dp = dot<DS>(buf[step % NBUF], vf);
+          if (step % R != R - 1) continue;
           const int i0 = t * TK + 16 * ib + 4 * (lane >> 4);
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
             p[ib][r] = i0 + r < my_k || i0 + r >= S ? 0.f : expf(fmaf(p[ib][r], scale, -li[ib][r]));
             ds[ib][r] = i0 + r < my_k || i0 + r >= S ? 0.f : p[ib][r] * (dp[r] - di[ib][r]);
           }
-        } else if (!(step & 1)) {
-          add_weighted<DS>(dva, buf[step % NBUF], p[(step - 4) >> 1]);
+        } else if (!((step - KSTEPS) & 1)) {
+          add_weighted<DS>(dva, buf[step % NBUF], p[(step - KSTEPS) >> 1]);
         } else {
-          add_weighted<DS>(dka, buf[step % NBUF], ds[(step - 4) >> 1]);
+          add_weighted<DS>(dka, buf[step % NBUF], ds[(step - KSTEPS) >> 1]);
         }
       }
     }
   }
   f32x4 outv[DS / KW], outk[DS / KW];
-  merge<DS>(outv, red, dva, wave, lane);
+  merge<DS>(outv, lds.red, dva, wave, lane);
   __syncthreads();   // the second merge reuses the buffer
-  merge<DS>(outk, red, dka, wave, lane);
-  const unsigned redo = rows_of(masks, my_k < S ? mark_of<DS>(outv) + mark_of<DS>(outk) : 0.f, wave);
+  merge<DS>(outk, lds.red, dka, wave, lane);
+  const unsigned redo = rows_of(lds.masks, my_k < S ? mark_of<DS>(outv) + mark_of<DS>(outk) : 0.f, wave);
 #pragma unroll
   for (int i = 0; i < DS / KW; ++i) {
     const int col = quad_col(KW * i + wave, lane);
@@ -432,8 +472,8 @@ __global__ __launch_bounds__(64 * KW) void attn_bwd_dkv_f32_kernel(int S, int dd
   }
   if (__builtin_expect(redo != 0, 0)) {
     const int64_t at = tok0 * ld + blk.h * dd;
-    redo_dkv_rows<DS>(rowbuf[wave], redo, k0, S, dd, q + at, k + at, v + at, ld, dout + tok0 * ldo + blk.h * dd, ldo, lse_h, dlt_h,
-                      scale, rope, dk + tok0 * ldd + blk.h * dd, dv + tok0 * ldd + blk.h * dd, ldd);
+    redo_dkv_rows<DS>(lds.rowbuf[wave], redo, k0, S, dd, q + at, k + at, v + at, ld, dout + tok0 * ldo + blk.h * dd, ldo, lse_h, dlt_h,
+                      BOTH ? o + tok0 * ldo + blk.h * dd : nullptr, scale, rope, dk + tok0 * ldd + blk.h * dd, dv + tok0 * ldd + blk.h * dd, ldd);
   }
 }
 
@@ -461,19 +501,26 @@ hipError_t attn_fwd_f32(hipStream_t st, int mb, int S, int nh, int d, const void
 hipError_t attn_bwd_f32(hipStream_t st, int mb, int S, int nh, int d, const void* q, const void* k, const void* v, int64_t ld,
                         const void* o, const void* dout, int64_t ldo, const float* lse, float* delta, void* dq, void* dk, void* dv,
                         int64_t ldd, const float2* rope) {
-  dim3 grid((unsigned)(cdiv(S, 16) * nh * mb)), blk(64 * KW);
+  const int64_t blocks = cdiv(S, 16) * nh * mb;
   const float scale = 1.0f / sqrtf((float)d);
-  if (d <= 64) {
-    hipLaunchKernelGGL((attn_bwd_dq_f32_kernel<4, 6>), grid, blk, 0, st, S, d, (const float*)q, (const float*)k, (const float*)v, ld,
-                       (const float*)o, (const float*)dout, ldo, lse, delta, (float*)dq, ldd, scale, nh, mb, rope);
-    hipLaunchKernelGGL((attn_bwd_dkv_f32_kernel<4, 8>), grid, blk, 0, st, S, d, (const float*)q, (const float*)k, (const float*)v, ld,
-                       (const float*)dout, ldo, lse, delta, (float*)dk, (float*)dv, ldd, scale, nh, mb, rope);
-  } else {
-    hipLaunchKernelGGL((attn_bwd_dq_f32_kernel<8, 3>), grid, blk, 0, st, S, d, (const float*)q, (const float*)k, (const float*)v, ld,
-                       (const float*)o, (const float*)dout, ldo, lse, delta, (float*)dq, ldd, scale, nh, mb, rope);
-    hipLaunchKernelGGL((attn_bwd_dkv_f32_kernel<8, 4>), grid, blk, 0, st, S, d, (const float*)q, (const float*)k, (const float*)v, ld,
-                       (const float*)dout, ldo, lse, delta, (float*)dk, (float*)dv, ldd, scale, nh, mb, rope);
+  const float *qp = (const float*)q, *kp = (const float*)k, *vp = (const float*)v, *op = (const float*)o, *dop = (const float*)dout;
+  float *dqp = (float*)dq, *dkp = (float*)dk, *dvp = (float*)dv;
+  const dim3 blk(64 * KW);
+  // Together up to 256 blocks, a CU each for every kernel's: the time is that of dK/dV and what dQ finds free beside it.  Separate :
+  // together, us: S = 256, 4 heads of 128 (64 blocks) 38 : 26; S = 512, 8 of 128 (256) 61 : 52, 8 of 64 36 : 31; S = 1024, 4 of 128 (256) 105 : 81; S = 128, 30
+  // of 64 (240) 18.0 : 17.2; S = 512, 2 x 6 of 128 (384) 77 : 75, 2 x 8 (512) 86 : 95.
+  if (blocks <= 256) {
+    auto kern = d <= 64 ? attn_bwd_dkv_f32_kernel<4, 10, 6> : attn_bwd_dkv_f32_kernel<8, 5, 3>;
+    hipLaunchKernelGGL(kern, dim3((unsigned)(2 * blocks)), blk, 0, st, S, d, qp, kp, vp, ld, dop, ldo, lse, nullptr, dkp, dvp, ldd, scale, nh, mb,
+                       rope, (int)blocks, op, delta, dqp);
+    return hipGetLastError();
   }
+  const dim3 grid((unsigned)blocks);
+  auto kern_dq = d <= 64 ? attn_bwd_dq_f32_kernel<4, 6> : attn_bwd_dq_f32_kernel<8, 3>;
+  auto kern_dkv = d <= 64 ? attn_bwd_dkv_f32_kernel<4, 8, 0> : attn_bwd_dkv_f32_kernel<8, 4, 0>;
+  hipLaunchKernelGGL(kern_dq, grid, blk, 0, st, S, d, qp, kp, vp, ld, op, dop, ldo, lse, delta, dqp, ldd, scale, nh, mb, rope);
+  hipLaunchKernelGGL(kern_dkv, grid, blk, 0, st, S, d, qp, kp, vp, ld, dop, ldo, lse, delta, dkp, dvp, ldd, scale, nh, mb, rope, 0, nullptr, nullptr,
+                     nullptr);
   return hipGetLastError();
 }
 

@@ -308,7 +308,7 @@ __device__ __attribute__((noinline)) void redo_dkv_rows(char* smem, int groups, 
       for (int c = lane; c < dd; c += 64) dkh[to + c] = dvh[to + c] = (e16)NAN;
       return;
     }
-    attn_dkv_row<2>(rl.rows[wave], j, S, dd, qh, kh, vh, ld, doh, ldo, lse_h, dlt_h, scale, lane, [&](int c, float xk, float xv) {
+    attn_dkv_row<2>(rl.rows[wave], j, S, dd, qh, kh, vh, ld, doh, ldo, lse_h, [&](int i) { return dlt_h[i]; }, scale, lane, [&](int c, float xk, float xv) {
       dkh[to + c] = (e16)(rope ? unrotate_column(xk, rope, j, c, dd) : xk);
       dvh[to + c] = (e16)xv;
     });

@@ -97,12 +97,12 @@ __device__ __forceinline__ void attn_dq_row(float* rows, int i, int d, const T* 
     if (c * 64 + lane < d) out(c * 64 + lane, acc[c] * scale);
 }
 
-// dv_j = sum_{i>=j} p_ij do_i,  dk_j = scale * sum_{i>=j} ds_ij q_i: out(c, dk[j][c], dv[j][c]).  lse, delta: the head's rows.
+// dv_j = sum_{i>=j} p_ij do_i,  dk_j = scale * sum_{i>=j} ds_ij q_i: out(c, dk[j][c], dv[j][c]).  lse: the head's rows, delta(i): row i's.
 // rows: LDS of the wave's own, 128 NC floats.
-template <int NC, typename T, typename F>
+template <int NC, typename T, typename Delta, typename F>
 __device__ __forceinline__ void attn_dkv_row(float* rows, int j, int S, int d, const T* __restrict__ q, const T* __restrict__ k,
                                              const T* __restrict__ v, int64_t ld, const T* __restrict__ dout, int64_t ldo,
-                                             const float* __restrict__ lse, const float* __restrict__ delta, float scale, int lane,
+                                             const float* __restrict__ lse, Delta&& delta, float scale, int lane,
                                              F&& out) {
   float *ks = rows, *vs = rows + 64 * NC;
   for (int c = lane; c < d; c += 64) {
@@ -120,7 +120,7 @@ __device__ __forceinline__ void attn_dkv_row(float* rows, int j, int S, int d, c
       const float s = dot_row(ks, q + (int64_t)i * ld, d);
       const float dp = dot_row(vs, dout + (int64_t)i * ldo, d);
       p = expf(s - lse[i]);
-      ds = p * (dp - delta[i]);
+      ds = p * (dp - delta(i));
     }
     const int in = min(64, S - i0);
     for (int ii = 0; ii < in; ++ii) {

@@ -69,7 +69,7 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_simple(int S, int d, const T
   const int h = blockIdx.y, b = blockIdx.z, nh = gridDim.y;
   if (j >= S) return;
   const int64_t tok0 = (int64_t)b * S, at = tok0 * ld + h * d, stat = ((int64_t)b * nh + h) * S, to = (tok0 + j) * ldd + h * d;
-  attn_dkv_row<MAXD / 64>(rows[w], j, S, d, q + at, k + at, v + at, ld, dout + tok0 * ldo + h * d, ldo, lse + stat, delta + stat, scale,
+  attn_dkv_row<MAXD / 64>(rows[w], j, S, d, q + at, k + at, v + at, ld, dout + tok0 * ldo + h * d, ldo, lse + stat, [&](int i) { return delta[stat + i]; }, scale,
                           lane, [&](int c, float xk, float xv) { dk[to + c] = from_f<T>(xk); dv[to + c] = from_f<T>(xv); });
 }
 
