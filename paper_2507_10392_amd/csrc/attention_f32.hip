@@ -10,7 +10,7 @@
 // in register r, which is the operand layout that step e = r of the second product wants, so P never moves between lanes.
 // The loads of a tile run one tile-quarter (or more, registers permitting) ahead of their use.
 //
-// Measured, forward + backward, against the wave-per-row kernel: 8 heads of 64, S = 128: 91 -> 30 us; 4 heads of 128, S = 256:
+// Measured, forward + backward in three launches, against the wave-per-row kernel: 8 heads of 64, S = 128: 91 -> 30 us; 4 heads of 128, S = 256:
 // 273 -> 51 us; 16 heads of 64, S = 1000: 2080 -> 188 us; the errors against float64 are smaller (dk 8.1e-7 -> 4.8e-7).
 #include "kernels.h"
 #include "attention_rows.h"
