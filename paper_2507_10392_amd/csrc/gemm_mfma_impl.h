@@ -582,17 +582,18 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BM * BN <= 128 * 128) ? 2 : 1)
     // Waves with 4 rows of blocks have registers for the fragments of a whole half slab (32 k) ahead, so the barrier stands
     // between a slab's halves: behind it the next slab is complete in LDS and this slab's fragments are all in registers.
     // This multiplies the half whose fragments are in a[ks], b[ks].  Meanwhile the fragments of the next half are read from
-    // LDS (`buf`, its half ks ^ 1), and the vectors of fa (part 0) or fb (part 1) go to LDS buffer `to` and are loaded again.
-    auto half_slab = [&](int ks, int buf, int to, Frag<BM, NT>& fa, Frag<BN, NT>& fb, int part) {
+    // LDS (`buf`, its half ks ^ 1; read), and the vectors of fa (part 0) or fb (part 1) go to LDS buffer `to` (stash) and are
+    // loaded again (more).
+    auto half_slab = [&](int ks, int buf, int to, Frag<BM, NT>& fa, Frag<BN, NT>& fb, int part, bool read, bool stash, bool more) {
       const bf16* As = smem + buf * (SLAB_A + SLAB_B);
       const bf16* Bs = As + SLAB_A;
       const int nx = ks ^ 1, k32 = nx * 32;
 #pragma unroll
       for (int e = 0; e < MI; ++e) {
-        if (e == 0) {
+        if (e == 0 && read) {
 #pragma unroll
           for (int j = 0; j < NJ; ++j) b[nx][j] = TB == 1 ? frag_kmajor(Bs, wn + j * 16, k32, lane) : frag_rmajor<BN>(Bs, wn + j * 16, k32, lane);
-        } else if (e == 1) {
+        } else if (e == 1 && read) {
 #pragma unroll
           for (int i = 0; i < MI; ++i) a[nx][i] = TA == 0 ? frag_kmajor(As, wm + i * 16, k32, lane) : frag_rmajor<BM>(As, wm + i * 16, k32, lane);
         }
@@ -601,12 +602,40 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BM * BN <= 128 * 128) ? 2 : 1)
         for (int j = 0; j < NJ; ++j) acc[e][j] = mfma_16x16x32<E>(b[ks][j], a[ks][e], acc[e][j]);
         const int i0 = e * (part ? VB : VA) / 4, i1 = (e + 1) * (part ? VB : VA) / 4;
         const int a0 = part ? 0 : i0, a1 = part ? 0 : i1, b0 = part ? i0 : 0, b1 = part ? i1 : 0;
-        stash_a(to, fa, a0, a1);
-        stash_b(to, fb, b0, b1);
+        if (stash) {
+          stash_a(to, fa, a0, a1);
+          stash_b(to, fb, b0, b1);
+        }
         __builtin_amdgcn_sched_barrier(0);
-        fetch(fa, fb, a0, a1, b0, b1);
+        if (more) fetch(fa, fb, a0, a1, b0, b1);
         __builtin_amdgcn_sched_barrier(0);
       }
+    };
+    // From slab 0 in LDS to the fragments of its first half in registers and slab 1's part of A in LDS.
+    auto begin = [&](bool more) {
+      if (STAGES == 1 || more) fetch(fa[0], fb[0], 0, VA, 0, VB);
+      advance(STAGES == 1);
+      __syncthreads();
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) b[0][j] = TB == 1 ? frag_kmajor(smem + SLAB_A, wn + j * 16, 0, lane) : frag_rmajor<BN>(smem + SLAB_A, wn + j * 16, 0, lane);
+#pragma unroll
+      for (int i = 0; i < MI; ++i) a[0][i] = TA == 0 ? frag_kmajor(smem, wm + i * 16, 0, lane) : frag_rmajor<BM>(smem, wm + i * 16, 0, lane);
+      stash_a(1, fa[1 % STAGES]);
+      if (more) fetch(fa[1 % STAGES], fb[1 % STAGES], 0, VA, 0, 0);
+    };
+    // A pair of slabs; pairs: how many follow, 2: two or more.
+    auto pair = [&](int pairs) {
+      const bool next = pairs > 0, more = pairs > 1;
+      half_slab(0, 0, 1, fa[1 % STAGES], fb[1 % STAGES], 1, true, true, next);
+      advance(STAGES == 2);
+      __syncthreads();
+      half_slab(1, 1, 0, fa[0], fb[0], 0, true, next, more);
+      half_slab(0, 1, 0, fa[0], fb[0], 1, true, next, more);
+      if (next) {
+        advance(STAGES == 1);
+        __syncthreads();
+      }
+      half_slab(1, 0, 1, fa[1 % STAGES], fb[1 % STAGES], 0, next, next, more);
     };
 #pragma unroll
     for (int i = 0; i < STAGES; ++i) {
@@ -615,24 +644,21 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BM * BN <= 128 * 128) ? 2 : 1)
     }
     stash_a(0, fa[0]);
     stash_b(0, fb[0]);
-    fetch(fa[0], fb[0], 0, VA, 0, VB);
-    advance(STAGES == 1);
-    __syncthreads();
-#pragma unroll
-    for (int j = 0; j < NJ; ++j) b[0][j] = TB == 1 ? frag_kmajor(smem + SLAB_A, wn + j * 16, 0, lane) : frag_rmajor<BN>(smem + SLAB_A, wn + j * 16, 0, lane);
-#pragma unroll
-    for (int i = 0; i < MI; ++i) a[0][i] = TA == 0 ? frag_kmajor(smem, wm + i * 16, 0, lane) : frag_rmajor<BM>(smem, wm + i * 16, 0, lane);
-    stash_a(1, fa[1 % STAGES]);
-    fetch(fa[1 % STAGES], fb[1 % STAGES], 0, VA, 0, 0);
-    for (int kt = 0; kt < nk; kt += 2) {
-      half_slab(0, 0, 1, fa[1 % STAGES], fb[1 % STAGES], 1);
-      advance(STAGES == 2);
-      __syncthreads();
-      half_slab(1, 1, 0, fa[0], fb[0], 0);
-      half_slab(0, 1, 0, fa[0], fb[0], 1);
-      advance(STAGES == 1);
-      __syncthreads();
-      half_slab(1, 0, 1, fa[1 % STAGES], fb[1 % STAGES], 0);
+    if constexpr (STAGES == 2) {
+      // Slabs past the end cost their loads' issue (16 cycles per wave) although they read zeros, so the last two pairs of slabs
+      // load none.  us on 128x128 tiles, 694 x 6888 (x W^T), with loads up to the fourth slab past the end : up to the end: K = 64
+      // 9.6 : 8.4, K = 256 10.9 : 10.5, K = 1024 19.3 : 18.9.  The other tiles have no registers for further bodies.
+      if (nk > 2) {
+        begin(true);
+        for (int kt = 0; kt + 4 < nk; kt += 2) pair(2);
+        pair(1);
+      } else {
+        begin(false);
+      }
+      pair(0);
+    } else {
+      begin(true);
+      for (int kt = 0; kt < nk; kt += 2) pair(2);
     }
   } else {
     fetch(fa[0], fb[0], 0, VA, 0, VB);
