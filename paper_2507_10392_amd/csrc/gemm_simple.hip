@@ -219,8 +219,8 @@ GemmRoute gemm_route(DType dt, const Gemm& g) {
   return route_one(dt, p, GEMM_AUTO);
 }
 
-// Products that leave most of the chip idle cost a launch, a walk over K and a store each; in one grid they cost the longest.  A
-// group of 16-bit products has to win 10 % by the estimates.
+// Products that leave most of the chip idle cost a launch, a walk over K and a store each; in one grid they cost the longest.  fp32: by
+// gemm_f32_group_pays; a group of 16-bit products has to win 10 % by the estimates.
 GemmRoute gemm_group_route(DType dt, const Gemm* g, int n) {
   if (n < 2 || n > GEMM_GROUP_MAX) return ROUTE_SIMPLE;
   double us = 0.0;
@@ -237,7 +237,8 @@ GemmRoute gemm_group_route(DType dt, const Gemm* g, int n) {
     us += gemm_small_tile(g[i], &own) ? own : gemm_mfma_us(g[i]);
   }
   if (blocks >= (1ll << 31)) return ROUTE_SIMPLE;
-  return dt == F32 ? ROUTE_F32 : gemm_small_group_us(g, n) < 0.9 * us ? ROUTE_SMALL : ROUTE_SIMPLE;
+  if (dt == F32) return gemm_f32_group_pays(g, n) ? ROUTE_F32 : ROUTE_SIMPLE;
+  return gemm_small_group_us(g, n) < 0.9 * us ? ROUTE_SMALL : ROUTE_SIMPLE;
 }
 
 hipError_t gemm_group(hipStream_t st, DType dt, const Gemm* g, int n) {

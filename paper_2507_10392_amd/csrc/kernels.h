@@ -112,6 +112,7 @@ hipError_t gemm_simple(hipStream_t st, DType dt, const Gemm& g);
 // fp32 products on the fp32 matrix cores (gemm_f32.hip); no multi-part K range, no gated unit.
 bool gemm_f32_supported(const Gemm& g);
 hipError_t gemm_f32(hipStream_t st, const Gemm& g);
+bool gemm_f32_group_pays(const Gemm* g, int n);
 hipError_t gemm_f32_group(hipStream_t st, const Gemm* g, int n);
 // What the 16-bit MFMA kernel takes (the dispatcher's rule), and the narrower set (K a multiple of 8) for which a caller may
 // force it.

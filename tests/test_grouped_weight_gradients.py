@@ -34,3 +34,18 @@ def test_grouped_weight_gradients_match_the_oracle(gpu_device, name, changes):
     tn = {k: v["launches"] for k, v in rows.items() if "_tn" in k}
     assert sum(tn.values()) == per_layer + (2 if cfg.has_head else 0), tn
     compare_step(cfg, gpu, oracle_step(cfg, inp, M=2), TOL[cfg.dtype])
+
+
+# fp32 layers whose products fill their rounds of 128x128 tiles keep them: grouped, on smaller tiles, they are slower
+@pytest.mark.parametrize("seq,launches", [(256, 1), (640, 4)])
+def test_fp32_layers_that_fill_their_rounds_are_not_grouped(gpu_device, seq, launches):
+    cfg = get_config("C1").with_(layers=1, hidden=2048, heads=16, ffn=8192, seq=seq, microbatch=1, num_microbatches=1)
+    print(f"[case] fp32 weight gradients, hidden 2048, {seq} tokens", flush=True)
+    inp = make_inputs(cfg, perturbed=True, num_microbatches=1)
+    g = GpuStage(cfg, inp, max_microbatches=1)
+    g.stage.profile(True)
+    gpu = g.run_microbatches(inp, M=1)
+    rows = g.stage.profile_read()
+    g.stage.close()
+    assert rows["gemm_f32_tn"]["launches"] == launches, rows
+    compare_step(cfg, gpu, oracle_step(cfg, inp, M=1), TOL[cfg.dtype])
