@@ -110,7 +110,8 @@ int stage_op_swiglu(void* stream, int32_t dtype, int32_t T, int32_t F, const voi
  * exception are 16-bit heads of 128 (impl 0 and 2), where it also reaches rows of the same tile that do not see the token. */
 int stage_op_attention_fwd(void* stream, int32_t dtype, int32_t mb, int32_t S, int32_t nh, int32_t d, const void* q,
                            const void* k, const void* v, int64_t ld, void* o, int64_t ldo, float* lse, int32_t impl);
-/* Gradients dq, dk, dv (row stride ldd) from dout; delta: float[mb,nh,S] scratch. */
+/* Gradients dq, dk, dv (row stride ldd) from dout; delta: float[mb,nh,S] scratch.  Each of them may lie over o, which is lost then;
+ * otherwise no output overlaps an input or another output. */
 int stage_op_attention_bwd(void* stream, int32_t dtype, int32_t mb, int32_t S, int32_t nh, int32_t d, const void* q,
                            const void* k, const void* v, int64_t ld, const void* o, const void* dout, int64_t ldo,
                            const float* lse, float* delta, void* dq, void* dk, void* dv, int64_t ldd, int32_t impl);

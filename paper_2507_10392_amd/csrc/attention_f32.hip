@@ -509,7 +509,7 @@ hipError_t attn_bwd_f32(hipStream_t st, int mb, int S, int nh, int d, const void
   // Together up to 256 blocks, a CU each for every kernel's: the time is that of dK/dV and what dQ finds free beside it.  Separate :
   // together, us: S = 256, 4 heads of 128 (64 blocks) 38 : 26; S = 512, 8 of 128 (256) 61 : 52, 8 of 64 36 : 31; S = 1024, 4 of 128 (256) 105 : 81; S = 128, 30
   // of 64 (240) 18.0 : 17.2; S = 512, 2 x 6 of 128 (384) 77 : 75, 2 x 8 (512) 86 : 95.
-  if (blocks <= 256) {
+  if (blocks <= 256 && attn_bwd_apart((int64_t)mb * S, 4ll * nh * d, k, v, 4 * ld, o, 4 * ldo, dq, dk, dv, 4 * ldd)) {
     auto kern = d <= 64 ? attn_bwd_dkv_f32_kernel<4, 10, 6> : attn_bwd_dkv_f32_kernel<8, 5, 3>;
     hipLaunchKernelGGL(kern, dim3((unsigned)(2 * blocks)), blk, 0, st, S, d, qp, kp, vp, ld, dop, ldo, lse, nullptr, dkp, dvp, ldd, scale, nh, mb,
                        rope, (int)blocks, op, delta, dqp);

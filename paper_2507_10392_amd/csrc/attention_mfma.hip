@@ -935,7 +935,8 @@ hipError_t bwd_128(hipStream_t st, int mb, int S, int nh, int d, const void* q, 
   } else {
     const int64_t per_head = cdiv(S, 128), blocks = per_head * nh * mb;
     if constexpr (!SPLIT && D == 128)
-      if (!wide_dkv && blocks <= (per_head == 1 ? 128 : per_head < 4 ? 192 : 256))
+      if (!wide_dkv && blocks <= (per_head == 1 ? 128 : per_head < 4 ? 192 : 256) &&
+          attn_bwd_apart((int64_t)mb * S, 2ll * nh * d, k, v, 2 * ld, o, 2 * ldo, dq, dk, dv, 2 * ldd))
         return launch_bwd<D>(st, mb, S, nh, q, k, v, ld, o, dout, ldo, lse, delta, dq, dk, dv, ldd, rope);
     const hipError_t e = S > 256 && blocks < 512 && blocks <= 256 + 28 * (per_head > 6 ? per_head - 6 : 0)
                              ? launch_dq<8, 2, D, SPLIT>(st, mb, S, nh, d, q, k, v, ld, o, dout, ldo, lse, delta, dq, ldd, rope)

@@ -3,6 +3,8 @@
 #pragma once
 #include "common.h"
 
+#include <initializer_list>
+
 namespace zs {
 
 // C[M,N] (op)= sum_k A(m,k) * B(k,n)  (+ bias[n]) (+ R[m,n])
@@ -182,6 +184,21 @@ hipError_t swiglu_bwd(hipStream_t st, DType dt, int T, int F, const void* gu, co
 // buffer with row stride ld (elements); token t = b*S + s.  lse is float[mb, nh, S].
 enum AttnImpl { ATTN_AUTO = 0, ATTN_SIMPLE = 1, ATTN_MFMA = 2 };
 int attn_select(DType dt, int S, int d, int force);
+// Whether dQ and dK/dV may run side by side: no gradient lies over k, v or o, which both read.  One after the other they may take the
+// place of o, and dk and dv that of k and v: dQ reads its own rows of o before it writes them, and dK/dV reads no o and its own rows
+// of k and v only.  rows: of every block, w: bytes of a row, strides in bytes.
+inline bool attn_blocks_apart(const void* a, int64_t lda, const void* b, int64_t ldb, int64_t rows, int64_t w) {
+  const int64_t d = (int64_t)((intptr_t)b - (intptr_t)a);
+  if (d >= (rows - 1) * lda + w || -d >= (rows - 1) * ldb + w) return true;
+  const int64_t col = lda == ldb ? (d % lda + lda) % lda : 0;   // blocks of one matrix, side by side
+  return col >= w && lda - col >= w;
+}
+inline bool attn_bwd_apart(int64_t rows, int64_t w, const void* k, const void* v, int64_t ld, const void* o, int64_t ldo, const void* dq,
+                           const void* dk, const void* dv, int64_t ldd) {
+  for (const void* g : {dq, dk, dv})
+    if (!attn_blocks_apart(k, ld, g, ldd, rows, w) || !attn_blocks_apart(v, ld, g, ldd, rows, w) || !attn_blocks_apart(o, ldo, g, ldd, rows, w)) return false;
+  return true;
+}
 // The kernels behind attn_fwd and attn_bwd: a wave per row, fp32 matrix cores, 16-bit matrix cores (head dim 128, and narrower
 // heads with split probabilities).  pointers: all arguments or-ed together; strides: all row strides or-ed together.
 enum AttnRoute { ATTN_ROUTE_SIMPLE, ATTN_ROUTE_F32, ATTN_ROUTE_MFMA, ATTN_ROUTE_SPLIT };
