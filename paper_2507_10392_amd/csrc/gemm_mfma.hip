@@ -245,7 +245,7 @@ __global__ __launch_bounds__(256) void add_partials_kernel(float* C, int64_t ldc
 
 // ---- parts of K side by side ---------------------------------------------------------------------------------------
 // An input gradient over few tokens has few tiles and a long K (512 x 4096 with K = 22016: 128 tiles of 128x128, half the CUs idle,
-// and each of the others waits for cold lines of the weights).  With scratch for as many fp32 results two or four equal parts of
+// and each of the others waits for cold lines of the weights).  With scratch for as many fp32 results the two halves of
 // its K, or its segments (gate and up; Q, K and V), run as a batch, and a second kernel adds and rounds them: taken when the
 // estimate of both kernels (the second one at 4.5 TB/s) is the shorter time.  us: 512 x 4096, K = 22016 in 2 parts 176 -> 130 (128x128
 // tiles); K = 12288 in 3 segments 129 -> 82.
@@ -256,8 +256,8 @@ bool plan_parts(DType dt, const Gemm& g, Gemm& best) {
   if (tiles > 128 || g.N % 8 || ((uintptr_t)g.ws & 15)) return false;
   double us = 0.95 * gemm_mfma_us(g);
   best.batch = 1;
-  for (int n = 2; n <= 4; ++n) {
-    if (g.kseg ? (int64_t)n * g.kseg != g.K : (n == 3 || g.K % (8 * n) || n * tiles > 256)) continue;
+  for (int n = 2; n <= 3; ++n) {
+    if (g.kseg ? (int64_t)n * g.kseg != g.K : n > 2 || g.K % 16) continue;
     if (g.ws_bytes < 4ll * n * g.M * g.N) continue;
     Gemm h = g;
     h.ws = nullptr; h.ws_bytes = 0; h.kseg = 0; h.segB = 0;
@@ -293,7 +293,7 @@ __global__ __launch_bounds__(256) void add_parts_kernel(int64_t nvec, int vec_pe
 }
 template <typename E> hipError_t add_parts(hipStream_t st, const Gemm& g, int n) {
   const int64_t nvec = (int64_t)g.M * g.N / 8;
-  auto kern = n == 2 ? add_parts_kernel<E, 2> : n == 3 ? add_parts_kernel<E, 3> : add_parts_kernel<E, 4>;
+  auto kern = n == 2 ? add_parts_kernel<E, 2> : add_parts_kernel<E, 3>;
   hipLaunchKernelGGL(kern, dim3((unsigned)cdiv(nvec, 256)), dim3(256), 0, st, nvec, g.N / 8, (const float*)g.ws, (int64_t)g.M * g.N, (E*)g.C, g.ldc);
   return hipGetLastError();
 }

@@ -19,7 +19,7 @@ namespace zs {
 //             their own, part 0 from A, B and part p from Ax[p-1], Bx[p-1] (same leading dimensions and batch
 //             strides); parts 0..nx-1 have kseg rows each, the last one the remaining K - nx*kseg > 0 rows:
 //             C += sum_p A_p^T B_p in one K loop (weight gradients of several microbatches).
-//   ws != NULL (nx = 0, an input gradient): ws_bytes of scratch with which a product of few tiles and long K may run two to four
+//   ws != NULL (nx = 0, an input gradient): ws_bytes of scratch with which a product of few tiles and long K may run two or three
 //             parts of K side by side, as fp32 results in ws that a second kernel adds and rounds.
 //   ws != NULL (nx > 0): ws_bytes of scratch that the MFMA path may use when the 256x256 tiles of the product do
 //             not fill whole rounds of 256 workgroups: the tiles beyond the whole rounds (the last ones of the kernel's
@@ -101,7 +101,7 @@ enum GemmImpl { GEMM_AUTO = 0, GEMM_SIMPLE = 1, GEMM_MFMA = 2 };
 // Returns which implementation a call with these arguments runs (GEMM_SIMPLE or GEMM_MFMA).
 int gemm_select(DType dt, const Gemm& g, int force);
 hipError_t gemm(hipStream_t st, DType dt, const Gemm& g, int force);
-// The kernels behind gemm(): plain, fp32 matrix cores, 16-bit matrix cores on small tiles, on staged tiles as two halves or as more
+// The kernels behind gemm(): plain, fp32 matrix cores, 16-bit matrix cores on small tiles, on staged tiles as two halves or three
 // parts of K that a second kernel adds (see ws), and on staged tiles.  gemm_route is the
 // choice that gemm(GEMM_AUTO) makes for a call (of its first launch, where it takes several), for the names of timing classes.
 enum GemmRoute { ROUTE_SIMPLE, ROUTE_F32, ROUTE_SMALL, ROUTE_HALVES, ROUTE_PARTS, ROUTE_STAGED };
