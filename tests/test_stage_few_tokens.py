@@ -7,16 +7,16 @@ from workloads import get_config, make_inputs
 pytestmark = pytest.mark.gpu
 
 
-def run(name, hidden, heads, ffn, seq):
-    cfg = get_config(name).with_(layers=1, hidden=hidden, heads=heads, ffn=ffn, seq=seq, num_microbatches=1)
-    print(f"[case] few tokens {name} hidden={hidden} ffn={ffn} seq={seq}", flush=True)
+def run(name, hidden, heads, ffn, seq, M=1, **more):
+    cfg = get_config(name).with_(**{"layers": 1, **more}, hidden=hidden, heads=heads, ffn=ffn, seq=seq, num_microbatches=M)
+    print(f"[case] few tokens {name} hidden={hidden} ffn={ffn} seq={seq} {more}", flush=True)
     scale = 256.0 if cfg.dtype == 2 else 1.0
-    inp = make_inputs(cfg, perturbed=True, num_microbatches=1, dy_scale=scale)
-    g = GpuStage(cfg, inp, max_microbatches=1)
+    inp = make_inputs(cfg, perturbed=True, num_microbatches=M, dy_scale=scale)
+    g = GpuStage(cfg, inp, max_microbatches=M)
     g.stage.profile(True)
-    gpu = g.run_microbatches(inp, M=1)
+    gpu = g.run_microbatches(inp, M=M)
     classes = g.stage.profile_read()
-    compare_step(cfg, gpu, oracle_step(cfg, inp, M=1), TOL[cfg.dtype])
+    compare_step(cfg, gpu, oracle_step(cfg, inp, M=M), TOL[cfg.dtype])
     g.stage.close()
     return classes
 
@@ -37,3 +37,23 @@ def test_layer_on_few_tokens_against_the_oracle(gpu_device, name, hidden, heads,
 def test_input_gradients_as_two_halves_of_k(gpu_device, name, ffn, seq, products):
     classes = run(name, 2048, 16, ffn, seq)
     assert classes.get("gemm_halves_nt", {"launches": 0})["launches"] == products, sorted(classes)
+
+
+# Llama with ffn >= 2 hidden: the QKV projection's three segments run as a batch of three, whose results lie over the microbatch's
+# saved gate, up and activation; the last size's batch is on 256x128 tiles, the others' on 128x128.
+@pytest.mark.parametrize("name,hidden,heads,ffn,seq", [("C3t", 2048, 16, 5120, 640), ("C3h", 2048, 16, 6144, 600), ("C3t", 4096, 32, 8192, 320)])
+def test_input_gradient_as_three_segments(gpu_device, name, hidden, heads, ffn, seq):
+    assert run(name, hidden, heads, ffn, seq)["gemm_parts_nt"]["launches"] == 1
+
+
+# pair_wgrad, three backwards: the first one's weight gradients wait, so it keeps what they read and its QKV gradient runs in one part;
+# the second multiplies for both, the third for itself.  Recomputation: the layer's saved values are made again for each microbatch.
+@pytest.mark.parametrize("more,M,launches", [(dict(pair_wgrad=1), 3, 2), (dict(recompute=1, layers=2), 2, 4)])
+def test_three_segments_over_several_microbatches(gpu_device, more, M, launches):
+    assert run("C3t", 2048, 16, 5120, 640, M, **more)["gemm_parts_nt"]["launches"] == launches
+
+
+@pytest.mark.parametrize("name,vocab", [("C5t", 8000), ("C5h", 8016)])
+def test_lm_head_gradient_as_two_halves(gpu_device, name, vocab):
+    """The scratch lies over buffers that the layers' backward writes later.  The FFN's gradient is the other product in halves."""
+    assert run(name, 2048, 16, 2048, 640, vocab=vocab)["gemm_halves_nt"]["launches"] == 2
