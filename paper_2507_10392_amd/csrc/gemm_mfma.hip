@@ -17,7 +17,7 @@ hipError_t gemm_mfma_128x128_f16(hipStream_t st, const Gemm& g);
 
 namespace {
 bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }
-int g_force_tile = 0;   // 0 automatic; 1: 256x256, 2: 128x128 (set through gemm_mfma_force_tile); unforced also 3: 256x192, 4: 256x128
+int g_force_tile = 0;   // 0 automatic; 1: 256x256, 2: 128x128, 3: 256x192, 4: 256x128 (set through gemm_mfma_force_tile)
 }  // namespace
 
 // The kernel needs 16-byte aligned rows for its vector loads: base pointers 16-byte aligned and

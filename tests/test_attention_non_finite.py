@@ -45,8 +45,9 @@ def same(name, got, want, bar):
     assert not f.any() or np.abs(g[f] - w[f]).max() <= bar * np.abs(w[f]).max(), name
 
 
-# one block; a last block of one row; several tiles and, in 16 bits above S = 256, rows that two waves share; padded head dims
-CASES = [(0, 1, 45, 2, 64), (0, 2, 97, 1, 40), (0, 1, 161, 1, 128),
+# one block; a last block of one row; several tiles and, in 16 bits above S = 256, rows that two waves share; padded head dims.  fp32: dQ and
+# dK/dV in one launch up to 256 blocks of 16 rows, in two above (25 heads)
+CASES = [(0, 1, 45, 2, 64), (0, 2, 97, 1, 40), (0, 1, 161, 1, 128), (0, 1, 161, 25, 128), (0, 1, 170, 25, 40),
          *((t, *c) for t in (1, 2) for c in ((1, 45, 2, 64), (2, 97, 1, 40), (1, 300, 2, 64), (1, 161, 1, 96), (1, 321, 1, 104)))]
 
 
