@@ -72,6 +72,9 @@ bool gemm_mfma_takes(DType dt, const Gemm& g) {
   const int64_t nsegB = g.nx ? 1 : nseg;
   const int64_t extB = (g.transB ? (nsegB - 1) * g.segB + (int64_t)g.N * g.ldb : rowsA * g.ldb + (g.glu == 1 ? g.sB : 0)) * 2;
   if (extA >= (1ll << 30) || extB >= (1ll << 30)) return false;
+  // k-lines that fill up the last pair of slabs lie behind the descriptors, unless their offsets wrap around: few rows, far apart.
+  // (With one operand k-contiguous its zeros stand against them.)
+  if (g.transA && !g.transB && cdiv(rowsA, 128) * 128 * (g.lda > g.ldb ? g.lda : g.ldb) * 2 >= (1ll << 32)) return false;
   return true;
 }
 

@@ -52,7 +52,7 @@ def test_last_of_several_parts_with_an_odd_number_of_tokens(gpu_device, M, N, pa
     assert err <= 2e-5            # exact 16-bit products, fp32 sums: the bar of the other accumulating products
 
 
-@pytest.mark.parametrize("M,N,T,ld", [(64, 64, 3, 72 * 2 ** 20), (4096, 4096, 31, 33 * 2 ** 19)])
+@pytest.mark.parametrize("M,N,T,ld", [(64, 64, 3, 72 * 2 ** 20), (4096, 4096, 31, 33 * 2 ** 19), (64, 64, 3, 2 ** 27)])
 def test_rows_so_far_apart_that_the_tile_would_wrap_around(gpu_device, M, N, T, ld):
     """A tile's k-lines past the last token, at 32-bit byte offsets beyond 2^32, must not come back into the operand."""
     print(f"[case] wgrad with far rows M={M} N={N} T={T} ld={ld}", flush=True)
