@@ -921,7 +921,8 @@ hipError_t launch_bwd(hipStream_t st, int mb, int S, int nh, const void* q, cons
 // differ a lot in their work.  Both directions, S = 513, 98 heads (490 blocks) 83 us shared, 75 not; S = 1700, 24 heads (336 blocks)
 // 104 and 117.  Of 116 shapes with 216 to 550 blocks the rule takes the faster form but for 1.6 %.
 // Where 2 x blocks leave CUs idle, or nearly, dQ and dK/dV share a launch and the time is that of dK/dV, whose blocks then form delta
-// themselves.  Separate : together, us: 4 heads, S = 256 31.4 : 20.0; 32 heads, S = 512 45.5 : 32.9; 16 heads, S = 2048 (256 blocks) 115 :
+// themselves, with additions in another order than dQ's: fp32 sums that may differ in their last place, and 16-bit gradients that now
+// and then round the other way.  Separate : together, us: 4 heads, S = 256 31.4 : 20.0; 32 heads, S = 512 45.5 : 32.9; 16 heads, S = 2048 (256 blocks) 115 :
 // 100.  Up to 256 blocks the long sequences' unequal blocks fill one another's gaps; 288 blocks are a tie at S = 2048, 480 lose 22 %.
 // Sequences of one or two blocks have equal ones, and a second round costs what it saves: S = 128, 160 blocks 27.7 : 28.2, 240 30.4 : 33.8;
 // S = 200, 192 blocks 32.2 : 26.5, 200 33.6 : 35.9; S = 300, 252 blocks 38.3 : 39.5.

@@ -84,7 +84,8 @@ bool gemm_mfma_takes(DType dt, const Gemm& g) {
 // time is taken.  The estimate: per round of workgroups a fixed time (first loads, store) and a time per 64-wide slab, which
 // grows by 0.3 with the share of the chip at work (the clock drops); and the traffic of the result.  Constants fitted to 830
 // times of 207 products (M 256 .. 8000, N 768 .. 16000, K 64 .. 14000, the three layouts): of these the pick is on the geometric mean
-// within 0.3 % of the fastest tile, 12 % at worst.  us, bf16, 256x256 : 128x128 : 256x192 : 256x128: 2048 x 4096, K = 12288
+// within 0.3 % of the fastest tile, 12 % at worst; of 640 others, half of them with K up to 600, within 0.5 %, 18 % at worst (762 x 5904,
+// K = 312, da: 18.6 on 128x128, 15.8 on 256x128).  us, bf16, 256x256 : 128x128 : 256x192 : 256x128: 2048 x 4096, K = 12288
 // 244 : 207 : 221 : 185; 2048 x 5120, K = 12288 (dx) 248 : 310 : 219 : 349; 2048 x 6144, K = 2048 50 : 54 : 48 : 61;
 // 2048 x 2048, K = 12288 225 : 119 : 201 : 155; 4096 x 11008, K = 4096 (dx) 297 : 357 : 318 : 348.
 namespace {
@@ -199,7 +200,9 @@ bool plan_kcut(DType dt, const Gemm& g, KCut& k) {
   const double fx = kcut_round_fixed_parts(g.kseg);
   double t_now = (double)parts + fx;                                  // a whole round
   Gemm h2, t2;
-  if (rem <= 128 && rem % (tm * g.batch) == 0 && split_tail(dt, g, 1, h2, t2))   // the other way: the rest on 128x128 tiles
+  // The other way is priced in one form: remaining tiles that are whole tile columns, and at most 128, on 128x128 tiles.  What else
+  // gemm_mfma would cut along N counts as a whole round here.
+  if (rem <= 128 && rem % (tm * g.batch) == 0 && split_tail(dt, g, 1, h2, t2))
     t_now = std::min(t_now, small_rounds(cdiv(t2.M, 128) * tile_cols(t2, 128) * t2.batch) * (parts + fx));
   double best = t_now * 0.97;                                         // a cut has to win at least 3 %
   int best_cp = 0;

@@ -400,7 +400,7 @@ __device__ __forceinline__ void epilogue_glu(const Gemm& g, f32x4 (&acc)[MI][NJ]
   }
 }
 
-// NW wavefronts: 4 as a 2 x 2 grid, or 8 as 2 (m) x 4 (n), in which case two waves share each SIMD and one
+// NW wavefronts: 4 as a 2 x 2 grid, or 8 as 2 (m) x 4 (n), on oblong tiles 4 x 2, in which case two waves share each SIMD and one
 // wave's loads, LDS traffic and barrier waits overlap the other's MFMAs.
 template <typename E, int BM, int BN, int NW, int TA, int TB, int SEG, int ACC, int GLU>
 __global__ __launch_bounds__(64 * NW, (NW == 4 && BM * BN <= 128 * 128) ? 2 : 1) void gemm_mfma_kernel(Gemm g, int tiles_m,
