@@ -1,9 +1,9 @@
 // fp32 GEMM on the fp32 matrix cores (v_mfma_f32_16x16x4_f32: fp32 operands, fp32 accumulation), for the fp32 configuration.
 //
 // What bounds it: the fp32 products of this library are small (a microbatch of a small model), so the time is the latency of
-// one pass over K on too few workgroups, not arithmetic.  Hence no LDS staging and no barrier in the K loop: a wave loads
-// its operands from L2 straight into the registers that the matrix instruction reads, 16 bytes per lane, and small outputs
-// have their K range divided over the waves of a workgroup, whose partial tiles are added through LDS in a fixed order.
+// one pass over K on too few workgroups, not arithmetic.  Hence no LDS staging shared by waves and no barrier in the K loop: a wave
+// loads its own operands from L2, 16 bytes per lane, and small outputs have their K range divided over the waves of a
+// workgroup, whose partial tiles are added through LDS in a fixed order.
 //
 // How the operands fit without a transpose.  A 16x16x4 step takes from lane l one value of row l%16 at k = l/16.  Which
 // memory row stands behind "row l%16" and which k behind "k = l/16" of step e is free as long as both operands agree on k:
@@ -58,13 +58,44 @@ template <int NB> struct Frag<1, NB> {   // row-contiguous
   }
 };
 
+// Forms that share out K bring k-contiguous operands in through LDS.  Read straight into fragments, neighbouring lanes of a load lie in
+// different rows, and the address unit takes their 16-byte pieces one by one, four times as long as whole lines: of the 5.9 us of
+// 256 x 256, K = 1024 on 16x16 tiles such loads of A alone were 1.7.  So a wave loads two slabs at a time, 128 bytes of each row,
+// puts them into LDS that no other wave touches (no barrier), the 16-byte piece p of row r at position p ^ r % 8, and reads the
+// fragments back; up to four such pairs of slabs are in flight (64x64: two, more leave no second workgroup per CU; it gains
+// 8 to 15 % over one pair where CUs have one workgroup).  The sums and their order are those of the direct loads.
+// us, direct : through LDS, over 224 products of a stage with 64 to 2048 rows 0.89 on the geometric mean; 256 x 512, K = 1536 (dx) 10.9 :
+// 7.3; 256 x 256, K = 1024 6.1 : 4.4; 1024 x 1024, K = 1024 26.9 : 22.5; 128 x 1024, K = 2768 loses (16.4 : 17.6).  128x128 tiles
+// reach the matrix cores' rate without.
+template <int NB> struct Rows { u32x4 v[2 * NB]; };   // NB blocks of 16 rows, two slabs
+// at: byte offset of the lane's piece of its first row, or OUT; 8 rows a load
+template <int NB> __device__ __forceinline__ void load_rows(Rows<NB>& f, __amdgpu_buffer_rsrc_t rs, unsigned at, unsigned ld, unsigned soff) {
+#pragma unroll
+  for (int i = 0; i < 2 * NB; ++i) f.v[i] = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)at, (int)(soff + 8 * i * ld * 4), 0);
+}
+template <int NB> __device__ __forceinline__ void put_rows(const Rows<NB>& f, u32x4* lds, int lane) {
+  u32x4* p = lds + (lane & ~7) + ((lane & 7) ^ (lane >> 3));
+#pragma unroll
+  for (int i = 0; i < 2 * NB; ++i) p[64 * i] = f.v[i];
+}
+template <int NB> __device__ __forceinline__ void get_rows(Frag<0, NB>& f, const u32x4* lds, int slab, int lane) {
+  const u32x4* p = lds + (lane & 15) * 8 + ((4 * slab + (lane >> 4)) ^ (lane & 7));
+#pragma unroll
+  for (int b = 0; b < NB; ++b) f.v[b] = __builtin_bit_cast(f32x4, p[128 * b]);
+}
+
 // A workgroup owns a (16 MI WM) x (16 NI WN) tile of C (MI, NI = 1, 2 or 4): WM x WN waves side by side, times KW waves
 // that share out K.
 template <int TA, int TB, int MI, int NI, int WM, int WN, int KW, int SEG>
 __device__ __forceinline__ void f32_tile(const Gemm& g, int tiles_m, int tiles_n, int pid, int z) {
   constexpr int NQ = MI * NI;   // quads of 4 consecutive columns a lane holds
-  __shared__ f32x4 red[KW > 1 ? (KW - 1) * WM * WN * NQ * 64 : 1];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  constexpr bool STAGED = KW > 1 && (TA == 0 || TB == 1);   // k-contiguous operands through LDS
+  constexpr int RED = KW > 1 ? (KW - 1) * WM * WN * NQ * 64 : 1, SA = STAGED && TA == 0 ? MI * 128 : 0, SB = STAGED && TB == 1 ? NI * 128 : 0;
+  constexpr int STAGE = KW * WM * WN * (SA + SB);
+  constexpr bool SHARED = (RED + STAGE) * 16 > 65536;       // partial tiles take the place of the slabs
+  __shared__ f32x4 lds[SHARED ? (RED > STAGE ? RED : STAGE) : RED + STAGE];
+  f32x4* red = lds + (SHARED ? 0 : STAGE);
+  const int lane = threadIdx.x & 63, wave = STAGED ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : threadIdx.x >> 6;
   const int lm = lane & 15, lg = lane >> 4;
   const int kw = wave / (WM * WN), wt = wave % (WM * WN);
   int tm, tn;
@@ -96,7 +127,7 @@ __device__ __forceinline__ void f32_tile(const Gemm& g, int tiles_m, int tiles_n
     for (int e = 0; e < 4; ++e) bo[e] = n0 + NI * lm < g.N ? ((4 * lg + e) * ldb + n0 + NI * lm) * 4 : OUT;
   }
 
-  Frag<TA, MI> fa[2];
+  Frag<TA, MI> fa[2];                                        // unless STAGED
   Frag<1 - TB, NI> fb[2];
   auto load = [&](Frag<TA, MI>& a, Frag<1 - TB, NI>& b, int k) {
     const unsigned past = k + 4 * lg < g.K ? 0u : OUT;   // K is a multiple of 4 where an operand is k-contiguous
@@ -136,10 +167,63 @@ __device__ __forceinline__ void f32_tile(const Gemm& g, int tiles_m, int tiles_n
         for (int j = 0; j < NI; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(b.at(j, e), a.at(i, e), acc[i][j], 0, 0, 0);
   };
 
-  // this wave's slabs [s0, s1): two in flight; loads behind s1 are issued and not used
   const int slabs = (g.K + 15) / 16, per = (slabs + KW - 1) / KW;
-  const int s0 = kw * per, s1 = min(slabs, s0 + per);
-  if (s0 < s1) {
+  const int s0 = kw * per, s1 = min(slabs, s0 + per);        // this wave's slabs
+  if constexpr (STAGED) {
+    constexpr int DEPTH = MI * NI == 16 ? 2 : MI * NI == 1 ? 4 : 3;
+    u32x4* la = reinterpret_cast<u32x4*>(lds) + wave * (SA + SB);
+    u32x4* lb = la + SA;
+    struct Pair { Rows<SA ? MI : 1> a; Rows<SB ? NI : 1> b; Frag<1, TA ? MI : 1> ra[2]; Frag<1, TB ? 1 : NI> rb[2]; } buf[DEPTH];
+    const unsigned ra0 = ((m0 + (lane >> 3)) * lda + 4 * (lane & 7)) * 4, rb0 = ((n0 + (lane >> 3)) * ldb + (SEG ? 0 : 4 * (lane & 7))) * 4;
+    auto load_pair = [&](Pair& f, int s) {
+      const int k = s * 16, kl = k + 4 * (lane & 7);
+      const unsigned past = kl < g.K ? 0u : OUT;               // K is a multiple of 4 where an operand is k-contiguous
+      if constexpr (SA > 0) load_rows<MI>(f.a, ra, ra0 | past, lda, k * 4);
+      else {
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) f.ra[h].v[e] = loadn<MI>(ra, ao[e], (k + 16 * h) * lda * 4);
+      }
+      if constexpr (SB > 0) {
+        if constexpr (SEG) {
+          const int seg = kl / g.kseg;
+          load_rows<NI>(f.b, rb, past ? OUT : rb0 + (unsigned)(seg * g.segB + (kl - seg * g.kseg)) * 4, ldb, 0);
+        } else load_rows<NI>(f.b, rb, rb0 | past, ldb, k * 4);
+      } else {
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) f.rb[h].v[e] = loadn<NI>(rb, bo[e], (k + 16 * h) * ldb * 4);
+      }
+    };
+    auto multiply_pair = [&](Pair& f, int s) {
+      if constexpr (SA > 0) put_rows<MI>(f.a, la, lane);
+      if constexpr (SB > 0) put_rows<NI>(f.b, lb, lane);
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+        if (s + h < s1) {
+          Frag<TA, MI> a;
+          Frag<1 - TB, NI> b;
+          if constexpr (SA > 0) get_rows<MI>(a, la, h, lane);
+          else a = f.ra[h];
+          if constexpr (SB > 0) get_rows<NI>(b, lb, h, lane);
+          else b = f.rb[h];
+          multiply(a, b);
+        }
+    };
+#pragma unroll
+    for (int i = 0; i < DEPTH; ++i)
+      if (s0 + 2 * i < s1) load_pair(buf[i], s0 + 2 * i);
+    for (int s = s0; s < s1; s += 2 * DEPTH)
+#pragma unroll
+      for (int i = 0; i < DEPTH; ++i)
+        if (s + 2 * i < s1) {
+          multiply_pair(buf[i], s + 2 * i);
+          if (s + 2 * (i + DEPTH) < s1) load_pair(buf[i], s + 2 * (i + DEPTH));
+        }
+    if constexpr (SHARED) __syncthreads();
+  } else if (s0 < s1) {   // two slabs in flight; loads behind s1 are issued and not used
     load(fa[0], fb[0], s0 * 16);
     for (int s = s0; s < s1; s += 2) {
       load(fa[1], fb[1], (s + 1) * 16);
@@ -253,7 +337,7 @@ bool gemm_f32_supported(const Gemm& g) {
 // Which tile: 128x128 (4 waves of 64x64), 64x64 with K over 4 waves, or 32x32, 16x32 or 16x16 with K over 8 waves.  The smaller
 // ones exist for outputs that give the 256 CUs too few workgroups; the fewer outputs a wave has the more bytes it loads per
 // flop.  The estimate: cycles of the busiest CU, at the 256 flops per cycle of its four matrix cores times what each form was
-// measured to reach of it, plus a fixed part per workgroup.  256 x 256, K = 1024: 9.6 us on 32x32, 7.0 on 16x32, 5.9 on
+// measured to reach of it, plus a fixed part per workgroup.  With direct loads throughout, 256 x 256, K = 1024: 9.6 us on 32x32, 7.0 on 16x32, 5.9 on
 // 16x16; 256 x 512, K = 2752 in two segments 25.1, 19.3 and 24.2; 256 x 1024, K = 256 4.9, 5.5 and 6.1; 64x64 9.4.
 namespace {
 const struct { int m, n; double share; } FORMS[5] = {{128, 128, 0.8}, {64, 64, 0.7}, {32, 32, 0.45}, {16, 32, 0.4}, {16, 16, 0.3}};
