@@ -16,6 +16,7 @@
 // Measured on the GEMMs of a [256 tokens] x 256..1024 GPT stage: 47-86 us per launch with the plain LDS-tiled kernel,
 // 3.4-6.5 us here.
 #include "kernels.h"
+#include "rows_lds.h"
 
 namespace zs {
 namespace {
@@ -58,32 +59,12 @@ template <int NB> struct Frag<1, NB> {   // row-contiguous
   }
 };
 
-// Forms that share out K bring k-contiguous operands in through LDS.  Read straight into fragments, neighbouring lanes of a load lie in
-// different rows, and the address unit takes their 16-byte pieces one by one, four times as long as whole lines: of the 5.9 us of
-// 256 x 256, K = 1024 on 16x16 tiles such loads of A alone were 1.7.  So a wave loads two slabs at a time, 128 bytes of each row,
-// puts them into LDS that no other wave touches (no barrier), the 16-byte piece p of row r at position p ^ r % 8, and reads the
-// fragments back; up to four such pairs of slabs are in flight (64x64: two, more leave no second workgroup per CU; it gains
-// 8 to 15 % over one pair where CUs have one workgroup).  The sums and their order are those of the direct loads.
-// us, direct : through LDS, over 224 products of a stage with 64 to 2048 rows 0.89 on the geometric mean; 256 x 512, K = 1536 (dx) 10.9 :
-// 7.3; 256 x 256, K = 1024 6.1 : 4.4; 1024 x 1024, K = 1024 26.9 : 22.5; 128 x 1024, K = 2768 loses (16.4 : 17.6).  128x128 tiles
-// reach the matrix cores' rate without.
-template <int NB> struct Rows { u32x4 v[2 * NB]; };   // NB blocks of 16 rows, two slabs
-// at: byte offset of the lane's piece of its first row, or OUT; 8 rows a load
-template <int NB> __device__ __forceinline__ void load_rows(Rows<NB>& f, __amdgpu_buffer_rsrc_t rs, unsigned at, unsigned ld, unsigned soff) {
-#pragma unroll
-  for (int i = 0; i < 2 * NB; ++i) f.v[i] = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)at, (int)(soff + 8 * i * ld * 4), 0);
-}
-template <int NB> __device__ __forceinline__ void put_rows(const Rows<NB>& f, u32x4* lds, int lane) {
-  u32x4* p = lds + (lane & ~7) + ((lane & 7) ^ (lane >> 3));
-#pragma unroll
-  for (int i = 0; i < 2 * NB; ++i) p[64 * i] = f.v[i];
-}
-template <int NB> __device__ __forceinline__ void get_rows(Frag<0, NB>& f, const u32x4* lds, int slab, int lane) {
-  const u32x4* p = lds + (lane & 15) * 8 + ((4 * slab + (lane >> 4)) ^ (lane & 7));
-#pragma unroll
-  for (int b = 0; b < NB; ++b) f.v[b] = __builtin_bit_cast(f32x4, p[128 * b]);
-}
-
+// Forms that share out K bring k-contiguous operands in through LDS, two slabs at a time (rows_lds.h): of the 5.9 us of 256 x 256, K = 1024
+// on 16x16 tiles direct loads of A alone were 1.7.  Up to four pairs of slabs are in flight (64x64: two, more leave no second
+// workgroup per CU; it gains 8 to 15 % over one pair where CUs have one workgroup).  The sums and their order are those of the
+// direct loads.  us, direct : through LDS, over 224 products of a stage with 64 to 2048 rows 0.88 on the geometric mean; 256 x 512,
+// K = 1536 (dx) 10.9 : 7.3; 256 x 256, K = 1024 6.1 : 4.4; 1024 x 1024, K = 1024 26.9 : 22.5; 128 x 1024, K = 2768 loses (16.4 : 17.6).
+// 128x128 tiles reach the matrix cores' rate without.
 // A workgroup owns a (16 MI WM) x (16 NI WN) tile of C (MI, NI = 1, 2 or 4): WM x WN waves side by side, times KW waves
 // that share out K.
 template <int TA, int TB, int MI, int NI, int WM, int WN, int KW, int SEG>
@@ -177,8 +158,8 @@ __device__ __forceinline__ void f32_tile(const Gemm& g, int tiles_m, int tiles_n
     const unsigned ra0 = ((m0 + (lane >> 3)) * lda + 4 * (lane & 7)) * 4, rb0 = ((n0 + (lane >> 3)) * ldb + (SEG ? 0 : 4 * (lane & 7))) * 4;
     auto load_pair = [&](Pair& f, int s) {
       const int k = s * 16, kl = k + 4 * (lane & 7);
-      const unsigned past = kl < g.K ? 0u : OUT;               // K is a multiple of 4 where an operand is k-contiguous
-      if constexpr (SA > 0) load_rows<MI>(f.a, ra, ra0 | past, lda, k * 4);
+      const unsigned past = kl < min(g.K, s1 * 16) ? 0u : OUT; // K is a multiple of 4 where an operand is k-contiguous
+      if constexpr (SA > 0) load_rows<MI>(f.a, ra, ra0 | past, lda * 4, k * 4);
       else {
 #pragma unroll
         for (int h = 0; h < 2; ++h)
@@ -188,8 +169,8 @@ __device__ __forceinline__ void f32_tile(const Gemm& g, int tiles_m, int tiles_n
       if constexpr (SB > 0) {
         if constexpr (SEG) {
           const int seg = kl / g.kseg;
-          load_rows<NI>(f.b, rb, past ? OUT : rb0 + (unsigned)(seg * g.segB + (kl - seg * g.kseg)) * 4, ldb, 0);
-        } else load_rows<NI>(f.b, rb, rb0 | past, ldb, k * 4);
+          load_rows<NI>(f.b, rb, past ? OUT : rb0 + (unsigned)(seg * g.segB + (kl - seg * g.kseg)) * 4, ldb * 4, 0);
+        } else load_rows<NI>(f.b, rb, rb0 | past, ldb * 4, k * 4);
       } else {
 #pragma unroll
         for (int h = 0; h < 2; ++h)
@@ -205,9 +186,9 @@ __device__ __forceinline__ void f32_tile(const Gemm& g, int tiles_m, int tiles_n
         if (s + h < s1) {
           Frag<TA, MI> a;
           Frag<1 - TB, NI> b;
-          if constexpr (SA > 0) get_rows<MI>(a, la, h, lane);
+          if constexpr (SA > 0) get_rows<MI>(a.v, la, h, lane);
           else a = f.ra[h];
-          if constexpr (SB > 0) get_rows<NI>(b, lb, h, lane);
+          if constexpr (SB > 0) get_rows<NI>(b.v, lb, h, lane);
           else b = f.rb[h];
           multiply(a, b);
         }

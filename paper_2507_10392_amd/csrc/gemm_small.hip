@@ -2,18 +2,21 @@
 //
 // What bounds such a product is the walk over K on few workgroups: with 128x128 tiles a 256 x 512 output has 8 of them, and
 // 248 CUs watch.  Here a workgroup owns 32x32 or 64x64 outputs, its waves share out K and add their partial tiles through LDS
-// in a fixed order, and the operands go from L2 straight into the registers that the matrix instruction reads: no LDS and
-// no barrier in the K loop, several slabs of 32 k in flight.  The price is L2 traffic (a wave re-reads what a neighbour has
-// read) and, for a k-contiguous operand, a load whose neighbouring lanes lie in different rows, which the address unit takes
-// four times as long for; so outputs that fill the chip stay with the staged kernels.  The rule stands with gemm_small_tile.
+// in a fixed order, and every wave loads its own operands from L2: no barrier in the K loop, several slabs of 32 k in flight.
+// The price is L2 traffic (a wave re-reads what a neighbour has read), so outputs that fill the chip stay with the staged
+// kernels.  The rule stands with gemm_small_tile.
 //
 // How the operands fit without an LDS transpose.  A 16x16x32 step takes from lane l eight values of row l%16; which k stand
 // behind them is free as long as both operands agree: k = 8 (l/16) + 0..7 of the slab.
-//   k-contiguous operand (A [M,K], B [N,K]): one 16-byte load per lane and block of 16 rows.
+//   k-contiguous operand (A [M,K], B [N,K]): 16 bytes per lane and block of 16 rows.  Input gradients, where both operands are, get
+//     them through LDS of the wave's own (rows_lds.h): with one direct load per fragment the address unit was the limit.  us,
+//     direct : through LDS, 64 x 768, K = 3072 12.8 : 6.9; 384 x 1024, K = 4096 30.3 : 15.8; 512 x 512, K = 512 4.2 : 3.7; 0.76 on the
+//     geometric mean of 96 products with 64 to 1000 rows, K = 256 .. 4096.
 //   row-contiguous operand (A [K,M], B [K,N]): lane l loads NV consecutive columns of each of its eight k-lines; pairs of
 //     k-lines are then interleaved by one v_perm_b32 per register, which leaves in NV fragments the columns NV (l%16) + j.
 // The matrix instruction gets B as its first operand, so a lane ends up with 4 consecutive columns of one row of C.
 #include "kernels.h"
+#include "rows_lds.h"
 
 #include <algorithm>
 #include <cmath>
@@ -85,7 +88,9 @@ __device__ __forceinline__ void small_tile(const Gemm& g, int tiles_m, int tiles
   constexpr int NB = GLU1 ? 2 : T;                 // blocks of columns of one matrix B
   constexpr int NJ = GLU1 ? 2 * NB : NB;           // ... of the tile
   constexpr int NQ = T * NJ;                       // quads of 4 consecutive columns a lane holds
-  __shared__ f32x4 red[KW > 1 ? (KW - 1) * NQ * 64 : 1];
+  constexpr bool STAGED = TB && KW > 1;            // both operands k-contiguous: through LDS
+  constexpr int RED = KW > 1 ? (KW - 1) * NQ * 64 : 1, STAGE = STAGED ? KW * 2 * T * 128 : 0;
+  __shared__ f32x4 red[RED > STAGE ? RED : STAGE]; // partial tiles take the place of the slabs
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lm = lane & 15, lg = lane >> 4;
   // ids are dealt round-robin to the 8 XCDs; each gets a contiguous run of the tile order
@@ -116,61 +121,102 @@ __device__ __forceinline__ void small_tile(const Gemm& g, int tiles_m, int tiles
     if (GLU1 && bo[0] != OUT) bo2 = bo[0] + (unsigned)g.sB * 2;
   }
 
-  struct Slab { Raw<TA, T> a; Raw<1 - TB, NB> b, b2; };
-  Slab buf[NBUF];
-  auto load = [&](Slab& s, int slab) {
-    const int k = slab * 32;
-    const unsigned past = k + 8 * lg < g.K ? 0u : OUT;   // K is a multiple of 8 where an operand is k-contiguous
-    if constexpr (FORM == TN_PARTS) {   // slabs do not straddle parts: kseg is a multiple of 128
-      const int p = min(k / g.kseg, g.nx), kin = k - p * g.kseg;
-      const int rows = p < g.nx ? g.kseg : g.K - g.nx * g.kseg;
-      const __amdgpu_buffer_rsrc_t pa = rsrc((p ? (const E*)g.Ax[p - 1] : (const E*)g.A) + (int64_t)z * g.sA, (int64_t)(rows - 1) * lda + g.M),
-                                   pb = rsrc((p ? (const E*)g.Bx[p - 1] : (const E*)g.B) + (int64_t)z * g.sB, (int64_t)(rows - 1) * ldb + g.N);
-      load_r(s.a, pa, ao[0], lda * 2, kin * lda * 2);
-      load_r(s.b, pb, bo[0], ldb * 2, kin * ldb * 2);
-      return;
-    }
-    if constexpr (TA) load_r(s.a, ra, ao[0], lda * 2, k * lda * 2);   // k-lines past K lie behind the descriptor
-    else load_k<T>(s.a, ra, ao, past, k * 2);
-    if constexpr (FORM == NT_SEG) {
-      const int kl = k + 8 * lg, seg = kl / g.kseg;
-      load_k<NB>(s.b, rb, bo, past ? OUT : (unsigned)(seg * g.segB + (kl - seg * g.kseg)) * 2, 0);
-    } else if constexpr (TB) {
-      load_k<NB>(s.b, rb, bo, past, k * 2);
-    } else {
-      load_r(s.b, rb, bo[0], ldb * 2, k * ldb * 2);
-      if constexpr (GLU1) load_r(s.b2, rb, bo2, ldb * 2, k * ldb * 2);
-    }
-  };
   f32x4 acc[T][NJ];
 #pragma unroll
   for (int i = 0; i < T; ++i)
 #pragma unroll
     for (int j = 0; j < NJ; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  auto multiply = [&](const Slab& s) {
-    u32x4 a[T];
-#pragma unroll
-    for (int i = 0; i < T; ++i) a[i] = s.a.frag(i);
-#pragma unroll
-    for (int j = 0; j < NJ; ++j) {
-      const u32x4 b = GLU1 && j >= NB ? s.b2.frag(j % NB) : s.b.frag(j % NB);
-#pragma unroll
-      for (int i = 0; i < T; ++i) acc[i][j] = mfma<E>(b, a[i], acc[i][j]);
-    }
-  };
-
   const int slabs = (g.K + 31) / 32, per = (slabs + KW - 1) / KW;
-  const int s0 = wave * per, s1 = min(slabs, s0 + per);
+  const int s0 = wave * per, s1 = min(slabs, s0 + per);   // this wave's slabs
+  if constexpr (STAGED) {
+    // Two pairs of slabs in flight, three on 32x32 tiles.  The fragments hold the same k as with direct loads.
+    constexpr int DEPTH = T == 2 ? 3 : 2;
+    u32x4* la = reinterpret_cast<u32x4*>(red) + wave * 2 * T * 128;
+    u32x4* lb = la + T * 128;
+    struct Pair { Rows<T> a, b; } pairs[DEPTH];
+    const unsigned a0 = ((m0 + (lane >> 3)) * lda + 8 * (lane & 7)) * 2, b0 = ((n0 + (lane >> 3)) * ldb + (FORM == NT_SEG ? 0 : 8 * (lane & 7))) * 2;
+    auto load = [&](Pair& f, int s) {
+      const int k = s * 32, kl = k + 8 * (lane & 7);
+      const bool past = kl >= min(g.K, s1 * 32);           // K is a multiple of 8 where an operand is k-contiguous
+      load_rows<T>(f.a, ra, past ? OUT : a0, lda * 2, k * 2);
+      if constexpr (FORM == NT_SEG) {
+        const int seg = kl / g.kseg;
+        load_rows<T>(f.b, rb, past ? OUT : b0 + (unsigned)(seg * g.segB + (kl - seg * g.kseg)) * 2, ldb * 2, 0);
+      } else load_rows<T>(f.b, rb, past ? OUT : b0, ldb * 2, k * 2);
+    };
 #pragma unroll
-  for (int i = 0; i < NBUF - 1; ++i)
-    if (s0 + i < s1) load(buf[i], s0 + i);
-  for (int s = s0; s < s1; s += NBUF)
+    for (int i = 0; i < DEPTH; ++i)
+      if (s0 + 2 * i < s1) load(pairs[i], s0 + 2 * i);
+    for (int s = s0; s < s1; s += 2 * DEPTH)
 #pragma unroll
-    for (int i = 0; i < NBUF; ++i)
-      if (s + i < s1) {
-        if (s + i + NBUF - 1 < s1) load(buf[(i + NBUF - 1) % NBUF], s + i + NBUF - 1);
-        multiply(buf[i]);
+      for (int i = 0; i < DEPTH; ++i)
+        if (s + 2 * i < s1) {
+          put_rows<T>(pairs[i].a, la, lane);
+          put_rows<T>(pairs[i].b, lb, lane);
+          if (s + 2 * (i + DEPTH) < s1) load(pairs[i], s + 2 * (i + DEPTH));
+#pragma unroll
+          for (int h = 0; h < 2; ++h)
+            if (s + 2 * i + h < s1) {
+              u32x4 a[T], b[T];
+              get_rows<T>(a, la, h, lane);
+              get_rows<T>(b, lb, h, lane);
+#pragma unroll
+              for (int j = 0; j < T; ++j)
+#pragma unroll
+                for (int q = 0; q < T; ++q) acc[q][j] = mfma<E>(b[j], a[q], acc[q][j]);
+            }
+        }
+    __syncthreads();
+  } else {
+    struct Slab { Raw<TA, T> a; Raw<1 - TB, NB> b, b2; };
+    Slab buf[NBUF];
+    auto load = [&](Slab& s, int slab) {
+      const int k = slab * 32;
+      const unsigned past = k + 8 * lg < g.K ? 0u : OUT;   // K is a multiple of 8 where an operand is k-contiguous
+      if constexpr (FORM == TN_PARTS) {   // slabs do not straddle parts: kseg is a multiple of 128
+        const int p = min(k / g.kseg, g.nx), kin = k - p * g.kseg;
+        const int rows = p < g.nx ? g.kseg : g.K - g.nx * g.kseg;
+        const __amdgpu_buffer_rsrc_t pa = rsrc((p ? (const E*)g.Ax[p - 1] : (const E*)g.A) + (int64_t)z * g.sA, (int64_t)(rows - 1) * lda + g.M),
+                                     pb = rsrc((p ? (const E*)g.Bx[p - 1] : (const E*)g.B) + (int64_t)z * g.sB, (int64_t)(rows - 1) * ldb + g.N);
+        load_r(s.a, pa, ao[0], lda * 2, kin * lda * 2);
+        load_r(s.b, pb, bo[0], ldb * 2, kin * ldb * 2);
+        return;
       }
+      if constexpr (TA) load_r(s.a, ra, ao[0], lda * 2, k * lda * 2);   // k-lines past K lie behind the descriptor
+      else load_k<T>(s.a, ra, ao, past, k * 2);
+      if constexpr (FORM == NT_SEG) {
+        const int kl = k + 8 * lg, seg = kl / g.kseg;
+        load_k<NB>(s.b, rb, bo, past ? OUT : (unsigned)(seg * g.segB + (kl - seg * g.kseg)) * 2, 0);
+      } else if constexpr (TB) {
+        load_k<NB>(s.b, rb, bo, past, k * 2);
+      } else {
+        load_r(s.b, rb, bo[0], ldb * 2, k * ldb * 2);
+        if constexpr (GLU1) load_r(s.b2, rb, bo2, ldb * 2, k * ldb * 2);
+      }
+    };
+    auto multiply = [&](const Slab& s) {
+      u32x4 a[T];
+#pragma unroll
+      for (int i = 0; i < T; ++i) a[i] = s.a.frag(i);
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        const u32x4 b = GLU1 && j >= NB ? s.b2.frag(j % NB) : s.b.frag(j % NB);
+#pragma unroll
+        for (int i = 0; i < T; ++i) acc[i][j] = mfma<E>(b, a[i], acc[i][j]);
+      }
+    };
+
+#pragma unroll
+    for (int i = 0; i < NBUF - 1; ++i)
+      if (s0 + i < s1) load(buf[i], s0 + i);
+    for (int s = s0; s < s1; s += NBUF)
+#pragma unroll
+      for (int i = 0; i < NBUF; ++i)
+        if (s + i < s1) {
+          if (s + i + NBUF - 1 < s1) load(buf[(i + NBUF - 1) % NBUF], s + i + NBUF - 1);
+          multiply(buf[i]);
+        }
+  }
 
   // A lane's quads: quad (i, q) is row m(i), columns n(q) .. n(q)+3 (NN_GLU: quads NB.. are the up columns).
   auto quad = [&](int i, int q) {
