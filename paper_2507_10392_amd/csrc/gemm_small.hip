@@ -20,12 +20,15 @@
 
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 namespace zs {
 namespace {
 
 constexpr unsigned OUT = 0x80000000u;   // pushes a lane's offset past every descriptor (extents are below 2^30 bytes): reads 0
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(const void* p, int64_t elements) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)(elements * 2), 0x00020000);
@@ -38,13 +41,9 @@ template <> __device__ __forceinline__ f32x4 mfma<f16>(u32x4 a, u32x4 b, f32x4 c
   return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
 }
 
-// One operand's share of a slab of 32 k, NB blocks of 16 rows, as loaded.
-template <int ROWC, int NB> struct Raw;
-template <int NB> struct Raw<0, NB> {   // k-contiguous
-  u32x4 v[NB];
-  __device__ __forceinline__ u32x4 frag(int b) const { return v[b]; }
-};
-template <> struct Raw<1, 4> {          // row-contiguous, 4 columns of 8 k-lines
+// A row-contiguous operand's share of a slab of 32 k, NB blocks of 16 rows, as loaded.
+template <int NB> struct Raw;
+template <> struct Raw<4> {          // 4 columns of 8 k-lines
   u32x2 v[8];
   __device__ __forceinline__ u32x4 frag(int b) const {
     u32x4 f;
@@ -54,7 +53,7 @@ template <> struct Raw<1, 4> {          // row-contiguous, 4 columns of 8 k-line
     return f;
   }
 };
-template <> struct Raw<1, 2> {          // row-contiguous, 2 columns of 8 k-lines
+template <> struct Raw<2> {          // 2 columns of 8 k-lines
   unsigned v[8];
   __device__ __forceinline__ u32x4 frag(int b) const {
     u32x4 f;
@@ -63,72 +62,53 @@ template <> struct Raw<1, 2> {          // row-contiguous, 2 columns of 8 k-line
     return f;
   }
 };
-template <int NB> __device__ __forceinline__ void load_k(Raw<0, NB>& f, __amdgpu_buffer_rsrc_t rs, const unsigned (&at)[NB], unsigned add, unsigned soff) {
-#pragma unroll
-  for (int b = 0; b < NB; ++b) f.v[b] = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)(add == OUT ? OUT : at[b] + add), (int)soff, 0);
-}
 // at: byte offset of the lane's columns in its first k-line (OUT for columns past the end), ld2: bytes of a k-line
-__device__ __forceinline__ void load_r(Raw<1, 4>& f, __amdgpu_buffer_rsrc_t rs, unsigned at, unsigned ld2, unsigned soff) {
+__device__ __forceinline__ void load_r(Raw<4>& f, __amdgpu_buffer_rsrc_t rs, unsigned at, unsigned ld2, unsigned soff) {
 #pragma unroll
   for (int i = 0; i < 8; ++i) f.v[i] = __builtin_amdgcn_raw_buffer_load_b64(rs, (int)(at + i * ld2), (int)soff, 0);
 }
-__device__ __forceinline__ void load_r(Raw<1, 2>& f, __amdgpu_buffer_rsrc_t rs, unsigned at, unsigned ld2, unsigned soff) {
+__device__ __forceinline__ void load_r(Raw<2>& f, __amdgpu_buffer_rsrc_t rs, unsigned at, unsigned ld2, unsigned soff) {
 #pragma unroll
   for (int i = 0; i < 8; ++i) f.v[i] = __builtin_amdgcn_raw_buffer_load_b32(rs, (int)(at + i * ld2), (int)soff, 0);
 }
 
-enum Form { NN, NT, NT_SEG, TN_ACC, TN_PARTS, NN_GLU, NT_GLU };
+enum Form { NT, NT_SEG, TN_ACC, TN_PARTS, NT_GLU };
 
-// T: blocks of 16 rows and columns a wave's tile has each way (2: 32x32, 4: 64x64), KW: waves that share out K, NBUF: slabs
-// held (NBUF - 1 of them in flight).  NN_GLU: the tile has two blocks of 16 columns of each of the two projections.
+__device__ __forceinline__ void tile_of(int pid, int tiles_m, int tiles_n, int& tm, int& tn) {
+  const int ntiles = tiles_m * tiles_n;   // ids are dealt round-robin to the 8 XCDs; each gets a contiguous run of the tile order
+  if (pid < ntiles / 8 * 8) pid = (pid % 8) * (ntiles / 8) + pid / 8;
+  gemm_tile_of(pid, tiles_m, tiles_n, tm, tn);
+}
+
+// T: blocks of 16 rows and columns a wave's tile has each way (2: 32x32, 4: 64x64), KW: waves that share out K, NBUF: slabs held of
+// row-contiguous operands (NBUF - 1 of them in flight).
 template <typename E, int FORM, int T, int KW, int NBUF>
 __device__ __forceinline__ void small_tile(const Gemm& g, int tiles_m, int tiles_n, int pid, int z) {
-  constexpr int TA = FORM == TN_ACC || FORM == TN_PARTS, TB = FORM == NT || FORM == NT_SEG || FORM == NT_GLU;
-  constexpr bool GLU1 = FORM == NN_GLU, ACC = TA;
-  constexpr int NB = GLU1 ? 2 : T;                 // blocks of columns of one matrix B
-  constexpr int NJ = GLU1 ? 2 * NB : NB;           // ... of the tile
-  constexpr int NQ = T * NJ;                       // quads of 4 consecutive columns a lane holds
-  constexpr bool STAGED = TB && KW > 1;            // both operands k-contiguous: through LDS
-  constexpr int RED = KW > 1 ? (KW - 1) * NQ * 64 : 1, STAGE = STAGED ? KW * 2 * T * 128 : 0;
+  constexpr bool TA = FORM == TN_ACC || FORM == TN_PARTS, TB = !TA, ACC = TA;
+  constexpr int NQ = T * T;                        // quads of 4 consecutive columns a lane holds
+  constexpr int RED = (KW - 1) * NQ * 64, STAGE = TB ? KW * 2 * T * 128 : 0;
   __shared__ f32x4 red[RED > STAGE ? RED : STAGE]; // partial tiles take the place of the slabs
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lm = lane & 15, lg = lane >> 4;
-  // ids are dealt round-robin to the 8 XCDs; each gets a contiguous run of the tile order
-  const int ntiles = tiles_m * tiles_n;
   int tm, tn;
-  if (pid < ntiles / 8 * 8) pid = (pid % 8) * (ntiles / 8) + pid / 8;
-  gemm_tile_of(pid, tiles_m, tiles_n, tm, tn);
-  const int m0 = tm * 16 * T, n0 = tn * 16 * NB;
+  tile_of(pid, tiles_m, tiles_n, tm, tn);
+  const int m0 = tm * 16 * T, n0 = tn * 16 * T;
   const E* A = (const E*)g.A + (int64_t)z * g.sA;
   const E* B = (const E*)g.B + (int64_t)z * g.sB;
   const unsigned lda = (unsigned)g.lda, ldb = (unsigned)g.ldb;
   const int K1 = FORM == TN_PARTS ? g.kseg : g.K;   // rows of a part, or of the only one
   const int64_t recB = TB ? (FORM == NT_SEG ? (int64_t)(g.K / g.kseg - 1) * g.segB + (int64_t)(g.N - 1) * ldb + g.kseg : (int64_t)(g.N - 1) * ldb + g.K)
-                          : (int64_t)(K1 - 1) * ldb + g.N + (GLU1 ? g.sB : 0);
+                          : (int64_t)(K1 - 1) * ldb + g.N;
   const __amdgpu_buffer_rsrc_t ra = rsrc(A, TA ? (int64_t)(K1 - 1) * lda + g.M : (int64_t)(g.M - 1) * lda + g.K), rb = rsrc(B, recB);
 
-  unsigned ao[TA ? 1 : T], bo[TB ? NB : 1], bo2 = OUT;
-  if constexpr (TA) ao[0] = m0 + T * lm < g.M ? (8 * lg * lda + m0 + T * lm) * 2 : OUT;
-  else {
-#pragma unroll
-    for (int i = 0; i < T; ++i) ao[i] = ((m0 + 16 * i + lm) * lda + 8 * lg) * 2;
-  }
-  if constexpr (TB) {
-#pragma unroll
-    for (int j = 0; j < NB; ++j) bo[j] = ((n0 + 16 * j + lm) * ldb + (FORM == NT_SEG ? 0 : 8 * lg)) * 2;
-  } else {
-    bo[0] = n0 + NB * lm < g.N ? (8 * lg * ldb + n0 + NB * lm) * 2 : OUT;
-    if (GLU1 && bo[0] != OUT) bo2 = bo[0] + (unsigned)g.sB * 2;
-  }
-
-  f32x4 acc[T][NJ];
+  f32x4 acc[T][T];
 #pragma unroll
   for (int i = 0; i < T; ++i)
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < T; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
   const int slabs = (g.K + 31) / 32, per = (slabs + KW - 1) / KW;
   const int s0 = wave * per, s1 = min(slabs, s0 + per);   // this wave's slabs
-  if constexpr (STAGED) {
+  if constexpr (TB) {
     // Two pairs of slabs in flight, three on 32x32 tiles.  The fragments hold the same k as with direct loads.
     constexpr int DEPTH = T == 2 ? 3 : 2;
     u32x4* la = reinterpret_cast<u32x4*>(red) + wave * 2 * T * 128;
@@ -168,30 +148,20 @@ __device__ __forceinline__ void small_tile(const Gemm& g, int tiles_m, int tiles
         }
     __syncthreads();
   } else {
-    struct Slab { Raw<TA, T> a; Raw<1 - TB, NB> b, b2; };
-    Slab buf[NBUF];
-    auto load = [&](Slab& s, int slab) {
+    const unsigned ao = m0 + T * lm < g.M ? (8 * lg * lda + m0 + T * lm) * 2 : OUT, bo = n0 + T * lm < g.N ? (8 * lg * ldb + n0 + T * lm) * 2 : OUT;
+    struct Slab { Raw<T> a, b; } buf[NBUF];
+    auto load = [&](Slab& s, int slab) {                   // k-lines past K lie behind the descriptors
       const int k = slab * 32;
-      const unsigned past = k + 8 * lg < g.K ? 0u : OUT;   // K is a multiple of 8 where an operand is k-contiguous
       if constexpr (FORM == TN_PARTS) {   // slabs do not straddle parts: kseg is a multiple of 128
         const int p = min(k / g.kseg, g.nx), kin = k - p * g.kseg;
         const int rows = p < g.nx ? g.kseg : g.K - g.nx * g.kseg;
         const __amdgpu_buffer_rsrc_t pa = rsrc((p ? (const E*)g.Ax[p - 1] : (const E*)g.A) + (int64_t)z * g.sA, (int64_t)(rows - 1) * lda + g.M),
                                      pb = rsrc((p ? (const E*)g.Bx[p - 1] : (const E*)g.B) + (int64_t)z * g.sB, (int64_t)(rows - 1) * ldb + g.N);
-        load_r(s.a, pa, ao[0], lda * 2, kin * lda * 2);
-        load_r(s.b, pb, bo[0], ldb * 2, kin * ldb * 2);
-        return;
-      }
-      if constexpr (TA) load_r(s.a, ra, ao[0], lda * 2, k * lda * 2);   // k-lines past K lie behind the descriptor
-      else load_k<T>(s.a, ra, ao, past, k * 2);
-      if constexpr (FORM == NT_SEG) {
-        const int kl = k + 8 * lg, seg = kl / g.kseg;
-        load_k<NB>(s.b, rb, bo, past ? OUT : (unsigned)(seg * g.segB + (kl - seg * g.kseg)) * 2, 0);
-      } else if constexpr (TB) {
-        load_k<NB>(s.b, rb, bo, past, k * 2);
+        load_r(s.a, pa, ao, lda * 2, kin * lda * 2);
+        load_r(s.b, pb, bo, ldb * 2, kin * ldb * 2);
       } else {
-        load_r(s.b, rb, bo[0], ldb * 2, k * ldb * 2);
-        if constexpr (GLU1) load_r(s.b2, rb, bo2, ldb * 2, k * ldb * 2);
+        load_r(s.a, ra, ao, lda * 2, k * lda * 2);
+        load_r(s.b, rb, bo, ldb * 2, k * ldb * 2);
       }
     };
     auto multiply = [&](const Slab& s) {
@@ -199,13 +169,12 @@ __device__ __forceinline__ void small_tile(const Gemm& g, int tiles_m, int tiles
 #pragma unroll
       for (int i = 0; i < T; ++i) a[i] = s.a.frag(i);
 #pragma unroll
-      for (int j = 0; j < NJ; ++j) {
-        const u32x4 b = GLU1 && j >= NB ? s.b2.frag(j % NB) : s.b.frag(j % NB);
+      for (int j = 0; j < T; ++j) {
+        const u32x4 b = s.b.frag(j);
 #pragma unroll
         for (int i = 0; i < T; ++i) acc[i][j] = mfma<E>(b, a[i], acc[i][j]);
       }
     };
-
 #pragma unroll
     for (int i = 0; i < NBUF - 1; ++i)
       if (s0 + i < s1) load(buf[i], s0 + i);
@@ -218,61 +187,37 @@ __device__ __forceinline__ void small_tile(const Gemm& g, int tiles_m, int tiles
         }
   }
 
-  // A lane's quads: quad (i, q) is row m(i), columns n(q) .. n(q)+3 (NN_GLU: quads NB.. are the up columns).
+  // A lane's quads: quad (i, q) is row m(i), columns n(q) .. n(q)+3.
   auto quad = [&](int i, int q) {
-    const int base = q / NB * NB, ql = q % NB;
     f32x4 v;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       if constexpr (TB) v[e] = acc[i][q][e];
-      else v[e] = acc[i][base + (4 * ql + e) % NB][(4 * ql + e) / NB];   // column NB (4 lg + r) + j  <->  block j, register r
+      else v[e] = acc[i][(4 * q + e) % T][(4 * q + e) / T];   // column T (4 lg + r) + j  <->  block j, register r
     }
     return v;
   };
   // quad s is finished by the wave s % KW; the others leave theirs in LDS, and it adds them in the order of the waves
 #pragma unroll
   for (int s = 0; s < NQ; ++s)
-    if (KW > 1 && s % KW != wave) red[((wave < s % KW ? wave : wave - 1) * NQ + s) * 64 + lane] = quad(s / NJ, s % NJ);
-  if (KW > 1) __syncthreads();
+    if (s % KW != wave) red[((wave < s % KW ? wave : wave - 1) * NQ + s) * 64 + lane] = quad(s / T, s % T);
+  __syncthreads();
   auto sum = [&](int s) {
-    if (KW == 1) return quad(s / NJ, s % NJ);
     f32x4 v = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int o = 0; o < KW; ++o) v += o == s % KW ? quad(s / NJ, s % NJ) : red[((o < s % KW ? o : o - 1) * NQ + s) * 64 + lane];
+    for (int o = 0; o < KW; ++o) v += o == s % KW ? quad(s / T, s % T) : red[((o < s % KW ? o : o - 1) * NQ + s) * 64 + lane];
     return v;
   };
   typedef E E4 __attribute__((ext_vector_type(4)));
   auto row_of = [&](int i) { return m0 + (TA ? T * lm + i : 16 * i + lm); };
-  auto col_of = [&](int q) { return n0 + (TB ? 16 * q + 4 * lg : 4 * NB * lg + 4 * q); };
-  if constexpr (GLU1) {
-    static_assert(KW == 1, "a lane holds the gate and the up quad of the same columns");
-#pragma unroll
-    for (int s = 0; s < NQ; ++s)
-      if (s % NJ < NB) {
-        const f32x4 gv = quad(s / NJ, s % NJ), uv = quad(s / NJ, s % NJ + NB);
-        const int m = row_of(s / NJ), n = col_of(s % NJ);
-        if (m >= g.M || n >= g.N) continue;
-        E4 og, ou, oa;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          og[e] = (E)gv[e];
-          ou[e] = (E)uv[e];
-          oa[e] = (E)glu_f((float)og[e], (float)ou[e]);
-        }
-        E* pg = (E*)g.gu + (int64_t)m * g.gu_ld + n;
-        *reinterpret_cast<E4*>(pg) = og;
-        *reinterpret_cast<E4*>(pg + g.gu_up) = ou;
-        *reinterpret_cast<E4*>((E*)g.C + (int64_t)m * g.ldc + n) = oa;
-      }
-    return;
-  }
+  auto col_of = [&](int q) { return n0 + (TB ? 16 * q + 4 * lg : 4 * T * lg + 4 * q); };
   const E* bias = g.bias ? (const E*)g.bias + (int64_t)z * g.sBias : nullptr;
   const E* R = g.resid ? (const E*)g.resid + (int64_t)z * g.sC : nullptr;
   const bool rot = g.rope && z < g.rope_batches;
 #pragma unroll
   for (int s = 0; s < NQ; ++s)
     if (s % KW == wave) {
-      const int m = row_of(s / NJ), n = col_of(s % NJ);
+      const int m = row_of(s / T), n = col_of(s % T);
       if (m >= g.M || n >= g.N) continue;              // N is a multiple of 4
       f32x4 v = sum(s);
       if constexpr (ACC) {
@@ -316,6 +261,137 @@ __device__ __forceinline__ void small_tile(const Gemm& g, int tiles_m, int tiles
     }
 }
 
+// y = x W (GLU: gate and up projection of the same columns, and the gated unit of the rounded values).  A workgroup of 4 waves owns 32x32
+// outputs, every wave one 16x16 block of them (GLU: of each projection), which walks K in the order of the staged kernels and so
+// gives their bits.  The waves share the loads: stages of 128 k, whole lines of x and the tile's 64 bytes of every line of W, go
+// to one of two LDS buffers, with four stages in flight (eight are 3 % slower).  x's 16-byte pieces are stored at position
+// p ^ row % 16; W stays [k][column], lines 96 bytes apart, and is read transposed.  A stage costs 0.33 us, its LDS round trip and barrier.
+// us against one wave per tile, whose address unit took the 64 pieces of every load of x one by one: 256 x 512, K = 512 4.5 : 3.9, K =
+// 1384 8.1 : 6.2; 256 x 3072, K = 768 (768 tiles) 8.2 : 8.4; 0.88 on the geometric mean of 96 products with 64 to 1000 rows.
+template <typename E, bool GLU>
+__device__ __forceinline__ void forward_tile(const Gemm& g, int tiles_m, int tiles_n, int pid, int z) {
+  constexpr int SK = 128, DEPTH = 4, NM = GLU ? 2 : 1;     // k of a stage, stages in flight, matrices W
+  constexpr int LINE = 6, SA = 32 * 16, SB = SK * LINE;    // 16-byte pieces: of a line of W, of a stage of x and of W
+  __shared__ u32x4 lds[2][SA + NM * SB];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), wi = wave >> 1, wj = wave & 1;
+  const int lm = lane & 15, lg = lane >> 4;
+  int tm, tn;
+  tile_of(pid, tiles_m, tiles_n, tm, tn);
+  const int m0 = tm * 32, n0 = tn * 32;
+  const E* B = (const E*)g.B + (int64_t)z * g.sB;
+  const unsigned lda = (unsigned)g.lda, ldb = (unsigned)g.ldb;
+  const __amdgpu_buffer_rsrc_t ra = rsrc((const E*)g.A + (int64_t)z * g.sA, (int64_t)(g.M - 1) * lda + g.K);
+  const __amdgpu_buffer_rsrc_t rb[2] = {rsrc(B, (int64_t)(g.K - 1) * ldb + g.N), rsrc(B + (GLU ? g.sB : 0), (int64_t)(g.K - 1) * ldb + g.N)};
+
+  struct Stage { u32x4 a[2], b[NM][2]; } st[DEPTH];
+  const unsigned ao = ((m0 + (tid >> 4)) * lda + 8 * (tid & 15)) * 2, bo = n0 + 8 * (tid & 3) < g.N ? ((tid >> 2) * ldb + n0 + 8 * (tid & 3)) * 2 : OUT;
+  auto load = [&](Stage& s, int k0) {
+    const unsigned at = k0 + 8 * (tid & 15) < g.K ? ao : OUT;   // K is a multiple of 8
+#pragma unroll
+    for (int i = 0; i < 2; ++i) s.a[i] = __builtin_amdgcn_raw_buffer_load_b128(ra, (int)at, (int)((16 * i * lda + k0) * 2), 0);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const unsigned line = k0 + 64 * i + (tid >> 2) < g.K ? bo : OUT;
+#pragma unroll
+      for (int w = 0; w < NM; ++w) s.b[w][i] = __builtin_amdgcn_raw_buffer_load_b128(rb[w], (int)line, (int)((k0 + 64 * i) * ldb * 2), 0);
+    }
+  };
+  auto put = [&](const Stage& s, u32x4* to) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      to[((tid >> 4) + 16 * i) * 16 + ((tid & 15) ^ (tid >> 4))] = s.a[i];
+#pragma unroll
+      for (int w = 0; w < NM; ++w) to[SA + w * SB + ((tid >> 2) + 64 * i) * LINE + (tid & 3)] = s.b[w][i];
+    }
+  };
+  f32x4 acc[NM];
+#pragma unroll
+  for (int w = 0; w < NM; ++w) acc[w] = f32x4{0.f, 0.f, 0.f, 0.f};
+  auto slabs = [&](auto count, const u32x4* from) {            // fragments of all slabs first: one LDS latency
+    constexpr int NS = decltype(count)::value;
+    u32x4 a[NS], b[NS][NM];
+#pragma unroll
+    for (int h = 0; h < NS; ++h) {
+      a[h] = from[(16 * wi + lm) * 16 + ((4 * h + lg) ^ lm)];
+#pragma unroll
+      for (int w = 0; w < NM; ++w) {
+        const short* p = reinterpret_cast<const short*>(from + SA + w * SB + (32 * h + 8 * lg + (lm >> 2)) * LINE) + 16 * wj + 4 * (lm & 3);
+        union { struct { s16x4 lo, hi; } s; u32x4 v; } u;
+        u.s.lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)p);
+        u.s.hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p + 4 * LINE * 8));
+        b[h][w] = u.v;
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int h = 0; h < NS; ++h)
+#pragma unroll
+      for (int w = 0; w < NM; ++w) acc[w] = mfma<E>(b[h][w], a[h], acc[w]);
+  };
+  auto multiply = [&](const u32x4* from, int k0) {
+    const int left = (g.K - k0 + 31) / 32;                      // slabs; the last stage may have fewer than four
+    if (left >= 4) slabs(std::integral_constant<int, 4>{}, from);
+    else if (left == 3) slabs(std::integral_constant<int, 3>{}, from);
+    else if (left == 2) slabs(std::integral_constant<int, 2>{}, from);
+    else slabs(std::integral_constant<int, 1>{}, from);
+  };
+
+  typedef E E4 __attribute__((ext_vector_type(4)));
+  const int m = m0 + 16 * wi + lm, n = n0 + 16 * wj + 4 * lg;   // the lane's row and first of its 4 columns
+  const bool inside = m < g.M && n < g.N;                       // N is a multiple of 8
+  const bool bias = !GLU && inside && g.bias, resid = !GLU && inside && g.resid, rot = !GLU && inside && g.rope && z < g.rope_batches;
+  const int stages = (g.K + SK - 1) / SK;
+#pragma unroll
+  for (int i = 0; i < DEPTH; ++i)
+    if (i < stages) load(st[i], i * SK);
+  E4 bb = {}, rr = {};                                          // what the store adds comes in behind the first stages
+  f32x4 t = {};
+  if (bias) bb = *reinterpret_cast<const E4*>((const E*)g.bias + (int64_t)z * g.sBias + n);
+  if (resid) rr = *reinterpret_cast<const E4*>((const E*)g.resid + (int64_t)z * g.sC + (int64_t)m * g.ldr + n);
+  if (rot) t = *reinterpret_cast<const f32x4*>(g.rope + (int64_t)(m % g.rope_S) * (g.rope_d / 2) + (n % g.rope_d) / 2);
+  for (int s = 0; s < stages; s += DEPTH)
+#pragma unroll
+    for (int i = 0; i < DEPTH; ++i)
+      if (s + i < stages) {
+        put(st[i], lds[i & 1]);                                 // last read before the previous stage's barrier
+        if (s + i + DEPTH < stages) load(st[i], (s + i + DEPTH) * SK);
+        __syncthreads();
+        multiply(lds[i & 1], (s + i) * SK);
+      }
+  if (!inside) return;
+  E4 o;
+  if constexpr (GLU) {
+    E4 ou, oa;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      o[e] = (E)acc[0][e];
+      ou[e] = (E)acc[1][e];
+      oa[e] = (E)glu_f((float)o[e], (float)ou[e]);
+    }
+    E* pg = (E*)g.gu + (int64_t)m * g.gu_ld + n;
+    *reinterpret_cast<E4*>(pg) = o;
+    *reinterpret_cast<E4*>(pg + g.gu_up) = ou;
+    *reinterpret_cast<E4*>((E*)g.C + (int64_t)m * g.ldc + n) = oa;
+  } else {
+    f32x4 v = acc[0];
+    if (bias) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] += (float)bb[e];
+    }
+    if (resid) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] += (float)rr[e];
+    }
+    if (rot) v = f32x4{v[0] * t[0] - v[1] * t[1], v[0] * t[1] + v[1] * t[0], v[2] * t[2] - v[3] * t[3], v[2] * t[3] + v[3] * t[2]};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) o[e] = (E)v[e];
+    *reinterpret_cast<E4*>((E*)g.C + (int64_t)z * g.sC + (int64_t)m * g.ldc + n) = o;
+  }
+}
+template <typename E, bool GLU> __global__ __launch_bounds__(256, GLU ? 2 : 4) void gemm_small_forward_kernel(Gemm g, int tiles_m, int tiles_n) {
+  forward_tile<E, GLU>(g, tiles_m, tiles_n, blockIdx.x, blockIdx.y);
+}
+
 template <typename E, int FORM, int T, int KW, int NBUF>
 __global__ __launch_bounds__(64 * KW) void gemm_small_kernel(Gemm g, int tiles_m, int tiles_n) {
   small_tile<E, FORM, T, KW, NBUF>(g, tiles_m, tiles_n, blockIdx.x, blockIdx.y);
@@ -333,33 +409,36 @@ template <typename E, int T, int KW, int NBUF> hipError_t launch_group(hipStream
 }
 
 template <typename E, int FORM, int T, int KW, int NBUF> hipError_t launch(hipStream_t st, const Gemm& g) {
-  const int tm = (int)cdiv(g.M, 16 * T), tn = (int)cdiv(g.N, 16 * (FORM == NN_GLU ? 2 : T));
+  const int tm = (int)cdiv(g.M, 16 * T), tn = (int)cdiv(g.N, 16 * T);
   hipLaunchKernelGGL((gemm_small_kernel<E, FORM, T, KW, NBUF>), dim3((unsigned)(tm * tn), (unsigned)g.batch), dim3(64 * KW), 0, st, g, tm, tn);
   return hipGetLastError();
 }
-// Forward products walk K with one wave, in the order of the staged kernels, and give their bits (with eight slabs in flight
-// that costs little: 256 x 512, K = 512 4.5 us against 3.9 us with K shared out); 64x64 tiles gain nothing there.  The
-// gradients' products share K out over 8 waves with either tile.
+template <typename E, bool GLU> hipError_t launch_forward(hipStream_t st, const Gemm& g) {
+  const int tm = (int)cdiv(g.M, 32), tn = (int)cdiv(g.N, 32);
+  hipLaunchKernelGGL((gemm_small_forward_kernel<E, GLU>), dim3((unsigned)(tm * tn), (unsigned)g.batch), dim3(256), 0, st, g, tm, tn);
+  return hipGetLastError();
+}
+// The gradients' products share K out over 8 waves with either tile.
 template <typename E, int FORM> hipError_t launch_form(hipStream_t st, const Gemm& g, int tile) {
-  if constexpr (FORM == NN || FORM == NN_GLU) return launch<E, FORM, 2, 1, 8>(st, g);
-  else return tile == 32 ? launch<E, FORM, 2, 8, 4>(st, g) : launch<E, FORM, 4, 8, 3>(st, g);
+  return tile == 32 ? launch<E, FORM, 2, 8, 4>(st, g) : launch<E, FORM, 4, 8, 3>(st, g);
 }
 template <typename E> hipError_t launch_type(hipStream_t st, const Gemm& g, int tile) {
-  if (g.glu == 1) return launch_form<E, NN_GLU>(st, g, tile);
+  if (g.glu == 1) return launch_forward<E, true>(st, g);
   if (g.glu == 2) return launch_form<E, NT_GLU>(st, g, tile);
   if (g.transA) return g.nx ? launch_form<E, TN_PARTS>(st, g, tile) : launch_form<E, TN_ACC>(st, g, tile);
   if (g.transB) return g.kseg ? launch_form<E, NT_SEG>(st, g, tile) : launch_form<E, NT>(st, g, tile);
-  return launch_form<E, NN>(st, g, tile);
+  return launch_forward<E, false>(st, g);
 }
 
 }  // namespace
 
 bool gemm_small_takes(const Gemm& g) {
   if (g.N % 4 || g.batch > 65535 || g.transA != g.c_f32_accum || (g.transA && g.transB)) return false;   // the forms of the stage's products
-  // The k-lines of a row-contiguous operand that fill up the last slab lie behind its descriptor, unless their 32-bit offsets
-  // wrap around: few rows, more than 2^32 / 64 bytes apart.
+  // k-lines of a row-contiguous operand that fill up the last slab (forward: stage) must not wrap around in 32 bits: few rows, far
+  // apart.  They lie behind the descriptor; the forward's lanes are pushed there by 2^31.
   const int64_t lines = cdiv(g.nx ? (int64_t)g.K - (int64_t)g.nx * g.kseg : g.K, 32) * 32;
-  return !(g.transA && lines * g.lda * 2 >= (1ll << 32)) && !(!g.transB && lines * g.ldb * 2 >= (1ll << 32));
+  if (g.transA) return lines * g.lda * 2 < (1ll << 32) && lines * g.ldb * 2 < (1ll << 32);
+  return g.transB || cdiv(g.K, 128) * 128 * g.ldb * 2 < (1ll << 31);
 }
 
 // Tile of the small kernel (32 or 64) when it is the faster way, else 0.  Times in us, fitted to single products of bf16 with
