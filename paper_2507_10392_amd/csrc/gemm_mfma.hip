@@ -250,14 +250,15 @@ __global__ __launch_bounds__(256) void add_partials_kernel(float* C, int64_t ldc
 }  // namespace
 
 // ---- parts of K side by side ---------------------------------------------------------------------------------------
-// An input gradient over few tokens has few tiles and a long K (512 x 4096 with K = 22016: 128 tiles of 128x128, half the CUs idle,
-// and each of the others waits for cold lines of the weights).  With scratch for as many fp32 results the two halves of
-// its K, or its segments (gate and up; Q, K and V), run as a batch, and a second kernel adds and rounds them: taken when the
-// estimate of both kernels (the second one at 4.5 TB/s) is the shorter time.  us: 512 x 4096, K = 22016 in 2 parts 176 -> 130 (128x128
-// tiles); K = 12288 in 3 segments 129 -> 82.
+// A forward product or an input gradient over few tokens has few tiles and a long K (512 x 4096 with K = 22016: 128 tiles of 128x128,
+// half the CUs idle, and each of the others waits for cold lines of the weights).  With scratch for as many fp32 results the two
+// halves of its K, or an input gradient's segments (gate and up; Q, K and V), run as a batch, and a second kernel adds them, bias
+// and residual, and rounds: taken when the estimate of both kernels (the second one at 4.5 TB/s) is the shorter time.  us: 512 x
+// 4096, K = 22016 in 2 parts 176 -> 130 (128x128 tiles); K = 12288 in 3 segments 129 -> 82;
+// forward, K = 11008 105 -> 65, K = 4096 49 -> 37.
 namespace {
 bool plan_parts(DType dt, const Gemm& g, Gemm& best) {
-  if (g_force_tile || !g.ws || g.transA || !g.transB || g.c_f32_accum || g.batch != 1 || g.bias || g.resid || g.rope || g.glu || g.nx) return false;
+  if (g_force_tile || !g.ws || g.transA || g.c_f32_accum || g.batch != 1 || (g.transB && (g.bias || g.resid)) || g.rope || g.glu || g.nx) return false;
   const int64_t tiles = cdiv(g.M, 128) * cdiv(g.N, 128);
   if (tiles > 128 || g.N % 8 || ((uintptr_t)g.ws & 15)) return false;
   double us = 0.95 * gemm_mfma_us(g);
@@ -267,23 +268,28 @@ bool plan_parts(DType dt, const Gemm& g, Gemm& best) {
     if (g.ws_bytes < 4ll * n * g.M * g.N) continue;
     Gemm h = g;
     h.ws = nullptr; h.ws_bytes = 0; h.kseg = 0; h.segB = 0;
-    h.K = g.K / n; h.sA = h.K; h.sB = g.kseg ? g.segB : h.K;
+    h.K = g.K / n; h.sA = h.K; h.sB = g.kseg ? g.segB : g.transB ? h.K : (int64_t)h.K * g.ldb;
+    h.bias = h.resid = nullptr; h.ldr = 0; h.sBias = 0;
     h.C = g.ws; h.ldc = g.N; h.sC = (int64_t)g.M * g.N;
     h.batch = n; h.c_f32_accum = 1; h.c_overwrite = 1;
-    const double t = gemm_mfma_us(h) + LAUNCH + (double)g.M * g.N * (4 * n + 2) / 4.5e6;
+    const double t = gemm_mfma_us(h) + LAUNCH + (double)g.M * g.N * (4 * n + (g.resid ? 4 : 2)) / 4.5e6;
     if (t < us && gemm_mfma_takes(dt, h)) { us = t; best = h; }
   }
   return best.batch > 1;
 }
 
-// C = p[0] + p[1] + .. in this order, rounded: 8 columns per thread.
+// C = p[0] + p[1] + .. in this order (+ bias, + residual R), rounded: 8 columns per thread.
 template <typename E, int n>
-__global__ __launch_bounds__(256) void add_parts_kernel(int64_t nvec, int vec_per_row, const float* __restrict__ p, int64_t part, E* __restrict__ C,
-                                                        int64_t ldc) {
+__global__ __launch_bounds__(256) void add_parts_kernel(int64_t nvec, int vec_per_row, const float* __restrict__ p, int64_t part, E* C,
+                                                        int64_t ldc, const E* __restrict__ bias, const E* R, int64_t ldr) {
   typedef typename Vec<E>::type E8;
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (i >= nvec) return;
+  const int64_t row = i / vec_per_row, col = (i % vec_per_row) * 8;
   f32x4 v[n][2];
+  E8 bb = {}, rr = {};
+  if (bias) bb = *reinterpret_cast<const E8*>(bias + col);
+  if (R) rr = *reinterpret_cast<const E8*>(R + row * ldr + col);
 #pragma unroll
   for (int z = 0; z < n; ++z) {
     const f32x4* a = reinterpret_cast<const f32x4*>(p + z * part + i * 8);
@@ -294,13 +300,18 @@ __global__ __launch_bounds__(256) void add_parts_kernel(int64_t nvec, int vec_pe
   for (int z = 1; z < n; ++z) { v[0][0] += v[z][0]; v[0][1] += v[z][1]; }
   E8 o;
 #pragma unroll
-  for (int e = 0; e < 8; ++e) o[e] = (E)v[0][e / 4][e & 3];
-  *reinterpret_cast<E8*>(C + i / vec_per_row * ldc + (i % vec_per_row) * 8) = o;
+  for (int e = 0; e < 8; ++e) {
+    float x = v[0][e / 4][e & 3];
+    if (bias) x += (float)bb[e];
+    if (R) x += (float)rr[e];
+    o[e] = (E)x;
+  }
+  *reinterpret_cast<E8*>(C + row * ldc + col) = o;
 }
 template <typename E> hipError_t add_parts(hipStream_t st, const Gemm& g, int n) {
   const int64_t nvec = (int64_t)g.M * g.N / 8;
   auto kern = n == 2 ? add_parts_kernel<E, 2> : add_parts_kernel<E, 3>;
-  hipLaunchKernelGGL(kern, dim3((unsigned)cdiv(nvec, 256)), dim3(256), 0, st, nvec, g.N / 8, (const float*)g.ws, (int64_t)g.M * g.N, (E*)g.C, g.ldc);
+  hipLaunchKernelGGL(kern, dim3((unsigned)cdiv(nvec, 256)), dim3(256), 0, st, nvec, g.N / 8, (const float*)g.ws, (int64_t)g.M * g.N, (E*)g.C, g.ldc, (const E*)g.bias, (const E*)g.resid, g.ldr);
   return hipGetLastError();
 }
 }  // namespace

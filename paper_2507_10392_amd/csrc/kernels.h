@@ -19,7 +19,7 @@ namespace zs {
 //             their own, part 0 from A, B and part p from Ax[p-1], Bx[p-1] (same leading dimensions and batch
 //             strides); parts 0..nx-1 have kseg rows each, the last one the remaining K - nx*kseg > 0 rows:
 //             C += sum_p A_p^T B_p in one K loop (weight gradients of several microbatches).
-//   ws != NULL (nx = 0, an input gradient): ws_bytes of scratch with which a product of few tiles and long K may run two or three
+//   ws != NULL (nx = 0, y = x W or dx = dy W^T): ws_bytes of scratch with which a product of few tiles and long K may run two or three
 //             parts of K side by side, as fp32 results in ws that a second kernel adds and rounds.
 //   ws != NULL (nx > 0): ws_bytes of scratch that the MFMA path may use when the 256x256 tiles of the product do
 //             not fill whole rounds of 256 workgroups: the tiles beyond the whole rounds (the last ones of the kernel's

@@ -483,6 +483,9 @@ bool layer_forward(stage_t* s, int l, char* x_in, LayerActs& A, char* y, const v
   g = Gemm();
   g.M = T; g.N = H; g.K = H; g.A = A.o; g.lda = H; g.B = W("Wo"); g.ldb = H; g.C = A.x2; g.ldc = H;
   g.resid = x_in; g.ldr = H; if (gpt) g.bias = W("bo");
+  // scratch of the layers' backward, one after the other: gO, gQKV and gF1 (gA, gB and ytmp may hold gradients beside a recomputation)
+  Plan& pl = s->plan;
+  g.ws = pl.gO; g.ws_bytes = pl.gF1 + (int64_t)T * F * h.E - pl.gO;
   if (!do_gemm(s, g)) return false;
   if (!run(s, "norm_fwd", 0, 2 * thb, [&] {
         return gpt ? norm_fwd(s->st, dt, 0, T, H, A.x2, W("ln2.g"), W("ln2.b"), s->cfg.norm_eps, A.n2, A.rstd2, A.mean2)
@@ -501,6 +504,7 @@ bool layer_forward(stage_t* s, int l, char* x_in, LayerActs& A, char* y, const v
   g = Gemm();
   g.M = T; g.N = H; g.K = F; g.A = A.a; g.lda = F; g.B = gpt ? W("W2") : W("Wd"); g.ldb = H; g.C = y; g.ldc = H;
   g.resid = A.x2; g.ldr = H; if (gpt) g.bias = W("b2");
+  g.ws = pl.gO; g.ws_bytes = pl.gF1 + (int64_t)T * F * h.E - pl.gO;
   return do_gemm(s, g);
 }
 

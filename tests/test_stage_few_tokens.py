@@ -57,3 +57,11 @@ def test_three_segments_over_several_microbatches(gpu_device, more, M, launches)
 def test_lm_head_gradient_as_two_halves(gpu_device, name, vocab):
     """The scratch lies over buffers that the layers' backward writes later.  The FFN's gradient is the other product in halves."""
     assert run(name, 2048, 16, 2048, 640, vocab=vocab)["gemm_halves_nt"]["launches"] == 2
+
+
+# Forward products of 80 or 96 tiles: the FFN's down projection, with its residual (GPT: and bias), and where K is long enough the attention
+# output's, in two halves over scratch of the backward, also beside gradients (recomputation).
+@pytest.mark.parametrize("name,ffn,seq,more", [("C3t", 5120, 640, {}), ("C3h", 5136, 600, {}), ("C2t", 8192, 600, {}), ("C2h", 8192, 760, {}),
+                                               ("C3t", 8192, 640, dict(recompute=1, layers=2))])
+def test_forward_products_as_two_halves_of_k(gpu_device, name, ffn, seq, more):
+    assert run(name, 2048, 16, ffn, seq, 2, **more)["gemm_halves_nn"]["launches"] >= 2
