@@ -347,9 +347,11 @@ hipError_t colsum_partials(hipStream_t st, DType dt, int T, const ColsumJob* job
 // waves, that many of them share a row (vector j of part p covers chunk j WPR + p), their sums of u and u*xhat meet in LDS
 // once per row, and 8 / WPR rows are walked side by side.  A wave thereby holds at most 4 vectors per lane and two waves fit
 // a SIMD, one's loads under the other's arithmetic (20 instructions per element).  FULL: H = 64 V J exactly (WPR = 1); else
-// the vectors past the row's end are masked.  bf16, us: LayerNorm, 4097 rows of 3080 48 as three kernels, 33 here (46 with 7
-// vectors in one of four waves); 4096 rows of 2560 34 : 23; RMSNorm, 4096 rows of 8192 97 : 65.  Exact rows of 4096 and 5120
-// elements stay with one wave per row (32 and 39 us; 34 and 45 with two).
+// the vectors past the row's end are masked.  With up to 4 vectors per lane the next row's loads are in flight beside a row's sums (with 8
+// or 10 there are no registers for them): without, a workgroup went through load, reduce, barrier and store 17 times with nothing
+// in flight in between.  bf16, us, without : with: LayerNorm, 4097 rows of 3080 28.0 : 23.4 (48 as three kernels), 8200 rows of 600
+// 16.7 : 13.8; RMSNorm, 4100 rows of 1288 13.7 : 10.4, 700 rows of 8192 13.8 : 11.9.  Exact rows of 4096 and 5120 elements stay with
+// one wave per row (LayerNorm 30 and 42 us, RMSNorm 24 and 18 for 4096 and 2048 rows).
 template <typename T, int KIND, int J, int WPR, bool FULL>
 __global__ __launch_bounds__(WPR == 1 ? 256 : 512) void norm_bwd_partials_reg_kernel(int Trows, int width, const T* __restrict__ dn, const T* __restrict__ x,
                                                                     const T* __restrict__ g, const float* __restrict__ rstd,
@@ -370,27 +372,51 @@ __global__ __launch_bounds__(WPR == 1 ? 256 : 512) void norm_bwd_partials_reg_ke
   for (int j = 0; j < J; ++j)
 #pragma unroll
     for (int i = 0; i < V; ++i) { pg[j][i] = 0.f; if (KIND == 0) pb[j][i] = 0.f; }
-  int turn = 0;
-  for (int row = r0 + q; (WPR == 1 ? row : row - q) < r1; row += RG) {   // WPR > 1: the same steps in every wave, for the barrier
-    const bool live = WPR == 1 || row < r1;
-    const float r = live ? rstd[row] : 0.f;
-    const float mu = (KIND == 0 && live) ? mean[row] : 0.f;
+  typedef typename Vec<T>::type TV;
+  // AHEAD: the next row's loads go out before this row's sums, and the gains stay in registers.  dx may lie over dres: other rows.
+  constexpr bool AHEAD = J <= 4;
+  struct Row { TV x[J], d[J], r[J]; float rstd, mean; };
+  auto load = [&](Row& w, int row) {
+    const bool live = row < r1;
+    w.rstd = live ? rstd[row] : 0.f;
+    w.mean = (KIND == 0 && live) ? mean[row] : 0.f;
     const int64_t off = (int64_t)row * H;
-    typename Vec<T>::type xv[J], dv[J], rv[J];
 #pragma unroll
     for (int j = 0; j < J; ++j) {
       if (!live || !in(j)) continue;
-      const int c = col(j);
-      xv[j] = *reinterpret_cast<const typename Vec<T>::type*>(x + off + c);
-      dv[j] = *reinterpret_cast<const typename Vec<T>::type*>(dn + off + c);
-      if (dres) rv[j] = *reinterpret_cast<const typename Vec<T>::type*>(dres + off + c);
+      w.x[j] = *reinterpret_cast<const TV*>(x + off + col(j));
+      w.d[j] = *reinterpret_cast<const TV*>(dn + off + col(j));
+      if (dres) w.r[j] = *reinterpret_cast<const TV*>(dres + off + col(j));
     }
+  };
+  TV gains[AHEAD ? J : 1];
+  if constexpr (AHEAD) {
+#pragma unroll
+    for (int j = 0; j < J; ++j)
+      if (in(j)) gains[j] = *reinterpret_cast<const TV*>(g + col(j));
+  }
+  auto gain = [&](int j, float (&gg)[V]) {
+    if constexpr (AHEAD) {
+#pragma unroll
+      for (int i = 0; i < V; ++i) gg[i] = to_f(gains[j][i]);
+    } else load_vec(g + col(j), gg);
+  };
+  int turn = 0;
+  Row cur, next;
+  if (AHEAD) load(cur, r0 + q);
+  for (int row = r0 + q; (WPR == 1 ? row : row - q) < r1; row += RG) {   // WPR > 1: the same steps in every wave, for the barrier
+    if (AHEAD) load(next, row + RG);
+    else load(cur, row);
+    const bool live = WPR == 1 || row < r1;
+    const float r = cur.rstd, mu = cur.mean;
+    const int64_t off = (int64_t)row * H;
+    const TV (&xv)[J] = cur.x, (&dv)[J] = cur.d, (&rv)[J] = cur.r;
     float su = 0.f, sux = 0.f;
 #pragma unroll
     for (int j = 0; j < J; ++j) {
       if (!live || !in(j)) continue;
       float gg[V];
-      load_vec(g + col(j), gg);
+      gain(j, gg);
 #pragma unroll
       for (int i = 0; i < V; ++i) {
         const float d = to_f(dv[j][i]), xx = to_f(xv[j][i]);
@@ -418,7 +444,7 @@ __global__ __launch_bounds__(WPR == 1 ? 256 : 512) void norm_bwd_partials_reg_ke
       if (!live || !in(j)) continue;
       const int c = col(j);
       float o[V], gg[V];
-      load_vec(g + c, gg);
+      gain(j, gg);
 #pragma unroll
       for (int i = 0; i < V; ++i) {
         const float u = to_f(dv[j][i]) * gg[i];
@@ -426,6 +452,7 @@ __global__ __launch_bounds__(WPR == 1 ? 256 : 512) void norm_bwd_partials_reg_ke
       }
       store_vec(dx + off + c, o);
     }
+    if (AHEAD) cur = next;
   }
   // sums over the rows walked side by side, in order, first of dn*xhat, then (LayerNorm) of dn
 #pragma unroll
