@@ -3,15 +3,15 @@
 //
 // What bounds it: the models that run in fp32 are small, so a launch has few rows and its time is a wave's walk over the keys.
 // A workgroup therefore owns only 16 queries (or keys), and its four waves share out the other side's tiles of 32 rows and
-// merge at the end through LDS, in a fixed order.  Operands go from L2 straight into the registers that the matrix
-// instruction reads, as in gemm_f32.hip: "k" fragments (4 consecutive elements along the head dim per lane) for the products
+// merge at the end through LDS, in a fixed order.  Every wave loads its own operands from L2, as in gemm_f32.hip: "k" fragments (4 consecutive elements along the head dim per lane) for the products
 // over d, "r" fragments (4 consecutive head-dim columns of rows 4 (l/16) + e) for the products over keys or queries.  All
 // products are transposed (S^T = K Q^T, O^T = V^T P^T): a lane then owns query l%16 and holds the scores of keys 4 (l/16) + r
 // in register r, which is the operand layout that step e = r of the second product wants, so P never moves between lanes.
 // The loads of a tile run one tile-quarter (or more, registers permitting) ahead of their use.
 //
-// Measured, forward + backward in three launches, against the wave-per-row kernel: 8 heads of 64, S = 128: 91 -> 30 us; 4 heads of 128, S = 256:
-// 273 -> 51 us; 16 heads of 64, S = 1000: 2080 -> 188 us; the errors against float64 are smaller (dk 8.1e-7 -> 4.8e-7).
+// Measured, forward + backward in three launches with direct loads of "k" fragments (now through LDS, see load_lines), against the
+// wave-per-row kernel: 8 heads of 64, S = 128: 91 -> 30 us; 4 heads of 128, S = 256: 273 -> 51 us; 16 heads of 64, S = 1000:
+// 2080 -> 188 us; the errors against float64 are smaller (dk 8.1e-7 -> 4.8e-7).
 #include "kernels.h"
 #include "attention_rows.h"
 
@@ -32,11 +32,27 @@ __device__ __forceinline__ f32x4 load4(const Head& h, unsigned voff, unsigned so
   c.u = __builtin_amdgcn_raw_buffer_load_b128(h.rs, (int)voff, (int)soff, 0);
   return c.f;
 }
-// 16 rows x 16 DS columns from row `row0`: k[s] = columns 16 s + 4 (l/16) .. +3 of row l%16.
-template <int DS> __device__ __forceinline__ void load_k(f32x4 (&f)[DS], const Head& h, int row0, int lane, int dd) {
-  const unsigned at = (lane & 15) * h.ld * 4 + (lane >> 4) * 16;
+// 16 rows x 16 DS columns from row `row0`: k[s] = columns 16 s + 4 (l/16) .. +3 of row l%16.  They come as whole lines (load_lines; read as
+// fragments, the lanes of a load would lie in 16 rows, and the address unit takes four times as long for their pieces) and change
+// places in LDS of the wave's own (to_k; no barrier, a wave's LDS accesses keep their order), the 16-byte piece p of row r at p ^ r.
+// us, fragments : lines: S = 256, 4 heads of 128 forward 13.0 : 10.8, backward 26.0 : 19.7; S = 128, 8 of 64 10.9 : 7.9 (backward); S = 1000, 16
+// of 64 40 : 30 and 138 : 105; 64 of 128 325 : 201 and 932 : 842.
+template <int DS> struct Lines { f32x4 v[16 * 4 * DS]; };
+template <int DS> __device__ __forceinline__ void load_lines(f32x4 (&f)[DS], const Head& h, int row0, int lane, int dd) {
+  constexpr int P = 4 * DS, R = 64 / P;   // pieces of a row, rows of a load
+  const unsigned at = 4 * (lane % P) < dd ? lane / P * h.ld * 4 + lane % P * 16 : OUT;
 #pragma unroll
-  for (int s = 0; s < DS; ++s) f[s] = load4(h, 16 * s + 4 * (lane >> 4) < dd ? at + 64 * s : OUT, row0 * h.ld * 4);
+  for (int s = 0; s < DS; ++s) f[s] = load4(h, at, (row0 + R * s) * h.ld * 4);
+}
+template <int DS> __device__ __forceinline__ void to_k(f32x4 (&f)[DS], Lines<DS>& lines, int lane) {
+  constexpr int P = 4 * DS, R = 64 / P;
+#pragma unroll
+  for (int s = 0; s < DS; ++s) {
+    const int row = R * s + lane / P;
+    lines.v[row * P + ((lane % P) ^ row)] = f[s];
+  }
+#pragma unroll
+  for (int s = 0; s < DS; ++s) f[s] = lines.v[(lane & 15) * P + ((4 * s + (lane >> 4)) ^ (lane & 15))];
 }
 // The same 16 rows by columns: r[4 g + e] = columns 64 g + 4 (l%16) .. +3 of row 4 (l/16) + e.
 template <int DS> __device__ __forceinline__ void load_r(f32x4 (&f)[DS], const Head& h, int row0, int lane, int dd) {
@@ -189,26 +205,28 @@ __global__ __launch_bounds__(64 * KW) void attn_fwd_f32_kernel(int S, int dd, co
   __shared__ float rowbuf[KW][32 * DS];   // rows that are redone
   __shared__ unsigned masks[KW];
   __shared__ float ms[KW][16], ls[KW][16];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  __shared__ Lines<DS> lines[KW];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const Block blk = block_of(blockIdx.x, nh, mb);
   const int q0 = ((S + 15) / 16 - 1 - blk.rank) * 16, my_q = q0 + (lane & 15);
   const int64_t tok0 = (int64_t)blk.b * S;
   const Head hq = head_of(q + tok0 * ld + blk.h * dd, ld, S, dd), hk = head_of(k + tok0 * ld + blk.h * dd, ld, S, dd),
              hv = head_of(v + tok0 * ld + blk.h * dd, ld, S, dd);
   f32x4 qf[DS], acc[DS], buf[NBUF][DS];
-  load_k<DS>(qf, hq, q0, lane, dd);
+  load_lines<DS>(qf, hq, q0, lane, dd);
 #pragma unroll
   for (int s = 0; s < DS; ++s) acc[s] = f32x4{0.f, 0.f, 0.f, 0.f};
   float m = -INFINITY, l = 0.f;
   // fragments of a tile in the order of their use: K rows 0-15, K rows 16-31, V rows 0-15, V rows 16-31
   auto load = [&](f32x4 (&f)[DS], int step, int tile) {
     const int row0 = tile * TK + 16 * (step & 1);
-    if (step < 2) load_k<DS>(f, hk, row0, lane, dd); else load_r<DS>(f, hv, row0, lane, dd);
+    if (step < 2) load_lines<DS>(f, hk, row0, lane, dd); else load_r<DS>(f, hv, row0, lane, dd);
   };
   const int tiles = (min(q0 + 15, S - 1)) / TK + 1;
   if (wave < tiles) {
 #pragma unroll
     for (int s = 0; s < NBUF - 1; ++s) load(buf[s], s, wave);
+    to_k<DS>(qf, lines[wave], lane);
     for (int t = wave; t < tiles; t += KW) {
       f32x4 p[2];
 #pragma unroll
@@ -216,6 +234,7 @@ __global__ __launch_bounds__(64 * KW) void attn_fwd_f32_kernel(int S, int dd, co
         const int ahead = step + NBUF - 1;   // loads behind the last tile are issued and not used
         load(buf[ahead % NBUF], ahead % 4, ahead < 4 ? t : t + KW);
         if (step < 2) {
+          to_k<DS>(buf[step % NBUF], lines[wave], lane);
           p[step] = dot<DS>(buf[step % NBUF], qf);
           if (step == 1) {
             const int key0 = t * TK + 4 * (lane >> 4);
@@ -281,13 +300,14 @@ template <int DS> struct BwdLds {
   f32x4 red[(KW - 1) * DS * 64];
   float rowbuf[KW][32 * DS];   // rows that are redone
   unsigned masks[KW];
+  Lines<DS> lines[KW];
 };
 template <int DS, int NBUF>
 __device__ __forceinline__ void dq_block(BwdLds<DS>& lds, int block, int S, int dd, const float* __restrict__ q, const float* __restrict__ k,
                                          const float* __restrict__ v, int64_t ld, const float* __restrict__ o, const float* __restrict__ dout,
                                          int64_t ldo, const float* __restrict__ lse, float* __restrict__ delta, float* __restrict__ dq,
                                          int64_t ldd, float scale, int nh, int mb, const float2* __restrict__ rope) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const Block blk = block_of(block, nh, mb);
   const int q0 = ((S + 15) / 16 - 1 - blk.rank) * 16, my_q = q0 + (lane & 15);
   const int64_t tok0 = (int64_t)blk.b * S;
@@ -295,10 +315,13 @@ __device__ __forceinline__ void dq_block(BwdLds<DS>& lds, int block, int S, int 
              hv = head_of(v + tok0 * ld + blk.h * dd, ld, S, dd), ho = head_of(o + tok0 * ldo + blk.h * dd, ldo, S, dd),
              hdo = head_of(dout + tok0 * ldo + blk.h * dd, ldo, S, dd);
   f32x4 qf[DS], dof[DS], acc[DS], buf[NBUF][DS];
-  load_k<DS>(qf, hq, q0, lane, dd);
-  load_k<DS>(dof, hdo, q0, lane, dd);
+  load_lines<DS>(qf, hq, q0, lane, dd);
+  load_lines<DS>(dof, hdo, q0, lane, dd);
   float dlt = 0.f;
-  load_k<DS>(acc, ho, q0, lane, dd);
+  load_lines<DS>(acc, ho, q0, lane, dd);
+  to_k<DS>(qf, lds.lines[wave], lane);
+  to_k<DS>(dof, lds.lines[wave], lane);
+  to_k<DS>(acc, lds.lines[wave], lane);
 #pragma unroll
   for (int s = 0; s < DS; ++s)
 #pragma unroll
@@ -312,7 +335,7 @@ __device__ __forceinline__ void dq_block(BwdLds<DS>& lds, int block, int S, int 
   // order of use: K, V of rows 0-15 by k, K, V of rows 16-31 by k, K of rows 0-15 and 16-31 by columns
   auto load = [&](f32x4 (&f)[DS], int step, int tile) {
     const int row0 = tile * TK;
-    if (step < 4) load_k<DS>(f, step & 1 ? hv : hk, row0 + 16 * (step >> 1), lane, dd);
+    if (step < 4) load_lines<DS>(f, step & 1 ? hv : hk, row0 + 16 * (step >> 1), lane, dd);
     else load_r<DS>(f, hk, row0 + 16 * (step - 4), lane, dd);
   };
   const int tiles = min(q0 + 15, S - 1) / TK + 1;
@@ -326,6 +349,7 @@ __device__ __forceinline__ void dq_block(BwdLds<DS>& lds, int block, int S, int 
         const int ahead = step + NBUF - 1;
         load(buf[ahead % NBUF], ahead % 6, ahead < 6 ? t : t + KW);
         if (step < 4) {
+          to_k<DS>(buf[step % NBUF], lds.lines[wave], lane);
           if (!(step & 1)) { sc = dot<DS>(buf[step % NBUF], qf); continue; }
           const f32x4 dp = dot<DS>(buf[step % NBUF], dof);
           const int key0 = t * TK + 16 * (step >> 1) + 4 * (lane >> 4);
@@ -387,7 +411,7 @@ __global__ __launch_bounds__(64 * KW) void attn_bwd_dkv_f32_kernel(int S, int dd
       dq_block<DS, QBUF>(lds, blockIdx.x - dkv_blocks, S, dd, q, k, v, ld, o, dout, ldo, lse, delta_out, dq, ldd, scale, nh, mb, rope);
       return;
     }
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const Block blk = block_of(blockIdx.x, nh, mb);
   const int k0 = blk.rank * 16, my_k = k0 + (lane & 15);
   const int64_t tok0 = (int64_t)blk.b * S;
@@ -397,19 +421,21 @@ __global__ __launch_bounds__(64 * KW) void attn_bwd_dkv_f32_kernel(int S, int dd
   const float* lse_h = lse + ((int64_t)blk.b * nh + blk.h) * S;
   const float* dlt_h = BOTH ? nullptr : delta + ((int64_t)blk.b * nh + blk.h) * S;
   f32x4 kf[DS], vf[DS], dka[DS], dva[DS], buf[NBUF][DS];
-  load_k<DS>(kf, hk, k0, lane, dd);
-  load_k<DS>(vf, hv, k0, lane, dd);
+  load_lines<DS>(kf, hk, k0, lane, dd);
+  load_lines<DS>(vf, hv, k0, lane, dd);
 #pragma unroll
   for (int s = 0; s < DS; ++s) dka[s] = dva[s] = f32x4{0.f, 0.f, 0.f, 0.f};
   // order of use: Q, dO (BOTH: and O) of rows 0-15 by k, the same of rows 16-31, then by columns dO, Q of rows 0-15 and of rows 16-31
   auto load = [&](f32x4 (&f)[DS], int step, int tile) {
-    if (step < KSTEPS) load_k<DS>(f, step % R == 0 ? hq : step % R == 1 ? hdo : ho, tile * TK + 16 * (step / R), lane, dd);
+    if (step < KSTEPS) load_lines<DS>(f, step % R == 0 ? hq : step % R == 1 ? hdo : ho, tile * TK + 16 * (step / R), lane, dd);
     else load_r<DS>(f, (step - KSTEPS) & 1 ? hq : hdo, tile * TK + 16 * ((step - KSTEPS) >> 1), lane, dd);
   };
   const int first = k0 / TK + wave, tiles = (S + TK - 1) / TK;
   if (first < tiles) {
 #pragma unroll
     for (int s = 0; s < NBUF - 1; ++s) load(buf[s], s, first);
+    to_k<DS>(kf, lds.lines[wave], lane);
+    to_k<DS>(vf, lds.lines[wave], lane);
     for (int t = first; t < tiles; t += KW) {
       f32x4 p[2], ds[2];
       float li[2][4], di[2][4];
@@ -425,6 +451,7 @@ __global__ __launch_bounds__(64 * KW) void attn_bwd_dkv_f32_kernel(int S, int dd
 #pragma unroll
       for (int step = 0; step < STEPS; ++step) {
         const int ib = step / R;
+        if (step < KSTEPS) to_k<DS>(buf[step % NBUF], lds.lines[wave], lane);
         if (BOTH && step < KSTEPS && step % R == 2) {   // before the load into the buffer of dO
           float x = 0.f;
 #pragma unroll

@@ -447,7 +447,9 @@ bool gemm_small_takes(const Gemm& g) {
 // time (a workgroup's launch, merge and store) plus the walk over K.  A k-contiguous B costs more per k (see above).  On the
 // geometric mean of 1400 products the choice is within 0.4 % of the fastest of 32, 64 and 128x128 with one slab in flight, one part
 // of K and no oblong tile beside it, which is what `staged` prices: gemm_mfma has become faster since, above all for input gradients
-// with scratch, and the line has not been drawn again.  Measured against those staged tiles, us: 256 x 512, K = 512 4.5 : 8.9, input gradient with K = 2752 in two
+// with scratch, and so have the small kernels' forward products and input gradients; the line still takes the fastest of 32, 64 and
+// the staged tiles within 0.3 % on the geometric mean of 150 more products of 32 to 2500 rows (15 % at worst), and has not been
+// drawn again.  Measured against those staged tiles, us: 256 x 512, K = 512 4.5 : 8.9, input gradient with K = 2752 in two
 // segments 10.9 : 27.1; 512 x 512, K = 256, accumulating 3.3 : 5.8; 1024 x 1024, K = 1024, accumulating 9.6 : 13.0.  At 1024 x
 // 2048, K = 1024 it loses (16.3 : 14.1), at 512 x 4096, K = 4096 (47 : 37), and accumulating over few tokens, where the rounds'
 // fixed time is all there is (1528 x 2624, K = 8: 16.6 : 7.8; 2376 x 1632, K = 16, two batches 30.4 : 11.7).
