@@ -157,8 +157,8 @@ template <int NT, int D> __device__ __forceinline__ void put_tile(const TileRegs
   }
 }
 
-// Row fragments kept in registers for a whole kernel: lane (row = row0 + lane%32, g) holds, for each of the
-// D/16 contraction steps over d, 8 consecutive elements.  Rows >= nrows and columns >= dd read as zero.
+// Row fragments kept in registers for a whole kernel: lane (row = row0 + lane%32, g) holds, for each of the D/16 contraction steps over
+// d, 8 consecutive elements.  Rows >= nrows and columns >= dd read as zero.
 template <int D>
 __device__ __forceinline__ void load_row_frags(e16x8 (&f)[D / 16], const e16* __restrict__ src, int64_t ld, int row0,
                                                int nrows, int lane, int dd) {
@@ -167,6 +167,51 @@ __device__ __forceinline__ void load_row_frags(e16x8 (&f)[D / 16], const e16* __
   for (int s = 0; s < D / 16; ++s) {
     const int c = 16 * s + 8 * (lane >> 5);
     f[s] = row < nrows && c < dd ? *reinterpret_cast<const e16x8*>(src + (int64_t)row * ld + c) : zero8();
+  }
+}
+// The same by way of LDS: the wave's 32 rows come as whole lines (load_lines) and change places in its own part of the LDS (to_frags; 32
+// rows of LDT).  Read as fragments, the lanes of a load lie in 32 rows, and the address unit takes four times as long for their
+// pieces; the same holds for stores of accumulators (store_rows).  The backward kernels load up to three blocks of rows that way
+// and store two; in the forward, whose only block is Q, the way round costs more than it saves (16 heads of 128, S = 2048: 46.3 us
+// with direct loads, 49.4 without), and only the store goes through LDS.  us, fragments : lines, backward of 16 heads of 128, S =
+// 2048 98.9 : 83.0; 32 heads, S = 4096 460 : 447; 4 heads, S = 256 19.8 : 16.3.
+template <int D>
+__device__ __forceinline__ void load_lines(e16x8 (&f)[D / 16], const e16* __restrict__ src, int64_t ld, int row0, int nrows, int lane, int dd) {
+  constexpr int P = D / 8;   // 16-byte pieces of a row
+#pragma unroll
+  for (int i = 0; i < D / 16; ++i) {
+    const int v = lane + 64 * i, row = row0 + v / P, c = v % P * 8;
+    f[i] = row < nrows && c < dd ? *reinterpret_cast<const e16x8*>(src + (int64_t)row * ld + c) : zero8();
+  }
+}
+template <int D> __device__ __forceinline__ void to_frags(e16x8 (&f)[D / 16], e16* rows, int lane) {
+#pragma unroll
+  for (int i = 0; i < D / 16; ++i) {
+    const int v = lane + 64 * i;
+    *reinterpret_cast<e16x8*>(rows + v / (D / 8) * LDT<D> + v % (D / 8) * 8) = f[i];
+  }
+#pragma unroll
+  for (int s = 0; s < D / 16; ++s) f[s] = lds_frag<D>(rows, 0, 16 * s, lane);
+}
+// Rows row0 .. of dst, but those past nrows and those marked in `skip`, from a wave's accumulators.
+template <int D>
+__device__ __forceinline__ void store_rows(const f32x16 (&acc)[D / 32], float factor, e16* rows, e16* dst, int64_t ld, int row0, int nrows, int lane,
+                                           int dd, unsigned skip) {
+#pragma unroll
+  for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      e16x4 w;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) w[e] = (e16)(acc[db][4 * c + e] * factor);
+      *reinterpret_cast<e16x4*>(rows + (lane & 31) * LDT<D> + db * 32 + 8 * c + 4 * (lane >> 5)) = w;
+    }
+  constexpr int P = D / 4;   // 8-byte pieces of a row, as aligned as a direct store's would be
+#pragma unroll
+  for (int i = 0; i < D / 8; ++i) {
+    const int v = lane + 64 * i, r = v / P, c = v % P * 4;
+    const e16x4 w = *reinterpret_cast<const e16x4*>(rows + r * LDT<D> + c);
+    if (row0 + r < nrows && c < dd && !(skip >> r & 1)) *reinterpret_cast<e16x4*>(dst + (int64_t)(row0 + r) * ld + c) = w;
   }
 }
 
@@ -259,6 +304,10 @@ template <int N> __device__ __forceinline__ float mark_of(const f32x16 (&x)[N]) 
   return (mark[0] + mark[1]) + (mark[2] + mark[3]);
 }
 template <int NW> struct RedoLds { float rows[NW][256]; unsigned masks[NW]; float delta[NW * 32]; };
+// A wave's 32 rows for store_rows: behind what redone rows need, at the start of the LDS where none are.
+template <int NW, int D, bool SPLIT> __device__ __forceinline__ e16* rows_lds(char* smem, int wave) {
+  return reinterpret_cast<e16*>(smem + (SPLIT ? (sizeof(RedoLds<NW>) + 15) / 16 * 16 : 0)) + wave * 32 * LDT<D>;
+}
 template <int NW> __device__ __forceinline__ RedoLds<NW>& redo_lds(char* smem) { return *reinterpret_cast<RedoLds<NW>*>(smem); }
 // Publishes the rows of this wave's group; writer: one wave per group.
 template <int NW> __device__ __forceinline__ unsigned rows_of(RedoLds<NW>& lds, int group, bool writer, bool live, float mark) {
@@ -438,19 +487,8 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_fwd_kernel(int 
   }
   unsigned redo = 0;
   if constexpr (SPLIT) redo = rows_of(redo_lds<NW>(smem_raw), wave, true, my_q < S && l == l, mark_of(oacc));
+  store_rows<D>(oacc, 1.0f / l, rows_lds<NW, D, SPLIT>(smem_raw, wave), o + tok0 * ldo + h * dd, ldo, wq0, S, lane, dd, redo);
   if (my_q < S) {
-    const float inv = 1.0f / l;
-    e16* orow = o + (tok0 + my_q) * ldo + h * dd;
-#pragma unroll
-    for (int db = 0; db < D / 32; ++db)
-#pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        e16x4 w;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) w[e] = (e16)(oacc[db][4 * c + e] * inv);
-        if (!SPLIT || (db * 32 + 8 * c + 4 * (lane >> 5) < dd && !(redo >> (lane & 31) & 1)))
-          *reinterpret_cast<e16x4*>(orow + db * 32 + 8 * c + 4 * (lane >> 5)) = w;
-      }
     if (lane < 32)   // SPLIT: formed in double, once per row: m may lag the maximum by 8, so log l alone would round like lse does
       lse[((int64_t)b * nh + h) * S + my_q] =
           SPLIT ? (float)((double)m * 0.6931471805599453 + log((double)l)) : (m + log2f(l)) * LN2;
@@ -492,16 +530,20 @@ __device__ __forceinline__ void dq_block(int block, int S, const e16* __restrict
   fetch_tile(kr, rsk, (int)ld, 0, tid, dd);
   fetch_tile(vr, rsv, (int)ld, 0, tid, dd);
   e16x8 qf[D / 16], dof[D / 16];
-  load_row_frags<D>(qf, qh, ld, wq0, S, lane, dd);
-  load_row_frags<D>(dof, doh, ldo, wq0, S, lane, dd);
+  e16x8 of[D / 16];
+  load_lines<D>(qf, qh, ld, wq0, S, lane, dd);
+  load_lines<D>(dof, doh, ldo, wq0, S, lane, dd);
+  load_lines<D>(of, o + tok0 * ldo + h * dd, ldo, wq0, S, lane, dd);
   const int64_t stat = ((int64_t)b * nh + h) * S + min(my_q, S - 1);
   const float lse2 = lse[stat] * LOG2E;
   // delta_q = dO_q . O_q: each lane sums its 64 of the row's 128 products, lane^32 holds the others.
   // The value is also stored for the dK/dV kernel, which runs after this one.
   float dlt = 0.f;
   {
-    e16x8 of[D / 16];
-    load_row_frags<D>(of, o + tok0 * ldo + h * dd, ldo, wq0, S, lane, dd);
+    e16* rows = smem + (tid >> 6) * 32 * LDT<D>;
+    to_frags<D>(qf, rows, lane);
+    to_frags<D>(dof, rows, lane);
+    to_frags<D>(of, rows, lane);
 #pragma unroll
     for (int s = 0; s < D / 16; ++s)
 #pragma unroll
@@ -517,6 +559,7 @@ __device__ __forceinline__ void dq_block(int block, int S, const e16* __restrict
 
   const int last_q = min(q0 + 32 * QW - 1, S - 1);
   const int ntiles = last_q / TR + 1;
+  __syncthreads();
   put_tile(kr, smem, tid);
   put_tile(vr, smem + TILE<D>, tid);
   __syncthreads();
@@ -584,23 +627,13 @@ __device__ __forceinline__ void dq_block(int block, int S, const e16* __restrict
     if (half == 0 && lane < 32) rl.delta[32 * wave + lane] = dlt;
     redo = rows_of(rl, wave, half == 0, my_q < S && lse2 == lse2 && dlt == dlt, mark_of(acc));
   }
-  if (my_q < S && half == 0 && !(redo >> (lane & 31) & 1)) {
-    e16* row = dq + (tok0 + my_q) * ldd + h * dd;
+  if (half == 0) {
 #pragma unroll
     for (int db = 0; db < D / 32; ++db)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[db][r] *= SPLIT ? scale / DS_SCALE : scale;
-    if (rope) unrotate_row<D, D / 32>(acc, rope, my_q, lane, dd);
-#pragma unroll
-    for (int db = 0; db < D / 32; ++db)
-#pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        if (SPLIT && db * 32 + 8 * c + 4 * (lane >> 5) >= dd) continue;
-        e16x4 w;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) w[e] = (e16)acc[db][4 * c + e];
-        *reinterpret_cast<e16x4*>(row + db * 32 + 8 * c + 4 * (lane >> 5)) = w;
-      }
+    if (rope) unrotate_row<D, D / 32>(acc, rope, min(my_q, S - 1), lane, dd);
+    store_rows<D>(acc, 1.0f, rows_lds<NW, D, SPLIT>(smem_raw, wave), dq + tok0 * ldd + h * dd, ldd, wq0, S, lane, dd, redo);
   }
   if constexpr (SPLIT) {
     if (__builtin_expect(any_row(redo_lds<NW>(smem_raw).masks, QW, lane), 0))
@@ -704,7 +737,7 @@ __global__ __attribute__((amdgpu_waves_per_eu(SPLIT && LO_ACC && D > 64 ? 1 : 2,
   const int t_begin = k0 / TR, t_end = (S - 1) / TR + 1;
   fetch(t_begin);
   e16x8 kf[D / 16];
-  load_row_frags<D>(kf, kh, ld, wk0, S, lane, dd);
+  load_lines<D>(kf, kh, ld, wk0, S, lane, dd);
   if (QS == 1 || half == 0) {   // QS = 2: the first of the two waves brings the rows, the barrier before the loop publishes them
     e16* Vw = reinterpret_cast<e16*>(stats + 256) + wave * 32 * LDT<D>;
     const __amdgpu_buffer_rsrc_t rsv = head_rsrc(vh, ld, S, dd);   // rows past S read as zero
@@ -730,6 +763,8 @@ __global__ __attribute__((amdgpu_waves_per_eu(SPLIT && LO_ACC && D > 64 ? 1 : 2,
       if (SPLIT && LO_ACC) dklo[SPLIT && LO_ACC ? i : 0][r] = dvlo[SPLIT && LO_ACC ? i : 0][r] = 0.f;
     }
 
+  to_frags<D>(kf, smem + (tid >> 6) * 32 * LDT<D>, lane);
+  __syncthreads();
   put(0);
   __syncthreads();
   for (int t = t_begin; t < t_end; ++t) {
@@ -808,28 +843,15 @@ __global__ __attribute__((amdgpu_waves_per_eu(SPLIT && LO_ACC && D > 64 ? 1 : 2,
   }
   unsigned redo = 0;
   if constexpr (SPLIT) redo = rows_of(redo_lds<NW>(smem_raw), wave, half == 0, my_k < S, mark_of(dkacc) + mark_of(dvacc));
-  if (my_k < S && half == 0 && !(redo >> (lane & 31) & 1)) {
-    e16* krow = dk + (tok0 + my_k) * ldd + h * dd;
-    e16* vrow = dv + (tok0 + my_k) * ldd + h * dd;
+  if (half == 0) {
+    e16* rows = rows_lds<NW, D, SPLIT>(smem_raw, wave);
+    store_rows<D>(dvacc, 1.0f, rows, dv + tok0 * ldd + h * dd, ldd, wk0, S, lane, dd, redo);
 #pragma unroll
     for (int db = 0; db < D / 32; ++db)
 #pragma unroll
       for (int r = 0; r < 16; ++r) dkacc[db][r] *= SPLIT ? scale / DS_SCALE : scale;
-    if (rope) unrotate_row<D, SPLIT ? 1 : 2>(dkacc, rope, my_k, lane, dd);   // the registers that dV leaves: no spills
-#pragma unroll
-    for (int db = 0; db < D / 32; ++db)
-#pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        if (SPLIT && db * 32 + 8 * c + 4 * (lane >> 5) >= dd) continue;
-        e16x4 wk, wv;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          wk[e] = (e16)dkacc[db][4 * c + e];
-          wv[e] = (e16)dvacc[db][4 * c + e];
-        }
-        *reinterpret_cast<e16x4*>(krow + db * 32 + 8 * c + 4 * (lane >> 5)) = wk;
-        *reinterpret_cast<e16x4*>(vrow + db * 32 + 8 * c + 4 * (lane >> 5)) = wv;
-      }
+    if (rope) unrotate_row<D, SPLIT ? 1 : 2>(dkacc, rope, min(my_k, S - 1), lane, dd);   // the registers that dV leaves: no spills
+    store_rows<D>(dkacc, 1.0f, rows, dk + tok0 * ldd + h * dd, ldd, wk0, S, lane, dd, redo);
   }
   if constexpr (SPLIT) {
     if (__builtin_expect(any_row(redo_lds<NW>(smem_raw).masks, KWV, lane), 0))
