@@ -67,7 +67,8 @@ template <int NB> struct Frag<1, NB> {   // row-contiguous
 // 128x128 tiles reach the matrix cores' rate without.
 // A workgroup owns a (16 MI WM) x (16 NI WN) tile of C (MI, NI = 1, 2 or 4): WM x WN waves side by side, times KW waves
 // that share out K.
-template <int TA, int TB, int MI, int NI, int WM, int WN, int KW, int SEG>
+// ACT: see Gemm::act; kernels of their own, because the branch alone costs the small products 0.5 %.
+template <int TA, int TB, int MI, int NI, int WM, int WN, int KW, int SEG, int ACT = 0>
 __device__ __forceinline__ void f32_tile(const Gemm& g, int tiles_m, int tiles_n, int pid, int z) {
   constexpr int NQ = MI * NI;   // quads of 4 consecutive columns a lane holds
   constexpr bool STAGED = KW > 1 && (TA == 0 || TB == 1);   // k-contiguous operands through LDS
@@ -241,6 +242,21 @@ __device__ __forceinline__ void f32_tile(const Gemm& g, int tiles_m, int tiles_n
       const f32x4 t = *reinterpret_cast<const f32x4*>(g.rope + (int64_t)(m % g.rope_S) * (g.rope_d / 2) + (n % g.rope_d) / 2);
       v = f32x4{v[0] * t[0] - v[1] * t[1], v[0] * t[1] + v[1] * t[0], v[2] * t[2] - v[3] * t[3], v[2] * t[3] + v[3] * t[2]};
     }
+    if constexpr (ACT != 0) {
+      f32x4* pz = reinterpret_cast<f32x4*>((float*)g.act_z + (int64_t)m * g.ldc + n);
+      f32x4 a;
+      if constexpr (ACT == 2) {
+        const f32x4 zz = *pz;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) a[e] = v[e] * gelu_df(zz[e]);
+      } else {
+        *pc = v;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) a[e] = gelu_f(v[e]);
+      }
+      *pz = a;
+      return;
+    }
     *pc = g.c_f32_accum ? *pc + v : v;
   };
   if constexpr (KW == 1) {
@@ -267,9 +283,9 @@ __device__ __forceinline__ void f32_tile(const Gemm& g, int tiles_m, int tiles_n
   }
 }
 
-template <int TA, int TB, int MI, int NI, int WM, int WN, int KW, int SEG>
+template <int TA, int TB, int MI, int NI, int WM, int WN, int KW, int SEG, int ACT = 0>
 __global__ __launch_bounds__(64 * WM * WN * KW) void gemm_f32_kernel(Gemm g, int tiles_m, int tiles_n) {
-  f32_tile<TA, TB, MI, NI, WM, WN, KW, SEG>(g, tiles_m, tiles_n, blockIdx.x, blockIdx.y);
+  f32_tile<TA, TB, MI, NI, WM, WN, KW, SEG, ACT>(g, tiles_m, tiles_n, blockIdx.x, blockIdx.y);
 }
 // Weight gradients of a layer in one launch (see gemm_group).
 template <int MI, int NI, int WM, int WN, int KW> __global__ __launch_bounds__(64 * WM * WN * KW) void gemm_f32_group_kernel(GemmGroup q) {
@@ -287,7 +303,9 @@ template <int MI, int NI, int WM, int WN, int KW> hipError_t launch_group(hipStr
 template <int MI, int NI, int WM, int WN, int KW> hipError_t launch(hipStream_t st, const Gemm& g) {
   const int tm = (int)cdiv(g.M, 16 * MI * WM), tn = (int)cdiv(g.N, 16 * NI * WN);
   dim3 grid((unsigned)(tm * tn), (unsigned)g.batch), blk(64 * WM * WN * KW);
-  if (g.kseg) hipLaunchKernelGGL((gemm_f32_kernel<0, 1, MI, NI, WM, WN, KW, 1>), grid, blk, 0, st, g, tm, tn);
+  if (g.act == 1) hipLaunchKernelGGL((gemm_f32_kernel<0, 0, MI, NI, WM, WN, KW, 0, 1>), grid, blk, 0, st, g, tm, tn);
+  else if (g.act) hipLaunchKernelGGL((gemm_f32_kernel<0, 1, MI, NI, WM, WN, KW, 0, 2>), grid, blk, 0, st, g, tm, tn);
+  else if (g.kseg) hipLaunchKernelGGL((gemm_f32_kernel<0, 1, MI, NI, WM, WN, KW, 1>), grid, blk, 0, st, g, tm, tn);
   else if (!g.transA && !g.transB) hipLaunchKernelGGL((gemm_f32_kernel<0, 0, MI, NI, WM, WN, KW, 0>), grid, blk, 0, st, g, tm, tn);
   else if (!g.transA) hipLaunchKernelGGL((gemm_f32_kernel<0, 1, MI, NI, WM, WN, KW, 0>), grid, blk, 0, st, g, tm, tn);
   else if (!g.transB) hipLaunchKernelGGL((gemm_f32_kernel<1, 0, MI, NI, WM, WN, KW, 0>), grid, blk, 0, st, g, tm, tn);
@@ -312,6 +330,7 @@ bool gemm_f32_supported(const Gemm& g) {
   if (g.ldb < (!g.transB ? g.N : g.kseg ? g.kseg : g.K)) return false;
   const int64_t rowsA = (g.transA ? g.K : g.M) + 160, rowsB = (g.transB ? g.N : g.K) + 160;   // a tile and two slabs over the end
   const int64_t segs = g.kseg ? (g.K / g.kseg - 1) * g.segB : 0;
+  if (g.act && (g.batch != 1 || g.transA || g.kseg || g.rope || g.c_f32_accum || g.act != 1 + g.transB || ((uintptr_t)g.act_z & 15))) return false;
   return rowsA * g.lda * 4 < (1ll << 30) && (rowsB * g.ldb + segs) * 4 < (1ll << 30);
 }
 

@@ -134,6 +134,7 @@ hipError_t gemm_one(hipStream_t st, DType dt, const Gemm& g, int force) {
   if (route == ROUTE_SMALL) return gemm_small(st, dt, g, gemm_small_tile(g));
   if (route >= ROUTE_HALVES) return gemm_mfma(st, dt, g);
   if (route == ROUTE_F32) return gemm_f32(st, g);
+  if (g.act) return hipErrorInvalidValue;            // the caller asks gemm_route first
   if (g.glu) {   // gated unit: the plain product(s), then the activation kernel over the dense [gate | up] rows
     Gemm p = g;
     p.glu = 0; p.gu = nullptr;

@@ -40,6 +40,9 @@ namespace zs {
 //             glu = 2 (transB = 1): the product is da[M,N]; the call replaces (gate, up) in gu by (dgate, dup).
 //               C is scratch of [M,N] elements whose content is unspecified afterwards (the fused kernel leaves it
 //               alone and uses da unrounded).
+//   act != 0 (fp32 matrix cores only, see gemm_route: batch = 1, no rotation): GELU in the store.  act = 1 (transB = 0): C receives the
+//             product z, act_z gelu(z).  act = 2 (transB = 1): act_z holds z and receives product * gelu'(z); C is not written.
+//             act_z has C's layout.  What the product followed by gelu_fwd or gelu_bwd leaves, bit for bit.
 constexpr int GEMM_MAX_PARTS = 16;   // parts of a multi-part K range
 struct Gemm {
   int M = 0, N = 0, K = 0, transA = 0, transB = 0;
@@ -59,6 +62,7 @@ struct Gemm {
   int chunk_parts = 0, nchunks = 1, tile_base = 0, tile_count = 0;
   const float2* rope = nullptr; int rope_S = 0, rope_d = 0, rope_batches = 0;
   int glu = 0; void* gu = nullptr; int64_t gu_ld = 0, gu_up = 0;
+  int act = 0; void* act_z = nullptr;
 };
 // Position `pos` of the MFMA kernels' tile order -> tile row and column: the order walks groups of 8 tile rows column by
 // column, so that tiles which run at the same time share A rows and B columns.

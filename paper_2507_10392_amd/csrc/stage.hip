@@ -433,6 +433,13 @@ bool do_gemm(stage_t* s, const Gemm& g) {
   return run(s, cls, flops, 0.0, [&] { return gemm(s->st, dt_of(s), g, GEMM_AUTO); });
 }
 
+// GELU in the store of the fp32 products: the kernel of its own is 2.4 us of a small step's queue each time.  The 16-bit products' store
+// pass would take as long for it as the kernel, whose time is traffic.
+bool act_in_store(stage_t* s, Gemm g, int act, void* z) {
+  g.act = act; g.act_z = z;
+  return dt_of(s) == F32 && gemm_route(F32, g) == ROUTE_F32;
+}
+
 // The weight gradients of a layer in one launch, where gemm_group takes them so.
 bool do_gemm_group(stage_t* s, GemmRoute route, const Gemm* g, int n) {
   double flops = 0;
@@ -497,9 +504,10 @@ bool layer_forward(stage_t* s, int l, char* x_in, LayerActs& A, char* y, const v
   else {   // gate and up projections in one product whose store applies the gated unit: ff = [gate | up], a = silu(gate) * up
     g.B = W("Wg"); g.sB = (int64_t)H * F; g.C = A.a; g.ldc = F; g.glu = 1; g.gu = A.ff; g.gu_ld = 2 * F; g.gu_up = F;
   }
+  if (gpt && act_in_store(s, g, 1, A.a)) { g.act = 1; g.act_z = A.a; }
   if (!do_gemm(s, g)) return false;
   const double tfb = (double)T * F * h.E;
-  if (gpt && !run(s, "activation", 0, 2 * tfb, [&] { return gelu_fwd(s->st, dt, (int64_t)T * F, A.ff, A.a); })) return false;
+  if (gpt && !g.act && !run(s, "activation", 0, 2 * tfb, [&] { return gelu_fwd(s->st, dt, (int64_t)T * F, A.ff, A.a); })) return false;
   if (!y) return true;
   g = Gemm();
   g.M = T; g.N = H; g.K = F; g.A = A.a; g.lda = F; g.B = gpt ? W("W2") : W("Wd"); g.ldb = H; g.C = y; g.ldc = H;
@@ -595,11 +603,13 @@ bool layer_backward(stage_t* s, int l, const char* x_in, LayerActs& A, const cha
   g.C = pl.gF1; g.ldc = F;
   // Llama: the store turns (gate, up), saved in ff, into (dgate, dup) in place; da itself is not kept
   if (!gpt) { g.glu = 2; g.gu = A.ff; g.gu_ld = 2 * F; g.gu_up = F; }
+  else if (act_in_store(s, g, 2, A.ff)) { g.act = 2; g.act_z = A.ff; }
+  const bool act_done = g.act != 0;
   if (!do_gemm(s, g)) return false;
   if (!wgrad(dw.down, &LayerActs::a, [&](int i) { return wg.dy_x[i]; })) return false;
 
   // GELU backward, in place over the saved pre-activations
-  if (gpt && !run(s, "activation", 0, 3 * tfb, [&] { return gelu_bwd(s->st, dt, (int64_t)T * F, A.ff, pl.gF1, A.ff); }))
+  if (gpt && !act_done && !run(s, "activation", 0, 3 * tfb, [&] { return gelu_bwd(s->st, dt, (int64_t)T * F, A.ff, pl.gF1, A.ff); }))
     return false;
   const char* dff = A.ff;   // dz [T,F] or [dgate | dup] [T,2F]
 
