@@ -3,9 +3,10 @@
 //
 // What bounds it: the models that run in fp32 are small, so a launch has few rows and its time is a wave's walk over the keys.
 // A workgroup therefore owns only 16 queries (or keys), and its four waves share out the other side's tiles of 32 rows and
-// merge at the end through LDS, in a fixed order.  Every wave loads its own operands from L2, as in gemm_f32.hip: "k" fragments (4 consecutive elements along the head dim per lane) for the products
-// over d, "r" fragments (4 consecutive head-dim columns of rows 4 (l/16) + e) for the products over keys or queries.  All
-// products are transposed (S^T = K Q^T, O^T = V^T P^T): a lane then owns query l%16 and holds the scores of keys 4 (l/16) + r
+// merge at the end through LDS, in a fixed order.  Every wave loads its own operands from L2: "k" fragments (4 consecutive
+// elements along the head dim per lane; whole lines that change places in LDS, see load_lines) for the products over d, "r" fragments
+// (4 consecutive head-dim columns of rows 4 (l/16) + e, which are whole lines as they are) for the products over keys or queries.
+// All products are transposed (S^T = K Q^T, O^T = V^T P^T): a lane then owns query l%16 and holds the scores of keys 4 (l/16) + r
 // in register r, which is the operand layout that step e = r of the second product wants, so P never moves between lanes.
 // The loads of a tile run one tile-quarter (or more, registers permitting) ahead of their use.
 //
