@@ -348,7 +348,7 @@ hipError_t colsum_partials(hipStream_t st, DType dt, int T, const ColsumJob* job
 // once per row, and 8 / WPR rows are walked side by side.  A wave thereby holds at most 4 vectors per lane and two waves fit
 // a SIMD, one's loads under the other's arithmetic (20 instructions per element).  FULL: H = 64 V J exactly (WPR = 1); else
 // the vectors past the row's end are masked.  With up to 4 vectors per lane the next row's loads are in flight beside a row's sums (with 8
-// or 10 there are no registers for them): without, a workgroup went through load, reduce, barrier and store 17 times with nothing
+// or 10, FULL only, there are no registers for them): without, a workgroup went through load, reduce, barrier and store 17 times with nothing
 // in flight in between.  bf16, us, without : with: LayerNorm, 4097 rows of 3080 28.0 : 23.4 (48 as three kernels), 8200 rows of 600
 // 16.7 : 13.8; RMSNorm, 4100 rows of 1288 13.7 : 10.4, 700 rows of 8192 13.8 : 11.9.  Exact rows of 4096 and 5120 elements stay with
 // one wave per row (LayerNorm 30 and 42 us, RMSNorm 24 and 18 for 4096 and 2048 rows).
@@ -373,86 +373,128 @@ __global__ __launch_bounds__(WPR == 1 ? 256 : 512) void norm_bwd_partials_reg_ke
 #pragma unroll
     for (int i = 0; i < V; ++i) { pg[j][i] = 0.f; if (KIND == 0) pb[j][i] = 0.f; }
   typedef typename Vec<T>::type TV;
-  // AHEAD: the next row's loads go out before this row's sums, and the gains stay in registers.  dx may lie over dres: other rows.
-  constexpr bool AHEAD = J <= 4;
-  struct Row { TV x[J], d[J], r[J]; float rstd, mean; };
-  auto load = [&](Row& w, int row) {
-    const bool live = row < r1;
-    w.rstd = live ? rstd[row] : 0.f;
-    w.mean = (KIND == 0 && live) ? mean[row] : 0.f;
-    const int64_t off = (int64_t)row * H;
+  if constexpr (J > 4) {   // exact rows in one wave each.  A loop of its own: which product of a sum is fused into a multiply-add, and so the
+                           // last bit of dx, is the compiler's choice and changes with the code around it
+    for (int row = r0 + q; row < r1; row += RG) {
+      const float r = rstd[row];
+      const float mu = KIND == 0 ? mean[row] : 0.f;
+      const int64_t off = (int64_t)row * H;
+      TV xv[J], dv[J], rv[J];
 #pragma unroll
-    for (int j = 0; j < J; ++j) {
-      if (!live || !in(j)) continue;
-      w.x[j] = *reinterpret_cast<const TV*>(x + off + col(j));
-      w.d[j] = *reinterpret_cast<const TV*>(dn + off + col(j));
-      if (dres) w.r[j] = *reinterpret_cast<const TV*>(dres + off + col(j));
+      for (int j = 0; j < J; ++j) {
+        const int c = col(j);
+        xv[j] = *reinterpret_cast<const TV*>(x + off + c);
+        dv[j] = *reinterpret_cast<const TV*>(dn + off + c);
+        if (dres) rv[j] = *reinterpret_cast<const TV*>(dres + off + c);
+      }
+      float su = 0.f, sux = 0.f;
+#pragma unroll
+      for (int j = 0; j < J; ++j) {
+        float gg[V];
+        load_vec(g + col(j), gg);
+#pragma unroll
+        for (int i = 0; i < V; ++i) {
+          const float d = to_f(dv[j][i]), xx = to_f(xv[j][i]);
+          const float u = d * gg[i];
+          su += u;
+          sux += u * (xx - mu) * r;
+          pg[j][i] += d * ((xx - mu) * r);
+          if (KIND == 0) pb[j][i] += d;
+        }
+      }
+      su = (KIND == 0) ? wave_sum(su) : 0.f;
+      sux = wave_sum(sux);
+      const float mu_u = su / (float)H;
+      const float mu_ux = sux / (float)H;
+#pragma unroll
+      for (int j = 0; j < J; ++j) {
+        const int c = col(j);
+        float o[V], gg[V];
+        load_vec(g + c, gg);
+#pragma unroll
+        for (int i = 0; i < V; ++i) {
+          const float u = to_f(dv[j][i]) * gg[i];
+          o[i] = r * (u - mu_u - (to_f(xv[j][i]) - mu) * r * mu_ux) + (dres ? to_f(rv[j][i]) : 0.f);
+        }
+        store_vec(dx + off + c, o);
+      }
     }
-  };
-  TV gains[AHEAD ? J : 1];
-  if constexpr (AHEAD) {
+  } else {
+    // The next row's loads go out before this row's sums, and the gains stay in registers.  dx may lie over dres: other rows.
+    struct Row { TV x[J], d[J], r[J]; float rstd, mean; };
+    auto load = [&](Row& w, int row) {
+      const bool live = row < r1;
+      w.rstd = live ? rstd[row] : 0.f;
+      w.mean = (KIND == 0 && live) ? mean[row] : 0.f;
+      const int64_t off = (int64_t)row * H;
+#pragma unroll
+      for (int j = 0; j < J; ++j) {
+        if (!live || !in(j)) continue;
+        w.x[j] = *reinterpret_cast<const TV*>(x + off + col(j));
+        w.d[j] = *reinterpret_cast<const TV*>(dn + off + col(j));
+        if (dres) w.r[j] = *reinterpret_cast<const TV*>(dres + off + col(j));
+      }
+    };
+    TV gains[J];
 #pragma unroll
     for (int j = 0; j < J; ++j)
       if (in(j)) gains[j] = *reinterpret_cast<const TV*>(g + col(j));
-  }
-  auto gain = [&](int j, float (&gg)[V]) {
-    if constexpr (AHEAD) {
+    auto gain = [&](int j, float (&gg)[V]) {
 #pragma unroll
       for (int i = 0; i < V; ++i) gg[i] = to_f(gains[j][i]);
-    } else load_vec(g + col(j), gg);
-  };
-  int turn = 0;
-  Row cur, next;
-  if (AHEAD) load(cur, r0 + q);
-  for (int row = r0 + q; (WPR == 1 ? row : row - q) < r1; row += RG) {   // WPR > 1: the same steps in every wave, for the barrier
-    if (AHEAD) load(next, row + RG);
-    else load(cur, row);
-    const bool live = WPR == 1 || row < r1;
-    const float r = cur.rstd, mu = cur.mean;
-    const int64_t off = (int64_t)row * H;
-    const TV (&xv)[J] = cur.x, (&dv)[J] = cur.d, (&rv)[J] = cur.r;
-    float su = 0.f, sux = 0.f;
+    };
+    int turn = 0;
+    Row cur, next;
+    load(cur, r0 + q);
+    for (int row = r0 + q; (WPR == 1 ? row : row - q) < r1; row += RG) {   // WPR > 1: the same steps in every wave, for the barrier
+      load(next, row + RG);
+      const bool live = WPR == 1 || row < r1;
+      const float r = cur.rstd, mu = cur.mean;
+      const int64_t off = (int64_t)row * H;
+      const TV (&xv)[J] = cur.x, (&dv)[J] = cur.d, (&rv)[J] = cur.r;
+      float su = 0.f, sux = 0.f;
 #pragma unroll
-    for (int j = 0; j < J; ++j) {
-      if (!live || !in(j)) continue;
-      float gg[V];
-      gain(j, gg);
+      for (int j = 0; j < J; ++j) {
+        if (!live || !in(j)) continue;
+        float gg[V];
+        gain(j, gg);
 #pragma unroll
-      for (int i = 0; i < V; ++i) {
-        const float d = to_f(dv[j][i]), xx = to_f(xv[j][i]);
-        const float u = d * gg[i];
-        su += u;
-        sux += u * (xx - mu) * r;
-        pg[j][i] += d * ((xx - mu) * r);
-        if (KIND == 0) pb[j][i] += d;
+        for (int i = 0; i < V; ++i) {
+          const float d = to_f(dv[j][i]), xx = to_f(xv[j][i]);
+          const float u = d * gg[i];
+          su += u;
+          sux += u * (xx - mu) * r;
+          pg[j][i] += d * ((xx - mu) * r);
+          if (KIND == 0) pb[j][i] += d;
+        }
       }
-    }
-    su = (KIND == 0) ? wave_sum(su) : 0.f;
-    sux = wave_sum(sux);
-    if constexpr (WPR > 1) {
-      if (lane == 0) { cross[turn][wave][0] = su; cross[turn][wave][1] = sux; }
-      __syncthreads();   // the other buffer was read before this barrier, so it may be written after it
-      su = sux = 0.f;
+      su = (KIND == 0) ? wave_sum(su) : 0.f;
+      sux = wave_sum(sux);
+      if constexpr (WPR > 1) {
+        if (lane == 0) { cross[turn][wave][0] = su; cross[turn][wave][1] = sux; }
+        __syncthreads();   // the other buffer was read before this barrier, so it may be written after it
+        su = sux = 0.f;
 #pragma unroll
-      for (int w = 0; w < WPR; ++w) { su += cross[turn][q * WPR + w][0]; sux += cross[turn][q * WPR + w][1]; }
-      turn ^= 1;
-    }
-    const float mu_u = su / (float)H;
-    const float mu_ux = sux / (float)H;
-#pragma unroll
-    for (int j = 0; j < J; ++j) {
-      if (!live || !in(j)) continue;
-      const int c = col(j);
-      float o[V], gg[V];
-      gain(j, gg);
-#pragma unroll
-      for (int i = 0; i < V; ++i) {
-        const float u = to_f(dv[j][i]) * gg[i];
-        o[i] = r * (u - mu_u - (to_f(xv[j][i]) - mu) * r * mu_ux) + (dres ? to_f(rv[j][i]) : 0.f);
+        for (int w = 0; w < WPR; ++w) { su += cross[turn][q * WPR + w][0]; sux += cross[turn][q * WPR + w][1]; }
+        turn ^= 1;
       }
-      store_vec(dx + off + c, o);
+      const float mu_u = su / (float)H;
+      const float mu_ux = sux / (float)H;
+#pragma unroll
+      for (int j = 0; j < J; ++j) {
+        if (!live || !in(j)) continue;
+        const int c = col(j);
+        float o[V], gg[V];
+        gain(j, gg);
+#pragma unroll
+        for (int i = 0; i < V; ++i) {
+          const float u = to_f(dv[j][i]) * gg[i];
+          o[i] = r * (u - mu_u - (to_f(xv[j][i]) - mu) * r * mu_ux) + (dres ? to_f(rv[j][i]) : 0.f);
+        }
+        store_vec(dx + off + c, o);
+      }
+      cur = next;
     }
-    if (AHEAD) cur = next;
   }
   // sums over the rows walked side by side, in order, first of dn*xhat, then (LayerNorm) of dn
 #pragma unroll
