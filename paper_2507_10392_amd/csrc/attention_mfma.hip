@@ -838,7 +838,7 @@ __global__ __attribute__((amdgpu_waves_per_eu(SPLIT && LO_ACC && D > 64 ? 1 : 2,
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         dkacc[db][r] = fmaf(dklo[db][r], LO_UNIT, dkacc[db][r]);
-        dvacc[db][r] = fmaf(dvlo[db][r], LO_UNIT, dvacc[db][r]);
+        dvacc[db][r] = fp32_value(fmaf(dvlo[db][r], LO_UNIT, dvacc[db][r]));   // stored as it is
       }
   }
   unsigned redo = 0;

@@ -28,6 +28,13 @@ template <> __device__ __forceinline__ float from_f<float>(float x) { return x; 
 template <> __device__ __forceinline__ bf16 from_f<bf16>(float x) { return (bf16)x; }  // round-to-nearest-even
 template <> __device__ __forceinline__ f16 from_f<f16>(float x) { return (f16)x; }     // round-to-nearest-even, overflow to inf
 
+// x as an fp32 value of its own: without this the compiler may fold the multiply-add that gives x and the rounding to half that follows into
+// one instruction (v_fma_mixlo_f16), which rounds once, and does or does not with the code around.
+__device__ __forceinline__ float fp32_value(float x) {
+  asm("" : "+v"(x));
+  return x;
+}
+
 // Elements moved per 16-byte access.
 template <typename T> struct Vec;
 template <> struct Vec<float> { static constexpr int N = 4; typedef f32x4 type; };
