@@ -35,7 +35,7 @@ __device__ __forceinline__ f32x4 load4(const Head& h, unsigned voff, unsigned so
 }
 // 16 rows x 16 DS columns from row `row0`: k[s] = columns 16 s + 4 (l/16) .. +3 of row l%16.  They come as whole lines (load_lines; read as
 // fragments, the lanes of a load would lie in 16 rows, and the address unit takes four times as long for their pieces) and change
-// places in LDS of the wave's own (to_k; no barrier, a wave's LDS accesses keep their order), the 16-byte piece p of row r at p ^ r.
+// places in LDS of the wave's own (to_k; wave_lds_order, no barrier), the 16-byte piece p of row r at p ^ r.
 // us, fragments : lines: S = 256, 4 heads of 128 forward 13.0 : 10.8, backward 26.0 : 19.7; S = 128, 8 of 64 10.9 : 7.9 (backward); S = 1000, 16
 // of 64 40 : 30 and 138 : 105; 64 of 128 325 : 201 and 932 : 842.
 template <int DS> struct Lines { f32x4 v[16 * 4 * DS]; };
@@ -47,11 +47,13 @@ template <int DS> __device__ __forceinline__ void load_lines(f32x4 (&f)[DS], con
 }
 template <int DS> __device__ __forceinline__ void to_k(f32x4 (&f)[DS], Lines<DS>& lines, int lane) {
   constexpr int P = 4 * DS, R = 64 / P;
+  wave_lds_order();   // the rows before have been read
 #pragma unroll
   for (int s = 0; s < DS; ++s) {
     const int row = R * s + lane / P;
     lines.v[row * P + ((lane % P) ^ row)] = f[s];
   }
+  wave_lds_order();
 #pragma unroll
   for (int s = 0; s < DS; ++s) f[s] = lines.v[(lane & 15) * P + ((4 * s + (lane >> 4)) ^ (lane & 15))];
 }
@@ -198,8 +200,10 @@ __device__ __attribute__((noinline)) void redo_dkv_rows(float* rowbuf, unsigned 
 }
 
 // ------------------------------------------------------------------------------------------ forward
+// Two waves per SIMD are asked for, here and in the dK/dV kernel of 64 columns: left alone, the compiler takes more registers than two waves
+// have (us, one : two waves: forward of 2 x 32 heads of 128, S = 512 90 : 63; backward of as many of 64 138 : 114).
 template <int DS, int NBUF>
-__global__ __launch_bounds__(64 * KW) void attn_fwd_f32_kernel(int S, int dd, const float* __restrict__ q, const float* __restrict__ k,
+__global__ __attribute__((amdgpu_waves_per_eu(2))) __launch_bounds__(64 * KW) void attn_fwd_f32_kernel(int S, int dd, const float* __restrict__ q, const float* __restrict__ k,
                                                               const float* __restrict__ v, int64_t ld, float* __restrict__ o,
                                                               int64_t ldo, float* __restrict__ lse, float scale, int nh, int mb) {
   __shared__ f32x4 red[(KW - 1) * DS * 64];
@@ -396,7 +400,7 @@ __global__ __launch_bounds__(64 * KW) void attn_bwd_dq_f32_kernel(int S, int dd,
 // blocks from dkv_blocks on are dQ's.  No block reads what another one writes: delta of a tile's rows is formed here from dO and
 // the same rows of O, in dQ's order of additions, instead of read.
 template <int DS, int NBUF, int QBUF>
-__global__ __launch_bounds__(64 * KW) void attn_bwd_dkv_f32_kernel(int S, int dd, const float* __restrict__ q, const float* __restrict__ k,
+__global__ __attribute__((amdgpu_waves_per_eu(DS == 4 && !QBUF ? 2 : 1))) __launch_bounds__(64 * KW) void attn_bwd_dkv_f32_kernel(int S, int dd, const float* __restrict__ q, const float* __restrict__ k,
                                                                   const float* __restrict__ v, int64_t ld,
                                                                   const float* __restrict__ dout, int64_t ldo,
                                                                   const float* __restrict__ lse, const float* __restrict__ delta,

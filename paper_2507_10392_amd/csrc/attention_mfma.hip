@@ -185,11 +185,13 @@ __device__ __forceinline__ void load_lines(e16x8 (&f)[D / 16], const e16* __rest
   }
 }
 template <int D> __device__ __forceinline__ void to_frags(e16x8 (&f)[D / 16], e16* rows, int lane) {
+  wave_lds_order();   // the rows before have been read
 #pragma unroll
   for (int i = 0; i < D / 16; ++i) {
     const int v = lane + 64 * i;
     *reinterpret_cast<e16x8*>(rows + v / (D / 8) * LDT<D> + v % (D / 8) * 8) = f[i];
   }
+  wave_lds_order();
 #pragma unroll
   for (int s = 0; s < D / 16; ++s) f[s] = lds_frag<D>(rows, 0, 16 * s, lane);
 }
@@ -197,6 +199,7 @@ template <int D> __device__ __forceinline__ void to_frags(e16x8 (&f)[D / 16], e1
 template <int D>
 __device__ __forceinline__ void store_rows(const f32x16 (&acc)[D / 32], float factor, e16* rows, e16* dst, int64_t ld, int row0, int nrows, int lane,
                                            int dd, unsigned skip) {
+  wave_lds_order();
 #pragma unroll
   for (int db = 0; db < D / 32; ++db)
 #pragma unroll
@@ -206,6 +209,7 @@ __device__ __forceinline__ void store_rows(const f32x16 (&acc)[D / 32], float fa
       for (int e = 0; e < 4; ++e) w[e] = (e16)(acc[db][4 * c + e] * factor);
       *reinterpret_cast<e16x4*>(rows + (lane & 31) * LDT<D> + db * 32 + 8 * c + 4 * (lane >> 5)) = w;
     }
+  wave_lds_order();
   constexpr int P = D / 4;   // 8-byte pieces of a row, as aligned as a direct store's would be
 #pragma unroll
   for (int i = 0; i < D / 8; ++i) {

@@ -28,6 +28,14 @@ template <> __device__ __forceinline__ float from_f<float>(float x) { return x; 
 template <> __device__ __forceinline__ bf16 from_f<bf16>(float x) { return (bf16)x; }  // round-to-nearest-even
 template <> __device__ __forceinline__ f16 from_f<f16>(float x) { return (f16)x; }     // round-to-nearest-even, overflow to inf
 
+// Between LDS writes of a wave and reads of what other lanes of it wrote, and between those reads and the next writes there.  The hardware
+// keeps a wave's LDS accesses in order; the compiler sees one lane, whose own addresses it may find distinct and its accesses free to move.
+__device__ __forceinline__ void wave_lds_order() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // x as an fp32 value of its own: without this the compiler may fold the multiply-add that gives x and the rounding to half that follows into
 // one instruction (v_fma_mixlo_f16), which rounds once, and does or does not with the code around.
 __device__ __forceinline__ float fp32_value(float x) {

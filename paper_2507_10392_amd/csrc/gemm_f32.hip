@@ -180,18 +180,29 @@ __device__ __forceinline__ void f32_tile(const Gemm& g, int tiles_m, int tiles_n
       }
     };
     auto multiply_pair = [&](Pair& f, int s) {
-      if constexpr (SA > 0) put_rows<MI>(f.a, la, lane);
-      if constexpr (SB > 0) put_rows<NI>(f.b, lb, lane);
+      constexpr bool TURN = MI * NI < 16;                    // 64x64: no registers for the fragments of both slabs, see turn_rows
+      f32x4 a[2][TURN && SA ? MI : 1], b[2][TURN && SB ? NI : 1];
+      if constexpr (TURN) {
+        if constexpr (SB > 0) turn_rows<NI, 2>(b, f.b, lb, lane);
+        if constexpr (SA > 0) turn_rows<MI, 2>(a, f.a, la, lane);
+      } else {
+        wave_lds_order();
+        if constexpr (SA > 0) put_rows<MI>(f.a, la, lane);
+        if constexpr (SB > 0) put_rows<NI>(f.b, lb, lane);
+        wave_lds_order();
+      }
 #pragma unroll
       for (int h = 0; h < 2; ++h)
         if (s + h < s1) {
-          Frag<TA, MI> a;
-          Frag<1 - TB, NI> b;
-          if constexpr (SA > 0) get_rows<MI>(a.v, la, h, lane);
-          else a = f.ra[h];
-          if constexpr (SB > 0) get_rows<NI>(b.v, lb, h, lane);
-          else b = f.rb[h];
-          multiply(a, b);
+          Frag<TA, MI> fa;
+          Frag<1 - TB, NI> fb;
+          if constexpr (SA == 0) fa = f.ra[h];
+          else if constexpr (TURN) __builtin_memcpy(fa.v, a[h], sizeof fa.v);
+          else get_rows<MI>(fa.v, la, h, lane);
+          if constexpr (SB == 0) fb = f.rb[h];
+          else if constexpr (TURN) __builtin_memcpy(fb.v, b[h], sizeof fb.v);
+          else get_rows<NI>(fb.v, lb, h, lane);
+          multiply(fa, fb);
         }
     };
 #pragma unroll

@@ -131,8 +131,10 @@ __device__ __forceinline__ void small_tile(const Gemm& g, int tiles_m, int tiles
 #pragma unroll
       for (int i = 0; i < DEPTH; ++i)
         if (s + 2 * i < s1) {
+          wave_lds_order();   // the pair before has been read
           put_rows<T>(pairs[i].a, la, lane);
           put_rows<T>(pairs[i].b, lb, lane);
+          wave_lds_order();
           if (s + 2 * (i + DEPTH) < s1) load(pairs[i], s + 2 * (i + DEPTH));
 #pragma unroll
           for (int h = 0; h < 2; ++h)
