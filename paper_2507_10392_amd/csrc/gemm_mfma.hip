@@ -27,7 +27,7 @@ int g_force_tile = 0;   // 0 automatic; 1: 256x256, 2: 128x128, 3: 256x192, 4: 2
 bool gemm_mfma_supported(DType dt, const Gemm& g) { return g.K % 8 == 0 && gemm_mfma_takes(dt, g); }
 
 bool gemm_mfma_takes(DType dt, const Gemm& g) {
-  if (dt != BF16 && dt != F16) return false;
+  if ((dt != BF16 && dt != F16) || g.act) return false;
   if (g.M < 1 || g.N < 1 || g.K < 1 || g.batch < 1) return false;
   if (!aligned16(g.A) || !aligned16(g.B)) return false;
   if (g.lda % 8 || g.ldb % 8 || g.sA % 8 || g.sB % 8) return false;
