@@ -174,7 +174,8 @@ __device__ __forceinline__ void load_row_frags(e16x8 (&f)[D / 16], const e16* __
 // pieces; the same holds for stores of accumulators (store_rows).  The backward kernels load up to three blocks of rows that way
 // and store two; in the forward, whose only block is Q, the way round costs more than it saves (16 heads of 128, S = 2048: 46.3 us
 // with direct loads, 49.4 without), and only the store goes through LDS.  us, fragments : lines, backward of 16 heads of 128, S =
-// 2048 98.9 : 83.0; 32 heads, S = 4096 460 : 447; 4 heads, S = 256 19.8 : 16.3.
+// 2048 98.9 : 83.0; 32 heads, S = 4096 460 : 447; 4 heads, S = 256 19.8 : 16.3.  Where a CU has few waves at work on rows, as in short
+// sequences, there is no queue before the address unit and the way round only adds its latencies: see lines_fwd.
 template <int D>
 __device__ __forceinline__ void load_lines(e16x8 (&f)[D / 16], const e16* __restrict__ src, int64_t ld, int row0, int nrows, int lane, int dd) {
   constexpr int P = D / 8;   // 16-byte pieces of a row
@@ -217,6 +218,25 @@ __device__ __forceinline__ void store_rows(const f32x16 (&acc)[D / 32], float fa
     const e16x4 w = *reinterpret_cast<const e16x4*>(rows + r * LDT<D> + c);
     if (row0 + r < nrows && c < dd && !(skip >> r & 1)) *reinterpret_cast<e16x4*>(dst + (int64_t)(row0 + r) * ld + c) = w;
   }
+}
+
+// The same straight from the accumulators, every lane into the row that it holds.
+template <int D, bool SPLIT>
+__device__ __forceinline__ void store_direct(const f32x16 (&acc)[D / 32], float factor, e16* dst, int64_t ld, int row, int nrows, int lane, int dd,
+                                             unsigned skip) {
+  if (row >= nrows || skip >> (lane & 31) & 1) return;
+  e16* to = dst + (int64_t)row * ld;
+#pragma unroll
+  for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const int col = db * 32 + 8 * c + 4 * (lane >> 5);
+      if (SPLIT && col >= dd) continue;
+      e16x4 w;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) w[e] = (e16)(acc[db][4 * c + e] * factor);
+      *reinterpret_cast<e16x4*>(to + col) = w;
+    }
 }
 
 // Row index (inside a 32-row MFMA block) held by accumulator register r of this lane.
@@ -372,7 +392,7 @@ __device__ __attribute__((noinline)) void redo_dkv_rows(char* smem, int groups, 
 // grid ceil(S/(32 NW))*nh*mb, NW waves; wave w owns queries q0 + 32w .. +31; heavy (late) blocks are launched first.
 // NW = 4: two workgroups per CU.  NW = 8: one workgroup per CU whose staged K/V tiles serve 256 queries, so a wave
 // issues half as many tile loads and LDS stores per key tile (used when that still gives every CU a workgroup).
-template <int NW, int D, bool SPLIT>
+template <int NW, int D, bool SPLIT, bool LINES>
 __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_fwd_kernel(int S, const e16* __restrict__ q, const e16* __restrict__ k,
                                                        const e16* __restrict__ v, int64_t ld, e16* __restrict__ o,
                                                        int64_t ldo, float* __restrict__ lse, float scale_log2, float scale_lo,
@@ -491,7 +511,8 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_fwd_kernel(int 
   }
   unsigned redo = 0;
   if constexpr (SPLIT) redo = rows_of(redo_lds<NW>(smem_raw), wave, true, my_q < S && l == l, mark_of(oacc));
-  store_rows<D>(oacc, 1.0f / l, rows_lds<NW, D, SPLIT>(smem_raw, wave), o + tok0 * ldo + h * dd, ldo, wq0, S, lane, dd, redo);
+  if constexpr (LINES) store_rows<D>(oacc, 1.0f / l, rows_lds<NW, D, SPLIT>(smem_raw, wave), o + tok0 * ldo + h * dd, ldo, wq0, S, lane, dd, redo);
+  else store_direct<D, SPLIT>(oacc, 1.0f / l, o + tok0 * ldo + h * dd, ldo, my_q, S, lane, dd, redo);
   if (my_q < S) {
     if (lane < 32)   // SPLIT: formed in double, once per row: m may lag the maximum by 8, so log l alone would round like lse does
       lse[((int64_t)b * nh + h) * S + my_q] =
@@ -508,7 +529,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_fwd_kernel(int 
 // tiles up to the diagonal.
 // dQ^T[d][q] += K^T[d][key] dS^T[key][q],  dS^T = P^T o (dP^T - delta_q),  dP^T = V dO^T.
 // QS = 2: two waves share 32 queries, each taking one half of every tile's keys; their sums meet in LDS at the end.
-template <int NW, int QS, int D, bool SPLIT>
+template <int NW, int QS, int D, bool SPLIT, bool LINES>
 __device__ __forceinline__ void dq_block(int block, int S, const e16* __restrict__ q, const e16* __restrict__ k, const e16* __restrict__ v, int64_t ld,
                                          const e16* __restrict__ o, const e16* __restrict__ dout, int64_t ldo, const float* __restrict__ lse,
                                          float* __restrict__ delta, e16* __restrict__ dq, int64_t ldd, float scale, int nh, int mb,
@@ -535,19 +556,26 @@ __device__ __forceinline__ void dq_block(int block, int S, const e16* __restrict
   fetch_tile(vr, rsv, (int)ld, 0, tid, dd);
   e16x8 qf[D / 16], dof[D / 16];
   e16x8 of[D / 16];
-  load_lines<D>(qf, qh, ld, wq0, S, lane, dd);
-  load_lines<D>(dof, doh, ldo, wq0, S, lane, dd);
-  load_lines<D>(of, o + tok0 * ldo + h * dd, ldo, wq0, S, lane, dd);
+  if constexpr (LINES) {
+    load_lines<D>(qf, qh, ld, wq0, S, lane, dd);
+    load_lines<D>(dof, doh, ldo, wq0, S, lane, dd);
+    load_lines<D>(of, o + tok0 * ldo + h * dd, ldo, wq0, S, lane, dd);
+  } else {
+    load_row_frags<D>(qf, qh, ld, wq0, S, lane, dd);
+    load_row_frags<D>(dof, doh, ldo, wq0, S, lane, dd);
+  }
   const int64_t stat = ((int64_t)b * nh + h) * S + min(my_q, S - 1);
   const float lse2 = lse[stat] * LOG2E;
   // delta_q = dO_q . O_q: each lane sums its 64 of the row's 128 products, lane^32 holds the others.
   // The value is also stored for the dK/dV kernel, which runs after this one.
   float dlt = 0.f;
   {
-    e16* rows = smem + (tid >> 6) * 32 * LDT<D>;
-    to_frags<D>(qf, rows, lane);
-    to_frags<D>(dof, rows, lane);
-    to_frags<D>(of, rows, lane);
+    if constexpr (LINES) {
+      e16* rows = smem + (tid >> 6) * 32 * LDT<D>;
+      to_frags<D>(qf, rows, lane);
+      to_frags<D>(dof, rows, lane);
+      to_frags<D>(of, rows, lane);
+    } else load_row_frags<D>(of, o + tok0 * ldo + h * dd, ldo, wq0, S, lane, dd);
 #pragma unroll
     for (int s = 0; s < D / 16; ++s)
 #pragma unroll
@@ -563,7 +591,7 @@ __device__ __forceinline__ void dq_block(int block, int S, const e16* __restrict
 
   const int last_q = min(q0 + 32 * QW - 1, S - 1);
   const int ntiles = last_q / TR + 1;
-  __syncthreads();
+  if (LINES) __syncthreads();
   put_tile(kr, smem, tid);
   put_tile(vr, smem + TILE<D>, tid);
   __syncthreads();
@@ -631,13 +659,14 @@ __device__ __forceinline__ void dq_block(int block, int S, const e16* __restrict
     if (half == 0 && lane < 32) rl.delta[32 * wave + lane] = dlt;
     redo = rows_of(rl, wave, half == 0, my_q < S && lse2 == lse2 && dlt == dlt, mark_of(acc));
   }
-  if (half == 0) {
+  if (half == 0 && (LINES || my_q < S)) {
 #pragma unroll
     for (int db = 0; db < D / 32; ++db)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[db][r] *= SPLIT ? scale / DS_SCALE : scale;
     if (rope) unrotate_row<D, D / 32>(acc, rope, min(my_q, S - 1), lane, dd);
-    store_rows<D>(acc, 1.0f, rows_lds<NW, D, SPLIT>(smem_raw, wave), dq + tok0 * ldd + h * dd, ldd, wq0, S, lane, dd, redo);
+    if constexpr (LINES) store_rows<D>(acc, 1.0f, rows_lds<NW, D, SPLIT>(smem_raw, wave), dq + tok0 * ldd + h * dd, ldd, wq0, S, lane, dd, redo);
+    else store_direct<D, SPLIT>(acc, 1.0f, dq + tok0 * ldd + h * dd, ldd, my_q, S, lane, dd, redo);
   }
   if constexpr (SPLIT) {
     if (__builtin_expect(any_row(redo_lds<NW>(smem_raw).masks, QW, lane), 0))
@@ -646,7 +675,7 @@ __device__ __forceinline__ void dq_block(int block, int S, const e16* __restrict
   }
 }
 
-template <int NW, int QS, int D, bool SPLIT>
+template <int NW, int QS, int D, bool SPLIT, bool LINES>
 __global__ __launch_bounds__(64 * NW, NW == 4 && !(SPLIT && LO_ACC && D > 64) ? 2 : 1) void attn_bwd_dq_kernel(int S, const e16* __restrict__ q, const e16* __restrict__ k,
                                                           const e16* __restrict__ v, int64_t ld,
                                                           const e16* __restrict__ o, const e16* __restrict__ dout,
@@ -654,7 +683,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 && !(SPLIT && LO_ACC && D > 64) ? 
                                                           float* __restrict__ delta,
                                                           e16* __restrict__ dq, int64_t ldd, float scale, int nh,
                                                           int mb, const float2* __restrict__ rope, int head_dim) {
-  dq_block<NW, QS, D, SPLIT>(blockIdx.x, S, q, k, v, ld, o, dout, ldo, lse, delta, dq, ldd, scale, nh, mb, rope, head_dim);
+  dq_block<NW, QS, D, SPLIT, LINES>(blockIdx.x, S, q, k, v, ld, o, dout, ldo, lse, delta, dq, ldd, scale, nh, mb, rope, head_dim);
 }
 
 // ------------------------------------------------------------------------------------------ dK, dV
@@ -669,7 +698,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 && !(SPLIT && LO_ACC && D > 64) ? 
 // BOTH: dQ and dK/dV in one launch, for grids that leave CUs idle when they run one after the other: the blocks from dkv_blocks on are
 // dQ's.  No block reads what another one writes: delta of a tile's rows is formed here from dO and the same rows of O, 16 lanes to a
 // row, instead of read.
-template <int NW, int QS, int D, bool SPLIT, bool BOTH>
+template <int NW, int QS, int D, bool SPLIT, bool BOTH, bool LINES>
 __global__ __attribute__((amdgpu_waves_per_eu(SPLIT && LO_ACC && D > 64 ? 1 : 2, 2))) __launch_bounds__(64 * NW) void attn_bwd_dkv_kernel(int S, const e16* __restrict__ q, const e16* __restrict__ k,
                                                            const e16* __restrict__ v, int64_t ld,
                                                            const e16* __restrict__ dout, int64_t ldo,
@@ -679,7 +708,7 @@ __global__ __attribute__((amdgpu_waves_per_eu(SPLIT && LO_ACC && D > 64 ? 1 : 2,
                                                            int dkv_blocks, const e16* __restrict__ o, float* __restrict__ delta_out, e16* __restrict__ dq) {
   static_assert(!BOTH || (!SPLIT && 64 * NW % (D / 8) == 0 && D == 128), "16 lanes share a row; rows that are redone read delta");
   if (BOTH && (int)blockIdx.x >= dkv_blocks) {
-    dq_block<NW, QS, D, SPLIT>(blockIdx.x - dkv_blocks, S, q, k, v, ld, o, dout, ldo, lse, delta_out, dq, ldd, scale, nh, mb, rope, head_dim);
+    dq_block<NW, QS, D, SPLIT, LINES>(blockIdx.x - dkv_blocks, S, q, k, v, ld, o, dout, ldo, lse, delta_out, dq, ldd, scale, nh, mb, rope, head_dim);
     return;
   }
   const int dd = SPLIT ? head_dim : D;
@@ -741,7 +770,8 @@ __global__ __attribute__((amdgpu_waves_per_eu(SPLIT && LO_ACC && D > 64 ? 1 : 2,
   const int t_begin = k0 / TR, t_end = (S - 1) / TR + 1;
   fetch(t_begin);
   e16x8 kf[D / 16];
-  load_lines<D>(kf, kh, ld, wk0, S, lane, dd);
+  if constexpr (LINES) load_lines<D>(kf, kh, ld, wk0, S, lane, dd);
+  else load_row_frags<D>(kf, kh, ld, wk0, S, lane, dd);
   if (QS == 1 || half == 0) {   // QS = 2: the first of the two waves brings the rows, the barrier before the loop publishes them
     e16* Vw = reinterpret_cast<e16*>(stats + 256) + wave * 32 * LDT<D>;
     const __amdgpu_buffer_rsrc_t rsv = head_rsrc(vh, ld, S, dd);   // rows past S read as zero
@@ -767,8 +797,10 @@ __global__ __attribute__((amdgpu_waves_per_eu(SPLIT && LO_ACC && D > 64 ? 1 : 2,
       if (SPLIT && LO_ACC) dklo[SPLIT && LO_ACC ? i : 0][r] = dvlo[SPLIT && LO_ACC ? i : 0][r] = 0.f;
     }
 
-  to_frags<D>(kf, smem + (tid >> 6) * 32 * LDT<D>, lane);
-  __syncthreads();
+  if constexpr (LINES) {
+    to_frags<D>(kf, smem + (tid >> 6) * 32 * LDT<D>, lane);
+    __syncthreads();
+  }
   put(0);
   __syncthreads();
   for (int t = t_begin; t < t_end; ++t) {
@@ -847,15 +879,20 @@ __global__ __attribute__((amdgpu_waves_per_eu(SPLIT && LO_ACC && D > 64 ? 1 : 2,
   }
   unsigned redo = 0;
   if constexpr (SPLIT) redo = rows_of(redo_lds<NW>(smem_raw), wave, half == 0, my_k < S, mark_of(dkacc) + mark_of(dvacc));
-  if (half == 0) {
-    e16* rows = rows_lds<NW, D, SPLIT>(smem_raw, wave);
-    store_rows<D>(dvacc, 1.0f, rows, dv + tok0 * ldd + h * dd, ldd, wk0, S, lane, dd, redo);
+  if (half == 0 && (LINES || my_k < S)) {
+    e16* to_k = dk + tok0 * ldd + h * dd;
+    e16* to_v = dv + tok0 * ldd + h * dd;
+    if constexpr (LINES) store_rows<D>(dvacc, 1.0f, rows_lds<NW, D, SPLIT>(smem_raw, wave), to_v, ldd, wk0, S, lane, dd, redo);
 #pragma unroll
     for (int db = 0; db < D / 32; ++db)
 #pragma unroll
       for (int r = 0; r < 16; ++r) dkacc[db][r] *= SPLIT ? scale / DS_SCALE : scale;
     if (rope) unrotate_row<D, SPLIT ? 1 : 2>(dkacc, rope, min(my_k, S - 1), lane, dd);   // the registers that dV leaves: no spills
-    store_rows<D>(dkacc, 1.0f, rows, dk + tok0 * ldd + h * dd, ldd, wk0, S, lane, dd, redo);
+    if constexpr (LINES) store_rows<D>(dkacc, 1.0f, rows_lds<NW, D, SPLIT>(smem_raw, wave), to_k, ldd, wk0, S, lane, dd, redo);
+    else {
+      store_direct<D, SPLIT>(dkacc, 1.0f, to_k, ldd, my_k, S, lane, dd, redo);
+      store_direct<D, SPLIT>(dvacc, 1.0f, to_v, ldd, my_k, S, lane, dd, redo);
+    }
   }
   if constexpr (SPLIT) {
     if (__builtin_expect(any_row(redo_lds<NW>(smem_raw).masks, KWV, lane), 0))
@@ -876,6 +913,16 @@ template <int D> constexpr size_t smem_dkv(int nw) {
 inline bool wide_blocks(int S, int nh, int mb) { return cdiv(S, 256) * nh * mb >= 256; }
 inline bool wide_query_blocks(int S, int nh, int mb) { return wide_blocks(S, nh, mb) && S >= 4096; }
 
+// Whether the row blocks and results of a kernel pass through LDS as whole lines (D: padded head dim).  With one or two of a block's
+// four waves at work the way round costs more than it saves, and in the forward of narrow heads, with its shorter rows, at any
+// length.  us, lines : direct, 2 x 16 heads, forward of 128 columns S = 32 5.2 : 4.6, 64 5.4 : 5.2, 100 7.2 : 7.6; of 64 S = 64 5.1 : 4.7, 1000
+// 25.3 : 24.8, of 96 200 10.4 : 9.9; backward of 128 columns S = 32 9.6 : 8.8, 64 9.6 : 10.2; of 96 S = 64 15.9 : 14.7, 128 20.2 : 22.4.  dQ of
+// a padded 64 or 96 columns wants all four waves or two blocks (S = 192 loses 3 to 7 %, 128 gains as much), of a padded 128 the form
+// in which two waves share rows, which lengths over 256 have; half heads over 64, one wave per SIMD, neither gain nor lose but at S = 128.  dK/dV of 64 columns, long: S = 4096, 4 heads 101.9 : 98.2.
+template <int D, bool SPLIT> bool lines_fwd(int S) { return D == 128 && (SPLIT ? S >= 256 : S > 64); }
+template <int D, bool SPLIT> bool lines_dq(int S) { return SPLIT ? D < 128 && (S >= 256 || (S > 96 && S <= 128)) : S > 64; }
+template <int D, bool SPLIT> bool lines_dkv(int S) { return SPLIT ? S > 64 && (D > 64 || S <= 1024) : S > 32; }
+
 template <typename K> hipError_t set_smem(K kern, size_t bytes, bool& done) {
   if (done) return hipSuccess;
   hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
@@ -884,11 +931,11 @@ template <typename K> hipError_t set_smem(K kern, size_t bytes, bool& done) {
 }
 
 // One launch of each kernel with NW waves; `set` remembers that its LDS size has been allowed.
-template <int NW, int D, bool SPLIT>
+template <int NW, int D, bool SPLIT, bool LINES>
 hipError_t launch_fwd(hipStream_t st, int mb, int S, int nh, int d, const void* q, const void* k, const void* v, int64_t ld, void* o,
                       int64_t ldo, float* lse) {
   static bool set = false;
-  const hipError_t e = set_smem(attn_fwd_kernel<NW, D, SPLIT>, SMEM_FWD<D>, set);
+  const hipError_t e = set_smem(attn_fwd_kernel<NW, D, SPLIT, LINES>, SMEM_FWD<D>, set);
   if (e != hipSuccess) return e;
   // SPLIT adds scale_lo * score: above zero, so that a masked score stays -inf
   float hi = LOG2E / sqrtf((float)d), lo = 0.f;
@@ -897,43 +944,43 @@ hipError_t launch_fwd(hipStream_t st, int mb, int S, int nh, int d, const void* 
     if ((double)hi >= c) hi = nextafterf(hi, 0.f);
     lo = (float)(c - (double)hi);
   }
-  hipLaunchKernelGGL((attn_fwd_kernel<NW, D, SPLIT>), dim3((unsigned)(cdiv(S, 32 * NW) * nh * mb)), dim3(64 * NW), SMEM_FWD<D>, st, S,
+  hipLaunchKernelGGL((attn_fwd_kernel<NW, D, SPLIT, LINES>), dim3((unsigned)(cdiv(S, 32 * NW) * nh * mb)), dim3(64 * NW), SMEM_FWD<D>, st, S,
                      (const e16*)q, (const e16*)k, (const e16*)v, ld, (e16*)o, ldo, lse, hi, lo, nh, mb, d);
   return hipGetLastError();
 }
-template <int NW, int QS, int D, bool SPLIT>
+template <int NW, int QS, int D, bool SPLIT, bool LINES>
 hipError_t launch_dq(hipStream_t st, int mb, int S, int nh, int d, const void* q, const void* k, const void* v, int64_t ld, const void* o,
                      const void* dout, int64_t ldo, const float* lse, float* delta, void* dq, int64_t ldd, const float2* rope) {
   static bool set = false;
-  const hipError_t e = set_smem(attn_bwd_dq_kernel<NW, QS, D, SPLIT>, SMEM_FWD<D>, set);
+  const hipError_t e = set_smem(attn_bwd_dq_kernel<NW, QS, D, SPLIT, LINES>, SMEM_FWD<D>, set);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((attn_bwd_dq_kernel<NW, QS, D, SPLIT>), dim3((unsigned)(cdiv(S, 32 * (NW / QS)) * nh * mb)), dim3(64 * NW), SMEM_FWD<D>, st,
+  hipLaunchKernelGGL((attn_bwd_dq_kernel<NW, QS, D, SPLIT, LINES>), dim3((unsigned)(cdiv(S, 32 * (NW / QS)) * nh * mb)), dim3(64 * NW), SMEM_FWD<D>, st,
                      S, (const e16*)q, (const e16*)k, (const e16*)v, ld, (const e16*)o, (const e16*)dout, ldo, lse, delta, (e16*)dq,
                      ldd, 1.0f / sqrtf((float)d), nh, mb, rope, d);
   return hipGetLastError();
 }
-template <int NW, int QS, int D, bool SPLIT>
+template <int NW, int QS, int D, bool SPLIT, bool LINES>
 hipError_t launch_dkv(hipStream_t st, int mb, int S, int nh, int d, const void* q, const void* k, const void* v, int64_t ld,
                       const void* dout, int64_t ldo, const float* lse, const float* delta, void* dk, void* dv, int64_t ldd,
                       const float2* rope) {
   static bool set = false;
-  const hipError_t e = set_smem(attn_bwd_dkv_kernel<NW, QS, D, SPLIT, false>, smem_dkv<D>(NW / QS), set);
+  const hipError_t e = set_smem(attn_bwd_dkv_kernel<NW, QS, D, SPLIT, false, LINES>, smem_dkv<D>(NW / QS), set);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((attn_bwd_dkv_kernel<NW, QS, D, SPLIT, false>), dim3((unsigned)(cdiv(S, 32 * (NW / QS)) * nh * mb)), dim3(64 * NW), smem_dkv<D>(NW / QS),
+  hipLaunchKernelGGL((attn_bwd_dkv_kernel<NW, QS, D, SPLIT, false, LINES>), dim3((unsigned)(cdiv(S, 32 * (NW / QS)) * nh * mb)), dim3(64 * NW), smem_dkv<D>(NW / QS),
                      st, S, (const e16*)q, (const e16*)k, (const e16*)v, ld, (const e16*)dout, ldo, lse, delta, (e16*)dk, (e16*)dv,
                      ldd, 1.0f / sqrtf((float)d), nh, mb, rope, d, 0, nullptr, nullptr, nullptr);
   return hipGetLastError();
 }
 // dQ and dK/dV together, 8 waves to a block of 128 rows, two of them per 32 rows.
-template <int D>
+template <int D, bool LINES>
 hipError_t launch_bwd(hipStream_t st, int mb, int S, int nh, const void* q, const void* k, const void* v, int64_t ld, const void* o, const void* dout,
                       int64_t ldo, const float* lse, float* delta, void* dq, void* dk, void* dv, int64_t ldd, const float2* rope) {
   constexpr size_t SMEM = smem_dkv<D>(4) > SMEM_FWD<D> ? smem_dkv<D>(4) : SMEM_FWD<D>;
   static bool set = false;
-  const hipError_t e = set_smem(attn_bwd_dkv_kernel<8, 2, D, false, true>, SMEM, set);
+  const hipError_t e = set_smem(attn_bwd_dkv_kernel<8, 2, D, false, true, LINES>, SMEM, set);
   if (e != hipSuccess) return e;
   const int blocks = (int)(cdiv(S, 128) * nh * mb);
-  hipLaunchKernelGGL((attn_bwd_dkv_kernel<8, 2, D, false, true>), dim3((unsigned)(2 * blocks)), dim3(512), SMEM, st, S, (const e16*)q, (const e16*)k,
+  hipLaunchKernelGGL((attn_bwd_dkv_kernel<8, 2, D, false, true, LINES>), dim3((unsigned)(2 * blocks)), dim3(512), SMEM, st, S, (const e16*)q, (const e16*)k,
                      (const e16*)v, ld, (const e16*)dout, ldo, lse, nullptr, (e16*)dk, (e16*)dv, ldd, 1.0f / sqrtf((float)D), nh, mb, rope, D,
                      blocks, (const e16*)o, delta, (e16*)dq);
   return hipGetLastError();
@@ -957,19 +1004,24 @@ hipError_t bwd_128(hipStream_t st, int mb, int S, int nh, int d, const void* q, 
                    const void* dout, int64_t ldo, const float* lse, float* delta, void* dq, void* dk, void* dv, int64_t ldd,
                    const float2* rope, bool wide_dkv) {
   if constexpr (SPLIT && LO_ACC && D > 64) {   // the low accumulators of wide half heads leave no registers for 8 waves
-    const hipError_t e = launch_dq<4, 1, D, SPLIT>(st, mb, S, nh, d, q, k, v, ld, o, dout, ldo, lse, delta, dq, ldd, rope);
-    return e != hipSuccess ? e : launch_dkv<4, 1, D, SPLIT>(st, mb, S, nh, d, q, k, v, ld, dout, ldo, lse, delta, dk, dv, ldd, rope);
+    const hipError_t e = launch_dq<4, 1, D, SPLIT, false>(st, mb, S, nh, d, q, k, v, ld, o, dout, ldo, lse, delta, dq, ldd, rope);
+    if (e != hipSuccess) return e;
+    return lines_dkv<D, SPLIT>(S) ? launch_dkv<4, 1, D, SPLIT, true>(st, mb, S, nh, d, q, k, v, ld, dout, ldo, lse, delta, dk, dv, ldd, rope)
+                                  : launch_dkv<4, 1, D, SPLIT, false>(st, mb, S, nh, d, q, k, v, ld, dout, ldo, lse, delta, dk, dv, ldd, rope);
   } else {
     const int64_t per_head = cdiv(S, 128), blocks = per_head * nh * mb;
     if constexpr (!SPLIT && D == 128)
       if (!wide_dkv && blocks <= (per_head == 1 ? 128 : per_head < 4 ? 192 : 256) &&
           attn_bwd_apart((int64_t)mb * S, 2ll * nh * d, k, v, 2 * ld, o, 2 * ldo, dq, dk, dv, 2 * ldd))
-        return launch_bwd<D>(st, mb, S, nh, q, k, v, ld, o, dout, ldo, lse, delta, dq, dk, dv, ldd, rope);
+        return lines_dkv<D, SPLIT>(S) ? launch_bwd<D, true>(st, mb, S, nh, q, k, v, ld, o, dout, ldo, lse, delta, dq, dk, dv, ldd, rope)
+                                      : launch_bwd<D, false>(st, mb, S, nh, q, k, v, ld, o, dout, ldo, lse, delta, dq, dk, dv, ldd, rope);
     const hipError_t e = S > 256 && blocks < 512 && blocks <= 256 + 28 * (per_head > 6 ? per_head - 6 : 0)
-                             ? launch_dq<8, 2, D, SPLIT>(st, mb, S, nh, d, q, k, v, ld, o, dout, ldo, lse, delta, dq, ldd, rope)
-                             : launch_dq<4, 1, D, SPLIT>(st, mb, S, nh, d, q, k, v, ld, o, dout, ldo, lse, delta, dq, ldd, rope);
+                             ? launch_dq<8, 2, D, SPLIT, true>(st, mb, S, nh, d, q, k, v, ld, o, dout, ldo, lse, delta, dq, ldd, rope)
+                         : lines_dq<D, SPLIT>(S) ? launch_dq<4, 1, D, SPLIT, !(SPLIT && D == 128)>(st, mb, S, nh, d, q, k, v, ld, o, dout, ldo, lse, delta, dq, ldd, rope)
+                                                 : launch_dq<4, 1, D, SPLIT, false>(st, mb, S, nh, d, q, k, v, ld, o, dout, ldo, lse, delta, dq, ldd, rope);
     if (e != hipSuccess || wide_dkv) return e;
-    return launch_dkv<8, 2, D, SPLIT>(st, mb, S, nh, d, q, k, v, ld, dout, ldo, lse, delta, dk, dv, ldd, rope);
+    return lines_dkv<D, SPLIT>(S) ? launch_dkv<8, 2, D, SPLIT, true>(st, mb, S, nh, d, q, k, v, ld, dout, ldo, lse, delta, dk, dv, ldd, rope)
+                                  : launch_dkv<8, 2, D, SPLIT, false>(st, mb, S, nh, d, q, k, v, ld, dout, ldo, lse, delta, dk, dv, ldd, rope);
   }
 }
 
@@ -979,9 +1031,9 @@ hipError_t bwd_128(hipStream_t st, int mb, int S, int nh, int d, const void* q, 
 hipError_t ZS_ATTN_NAME(attn_fwd_split)(hipStream_t st, int mb, int S, int nh, int d, const void* q, const void* k, const void* v,
                          int64_t ld, void* o, int64_t ldo, float* lse) {
   if (d >= 128 || (int64_t)S * ld * 2 >= (1ll << 31)) return hipErrorInvalidValue;      // 32-bit buffer offsets
-  if (d <= 64) return launch_fwd<4, 64, true>(st, mb, S, nh, d, q, k, v, ld, o, ldo, lse);
-  if (d <= 96) return launch_fwd<4, 96, true>(st, mb, S, nh, d, q, k, v, ld, o, ldo, lse);
-  return launch_fwd<4, 128, true>(st, mb, S, nh, d, q, k, v, ld, o, ldo, lse);
+  if (d <= 64) return launch_fwd<4, 64, true, false>(st, mb, S, nh, d, q, k, v, ld, o, ldo, lse);
+  if (d <= 96) return launch_fwd<4, 96, true, false>(st, mb, S, nh, d, q, k, v, ld, o, ldo, lse);
+  return lines_fwd<128, true>(S) ? launch_fwd<4, 128, true, true>(st, mb, S, nh, d, q, k, v, ld, o, ldo, lse) : launch_fwd<4, 128, true, false>(st, mb, S, nh, d, q, k, v, ld, o, ldo, lse);
 }
 
 hipError_t ZS_ATTN_NAME(attn_bwd_split)(hipStream_t st, int mb, int S, int nh, int d, const void* q, const void* k, const void* v,
@@ -1001,8 +1053,9 @@ hipError_t ZS_ATTN_NAME(attn_fwd_mfma)(hipStream_t st, int mb, int S, int nh, in
                          int64_t ld, void* o, int64_t ldo, float* lse) {
   if ((int64_t)S * ld * 2 >= (1ll << 31)) return hipErrorInvalidValue;      // 32-bit buffer offsets
   // 256 queries per workgroup when that still gives every CU a workgroup, else 128
-  return wide_query_blocks(S, nh, mb) ? launch_fwd<8, 128, false>(st, mb, S, nh, d, q, k, v, ld, o, ldo, lse)
-                                      : launch_fwd<4, 128, false>(st, mb, S, nh, d, q, k, v, ld, o, ldo, lse);
+  return wide_query_blocks(S, nh, mb) ? launch_fwd<8, 128, false, true>(st, mb, S, nh, d, q, k, v, ld, o, ldo, lse)
+         : lines_fwd<128, false>(S)   ? launch_fwd<4, 128, false, true>(st, mb, S, nh, d, q, k, v, ld, o, ldo, lse)
+                                      : launch_fwd<4, 128, false, false>(st, mb, S, nh, d, q, k, v, ld, o, ldo, lse);
 }
 
 hipError_t ZS_ATTN_NAME(attn_bwd_mfma)(hipStream_t st, int mb, int S, int nh, int d, const void* q, const void* k, const void* v,
@@ -1011,10 +1064,11 @@ hipError_t ZS_ATTN_NAME(attn_bwd_mfma)(hipStream_t st, int mb, int S, int nh, in
   if ((int64_t)S * (ld > ldo ? ld : ldo) * 2 >= (1ll << 31)) return hipErrorInvalidValue;   // 32-bit buffer offsets
   const bool wide = wide_blocks(S, nh, mb);
   const hipError_t e =
-      wide_query_blocks(S, nh, mb) ? launch_dq<8, 1, 128, false>(st, mb, S, nh, d, q, k, v, ld, o, dout, ldo, lse, delta, dq, ldd, rope)
+      wide_query_blocks(S, nh, mb) ? launch_dq<8, 1, 128, false, true>(st, mb, S, nh, d, q, k, v, ld, o, dout, ldo, lse, delta, dq, ldd, rope)
                                    : bwd_128<128, false>(st, mb, S, nh, d, q, k, v, ld, o, dout, ldo, lse, delta, dq, dk, dv, ldd, rope, wide);
   if (e != hipSuccess || !wide) return e;
-  return launch_dkv<8, 1, 128, false>(st, mb, S, nh, d, q, k, v, ld, dout, ldo, lse, delta, dk, dv, ldd, rope);
+  return lines_dkv<128, false>(S) ? launch_dkv<8, 1, 128, false, true>(st, mb, S, nh, d, q, k, v, ld, dout, ldo, lse, delta, dk, dv, ldd, rope)
+                                  : launch_dkv<8, 1, 128, false, false>(st, mb, S, nh, d, q, k, v, ld, dout, ldo, lse, delta, dk, dv, ldd, rope);
 }
 #endif
 
