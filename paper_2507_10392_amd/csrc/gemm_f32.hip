@@ -59,19 +59,19 @@ template <int NB> struct Frag<1, NB> {   // row-contiguous
   }
 };
 
-// Forms that share out K bring k-contiguous operands in through LDS, two slabs at a time (rows_lds.h): of the 5.9 us of 256 x 256, K = 1024
-// on 16x16 tiles direct loads of A alone were 1.7.  Up to four pairs of slabs are in flight (64x64: two, more leave no second
-// workgroup per CU; it gains 8 to 15 % over one pair where CUs have one workgroup).  The sums and their order are those of the
-// direct loads.  us, direct : through LDS, over 224 products of a stage with 64 to 2048 rows 0.88 on the geometric mean; 256 x 512,
-// K = 1536 (dx) 10.9 : 7.3; 256 x 256, K = 1024 6.1 : 4.4; 1024 x 1024, K = 1024 26.9 : 22.5; 128 x 1024, K = 2768 loses (16.4 : 17.6).
-// 128x128 tiles reach the matrix cores' rate without.
+// Forms that share out K bring k-contiguous operands in through LDS, two slabs at a time (rows_lds.h), where through_lds says so: of the
+// 5.9 us of 256 x 256, K = 1024 on 16x16 tiles direct loads of A alone were 1.7.  Two pairs of slabs are in flight on 64x64 and 32x32
+// tiles, where more leave no second workgroup per CU (32x32: 369 x 1232, K = 176, 468 tiles 6.4 us with three, 5.2 with two; 64x64: two
+// gain 8 to 15 % over one where CUs have one workgroup), three or four on smaller ones.  The sums and their order are those of the
+// direct loads.  us, direct : through LDS: 256 x 512, K = 1536 (dx) 10.9 : 7.3; 256 x 256, K = 1024 6.1 : 4.4; 1024 x 1024, K = 1024 26.9 :
+// 22.5; 0.88 on the geometric mean of 645 products.  128x128 tiles reach the matrix cores' rate without.
 // A workgroup owns a (16 MI WM) x (16 NI WN) tile of C (MI, NI = 1, 2 or 4): WM x WN waves side by side, times KW waves
 // that share out K.
 // ACT: see Gemm::act; kernels of their own, because the branch alone costs the small products 0.5 %.
-template <int TA, int TB, int MI, int NI, int WM, int WN, int KW, int SEG, int ACT = 0>
+template <int TA, int TB, int MI, int NI, int WM, int WN, int KW, int SEG, int ACT = 0, bool LINES = (KW > 1)>
 __device__ __forceinline__ void f32_tile(const Gemm& g, int tiles_m, int tiles_n, int pid, int z) {
   constexpr int NQ = MI * NI;   // quads of 4 consecutive columns a lane holds
-  constexpr bool STAGED = KW > 1 && (TA == 0 || TB == 1);   // k-contiguous operands through LDS
+  constexpr bool STAGED = LINES && (TA == 0 || TB == 1);   // k-contiguous operands through LDS
   constexpr int RED = KW > 1 ? (KW - 1) * WM * WN * NQ * 64 : 1, SA = STAGED && TA == 0 ? MI * 128 : 0, SB = STAGED && TB == 1 ? NI * 128 : 0;
   constexpr int STAGE = KW * WM * WN * (SA + SB);
   constexpr bool SHARED = (RED + STAGE) * 16 > 65536;       // partial tiles take the place of the slabs
@@ -152,7 +152,7 @@ __device__ __forceinline__ void f32_tile(const Gemm& g, int tiles_m, int tiles_n
   const int slabs = (g.K + 15) / 16, per = (slabs + KW - 1) / KW;
   const int s0 = kw * per, s1 = min(slabs, s0 + per);        // this wave's slabs
   if constexpr (STAGED) {
-    constexpr int DEPTH = MI * NI == 16 ? 2 : MI * NI == 1 ? 4 : 3;
+    constexpr int DEPTH = MI * NI >= 4 ? 2 : MI * NI == 1 ? 4 : 3;
     u32x4* la = reinterpret_cast<u32x4*>(lds) + wave * (SA + SB);
     u32x4* lb = la + SA;
     struct Pair { Rows<SA ? MI : 1> a; Rows<SB ? NI : 1> b; Frag<1, TA ? MI : 1> ra[2]; Frag<1, TB ? 1 : NI> rb[2]; } buf[DEPTH];
@@ -294,9 +294,9 @@ __device__ __forceinline__ void f32_tile(const Gemm& g, int tiles_m, int tiles_n
   }
 }
 
-template <int TA, int TB, int MI, int NI, int WM, int WN, int KW, int SEG, int ACT = 0>
+template <int TA, int TB, int MI, int NI, int WM, int WN, int KW, int SEG, int ACT, bool LINES>
 __global__ __launch_bounds__(64 * WM * WN * KW) void gemm_f32_kernel(Gemm g, int tiles_m, int tiles_n) {
-  f32_tile<TA, TB, MI, NI, WM, WN, KW, SEG, ACT>(g, tiles_m, tiles_n, blockIdx.x, blockIdx.y);
+  f32_tile<TA, TB, MI, NI, WM, WN, KW, SEG, ACT, LINES>(g, tiles_m, tiles_n, blockIdx.x, blockIdx.y);
 }
 // Weight gradients of a layer in one launch (see gemm_group).
 template <int MI, int NI, int WM, int WN, int KW> __global__ __launch_bounds__(64 * WM * WN * KW) void gemm_f32_group_kernel(GemmGroup q) {
@@ -311,17 +311,34 @@ template <int MI, int NI, int WM, int WN, int KW> hipError_t launch_group(hipStr
   return hipGetLastError();
 }
 
-template <int MI, int NI, int WM, int WN, int KW> hipError_t launch(hipStream_t st, const Gemm& g) {
+template <int MI, int NI, int WM, int WN, int KW, bool LINES> hipError_t launch_kernel(hipStream_t st, const Gemm& g) {
   const int tm = (int)cdiv(g.M, 16 * MI * WM), tn = (int)cdiv(g.N, 16 * NI * WN);
   dim3 grid((unsigned)(tm * tn), (unsigned)g.batch), blk(64 * WM * WN * KW);
-  if (g.act == 1) hipLaunchKernelGGL((gemm_f32_kernel<0, 0, MI, NI, WM, WN, KW, 0, 1>), grid, blk, 0, st, g, tm, tn);
-  else if (g.act) hipLaunchKernelGGL((gemm_f32_kernel<0, 1, MI, NI, WM, WN, KW, 0, 2>), grid, blk, 0, st, g, tm, tn);
-  else if (g.kseg) hipLaunchKernelGGL((gemm_f32_kernel<0, 1, MI, NI, WM, WN, KW, 1>), grid, blk, 0, st, g, tm, tn);
-  else if (!g.transA && !g.transB) hipLaunchKernelGGL((gemm_f32_kernel<0, 0, MI, NI, WM, WN, KW, 0>), grid, blk, 0, st, g, tm, tn);
-  else if (!g.transA) hipLaunchKernelGGL((gemm_f32_kernel<0, 1, MI, NI, WM, WN, KW, 0>), grid, blk, 0, st, g, tm, tn);
-  else if (!g.transB) hipLaunchKernelGGL((gemm_f32_kernel<1, 0, MI, NI, WM, WN, KW, 0>), grid, blk, 0, st, g, tm, tn);
-  else hipLaunchKernelGGL((gemm_f32_kernel<1, 1, MI, NI, WM, WN, KW, 0>), grid, blk, 0, st, g, tm, tn);
+  if (g.act == 1) hipLaunchKernelGGL((gemm_f32_kernel<0, 0, MI, NI, WM, WN, KW, 0, 1, LINES>), grid, blk, 0, st, g, tm, tn);
+  else if (g.act) hipLaunchKernelGGL((gemm_f32_kernel<0, 1, MI, NI, WM, WN, KW, 0, 2, LINES>), grid, blk, 0, st, g, tm, tn);
+  else if (g.kseg) hipLaunchKernelGGL((gemm_f32_kernel<0, 1, MI, NI, WM, WN, KW, 1, 0, LINES>), grid, blk, 0, st, g, tm, tn);
+  else if (!g.transA && !g.transB) hipLaunchKernelGGL((gemm_f32_kernel<0, 0, MI, NI, WM, WN, KW, 0, 0, LINES>), grid, blk, 0, st, g, tm, tn);
+  else if (!g.transA) hipLaunchKernelGGL((gemm_f32_kernel<0, 1, MI, NI, WM, WN, KW, 0, 0, LINES>), grid, blk, 0, st, g, tm, tn);
+  else if (!g.transB) hipLaunchKernelGGL((gemm_f32_kernel<1, 0, MI, NI, WM, WN, KW, 0, 0, false>), grid, blk, 0, st, g, tm, tn);
+  else hipLaunchKernelGGL((gemm_f32_kernel<1, 1, MI, NI, WM, WN, KW, 0, 0, LINES>), grid, blk, 0, st, g, tm, tn);
   return hipGetLastError();
+}
+// Through LDS or direct.  A short K has nothing to run beside the way round.  Where rows are not whole lines, so that a piece of 128 bytes lies in
+// two, forward products on 16x32 tiles gain nothing once W no longer fits an XCD's L2, and input gradients on 32x32 tiles lose if their
+// waves' shares end in half a pair of slabs and are short.  us, through LDS : direct: 66 x 208, K = 56 (dx) 2.56 : 2.35; 256 x 128, K = 128
+// 2.83 : 2.70; 128 x 1024, K = 2768 17.7 : 16.3, but 221 x 304, K = 1224 6.4 : 7.5; 512 x 512, K = 1384 (dx, 11 slabs a wave) 11.7 : 10.9,
+// but 266 x 888, K = 216 (dx, 2 slabs) 4.0 : 4.4 and 269 x 624, K = 3728 (30 slabs) 23.8 : 25.8.
+template <int MI, int NI, int KW> bool through_lds(const Gemm& g) {
+  if (g.K <= (MI * NI == 1 ? 128 : 64)) return false;
+  if ((g.transA || g.lda % 32 == 0) && (!g.transB || g.ldb % 32 == 0)) return true;
+  const int64_t share = cdiv(cdiv(g.K, 16), KW);
+  if (g.transB) return MI * NI != 4 || share % 2 == 0 || share > 12;
+  return MI * NI != 2 || (int64_t)g.K * g.N * 4 < (4 << 20);
+}
+template <int MI, int NI, int WM, int WN, int KW> hipError_t launch(hipStream_t st, const Gemm& g) {
+  if constexpr (KW > 1)
+    if (through_lds<MI, NI, KW>(g)) return launch_kernel<MI, NI, WM, WN, KW, true>(st, g);
+  return launch_kernel<MI, NI, WM, WN, KW, false>(st, g);
 }
 
 }  // namespace
