@@ -9,9 +9,9 @@
 // How the operands fit without an LDS transpose.  A 16x16x32 step takes from lane l eight values of row l%16; which k stand
 // behind them is free as long as both operands agree: k = 8 (l/16) + 0..7 of the slab.
 //   k-contiguous operand (A [M,K], B [N,K]): 16 bytes per lane and block of 16 rows.  Input gradients, where both operands are, get
-//     them through LDS of the wave's own (rows_lds.h): with one direct load per fragment the address unit was the limit.  us,
-//     direct : through LDS, 64 x 768, K = 3072 12.8 : 6.9; 384 x 1024, K = 4096 30.3 : 15.8; 512 x 512, K = 512 4.2 : 3.7; 0.76 on the
-//     geometric mean of 96 products with 64 to 1000 rows, K = 256 .. 4096.
+//     them through LDS of the wave's own (rows_lds.h) unless K is short (launch_form): with one direct load per fragment the address
+//     unit was the limit.  us, direct : through LDS, 64 x 768, K = 3072 12.7 : 6.4; 384 x 1024, K = 3072 23.6 : 11.3; 512 x 512, K = 512
+//     4.4 : 3.5.
 //   row-contiguous operand (A [K,M], B [K,N]): lane l loads NV consecutive columns of each of its eight k-lines; pairs of
 //     k-lines are then interleaved by one v_perm_b32 per register, which leaves in NV fragments the columns NV (l%16) + j.
 // The matrix instruction gets B as its first operand, so a lane ends up with 4 consecutive columns of one row of C.
@@ -72,6 +72,16 @@ __device__ __forceinline__ void load_r(Raw<2>& f, __amdgpu_buffer_rsrc_t rs, uns
   for (int i = 0; i < 8; ++i) f.v[i] = __builtin_amdgcn_raw_buffer_load_b32(rs, (int)(at + i * ld2), (int)soff, 0);
 }
 
+// A k-contiguous operand's share of a slab, read straight into fragments: 8 k of rows 16 apart.
+template <int NB> struct RawK {
+  u32x4 v[NB];
+  __device__ __forceinline__ u32x4 frag(int b) const { return v[b]; }
+};
+template <int NB> __device__ __forceinline__ void load_k(RawK<NB>& f, __amdgpu_buffer_rsrc_t rs, unsigned at, unsigned ld2, unsigned soff) {
+#pragma unroll
+  for (int b = 0; b < NB; ++b) f.v[b] = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)(at + 16 * b * ld2), (int)soff, 0);
+}
+
 enum Form { NT, NT_SEG, TN_ACC, TN_PARTS, NT_GLU };
 
 __device__ __forceinline__ void tile_of(int pid, int tiles_m, int tiles_n, int& tm, int& tn) {
@@ -80,13 +90,13 @@ __device__ __forceinline__ void tile_of(int pid, int tiles_m, int tiles_n, int& 
   gemm_tile_of(pid, tiles_m, tiles_n, tm, tn);
 }
 
-// T: blocks of 16 rows and columns a wave's tile has each way (2: 32x32, 4: 64x64), KW: waves that share out K, NBUF: slabs held of
-// row-contiguous operands (NBUF - 1 of them in flight).
-template <typename E, int FORM, int T, int KW, int NBUF>
+// T: blocks of 16 rows and columns a wave's tile has each way (2: 32x32, 4: 64x64), KW: waves that share out K, LINES: k-contiguous operands
+// come in through LDS, NBUF: slabs held otherwise (NBUF - 1 of them in flight).
+template <typename E, int FORM, int T, int KW, int NBUF, bool LINES>
 __device__ __forceinline__ void small_tile(const Gemm& g, int tiles_m, int tiles_n, int pid, int z) {
   constexpr bool TA = FORM == TN_ACC || FORM == TN_PARTS, TB = !TA, ACC = TA;
   constexpr int NQ = T * T;                        // quads of 4 consecutive columns a lane holds
-  constexpr int RED = (KW - 1) * NQ * 64, STAGE = TB ? KW * 2 * T * 128 : 0;
+  constexpr int RED = (KW - 1) * NQ * 64, STAGE = LINES ? KW * 2 * T * 128 : 0;
   __shared__ f32x4 red[RED > STAGE ? RED : STAGE]; // partial tiles take the place of the slabs
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lm = lane & 15, lg = lane >> 4;
@@ -108,9 +118,11 @@ __device__ __forceinline__ void small_tile(const Gemm& g, int tiles_m, int tiles
     for (int j = 0; j < T; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
   const int slabs = (g.K + 31) / 32, per = (slabs + KW - 1) / KW;
   const int s0 = wave * per, s1 = min(slabs, s0 + per);   // this wave's slabs
-  if constexpr (TB) {
-    // Two pairs of slabs in flight, three on 32x32 tiles.  The fragments hold the same k as with direct loads.
-    constexpr int DEPTH = T == 2 ? 3 : 2;
+  if constexpr (LINES) {
+    // Two pairs of slabs in flight: on 32x32 tiles a third takes the registers of a CU's second workgroup (512 x 768, K = 256 4.8 us, 4.2 with
+    // two).
+    // The fragments hold the same k as with direct loads.
+    constexpr int DEPTH = 2;
     u32x4* la = reinterpret_cast<u32x4*>(red) + wave * 2 * T * 128;
     u32x4* lb = la + T * 128;
     struct Pair { Rows<T> a, b; } pairs[DEPTH];
@@ -150,11 +162,20 @@ __device__ __forceinline__ void small_tile(const Gemm& g, int tiles_m, int tiles
         }
     __syncthreads();
   } else {
-    const unsigned ao = m0 + T * lm < g.M ? (8 * lg * lda + m0 + T * lm) * 2 : OUT, bo = n0 + T * lm < g.N ? (8 * lg * ldb + n0 + T * lm) * 2 : OUT;
-    struct Slab { Raw<T> a, b; } buf[NBUF];
+    const unsigned ao = TB ? ((m0 + lm) * lda + 8 * lg) * 2 : m0 + T * lm < g.M ? (8 * lg * lda + m0 + T * lm) * 2 : OUT,
+                   bo = TB ? ((n0 + lm) * ldb + (FORM == NT_SEG ? 0 : 8 * lg)) * 2 : n0 + T * lm < g.N ? (8 * lg * ldb + n0 + T * lm) * 2 : OUT;
+    struct Slab { std::conditional_t<TB, RawK<T>, Raw<T>> a, b; } buf[NBUF];
     auto load = [&](Slab& s, int slab) {                   // k-lines past K lie behind the descriptors
       const int k = slab * 32;
-      if constexpr (FORM == TN_PARTS) {   // slabs do not straddle parts: kseg is a multiple of 128
+      if constexpr (TB) {
+        const int kl = k + 8 * lg;
+        const bool past = kl >= g.K;                       // K is a multiple of 8
+        load_k<T>(s.a, ra, past ? OUT : ao, lda * 2, k * 2);
+        if constexpr (FORM == NT_SEG) {
+          const int seg = kl / g.kseg;
+          load_k<T>(s.b, rb, past ? OUT : bo + (unsigned)(seg * g.segB + (kl - seg * g.kseg)) * 2, ldb * 2, 0);
+        } else load_k<T>(s.b, rb, past ? OUT : bo, ldb * 2, k * 2);
+      } else if constexpr (FORM == TN_PARTS) {   // slabs do not straddle parts: kseg is a multiple of 128
         const int p = min(k / g.kseg, g.nx), kin = k - p * g.kseg;
         const int rows = p < g.nx ? g.kseg : g.K - g.nx * g.kseg;
         const __amdgpu_buffer_rsrc_t pa = rsrc((p ? (const E*)g.Ax[p - 1] : (const E*)g.A) + (int64_t)z * g.sA, (int64_t)(rows - 1) * lda + g.M),
@@ -271,7 +292,7 @@ __device__ __forceinline__ void small_tile(const Gemm& g, int tiles_m, int tiles
 // us against one wave per tile, whose address unit took the 64 pieces of every load of x one by one: 256 x 512, K = 512 4.5 : 3.9, K =
 // 1384 8.1 : 6.2; 256 x 3072, K = 768 (768 tiles) 8.2 : 8.4; 0.88 on the geometric mean of 96 products with 64 to 1000 rows.
 template <typename E, bool GLU>
-__device__ __forceinline__ void forward_tile(const Gemm& g, int tiles_m, int tiles_n, int pid, int z) {
+__device__ __forceinline__ void forward_together(const Gemm& g, int tiles_m, int tiles_n, int pid, int z) {
   constexpr int SK = 128, DEPTH = 4, NM = GLU ? 2 : 1;     // k of a stage, stages in flight, matrices W
   constexpr int LINE = 6, SA = 32 * 16, SB = SK * LINE;    // 16-byte pieces: of a line of W, of a stage of x and of W
   __shared__ u32x4 lds[2][SA + NM * SB];
@@ -390,19 +411,133 @@ __device__ __forceinline__ void forward_tile(const Gemm& g, int tiles_m, int til
     *reinterpret_cast<E4*>((E*)g.C + (int64_t)z * g.sC + (int64_t)m * g.ldc + n) = o;
   }
 }
-template <typename E, bool GLU> __global__ __launch_bounds__(256, GLU ? 2 : 4) void gemm_small_forward_kernel(Gemm g, int tiles_m, int tiles_n) {
-  forward_tile<E, GLU>(g, tiles_m, tiles_n, blockIdx.x, blockIdx.y);
+
+// The same with one wave per tile, which reads its operands straight into fragments, seven slabs of 32 k ahead: see forward_shared.
+template <typename E, bool GLU>
+__device__ __forceinline__ void forward_alone(const Gemm& g, int tiles_m, int tiles_n, int pid, int z) {
+  constexpr int T = 2, NB = 2, NJ = GLU ? 2 * NB : NB, NBUF = 8;   // blocks of rows, of columns of one matrix and of the tile; slabs held
+  const int lane = threadIdx.x & 63, lm = lane & 15, lg = lane >> 4;
+  int tm, tn;
+  tile_of(pid, tiles_m, tiles_n, tm, tn);
+  const int m0 = tm * 16 * T, n0 = tn * 16 * NB;
+  const E* A = (const E*)g.A + (int64_t)z * g.sA;
+  const E* B = (const E*)g.B + (int64_t)z * g.sB;
+  const unsigned lda = (unsigned)g.lda, ldb = (unsigned)g.ldb;
+  const __amdgpu_buffer_rsrc_t ra = rsrc(A, (int64_t)(g.M - 1) * lda + g.K), rb = rsrc(B, (int64_t)(g.K - 1) * ldb + g.N);
+  const __amdgpu_buffer_rsrc_t rb2 = rsrc(B + (GLU ? g.sB : 0), (int64_t)(g.K - 1) * ldb + g.N);
+  unsigned ao[T];
+#pragma unroll
+  for (int i = 0; i < T; ++i) ao[i] = ((m0 + 16 * i + lm) * lda + 8 * lg) * 2;
+  const unsigned bo = n0 + NB * lm < g.N ? (8 * lg * ldb + n0 + NB * lm) * 2 : OUT;
+  struct Slab { RawK<T> a; Raw<NB> b, b2; };
+  Slab buf[NBUF];
+  auto load = [&](Slab& s, int slab) {   // k-lines past K lie behind the descriptors
+    const int k = slab * 32;
+    const bool past = k + 8 * lg >= g.K;
+#pragma unroll
+    for (int i = 0; i < T; ++i) s.a.v[i] = __builtin_amdgcn_raw_buffer_load_b128(ra, (int)(past ? OUT : ao[i]), k * 2, 0);
+    load_r(s.b, rb, bo, ldb * 2, k * ldb * 2);
+    if constexpr (GLU) load_r(s.b2, rb2, bo, ldb * 2, k * ldb * 2);
+  };
+  f32x4 acc[T][NJ];
+#pragma unroll
+  for (int i = 0; i < T; ++i)
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  auto multiply = [&](const Slab& s) {
+    u32x4 a[T];
+#pragma unroll
+    for (int i = 0; i < T; ++i) a[i] = s.a.frag(i);
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+      const u32x4 b = GLU && j >= NB ? s.b2.frag(j % NB) : s.b.frag(j % NB);
+#pragma unroll
+      for (int i = 0; i < T; ++i) acc[i][j] = mfma<E>(b, a[i], acc[i][j]);
+    }
+  };
+  // s0 is the only wave's first slab, 0, which the compiler cannot see: where it can, it peels the loop and then waits for all loads in
+  // flight at every slab (512 x 768, K = 2080 16.2 us instead of 11.4).
+  const int slabs = (g.K + 31) / 32, s0 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * slabs, s1 = min(slabs, s0 + slabs);
+#pragma unroll
+  for (int i = 0; i < NBUF - 1; ++i)
+    if (s0 + i < s1) load(buf[i], s0 + i);
+  for (int s = s0; s < s1; s += NBUF)
+#pragma unroll
+    for (int i = 0; i < NBUF; ++i)
+      if (s + i < s1) {
+        if (s + i + NBUF - 1 < s1) load(buf[(i + NBUF - 1) % NBUF], s + i + NBUF - 1);
+        multiply(buf[i]);
+      }
+
+  // column NB (4 lg + r) + j  <->  block j, register r
+  auto quad = [&](int i, int q) {
+    const int base = q / NB * NB, ql = q % NB;
+    f32x4 v;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = acc[i][base + (4 * ql + e) % NB][(4 * ql + e) / NB];
+    return v;
+  };
+  typedef E E4 __attribute__((ext_vector_type(4)));
+#pragma unroll
+  for (int i = 0; i < T; ++i)
+#pragma unroll
+    for (int q = 0; q < NB; ++q) {
+      const int m = m0 + 16 * i + lm, n = n0 + 4 * NB * lg + 4 * q;
+      if (m >= g.M || n >= g.N) continue;
+      f32x4 v = quad(i, q);
+      E* out = (E*)g.C + (int64_t)z * g.sC + (int64_t)m * g.ldc + n;
+      E4 o;
+      if constexpr (GLU) {
+        const f32x4 u = quad(i, q + NB);
+        E4 ou, oa;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          o[e] = (E)v[e];
+          ou[e] = (E)u[e];
+          oa[e] = (E)glu_f((float)o[e], (float)ou[e]);
+        }
+        E* pg = (E*)g.gu + (int64_t)m * g.gu_ld + n;
+        *reinterpret_cast<E4*>(pg) = o;
+        *reinterpret_cast<E4*>(pg + g.gu_up) = ou;
+        *reinterpret_cast<E4*>(out) = oa;
+      } else {
+        if (g.bias) {
+          const E4 bb = *reinterpret_cast<const E4*>((const E*)g.bias + (int64_t)z * g.sBias + n);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) v[e] += (float)bb[e];
+        }
+        if (g.resid) {
+          const E4 rr = *reinterpret_cast<const E4*>((const E*)g.resid + (int64_t)z * g.sC + (int64_t)m * g.ldr + n);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) v[e] += (float)rr[e];
+        }
+        if (g.rope && z < g.rope_batches) {
+          const f32x4 t = *reinterpret_cast<const f32x4*>(g.rope + (int64_t)(m % g.rope_S) * (g.rope_d / 2) + (n % g.rope_d) / 2);
+          v = f32x4{v[0] * t[0] - v[1] * t[1], v[0] * t[1] + v[1] * t[0], v[2] * t[2] - v[3] * t[3], v[2] * t[3] + v[3] * t[2]};
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[e] = (E)v[e];
+        *reinterpret_cast<E4*>(out) = o;
+      }
+    }
 }
 
-template <typename E, int FORM, int T, int KW, int NBUF>
+template <typename E, bool GLU> __global__ __launch_bounds__(64) void gemm_small_forward_alone_kernel(Gemm g, int tiles_m, int tiles_n) {
+  forward_alone<E, GLU>(g, tiles_m, tiles_n, blockIdx.x, blockIdx.y);
+}
+template <typename E, bool GLU> __global__ __launch_bounds__(256, GLU ? 2 : 4) void gemm_small_forward_kernel(Gemm g, int tiles_m, int tiles_n) {
+  forward_together<E, GLU>(g, tiles_m, tiles_n, blockIdx.x, blockIdx.y);
+}
+
+template <typename E, int FORM, int T, int KW, int NBUF, bool LINES>
 __global__ __launch_bounds__(64 * KW) void gemm_small_kernel(Gemm g, int tiles_m, int tiles_n) {
-  small_tile<E, FORM, T, KW, NBUF>(g, tiles_m, tiles_n, blockIdx.x, blockIdx.y);
+  small_tile<E, FORM, T, KW, NBUF, LINES>(g, tiles_m, tiles_n, blockIdx.x, blockIdx.y);
 }
 // Weight gradients of a layer in one launch (see gemm_group).
 template <typename E, int T, int KW, int NBUF> __global__ __launch_bounds__(64 * KW) void gemm_small_group_kernel(GemmGroup q) {
   int tiles_m, tiles_n, pid, z;
   const Gemm g = q.product_of(blockIdx.x, tiles_m, tiles_n, pid, z);
-  small_tile<E, TN_ACC, T, KW, NBUF>(g, tiles_m, tiles_n, pid, z);
+  small_tile<E, TN_ACC, T, KW, NBUF, false>(g, tiles_m, tiles_n, pid, z);
 }
 template <typename E, int T, int KW, int NBUF> hipError_t launch_group(hipStream_t st, const Gemm* g, int n) {
   GemmGroup q(g, n, 16 * T, 16 * T);
@@ -410,19 +545,36 @@ template <typename E, int T, int KW, int NBUF> hipError_t launch_group(hipStream
   return hipGetLastError();
 }
 
-template <typename E, int FORM, int T, int KW, int NBUF> hipError_t launch(hipStream_t st, const Gemm& g) {
+template <typename E, int FORM, int T, int KW, int NBUF, bool LINES> hipError_t launch(hipStream_t st, const Gemm& g) {
   const int tm = (int)cdiv(g.M, 16 * T), tn = (int)cdiv(g.N, 16 * T);
-  hipLaunchKernelGGL((gemm_small_kernel<E, FORM, T, KW, NBUF>), dim3((unsigned)(tm * tn), (unsigned)g.batch), dim3(64 * KW), 0, st, g, tm, tn);
+  hipLaunchKernelGGL((gemm_small_kernel<E, FORM, T, KW, NBUF, LINES>), dim3((unsigned)(tm * tn), (unsigned)g.batch), dim3(64 * KW), 0, st, g, tm, tn);
   return hipGetLastError();
+}
+// Four waves to a tile that share its loads, or one wave.  With more than a tile per CU other tiles cover a lone wave's waits, and it is the faster
+// way over a short K, where the shared form still fills its stages; where rows of x are not whole lines, unless K is long; and for gate and
+// up together, whose LDS leaves a CU two workgroups, until every CU has them.  us, shared : alone: 829 x 2424, K = 48 5.8 : 4.0; 548 x 1376, K =
+// 912 11.0 : 8.3; 700 x 1024, K = 2768 21.3 : 22.7; gate and up: 128 x 2088, K = 776 9.9 : 8.6 (264 tiles), 256 x 1376, K = 512 7.2 : 6.8 (344),
+// 400 x 1024, K = 256 4.9 : 5.3 (416).  It loses up to 7 % at 512 to 768 tiles (512 x 1024, K = 2768 15.5 : 14.5).
+bool forward_shared(const Gemm& g) {
+  const int64_t tiles = cdiv(g.M, 32) * cdiv(g.N, 32) * g.batch;
+  if (tiles <= 256 || g.K <= 96) return tiles <= 256;
+  return g.K <= 256 || (g.glu ? tiles > 400 : g.lda % 64 == 0 || g.K > 2600);
 }
 template <typename E, bool GLU> hipError_t launch_forward(hipStream_t st, const Gemm& g) {
   const int tm = (int)cdiv(g.M, 32), tn = (int)cdiv(g.N, 32);
-  hipLaunchKernelGGL((gemm_small_forward_kernel<E, GLU>), dim3((unsigned)(tm * tn), (unsigned)g.batch), dim3(256), 0, st, g, tm, tn);
+  const dim3 grid((unsigned)(tm * tn), (unsigned)g.batch);
+  if (forward_shared(g)) hipLaunchKernelGGL((gemm_small_forward_kernel<E, GLU>), grid, dim3(256), 0, st, g, tm, tn);
+  else hipLaunchKernelGGL((gemm_small_forward_alone_kernel<E, GLU>), grid, dim3(64), 0, st, g, tm, tn);
   return hipGetLastError();
 }
-// The gradients' products share K out over 8 waves with either tile.
+// The gradients' products share K out over 8 waves with either tile.  Input gradients of one slab per wave have nothing to run beside the way
+// through LDS, and up to three where a piece of 128 bytes lies in two lines: us, through LDS : direct: 334 x 1016, K = 232 3.9 : 3.6; 1024 x 512, K =
+// 128 4.5 : 3.5; 232 x 680, K = 648 4.1 : 3.8; 678 x 624, K = 280 3.9 : 3.6.
 template <typename E, int FORM> hipError_t launch_form(hipStream_t st, const Gemm& g, int tile) {
-  return tile == 32 ? launch<E, FORM, 2, 8, 4>(st, g) : launch<E, FORM, 4, 8, 3>(st, g);
+  if constexpr (FORM == NT || FORM == NT_SEG || FORM == NT_GLU)
+    if (g.K > 768 || (g.K >= 256 && g.lda % 64 == 0 && g.ldb % 64 == 0))
+      return tile == 32 ? launch<E, FORM, 2, 8, 4, true>(st, g) : launch<E, FORM, 4, 8, 3, true>(st, g);
+  return tile == 32 ? launch<E, FORM, 2, 8, 4, false>(st, g) : launch<E, FORM, 4, 8, 3, false>(st, g);
 }
 template <typename E> hipError_t launch_type(hipStream_t st, const Gemm& g, int tile) {
   if (g.glu == 1) return launch_forward<E, true>(st, g);
