@@ -42,7 +42,7 @@ namespace zs {
 //               alone and uses da unrounded).
 //   act != 0 (fp32 matrix cores only, see gemm_route: batch = 1, no rotation): GELU in the store.  act = 1 (transB = 0): C receives the
 //             product z, act_z gelu(z).  act = 2 (transB = 1): act_z holds z and receives product * gelu'(z); C is not written.
-//             act_z has C's layout.  What the product followed by gelu_fwd or gelu_bwd leaves, bit for bit.
+//             act_z has C's layout.  gelu_fwd's and gelu_bwd's function of the same fp32 value.
 constexpr int GEMM_MAX_PARTS = 16;   // parts of a multi-part K range
 struct Gemm {
   int M = 0, N = 0, K = 0, transA = 0, transB = 0;

@@ -433,8 +433,8 @@ bool do_gemm(stage_t* s, const Gemm& g) {
   return run(s, cls, flops, 0.0, [&] { return gemm(s->st, dt_of(s), g, GEMM_AUTO); });
 }
 
-// GELU in the store of the fp32 products: the kernel of its own is 2.4 us of a small step's queue each time.  The 16-bit products' store
-// pass would take as long for it as the kernel, whose time is traffic.
+// GELU in the store of the fp32 products: the kernel of its own is 2.4 us of a small step's queue each time.  The 16-bit products have no
+// such store: there the kernel of its own still reads z again (backward: z and a da written for it).
 bool act_in_store(stage_t* s, Gemm g, int act, void* z) {
   g.act = act; g.act_z = z;
   return dt_of(s) == F32 && gemm_route(F32, g) == ROUTE_F32;

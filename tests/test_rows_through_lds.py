@@ -13,11 +13,13 @@ pytestmark = pytest.mark.gpu
 TD = {0: torch.float32, 1: torch.bfloat16, 2: torch.float16}
 ROUND = {0: lambda a: a, 1: round_bf16, 2: round_f16}
 TOL = {0: 2e-5, 1: 2.0 ** -8, 2: 2.0 ** -11}     # the bar of the other fp32 products; one rounding of the largest value
-# fp32: outputs that take 16x16, 16x32, 32x32 (K over 8 waves) and 64x64 tiles (K over 4); 16 bits: 32x32 and 64x64 (K over 8)
-OUTPUTS = [(0, 36, 40), (0, 100, 776), (0, 260, 1032), (0, 520, 2052), (1, 36, 40), (1, 260, 520), (1, 1000, 1032), (2, 36, 40), (2, 1000, 1032)]
+# fp32: outputs that take 16x16, 16x32, 32x32 (K over 8 waves) and 64x64 tiles (K over 4) at each of these K, the larger ones as one round of
+# 256 workgroups; 16 bits: input gradients on 32x32 and 64x64 (K over 8)
+OUTPUTS = [(0, 36, 40), (0, 100, 776), (0, 250, 1000), (0, 500, 2020), (1, 36, 40), (1, 260, 520), (1, 1000, 1016), (2, 36, 40), (2, 1000, 1016)]
+DEPTHS = [8, 40, 264, 528, 1304, 2720]
 
 
-@pytest.mark.parametrize("K", [8, 40, 264, 528, 1304, 2720])
+@pytest.mark.parametrize("K", DEPTHS)
 @pytest.mark.parametrize("dtype,M,N", OUTPUTS)
 def test_forward_input_gradient_and_segments(gpu_device, dtype, M, N, K):
     print(f"[case] rows through LDS dtype={dtype} M={M} N={N} K={K}", flush=True)

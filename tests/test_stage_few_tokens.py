@@ -59,9 +59,12 @@ def test_lm_head_gradient_as_two_halves(gpu_device, name, vocab):
     assert run(name, 2048, 16, 2048, 640, vocab=vocab)["gemm_halves_nt"]["launches"] == 2
 
 
-# Forward products of 80 or 96 tiles: the FFN's down projection, with its residual (GPT: and bias), and where K is long enough the attention
-# output's, in two halves over scratch of the backward, also beside gradients (recomputation).
-@pytest.mark.parametrize("name,ffn,seq,more", [("C3t", 5120, 640, {}), ("C3h", 5136, 600, {}), ("C2t", 8192, 600, {}), ("C2h", 8192, 760, {}),
-                                               ("C3t", 8192, 640, dict(recompute=1, layers=2))])
-def test_forward_products_as_two_halves_of_k(gpu_device, name, ffn, seq, more):
-    assert run(name, 2048, 16, ffn, seq, 2, **more)["gemm_halves_nn"]["launches"] >= 2
+# Forward products of 80 or 96 tiles in two microbatches: the FFN's down projection, with its residual (GPT: and bias), and where K is long
+# enough the attention output's, in two halves over scratch of the backward, also beside gradients (recomputation, of two layers, makes the
+# attention output again for each, and not the down projection, whose result nothing reads).
+@pytest.mark.parametrize("name,hidden,heads,ffn,seq,more,launches", [
+    ("C3t", 2048, 16, 5120, 640, {}, 4), ("C3h", 2048, 16, 5136, 600, {}, 4), ("C2t", 2048, 16, 8192, 600, {}, 4), ("C2h", 2048, 16, 8192, 760, {}, 2),
+    ("C3t", 4096, 32, 8192, 320, {}, 4), ("C2t", 4096, 32, 8192, 300, {}, 4), ("C3t", 2048, 16, 8192, 640, dict(recompute=1, layers=2), 12),
+    ("C3h", 4096, 32, 8192, 320, dict(recompute=1, layers=2), 12)])
+def test_forward_products_as_two_halves_of_k(gpu_device, name, hidden, heads, ffn, seq, more, launches):
+    assert run(name, hidden, heads, ffn, seq, 2, **more)["gemm_halves_nn"]["launches"] == launches
